@@ -11,6 +11,7 @@ Every output is a whole number (limbs of 32 bits in int32 tensors, or ASCII
 digits), so there is nothing to round.
 """
 import math
+import sys
 
 import numpy as np
 import torch
@@ -77,11 +78,20 @@ def draw(rng):
 
 # ---------------------------------------------------------------------------
 # Inputs.  C(n), binomials and factorisations have no input but their numbers:
-# the seed moves n down by less than 0.1 % (by less than 61 for small n).
+# the seed moves n down by less than 48, among those whose results have equally
+# many limbs (so that outputs of two seeds have one shape).
 
 
-def _shifted(n, seed):
-    return n - seed % max(61, n // 1000)
+def _log2_binomial(n, k):
+    return (math.lgamma(n + 1) - math.lgamma(k + 1) - math.lgamma(n - k + 1)) / math.log(2)
+
+
+def _shifted(n, seed, bits=lambda n: _log2_binomial(2 * n, n) - math.log2(n + 1)):
+    by_limbs = {}
+    for m in range(n - 47, n + 1):
+        by_limbs.setdefault(int(bits(m) // 32), []).append(m)
+    most = max(by_limbs.values(), key=len)
+    return most[seed % len(most)]
 
 
 def _limbs(count, seed):
@@ -110,6 +120,11 @@ def _requests(case, seed=0):
     return [_shifted(n, seed) for n in ns]
 
 
+def _binomial(case, seed):
+    k = min(case["k"], (case["n"] - 47) // 2)
+    return _shifted(case["n"], seed, lambda n: _log2_binomial(n, k)), k
+
+
 def prepare(case, seed):
     cat.init(torch.cuda.current_device())
     kind = case["kind"]
@@ -119,8 +134,7 @@ def prepare(case, seed):
     if kind == "serve":
         return {"kind": kind, "ns": _requests(case, seed)}
     if kind == "binomial":
-        n = _shifted(case["n"], seed)
-        k = min(case["k"], n // 2)
+        n, k = _binomial(case, seed)
         return {"kind": kind, "num": [n], "den": [k, n - k],
                 "out": torch.empty(cat.ratio_sizes([n], [k, n - k])[1], dtype=torch.int32, device="cuda")}
     if kind == "rebuild":
@@ -129,7 +143,7 @@ def prepare(case, seed):
                 "out": torch.empty(cat.product_sizes(exps, off)[0], dtype=torch.int32, device="cuda")}
     if kind == "decimal":
         x = _limbs(case["limbs"], seed)
-        x[-1] |= 1   # no leading zero limb
+        x[-1] = (1 << 30) + seed % (1 << 20)   # numbers of one length in digits too
         return {"kind": kind, "x": x}
     a_off, b_off = _lengths(case)
     state = {"kind": kind, "a": _limbs(int(a_off[-1]), 2 * seed), "b": _limbs(int(b_off[-1]), 2 * seed + 1),
@@ -225,14 +239,14 @@ def _catalan(n):
 
 def exact(case, seed):
     kind = case["kind"]
-    if kind in ("catalan", "rebuild") and case["n"] <= 100_000:
+    if kind in ("catalan", "rebuild") and case["n"] <= 200_000:
         return _to_limbs(_catalan(_shifted(case["n"], seed)))
     if kind == "serve" and case["hi"] <= 100_000:
         return [_to_limbs(_catalan(n)) for n in _requests(case, seed)]
     if kind == "binomial" and case["n"] <= 200_000:
-        n = _shifted(case["n"], seed)
-        return _to_limbs(math.comb(n, min(case["k"], n // 2)))
+        return _to_limbs(math.comb(*_binomial(case, seed)))
     if kind == "decimal" and case["limbs"] <= 10_000:
+        sys.set_int_max_str_digits(0)
         text = str(_to_int(prepare(case, seed)["x"]))
         return torch.from_numpy(np.frombuffer(text.encode(), dtype=np.uint8).copy())
     if kind in ("level", "products"):
