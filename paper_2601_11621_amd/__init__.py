@@ -233,9 +233,10 @@ def set_fused_levels(max_logn: Optional[int] = 12) -> None:
 
 
 def set_lazy_primes(max_logn: int = 23) -> None:
-    """Transforms of up to 2^max_logn points use the three primes below 2^30
-    with unreduced butterfly ranges (0: the primes above 2^31 everywhere).
-    The results are the same bit for bit either way."""
+    """23 (the default): transforms on the FP64 units over 64-bit digits.
+    Below: integer transforms, those of up to 2^max_logn points on the three
+    primes below 2^30 with unreduced butterfly ranges (0: the primes above
+    2^31 everywhere).  The results are the same bit for bit either way."""
     _check(load().cat_lazy_primes_set(int(max_logn)), "cat_lazy_primes_set")
 
 

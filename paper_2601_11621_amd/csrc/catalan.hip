@@ -1,6 +1,8 @@
-// Single translation unit of the gfx950 Catalan library (device code and
-// the C ABI), so that the __constant__ tables need no relocatable device code.
+// The integer kernels of the gfx950 Catalan library and its C ABI in one
+// translation unit, so that the __constant__ tables need no relocatable device
+// code (the FP64 transforms, with constants of their own, are fntt.hip).
 #include "common.hpp"
+#include "fntt.hpp"
 #include "ntt.inc.hip"
 #include "small.inc.hip"
 #include "fused.inc.hip"

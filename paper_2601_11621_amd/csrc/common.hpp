@@ -131,6 +131,8 @@ struct TreeLevel {
   uint64_t base[CAT_MAX_GROUPS];        // arena offset of group g
   uint64_t K[CAT_MAX_GROUPS];           // leaves (limbs) of group g
   uint64_t mpref[CAT_MAX_GROUPS + 1];   // prefix count of products per group
+  uint64_t rbase[CAT_MAX_GROUPS];       // residue position of group g, in limbs or in 64-bit digits:
+  uint32_t rshift;                      // product i's residues at rbase + (i 2^(j+1) >> rshift)
 };
 
 #define CAT_INLINE_DESC 16
@@ -170,7 +172,7 @@ struct DescView {
     d.a_off = tree.base[g] + 2 * il * sz;
     d.b_off = d.a_off + sz;
     d.c_off = d.a_off;
-    d.r_off = d.a_off;
+    d.r_off = tree.rbase[g] + ((2 * il * sz) >> tree.rshift);
     d.la = (uint32_t)sz;
     uint64_t rem = tree.K[g] - (2 * il + 1) * sz;
     d.lb = (uint32_t)(rem < sz ? rem : sz);
@@ -219,3 +221,138 @@ __device__ __forceinline__ void copy_tail_block(const CopyList& cl, const uint32
     cb -= (uint32_t)nb;
   }
 }
+
+// ----------------------------------------------------------------------------
+// Helpers of the transform and carry kernels.
+// ----------------------------------------------------------------------------
+// Word 3 of the gfx9 buffer descriptor: 32-bit data format, which untyped
+// accesses use for nothing but the range check against the buffer's size.
+#define CAT_BUF_DW3 0x00020000
+
+// bit reversal of an r-bit index, compile-time
+__host__ __device__ constexpr int brev_c(int x, int r) {
+  int y = 0;
+  for (int i = 0; i < r; i++) y |= ((x >> i) & 1) << (r - 1 - i);
+  return y;
+}
+
+__host__ __device__ constexpr uint32_t lds_pad(uint32_t i) { return i + (i >> 4); }
+
+// Word arrays read and written through raw buffer resources with byte
+// offsets in one VGPR: loads past the array's end return 0 and stores there
+// are dropped (the range check of an unswizzled buffer), which the column
+// kernels use for the zero padding of their operands and the end of a product.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t words_rsrc(const uint32_t* p, uint64_t words) {
+  return __builtin_amdgcn_make_buffer_rsrc((void*)p, (short)0, (int)(uint32_t)(words * 4u), CAT_BUF_DW3);
+}
+__device__ __forceinline__ uint32_t buf_ld(__amdgpu_buffer_rsrc_t r, uint32_t byte_off) {
+  return __builtin_amdgcn_raw_buffer_load_b32(r, (int)byte_off, 0, 0);
+}
+__device__ __forceinline__ void buf_st(__amdgpu_buffer_rsrc_t r, uint32_t byte_off, uint32_t v) {
+  __builtin_amdgcn_raw_buffer_store_b32(v, r, (int)byte_off, 0, 0);
+}
+
+// radix of the pass at sub-problem size 2^logS
+__host__ __device__ constexpr int pass_logr(int logS) { return (logS % 4) ? (logS % 4) : 4; }
+
+// Synchronisation between two radix-16 passes.  Both have total/16 groups,
+// and the 2^logSmall elements of a sub-problem of the smaller size are written
+// and read by the same 2^logSmall consecutive groups, i.e. consecutive
+// threads; in a plain vector (logC = 0) with 2^logSmall <= 64 those sit in one
+// wave, which orders its own LDS traffic, so no workgroup barrier is needed.
+// (Next to a pass of smaller radix the group counts differ: full barrier.)
+__device__ __forceinline__ void pass_sync(int logSmall, uint32_t logC) {
+  if (logC == 0 && logSmall <= 6) {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  } else {
+    __syncthreads();
+  }
+}
+
+// frequency held at output position q of the pass-structured transform of size 2^logS
+__device__ __forceinline__ uint32_t out_freq(uint32_t q, int logS) {
+  uint32_t f = 0, mult = 1;
+  while (logS > 0) {
+    const int r = pass_logr(logS);
+    const int rest = logS - r;
+    const uint32_t k1 = q >> rest;
+    f += k1 * mult;
+    mult <<= r;
+    q &= (1u << rest) - 1;
+    logS = rest;
+  }
+  return f;
+}
+
+// Workgroups are dealt round-robin to the 8 XCDs (each with its own L2) in
+// the order of their linear index.  Neighbouring column tiles share cache
+// lines (a tile row is C words), so block b of a grid of G is renumbered to
+// put consecutive tiles on one XCD: XCD x gets the tiles
+// [x ceil(G/8), ...) in order (a bijection of [0, G) for any G).
+#define CAT_XCDS 8
+__device__ __forceinline__ uint32_t xcd_remap(uint32_t b, uint32_t G) {
+  const uint32_t q = G / CAT_XCDS, r = G % CAT_XCDS;
+  const uint32_t x = b % CAT_XCDS, k = b / CAT_XCDS;
+  return x < r ? x * (q + 1) + k : r * (q + 1) + (x - r) * q + k;
+}
+
+// Wave-level: carry into each lane for (g, p) with wave carry-in `cin`;
+// returns lane's carry in, and the wave carry out in *cout.
+__device__ __forceinline__ uint32_t wave_carry(bool g, bool pr, uint32_t cin, uint32_t* cout, bool* allprop) {
+  const uint64_t gm = __ballot(g), pm = __ballot(pr);
+  const uint64_t a = gm, b = gm | pm;
+  const uint64_t s1 = a + b;
+  const uint64_t c1 = s1 < a;
+  const uint64_t s2 = s1 + cin;
+  const uint64_t c2 = s2 < s1;
+  *cout = (uint32_t)(c1 | c2);
+  *allprop = (pm == ~0ull);
+  const uint64_t cm = s2 ^ pm;   // carry into each bit position
+  return (uint32_t)((cm >> (threadIdx.x & 63)) & 1ull);
+}
+
+// Segments of a CRT launch: device tables (many segments) or up to
+// CAT_INLINE_SEG segments carried in the kernel arguments.
+#define CAT_INLINE_SEG 32
+struct SegView {
+  const CrtSeg* segs;        // nullptr => inline tables
+  const uint32_t* pref;      // pref[s] = first block of segment s (nseg+1 entries)
+  const uint32_t* b2s;       // with segs: the segment of every block (one load, no search)
+  uint32_t nseg;
+  uint32_t ubl;              // > 0: uniform segments of ubl blocks each (below)
+  CrtSeg iseg[CAT_INLINE_SEG];
+  uint32_t ipref[CAT_INLINE_SEG + 1];
+  // uniform: segment s is iseg[0] with out_pos, res_pos and add_pos advanced
+  // by s * ustep[0], s * iseg[0].len and s * ustep[1]
+  uint64_t ustep[2];
+  __device__ __forceinline__ void find(uint32_t b, CrtSeg* sg, uint32_t* first, uint32_t* end,
+                                       uint32_t* segi = nullptr) const {
+    if (ubl) {
+      const uint32_t q = b / ubl;
+      *sg = iseg[0];
+      sg->out_pos += q * ustep[0];
+      sg->res_pos += q * iseg[0].len;
+      sg->add_pos += q * ustep[1];
+      *first = q * ubl;
+      *end = *first + ubl;
+      if (segi) *segi = q;
+      return;
+    }
+    const uint32_t* pr = segs ? pref : ipref;
+    uint32_t lo = 0, hi = nseg;   // pr[lo] <= b < pr[lo+1]
+    if (segs && b2s) {
+      lo = b2s[b];
+    } else {
+      while (hi - lo > 1) {
+        const uint32_t mid = (lo + hi) >> 1;
+        if (pr[mid] <= b) lo = mid; else hi = mid;
+      }
+    }
+    *sg = segs ? segs[lo] : iseg[lo];
+    *first = pr[lo];
+    *end = pr[lo + 1];
+    if (segi) *segi = lo;
+  }
+};

@@ -1,0 +1,1164 @@
+// Exact big-integer products for the reconstruction phase (Sec. 3.2, Alg. 2):
+// cyclic convolution of 64-bit digits modulo three primes near 2^50 (or 2^51)
+// by number-theoretic transforms whose modular arithmetic runs on the FP64 FMA
+// units.
+//
+// Why FP64.  The transforms are bound by vector issue.  A modular product of
+// two 50-bit residues costs six FP64 instructions (below) and a modular sum
+// one; the 32-bit integer form costs four and about three, on residues that
+// hold 30 bits.  Measured on registers (radix-16 DFT with its 15 twiddles):
+// 1.26e11 per second in FP64, 1.50e11 in 30-bit integers, but each FP64
+// transform carries 64-bit digits, so a product needs half as many points and
+// one butterfly level less.
+//
+// Numbers.  A residue is a signed integer held exactly in a double, any
+// representative with |x| < 2^53.  With h = fl(a w), l = a w - h (exact by
+// FMA) and q = rint(fl(h / p)), the value (h - q p) + l is exactly a w - q p:
+// h - q p is an integer below 2^53, so its FMA does not round, and neither
+// does the last sum.  q is within 1/2 + e of a w / p, where e collects the
+// roundings of the quotient (each 2^-53 |a w / p|), so the result is below
+// (1/2 + e) p; sums and differences are plain additions.
+//
+// Ranges, in units of p, with |w| <= p/2 (table entries are balanced):
+//  * a product by a constant with its own quotient (mulc: two roundings) is
+//    at most 1/2 + a/8 for a < 8 and p near 2^50 (set 0), 1/2 + a/4 for a < 4
+//    and p near 2^51 (set 1);
+//  * a product with the quotient taken from h (mulm: three roundings) is at
+//    most 1/2 + 3a/16 (set 0), 1/2 + 3a/8 (set 1);
+//  * red() gives 1/2 (plus 2^-40).
+// A DFT multiplies the second input of every butterfly (by a constant, or
+// reduces it where the constant is 1 after the first stage), so a value grows
+// as x -> x + 1/2 + x/8 per stage: four stages take inputs of A to at most
+// 2.85 A + 1.70 (set 0).  Pass twiddles bring that back to 1/2 + 3/16 of it,
+// and outputs without a twiddle are reduced, so A stays at or below 1.76 and
+// every value below 6.8 < 8 = 2^53 / p.  Set 1 (limit 4) reduces all 16 inputs
+// of a DFT first: 2, 3.5/2, ... at most 3.87.
+//
+// Exactness of the product: a coefficient is at most min(la, lb) (2^64 - 1)^2
+// with the lengths in digits.  Set 0 (three primes above 2^50) covers operands
+// of up to 2^22 digits, that is transforms of up to 2^23 points; set 1 (above
+// 2^51) up to 2^25 digits, transforms of up to 2^26.
+//
+// Transform structure: passes of radix 16 (the first of radix 2^(log2 S mod
+// 4)) on registers, one thread holding 16 values, with LDS between the passes.
+// A transform of up to 2^14 points runs in one workgroup (k_flds); longer ones
+// are cut in rows of 2^10 .. 2^13 points and column DFTs of 2^4 .. 2^10 points
+// (Bailey 1990).  Both operands of a product pass through the same LDS buffer,
+// the first one's outputs waiting in registers, so a workgroup of T/16 threads
+// needs 8 T bytes of LDS: four waves per SIMD at 128 registers.
+#include "fntt.hpp"
+
+#include <vector>
+
+#pragma clang fp contract(off)
+
+namespace {
+
+struct FPrime {
+  double p, pinv;
+  double w[8], wp[8];     // omega_16^i and omega_16^i / p
+  double iw[8], iwp[8];   // inverse roots
+};
+__constant__ FPrime c_fp[2][CAT_NPRIMES];
+
+// Constants of the recombination, every constant with its quotient c / p:
+// x0 = k00 r0 mod p0, x1 = k11 r1 + k10 x0 mod p1, x2 = k22 r2 + k20 x0 + k21
+// x1 mod p2 (the transform's scale 2^-logD is in k00, k11, k22).
+struct FCrt {
+  double p[3], pinv[3];
+  double k00, k00q, k10, k10q, k11, k11q, k20, k20q, k21, k21q, k22, k22q;
+  uint64_t pi[2];         // p0, p1
+};
+
+#define FTWS_ENTRIES 32766u    // pass tables of sizes 2^1 .. 2^14, back to back
+#define FTW2_BITS 13u          // two-level table: omega_{2^26}^y = hi[y >> 13] lo[y mod 2^13]
+#define FTW2 (1u << FTW2_BITS)
+struct FTables {
+  const double* tws;           // [prime][FTWS_ENTRIES]: [2^s - 2 + (k << logSR) + j] = omega_S^(j k)
+  const double* itws;
+  const double* lo;            // [prime][FTW2]
+  const double* hi;
+  const double* ilo;
+  const double* ihi;
+};
+FTables g_ft[2];
+uint64_t g_fpr[2][CAT_NPRIMES];
+
+// ------------------------------------------------------------------ arithmetic
+__device__ __forceinline__ double red(double a, double p, double pinv) {
+  return __builtin_fma(-__builtin_rint(a * pinv), p, a);
+}
+// a w mod p for a constant w with wp = w / p
+__device__ __forceinline__ double mulc(double a, double w, double wp, double p) {
+  const double h = a * w;
+  const double q = __builtin_rint(a * wp);
+  const double l = __builtin_fma(a, w, -h);
+  return __builtin_fma(-q, p, h) + l;
+}
+__device__ __forceinline__ double mulm(double a, double w, double p, double pinv) {
+  const double h = a * w;
+  const double q = __builtin_rint(h * pinv);
+  const double l = __builtin_fma(a, w, -h);
+  return __builtin_fma(-q, p, h) + l;
+}
+
+// Radix-R DFT on registers, natural input, output y[k] in v[brev(k)].  Stage t
+// has 2^t blocks; block b takes (x, y) to x + w y, x - w y with w =
+// omega_16^brev3(b).  ZHI: the upper half of the input is zero (a zero-padded
+// operand, entries at most 1/2): the first stage copies, and the sums of
+// reduced inputs need no reduction (at most 4 after four stages, set 0).
+template <int LOGR, int PS, bool ZHI>
+__device__ __forceinline__ void fdft(double* v, const FPrime& c) {
+  constexpr int R = 1 << LOGR;
+  const double p = c.p, pinv = c.pinv;
+  if constexpr (PS == 1 && !ZHI) {
+#pragma unroll
+    for (int i = 0; i < R; i++) v[i] = red(v[i], p, pinv);
+  }
+#pragma unroll
+  for (int t = 0; t < LOGR; t++) {
+    const int h = R >> (t + 1);
+#pragma unroll
+    for (int b = 0; b < (1 << t); b++) {
+#pragma unroll
+      for (int i = 0; i < h; i++) {
+        double& x = v[2 * b * h + i];
+        double& y = v[2 * b * h + i + h];
+        if (t == 0 && ZHI) {
+          y = x;
+          continue;
+        }
+        double z;
+        if (b != 0) z = mulc(y, c.w[brev_c(b, 3)], c.wp[brev_c(b, 3)], p);
+        else if (t == 0 || (ZHI && PS == 0)) z = y;
+        else z = red(y, p, pinv);
+        y = x - z;
+        x = x + z;
+      }
+    }
+  }
+}
+
+// Inverse: input y[k] in v[brev(k)], output R x[j] in v[j].
+template <int LOGR, int PS>
+__device__ __forceinline__ void fidft(double* v, const FPrime& c) {
+  constexpr int R = 1 << LOGR;
+  const double p = c.p, pinv = c.pinv;
+  if constexpr (PS == 1) {
+#pragma unroll
+    for (int i = 0; i < R; i++) v[i] = red(v[i], p, pinv);
+  }
+#pragma unroll
+  for (int t = 0; t < LOGR; t++) {
+    const int h = 1 << t;
+#pragma unroll
+    for (int s = 0; s < R; s += 2 * h) {
+#pragma unroll
+      for (int i = 0; i < h; i++) {
+        double& x = v[s + i];
+        double& y = v[s + i + h];
+        double z;
+        if (i != 0) z = mulc(y, c.iw[i * (8 >> t)], c.iwp[i * (8 >> t)], p);
+        else z = t == 0 ? y : red(y, p, pinv);
+        y = x - z;
+        x = x + z;
+      }
+    }
+  }
+}
+
+// Pass twiddles omega_S^(j k) (S = R << logSR) of the R values y[k] in
+// v[brev(k)], read through a buffer resource: the uniform part k << logSR is
+// the scalar offset.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t ftw_rsrc(const double* tw, uint32_t entries) {
+  return __builtin_amdgcn_make_buffer_rsrc((void*)tw, (short)0, (int)(entries * 8u), CAT_BUF_DW3);
+}
+__device__ __forceinline__ double buf_ldd(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff) {
+  const auto u = __builtin_amdgcn_raw_buffer_load_b64(r, (int)voff, (int)soff, 0);
+  return __hiloint2double((int)u[1], (int)u[0]);
+}
+__device__ __forceinline__ void buf_std(__amdgpu_buffer_rsrc_t r, uint32_t voff, double x) {
+  typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+  u32x2 u;
+  u[0] = (uint32_t)__double2loint(x);
+  u[1] = (uint32_t)__double2hiint(x);
+  __builtin_amdgcn_raw_buffer_store_b64(u, r, (int)voff, 0, 0);
+}
+template <int LOGR>
+__device__ __forceinline__ void ptw(double* v, const double* tws, int logSR, uint32_t j, const FPrime& c) {
+  constexpr int R = 1 << LOGR;
+  const __amdgpu_buffer_rsrc_t rs = ftw_rsrc(tws + ((1u << (logSR + LOGR)) - 2u), (uint32_t)R << logSR);
+  v[0] = red(v[0], c.p, c.pinv);
+#pragma unroll
+  for (int k = 1; k < R; k++) {
+    const int r = brev_c(k, LOGR);
+    v[r] = mulm(v[r], buf_ldd(rs, j * 8u, ((uint32_t)k << logSR) * 8u), c.p, c.pinv);
+  }
+}
+
+// A 64-bit digit (lo, hi) as a residue: hi 2^32 reduced, plus lo (below
+// p/2 + 2^32).
+__device__ __forceinline__ double digit(uint32_t lo, uint32_t hi, double p, double pinv) {
+  return red((double)hi * 4294967296.0, p, pinv) + (double)lo;
+}
+
+// ------------------------------------------------------ passes in a workgroup
+// LDS element e of a tile of C = 2^logC columns (1: a plain vector) sits at
+// (e + e/16) C + column.  Every radix-16 pass after the first has one group
+// per thread: thread t = (h, c), h = t / C; its group in sub-problems of S =
+// 16 SR elements is j = h mod SR of sub-problem h / SR.
+template <int LOGSR, int PS>
+__device__ __forceinline__ void mid_fwd(double* lds, uint32_t logC, const double* tws, const FPrime& c, uint32_t tid) {
+  constexpr uint32_t SR = 1u << LOGSR;
+  const uint32_t h = tid >> logC, j = h & (SR - 1);
+  const uint32_t b = (lds_pad(((h >> LOGSR) << (LOGSR + 4)) + j) << logC) + (tid & ((1u << logC) - 1));
+  const uint32_t st = (SR + SR / 16) << logC;
+  double v[16];
+#pragma unroll
+  for (int k = 0; k < 16; k++) v[k] = lds[b + k * st];
+  fdft<4, PS, false>(v, c);
+  ptw<4>(v, tws, LOGSR, j, c);
+#pragma unroll
+  for (int k = 0; k < 16; k++) lds[b + k * st] = v[brev_c(k, 4)];
+}
+template <int LOGSR, int PS>
+__device__ __forceinline__ void mid_inv(double* lds, uint32_t logC, const double* itws, const FPrime& c, uint32_t tid) {
+  constexpr uint32_t SR = 1u << LOGSR;
+  const uint32_t h = tid >> logC, j = h & (SR - 1);
+  const uint32_t b = (lds_pad(((h >> LOGSR) << (LOGSR + 4)) + j) << logC) + (tid & ((1u << logC) - 1));
+  const uint32_t st = (SR + SR / 16) << logC;
+  double v[16];
+#pragma unroll
+  for (int k = 0; k < 16; k++) v[brev_c(k, 4)] = lds[b + k * st];
+  ptw<4>(v, itws, LOGSR, j, c);
+  fidft<4, PS>(v, c);
+#pragma unroll
+  for (int k = 0; k < 16; k++) lds[b + k * st] = v[k];
+}
+// Passes of a transform of 2^LOGS points below its first one (which left
+// sub-problems of 2^(LOGS - LR), a multiple of four bits): radix-16 passes
+// through LDS until sub-problems of 16 are left, which each thread then takes
+// into registers.
+template <int LOGSUB, int PS>
+__device__ __forceinline__ void rest_fwd(double* lds, uint32_t logC, const double* tws, const FPrime& c, uint32_t tid) {
+  if constexpr (LOGSUB > 4) {
+    mid_fwd<LOGSUB - 4, PS>(lds, logC, tws, c, tid);
+    pass_sync(LOGSUB - 4, logC);
+    rest_fwd<LOGSUB - 4, PS>(lds, logC, tws, c, tid);
+  }
+}
+// the inverse of rest_fwd, each pass followed by its synchronisation except
+// the last, which the caller does
+template <int LOGSUB, int LOGTOP, int PS>
+__device__ __forceinline__ void rest_inv(double* lds, uint32_t logC, const double* itws, const FPrime& c, uint32_t tid) {
+  if constexpr (LOGSUB <= LOGTOP) {
+    mid_inv<LOGSUB - 4, PS>(lds, logC, itws, c, tid);
+    if constexpr (LOGSUB < LOGTOP) pass_sync(LOGSUB, logC);
+    rest_inv<LOGSUB + 4, LOGTOP, PS>(lds, logC, itws, c, tid);
+  }
+}
+__device__ __forceinline__ uint32_t slot16(uint32_t tid, uint32_t logC) {
+  return (lds_pad(16 * (tid >> logC)) << logC) + (tid & ((1u << logC) - 1));
+}
+
+// First forward pass (radix 2^LR) of a tile whose elements i = 0 .. 15 of a
+// thread are the groups d + D k, D = 16 / R: group d holds x[d + D k], k < R,
+// and is group j of sub-problem `blk` (element positions j + SR k).
+template <int LR, int LOGSR, int PS, bool ZHI>
+__device__ __forceinline__ void first_fwd(double* lds, double* x, uint32_t NT, uint32_t logC, const double* tws,
+                                          const FPrime& c, uint32_t tid) {
+  constexpr int R = 1 << LR, D = 16 / R;
+  constexpr uint32_t SR = 1u << LOGSR;
+#pragma unroll
+  for (int d = 0; d < D; d++) {
+    const uint32_t g = tid + NT * d, h = g >> logC, j = h & (SR - 1);
+    double v[R];
+#pragma unroll
+    for (int k = 0; k < R; k++) v[k] = (ZHI && k >= R / 2) ? 0.0 : x[d + D * k];
+    fdft<LR, PS, ZHI>(v, c);
+    ptw<LR>(v, tws, LOGSR, j, c);
+    const uint32_t b = (lds_pad(((h >> LOGSR) << (LOGSR + LR)) + j) << logC) + (g & ((1u << logC) - 1));
+#pragma unroll
+    for (int k = 0; k < R; k++) lds[b + k * ((SR + SR / 16) << logC)] = v[brev_c(k, LR)];
+  }
+}
+// Last inverse pass into x[d + D k].
+template <int LR, int LOGSR, int PS>
+__device__ __forceinline__ void last_inv(const double* lds, double* x, uint32_t NT, uint32_t logC, const double* itws,
+                                         const FPrime& c, uint32_t tid) {
+  constexpr int R = 1 << LR, D = 16 / R;
+  constexpr uint32_t SR = 1u << LOGSR;
+#pragma unroll
+  for (int d = 0; d < D; d++) {
+    const uint32_t g = tid + NT * d, h = g >> logC, j = h & (SR - 1);
+    const uint32_t b = (lds_pad(((h >> LOGSR) << (LOGSR + LR)) + j) << logC) + (g & ((1u << logC) - 1));
+    double v[R];
+#pragma unroll
+    for (int k = 0; k < R; k++) v[brev_c(k, LR)] = lds[b + k * ((SR + SR / 16) << logC)];
+    ptw<LR>(v, itws, LOGSR, j, c);
+    fidft<LR, PS>(v, c);
+#pragma unroll
+    for (int k = 0; k < R; k++) x[d + D * k] = v[k];
+  }
+}
+// The synchronisation next to the pass of radix 2^LR over sub-problems of
+// 2^LOGSR: wave-local only when that pass too has one group per thread.
+template <int LR, int LOGSR>
+__device__ __forceinline__ void edge_sync(uint32_t logC) {
+  if constexpr (LR == 4) pass_sync(LOGSR, logC);
+  else __syncthreads();
+}
+template <int PS>
+__device__ __forceinline__ void load16(const double* lds, double* v, uint32_t tid, uint32_t logC) {
+  const uint32_t b = slot16(tid, logC);
+#pragma unroll
+  for (int k = 0; k < 16; k++) v[k] = lds[b + (k << logC)];
+}
+// y[k] in v[brev(k)] times w[k] likewise, then the inverse DFT of the 16 slots
+template <int PS>
+__device__ __forceinline__ void pointwise16(double* a, const double* b, const FPrime& c) {
+#pragma unroll
+  for (int k = 0; k < 16; k++) a[k] = mulm(red(a[k], c.p, c.pinv), b[k], c.p, c.pinv);
+}
+
+// Twiddles theta^(e0 + step i), i = 0 .. 15, times the 16 values of one or two
+// arrays.  theta = omega_S^f; e0 f and step f as exponents of omega_{2^26}.
+template <int PS>
+struct Geo {
+  double w[4], r4;
+  double p, pinv;
+  __device__ __forceinline__ static double tw2(const double* lo, const double* hi, uint32_t y, double p, double pinv) {
+    return fix(mulm(lo[y & (FTW2 - 1)], hi[y >> FTW2_BITS], p, pinv), p, pinv);
+  }
+  // set 0: |w| <= 0.68 throughout; set 1 reduces every power
+  __device__ __forceinline__ static double fix(double x, double p, double pinv) {
+    if constexpr (PS == 1) return red(x, p, pinv);
+    else return x;
+  }
+  __device__ __forceinline__ Geo(const double* lo, const double* hi, uint32_t y0, uint32_t ystep, double p_,
+                                 double pinv_)
+      : p(p_), pinv(pinv_) {
+    const uint32_t mask = (1u << FNTT_MAX_LOGD) - 1;
+    const double r1 = tw2(lo, hi, ystep & mask, p, pinv);
+    w[0] = tw2(lo, hi, y0 & mask, p, pinv);
+    const double r2 = fix(mulm(r1, r1, p, pinv), p, pinv);
+    r4 = fix(mulm(r2, r2, p, pinv), p, pinv);
+    w[1] = fix(mulm(w[0], r1, p, pinv), p, pinv);
+    w[2] = fix(mulm(w[0], r2, p, pinv), p, pinv);
+    w[3] = fix(mulm(w[1], r2, p, pinv), p, pinv);
+  }
+  __device__ __forceinline__ void step() {
+#pragma unroll
+    for (int i = 0; i < 4; i++) w[i] = fix(mulm(w[i], r4, p, pinv), p, pinv);
+  }
+};
+
+// limbs of an operand: the digit at position pos (zero past the end)
+__device__ __forceinline__ uint2 limb2(__amdgpu_buffer_rsrc_t rs, uint32_t byte_off) {
+  return make_uint2(buf_ld(rs, byte_off), buf_ld(rs, byte_off + 4u));
+}
+
+// ---------------------------------------------------------------------------
+// Whole products in one workgroup, transforms of 2^LOGD digits.  A tile holds
+// 2^LOGT slots (2^12 at least, 2^(LOGT - LOGD) products); grid: 3 x tiles,
+// renumbered so that each XCD takes a contiguous run of (tile, prime) pairs
+// and the three primes of a tile read the operands once from HBM.
+template <int LOGD>
+__global__ void __launch_bounds__((1 << (LOGD < 12 ? 12 : LOGD)) / 16) __attribute__((amdgpu_waves_per_eu(4)))
+k_flds(DescView dv, uint64_t m0_, uint64_t nmul, const uint32_t* __restrict__ ain, const uint32_t* __restrict__ bin,
+       double* __restrict__ res, uint64_t stride, FTables tb) {
+  constexpr int LOGT = LOGD < 12 ? 12 : LOGD, LR = pass_logr(LOGD), LOGSR = LOGD - LR;
+  constexpr uint32_t T = 1u << LOGT, NT = T / 16, N = 1u << LOGD, PER = T / N, SR = 1u << LOGSR;
+  constexpr int R = 1 << LR, D = 16 / R;
+  __shared__ double lds[lds_pad(T)];
+  __shared__ MulDesc ds[PER];
+  const uint32_t tid = threadIdx.x;
+  const uint32_t wid = xcd_remap(blockIdx.x, gridDim.x);
+  const uint32_t prime = wid % CAT_NPRIMES;
+  const FPrime& c = c_fp[0][prime];
+  const uint64_t m0 = (uint64_t)(wid / CAT_NPRIMES) * PER;
+  const uint32_t cnt = (uint32_t)min((uint64_t)PER, nmul - m0);
+  bool half = true;
+  for (uint32_t i = tid; i < PER; i += NT) {
+    MulDesc d{};   // slots without a product: empty operands
+    if (i < cnt) d = dv.get(m0_ + m0 + i);
+    ds[i] = d;
+    half = half && d.la <= N && d.lb <= N;   // at most N/2 digits each
+  }
+  const bool zhi = __syncthreads_and(half ? 1 : 0) != 0;
+  const double* tws = tb.tws + (size_t)prime * FTWS_ENTRIES;
+  const double* itws = tb.itws + (size_t)prime * FTWS_ENTRIES;
+  double a[16], b[16];
+  // thread t holds the elements t + NT i = group d of the first pass at k
+  // (i = d + D k): position j + SR k of product blk
+  if (zhi) {
+    uint2 ra[8], rb[8];
+#pragma unroll
+    for (int d = 0; d < D; d++) {
+      const uint32_t g = tid + NT * d, j = g & (SR - 1);
+      const MulDesc m = ds[g >> LOGSR];
+#pragma unroll
+      for (int k = 0; k < R / 2; k++) {
+        const uint32_t q = 2 * (j + SR * k);
+        const uint32_t la = m.la, lb = m.lb;
+        const uint64_t qa0 = q < la ? q : 0, qa1 = q + 1 < la ? q + 1 : 0;
+        const uint64_t qb0 = q < lb ? q : 0, qb1 = q + 1 < lb ? q + 1 : 0;
+        uint2 x = make_uint2(ain[m.a_off + qa0], ain[m.a_off + qa1]);
+        uint2 y = make_uint2(bin[m.b_off + qb0], bin[m.b_off + qb1]);
+        x.x = q < la ? x.x : 0u;
+        x.y = q + 1 < la ? x.y : 0u;
+        y.x = q < lb ? y.x : 0u;
+        y.y = q + 1 < lb ? y.y : 0u;
+        ra[d + D * k] = x;
+        rb[d + D * k] = y;
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < 8; i++) {
+      a[i] = digit(ra[i].x, ra[i].y, c.p, c.pinv);
+      b[i] = digit(rb[i].x, rb[i].y, c.p, c.pinv);
+    }
+    first_fwd<LR, LOGSR, 0, true>(lds, a, NT, 0, tws, c, tid);
+  } else {
+#pragma unroll
+    for (int d = 0; d < D; d++) {
+      const uint32_t g = tid + NT * d, j = g & (SR - 1);
+      const MulDesc m = ds[g >> LOGSR];
+#pragma unroll
+      for (int k = 0; k < R; k++) {
+        const uint32_t q = 2 * (j + SR * k);
+        const uint32_t la = m.la, lb = m.lb;
+        const uint32_t x0 = q < la ? ain[m.a_off + q] : 0u, x1 = q + 1 < la ? ain[m.a_off + q + 1] : 0u;
+        const uint32_t y0 = q < lb ? bin[m.b_off + q] : 0u, y1 = q + 1 < lb ? bin[m.b_off + q + 1] : 0u;
+        a[d + D * k] = digit(x0, x1, c.p, c.pinv);
+        b[d + D * k] = digit(y0, y1, c.p, c.pinv);
+      }
+    }
+    first_fwd<LR, LOGSR, 0, false>(lds, a, NT, 0, tws, c, tid);
+  }
+  edge_sync<LR, LOGSR>(0);
+  rest_fwd<LOGSR, 0>(lds, 0, tws, c, tid);
+  load16<0>(lds, a, tid, 0);
+  __syncthreads();
+  if (zhi) first_fwd<LR, LOGSR, 0, true>(lds, b, NT, 0, tws, c, tid);
+  else first_fwd<LR, LOGSR, 0, false>(lds, b, NT, 0, tws, c, tid);
+  edge_sync<LR, LOGSR>(0);
+  rest_fwd<LOGSR, 0>(lds, 0, tws, c, tid);
+  load16<0>(lds, b, tid, 0);
+  fdft<4, 0, false>(a, c);
+  fdft<4, 0, false>(b, c);
+  pointwise16<0>(a, b, c);
+  fidft<4, 0>(a, c);
+  {
+    const uint32_t s = slot16(tid, 0);
+#pragma unroll
+    for (int k = 0; k < 16; k++) lds[s + k] = a[k];
+  }
+  if constexpr (LOGSR > 4) {
+    pass_sync(4, 0);
+    rest_inv<8, LOGSR, 0>(lds, 0, itws, c, tid);
+  }
+  edge_sync<LR, LOGSR>(0);
+  last_inv<LR, LOGSR, 0>(lds, a, NT, 0, itws, c, tid);
+  double* out = res + (size_t)prime * stride;
+#pragma unroll
+  for (int d = 0; d < D; d++) {
+    const uint32_t g = tid + NT * d, j = g & (SR - 1);
+    const MulDesc m = ds[g >> LOGSR];
+    const uint32_t L = (m.la + m.lb + 1) / 2;
+#pragma unroll
+    for (int k = 0; k < R; k++) {
+      const uint32_t pos = j + SR * k;
+      if (pos < L) out[m.r_off + pos] = a[d + D * k];
+    }
+    if (j == 0 && L > N) out[m.r_off + N] = 0.0;   // la + lb = 2 N + 1: no coefficient there
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Four-step: F[((m*3 + prime)*2 + op) * 2^logD + position], doubles.
+struct FGeom {
+  int logD, logS, logC;
+  // tile bx of the pass over sub-problems of 2^logS with column length 2^logL
+  __device__ __forceinline__ void locate(int logL, uint64_t bx, uint64_t* m, uint32_t* base, uint32_t* j0) const {
+    const int lt = logS - logL - logC;                    // tiles per sub-problem (log2)
+    const int lp = logD - logS + lt;                      // tiles per product
+    *m = bx >> lp;
+    const uint32_t r = (uint32_t)(bx & ((1ull << lp) - 1));
+    *base = (r >> lt) << logS;
+    *j0 = (r & ((1u << lt) - 1)) << logC;
+  }
+};
+
+// Column DFT of 2^LOGL points over tiles of 2^LOGT values (C = 2^logC
+// neighbouring columns), one thread per 16 values.  FIRST: the operands'
+// digits come from limbs; otherwise from F, times the twiddles of the pass
+// before (sub-problems 2^prevS, column length 2^prevL).  The results go to F,
+// reduced; the twiddles of this pass are applied by the next one.
+// Bound by HBM: 8 B written per digit slot, prime and operand (and 4 to 8
+// read), about 70 FP64 instructions.
+template <int LOGL, int PS, bool FIRST>
+__global__ void __launch_bounds__(LOGL <= 8 ? 256 : 512)
+k_fcol_fwd(DescView dv, FGeom fg, uint64_t m0_, int prevS, int prevL, const uint32_t* __restrict__ ain,
+           const uint32_t* __restrict__ bin, double* __restrict__ F, FTables tb) {
+  constexpr int LOGT = LOGL <= 8 ? 12 : 13, LR = pass_logr(LOGL), LOGSR = LOGL - LR;
+  constexpr uint32_t T = 1u << LOGT, NT = T / 16;
+  constexpr uint32_t logC = LOGT - LOGL;
+  constexpr uint32_t C = 1u << logC, RI = NT >> logC;     // rows per step of i
+  __shared__ double lds[LOGL > 4 ? ((1u << LOGL) + (1u << LOGL) / 16) * C : 1];
+  const uint32_t tid = threadIdx.x;
+  const uint32_t wid = xcd_remap(blockIdx.x, gridDim.x);
+  const uint32_t prime = wid % CAT_NPRIMES, op = blockIdx.z;
+  const FPrime& c = c_fp[PS][prime];
+  uint64_t m;
+  uint32_t base, j0;
+  fg.locate(LOGL, wid / CAT_NPRIMES, &m, &base, &j0);
+  const int logSig = fg.logS - LOGL;
+  const uint64_t N = 1ull << fg.logD;
+  double* f = F + ((m * 3 + prime) * 2 + op) * N;
+  const __amdgpu_buffer_rsrc_t rf = __builtin_amdgcn_make_buffer_rsrc((void*)f, (short)0, (int)(uint32_t)(N * 8), CAT_BUF_DW3);
+  const uint32_t pos0 = base + ((tid >> logC) << logSig) + j0 + (tid & (C - 1));   // element i: + (RI i) << logSig
+  const double* tws = tb.tws + (size_t)prime * FTWS_ENTRIES;
+  double x[16];
+  bool zhi = false;
+  if constexpr (FIRST) {
+    const MulDesc d = dv.get(m0_ + m);
+    const uint32_t len = op ? d.lb : d.la;
+    zhi = len <= N;                                       // at most N/2 digits
+    const __amdgpu_buffer_rsrc_t rs = words_rsrc(op ? bin + d.b_off : ain + d.a_off, len);
+    uint2 r[16];
+    if (zhi) {
+#pragma unroll
+      for (int i = 0; i < 8; i++) r[i] = limb2(rs, (pos0 + ((RI * i) << logSig)) * 8u);
+#pragma unroll
+      for (int i = 0; i < 8; i++) x[i] = digit(r[i].x, r[i].y, c.p, c.pinv);
+    } else {
+#pragma unroll
+      for (int i = 0; i < 16; i++) r[i] = limb2(rs, (pos0 + ((RI * i) << logSig)) * 8u);
+#pragma unroll
+      for (int i = 0; i < 16; i++) x[i] = digit(r[i].x, r[i].y, c.p, c.pinv);
+    }
+  } else {
+#pragma unroll
+    for (int i = 0; i < 16; i++) x[i] = buf_ldd(rf, (pos0 + ((RI * i) << logSig)) * 8u, 0);
+    const uint32_t fr = out_freq((base >> fg.logS) & ((1u << prevL) - 1), prevL) << (FNTT_MAX_LOGD - prevS);
+    Geo<PS> gw(tb.lo + (size_t)prime * FTW2, tb.hi + (size_t)prime * FTW2, (pos0 - base) * fr, (RI << logSig) * fr,
+               c.p, c.pinv);
+#pragma unroll
+    for (int i = 0; i < 16; i++) {
+      x[i] = mulm(x[i], gw.w[i & 3], c.p, c.pinv);
+      if ((i & 3) == 3 && i < 15) gw.step();
+    }
+  }
+  double v[16];
+  if constexpr (LOGL == 4) {
+    if (FIRST && zhi) {
+#pragma unroll
+      for (int i = 8; i < 16; i++) x[i] = 0.0;
+      fdft<4, PS, FIRST>(x, c);
+    } else {
+      fdft<4, PS, false>(x, c);
+    }
+#pragma unroll
+    for (int k = 0; k < 16; k++) v[k] = x[k];
+  } else {
+    if (FIRST && zhi) first_fwd<LR, LOGSR, PS, FIRST>(lds, x, NT, logC, tws, c, tid);
+    else first_fwd<LR, LOGSR, PS, false>(lds, x, NT, logC, tws, c, tid);
+    __syncthreads();
+    rest_fwd<LOGSR, PS>(lds, logC, tws, c, tid);
+    load16<PS>(lds, v, tid, logC);
+    fdft<4, PS, false>(v, c);
+  }
+  const uint32_t q0 = base + ((16 * (tid >> logC)) << logSig) + j0 + (tid & (C - 1));
+#pragma unroll
+  for (int k = 0; k < 16; k++)
+    buf_std(rf, (q0 + ((uint32_t)k << logSig)) * 8u, red(v[brev_c(k, 4)], c.p, c.pinv));
+}
+
+// Inverse column DFT.  FIRST (the outermost pass): the residues of positions
+// below la + lb limbs; otherwise back to F, times the inverse twiddles of the
+// pass before.
+template <int LOGL, int PS, bool FIRST>
+__global__ void __launch_bounds__(LOGL <= 8 ? 256 : 512)
+k_fcol_inv(DescView dv, FGeom fg, uint64_t m0_, int prevS, int prevL, double* __restrict__ F,
+           double* __restrict__ res, uint64_t stride, FTables tb) {
+  constexpr int LOGT = LOGL <= 8 ? 12 : 13, LR = pass_logr(LOGL), LOGSR = LOGL - LR;
+  constexpr uint32_t T = 1u << LOGT, NT = T / 16;
+  constexpr uint32_t logC = LOGT - LOGL;
+  constexpr uint32_t C = 1u << logC, RI = NT >> logC;
+  __shared__ double lds[LOGL > 4 ? ((1u << LOGL) + (1u << LOGL) / 16) * C : 1];
+  const uint32_t tid = threadIdx.x;
+  const uint32_t prime = blockIdx.y;
+  const FPrime& c = c_fp[PS][prime];
+  uint64_t m;
+  uint32_t base, j0;
+  fg.locate(LOGL, xcd_remap(blockIdx.x, gridDim.x), &m, &base, &j0);
+  const int logSig = fg.logS - LOGL;
+  const uint64_t N = 1ull << fg.logD;
+  double* f = F + ((m * 3 + prime) * 2 + 0) * N;
+  const __amdgpu_buffer_rsrc_t rf = __builtin_amdgcn_make_buffer_rsrc((void*)f, (short)0, (int)(uint32_t)(N * 8), CAT_BUF_DW3);
+  const uint32_t pos0 = base + ((tid >> logC) << logSig) + j0 + (tid & (C - 1));
+  const double* itws = tb.itws + (size_t)prime * FTWS_ENTRIES;
+  double x[16];
+  {
+    const uint32_t q0 = base + ((16 * (tid >> logC)) << logSig) + j0 + (tid & (C - 1));
+#pragma unroll
+    for (int k = 0; k < 16; k++) x[brev_c(k, 4)] = buf_ldd(rf, (q0 + ((uint32_t)k << logSig)) * 8u, 0);
+  }
+  fidft<4, PS>(x, c);
+  if constexpr (LOGL > 4) {
+    const uint32_t s = slot16(tid, logC);
+#pragma unroll
+    for (int k = 0; k < 16; k++) lds[s + (k << logC)] = x[k];
+    __syncthreads();
+    if constexpr (LOGSR > 4) {
+      rest_inv<8, LOGSR, PS>(lds, logC, itws, c, tid);
+      __syncthreads();
+    }
+    last_inv<LR, LOGSR, PS>(lds, x, NT, logC, itws, c, tid);
+  }
+  if constexpr (FIRST) {
+    const MulDesc d = dv.get(m0_ + m);
+    const uint64_t L = ((uint64_t)d.la + d.lb + 1) / 2;
+    double* out = res + (size_t)prime * stride + d.r_off;
+    // positions at or past L fall outside the buffer's range: not written
+    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void*)out, (short)0, (int)(uint32_t)(L * 8), CAT_BUF_DW3);
+#pragma unroll
+    for (int i = 0; i < 16; i++) buf_std(rs, (pos0 + ((RI * i) << logSig)) * 8u, x[i]);
+    if (L > N && base == 0 && j0 == 0 && tid == 0) out[N] = 0.0;
+  } else {
+    const uint32_t fr = out_freq((base >> fg.logS) & ((1u << prevL) - 1), prevL) << (FNTT_MAX_LOGD - prevS);
+    Geo<PS> gw(tb.ilo + (size_t)prime * FTW2, tb.ihi + (size_t)prime * FTW2, (pos0 - base) * fr, (RI << logSig) * fr,
+               c.p, c.pinv);
+#pragma unroll
+    for (int i = 0; i < 16; i++) {
+      x[i] = mulm(red(x[i], c.p, c.pinv), gw.w[i & 3], c.p, c.pinv);
+      if ((i & 3) == 3 && i < 15) gw.step();
+      buf_std(rf, (pos0 + ((RI * i) << logSig)) * 8u, x[i]);
+    }
+  }
+}
+
+// Rows of 2^LOGD points of both operands: the column pass's twiddles, both
+// forward transforms, the pointwise product, the inverse transform and the
+// inverse twiddles.  Grid: rows of the batch x primes.  Bound by vector issue
+// and by HBM at once: 24 B per digit slot and prime, about 260 FP64
+// instructions.
+template <int LOGM, int PS>
+__global__ void __launch_bounds__((1 << LOGM) / 16) __attribute__((amdgpu_waves_per_eu(4)))
+k_frow(int logD, int logS, int logL, double* __restrict__ F, FTables tb) {
+  constexpr int LR = pass_logr(LOGM), LOGSR = LOGM - LR;
+  constexpr uint32_t M = 1u << LOGM, NT = M / 16;
+  __shared__ double lds[lds_pad(M)];
+  const uint32_t tid = threadIdx.x, prime = blockIdx.y;
+  const FPrime& c = c_fp[PS][prime];
+  const int logQ = logD - LOGM;
+  const uint64_t N = 1ull << logD;
+  const uint64_t m = blockIdx.x >> logQ;
+  const uint32_t q = blockIdx.x & ((1u << logQ) - 1);
+  double* fa = F + ((m * 3 + prime) * 2 + 0) * N + ((uint64_t)q << LOGM);
+  const double* fb = fa + N;
+  const double* tws = tb.tws + (size_t)prime * FTWS_ENTRIES;
+  const double* itws = tb.itws + (size_t)prime * FTWS_ENTRIES;
+  double a[16], b[16];
+#pragma unroll
+  for (int i = 0; i < 16; i++) {
+    a[i] = fa[tid + NT * i];
+    b[i] = fb[tid + NT * i];
+  }
+  // position j of row q takes omega_S^(j f), f the frequency of q
+  const uint32_t fr = out_freq(q & ((1u << logL) - 1), logL) << (FNTT_MAX_LOGD - logS);
+  {
+    Geo<PS> gw(tb.lo + (size_t)prime * FTW2, tb.hi + (size_t)prime * FTW2, tid * fr, NT * fr, c.p, c.pinv);
+#pragma unroll
+    for (int i = 0; i < 16; i++) {
+      a[i] = mulm(a[i], gw.w[i & 3], c.p, c.pinv);
+      b[i] = mulm(b[i], gw.w[i & 3], c.p, c.pinv);
+      if ((i & 3) == 3 && i < 15) gw.step();
+    }
+  }
+  first_fwd<LR, LOGSR, PS, false>(lds, a, NT, 0, tws, c, tid);
+  edge_sync<LR, LOGSR>(0);
+  rest_fwd<LOGSR, PS>(lds, 0, tws, c, tid);
+  load16<PS>(lds, a, tid, 0);
+  __syncthreads();
+  first_fwd<LR, LOGSR, PS, false>(lds, b, NT, 0, tws, c, tid);
+  edge_sync<LR, LOGSR>(0);
+  rest_fwd<LOGSR, PS>(lds, 0, tws, c, tid);
+  load16<PS>(lds, b, tid, 0);
+  fdft<4, PS, false>(a, c);
+  fdft<4, PS, false>(b, c);
+  pointwise16<PS>(a, b, c);
+  fidft<4, PS>(a, c);
+  {
+    const uint32_t s = slot16(tid, 0);
+#pragma unroll
+    for (int k = 0; k < 16; k++) lds[s + k] = a[k];
+  }
+  pass_sync(4, 0);
+  rest_inv<8, LOGSR, PS>(lds, 0, itws, c, tid);
+  edge_sync<LR, LOGSR>(0);
+  last_inv<LR, LOGSR, PS>(lds, a, NT, 0, itws, c, tid);
+  {
+    Geo<PS> gw(tb.ilo + (size_t)prime * FTW2, tb.ihi + (size_t)prime * FTW2, tid * fr, NT * fr, c.p, c.pinv);
+#pragma unroll
+    for (int i = 0; i < 16; i++) {
+      fa[tid + NT * i] = mulm(red(a[i], c.p, c.pinv), gw.w[i & 3], c.p, c.pinv);
+      if ((i & 3) == 3 && i < 15) gw.step();
+    }
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Recombination and carries.  V = x0 + p0 (x1 + p1 x2) < 2^153 by Garner's
+// method, as v0 + v1 2^64 + v2 2^128.
+__device__ __forceinline__ double canon(double x, double p, double pinv) {
+  x = red(x, p, pinv);
+  return x + (x < 0.0 ? p : 0.0);
+}
+// an integer 0 <= x < 2^52
+__device__ __forceinline__ uint64_t to_u52(double x) {
+  return (uint64_t)__double_as_longlong(x + 4503599627370496.0) & 0xFFFFFFFFFFFFFull;
+}
+__device__ __forceinline__ void fcrt_value(double r0, double r1, double r2, const FCrt& k, uint64_t& v0, uint64_t& v1,
+                                           uint32_t& v2) {
+  const double x0 = canon(mulc(r0, k.k00, k.k00q, k.p[0]), k.p[0], k.pinv[0]);
+  const double x1 = canon(mulc(r1, k.k11, k.k11q, k.p[1]) + mulc(x0, k.k10, k.k10q, k.p[1]), k.p[1], k.pinv[1]);
+  const double x2 = canon(mulc(r2, k.k22, k.k22q, k.p[2]) + (mulc(x0, k.k20, k.k20q, k.p[2]) +
+                                                             mulc(x1, k.k21, k.k21q, k.p[2])),
+                          k.p[2], k.pinv[2]);
+  const unsigned __int128 t = (unsigned __int128)k.pi[1] * to_u52(x2) + to_u52(x1);
+  const unsigned __int128 m1 = (unsigned __int128)k.pi[0] * (uint64_t)t + to_u52(x0);
+  const unsigned __int128 m2 = (unsigned __int128)k.pi[0] * (uint64_t)(t >> 64) + (uint64_t)(m1 >> 64);
+  v0 = (uint64_t)m1;
+  v1 = (uint64_t)m2;
+  v2 = (uint32_t)(m2 >> 64);
+}
+// s = a + b + c as s mod 2^64 and the carry h = s >> 64
+__device__ __forceinline__ uint64_t fcol_sum(uint64_t a, uint64_t b, uint64_t c, uint32_t* h) {
+  const uint64_t t = a + b, s = t + c;
+  *h = (t < a) + (s < c);
+  return s;
+}
+
+// Positions kb + E tid .. of a block, as in k_crt: digit k is v0(k) + v1(k-1)
+// + v2(k-2) plus carries; with s_k that sum, x_k = s_k mod 2^64, y_k = s_k >>
+// 64 and u_k = x_k + y_{k-1}, the carries left are binary.  The first wave
+// recomputes the CTX positions below the block for the left context; unless
+// every u of them propagates they also decide the carry into the block
+// (*spec: 0 or 1, else 2).
+#define FCRT_CTX 16
+__device__ __forceinline__ void fcrt_local(uint64_t len, const double* __restrict__ r0, const double* __restrict__ r1,
+                                           const double* __restrict__ r2, const FCrt& kc, uint64_t kb, uint4* xv,
+                                           uint32_t* tmp, uint64_t* ul, bool* gk, bool* Gt, bool* Pt, uint32_t* spec) {
+  static_assert(FCRT_E >= 3, "a thread's last column must lie inside the thread");
+  const uint32_t tid = threadIdx.x;
+  const uint64_t k0 = kb + (uint64_t)tid * FCRT_E;
+  const bool lctx = tid < FCRT_CTX && kb + tid >= FCRT_CTX;
+  double x0[FCRT_E], x1[FCRT_E], x2[FCRT_E], y0 = 0.0, y1 = 0.0, y2 = 0.0;
+  if (kb + FCRT_BLOCK <= len) {
+    // read once: non-temporal
+#pragma unroll
+    for (int i = 0; i < FCRT_E; i++) {
+      x0[i] = __builtin_nontemporal_load(r0 + k0 + i);
+      x1[i] = __builtin_nontemporal_load(r1 + k0 + i);
+      x2[i] = __builtin_nontemporal_load(r2 + k0 + i);
+    }
+  } else {
+#pragma unroll
+    for (int i = 0; i < FCRT_E; i++) {
+      const bool in = k0 + i < len;
+      const uint64_t kk = in ? k0 + i : 0;
+      x0[i] = in ? r0[kk] : 0.0;
+      x1[i] = in ? r1[kk] : 0.0;
+      x2[i] = in ? r2[kk] : 0.0;
+    }
+  }
+  if (lctx) {
+    y0 = r0[kb + tid - FCRT_CTX];
+    y1 = r1[kb + tid - FCRT_CTX];
+    y2 = r2[kb + tid - FCRT_CTX];
+  }
+  uint64_t a0[FCRT_E], a1[FCRT_E], lo[FCRT_E];
+  uint32_t a2[FCRT_E], h[FCRT_E];
+#pragma unroll
+  for (int i = 0; i < FCRT_E; i++) fcrt_value(x0[i], x1[i], x2[i], kc, a0[i], a1[i], a2[i]);
+#pragma unroll
+  for (int i = 2; i < FCRT_E; i++) lo[i] = fcol_sum(a0[i], a1[i - 1], a2[i - 2], &h[i]);
+  uint4 bctx = make_uint4(0, 0, 0, 0);
+  uint32_t sp = 2;
+  if (tid < 64) {
+    uint64_t c0, c1;
+    uint32_t c2;
+    fcrt_value(y0, y1, y2, kc, c0, c1, c2);
+    const uint64_t b1 = __shfl_up((unsigned long long)c1, 1, 64);
+    const uint32_t b2 = __shfl_up(c2, 1, 64), d2 = __shfl_up(c2, 2, 64);
+    uint32_t hh;
+    const uint64_t cl = fcol_sum(c0, b1, d2, &hh);          // column kb - CTX + tid (lanes >= 2)
+    const uint32_t hq = __shfl_up(hh, 1, 64);
+    const uint64_t cu = cl + hq;                            // u of it (lanes >= 3)
+    const bool g = cu < cl;
+    const bool valid = tid >= 3 && tid < FCRT_CTX;
+    const uint64_t gm = __ballot(valid && g);
+    const uint64_t dm = gm | __ballot(valid && !g && cu != ~0ull);
+    if (dm) sp = (uint32_t)((gm >> (63 - __builtin_clzll(dm))) & 1ull);
+    bctx = make_uint4((uint32_t)c1, (uint32_t)(c1 >> 32), c2 | (hh << 30), b2);
+  }
+  __syncthreads();   // xv may still be read by a previous call
+  // v2 < 2^26: the column's carry h <= 2 rides in the two bits above it
+  xv[tid + 1] = make_uint4((uint32_t)a1[FCRT_E - 1], (uint32_t)(a1[FCRT_E - 1] >> 32),
+                           a2[FCRT_E - 1] | (h[FCRT_E - 1] << 30), a2[FCRT_E - 2]);
+  if (tid == FCRT_CTX - 1) xv[0] = bctx;
+  if (tid == 0) *spec = sp;
+  __syncthreads();
+  const uint4 z = xv[tid];
+  const uint32_t zv2 = z.z & 0x3FFFFFFFu;
+  lo[0] = fcol_sum(a0[0], ((uint64_t)z.y << 32) | z.x, z.w, &h[0]);
+  lo[1] = fcol_sum(a0[1], a1[0], zv2, &h[1]);
+  bool G = false, P = true;
+  uint32_t hp = z.z >> 30;
+#pragma unroll
+  for (int i = 0; i < FCRT_E; i++) {
+    ul[i] = lo[i] + hp;
+    gk[i] = ul[i] < lo[i];
+    hp = h[i];
+    const bool pr = ul[i] == ~0ull;
+    G = gk[i] || (pr && G);
+    P = P && pr;
+  }
+  *Gt = G;
+  *Pt = P;
+  uint32_t cout;
+  bool ap;
+  wave_carry(G, P, 0, &cout, &ap);
+  if ((tid & 63) == 0) tmp[tid >> 6] = cout | (ap ? 2u : 0u);
+  __syncthreads();
+}
+__device__ __forceinline__ uint32_t fcrt_pair(const uint32_t* tmp) {
+  uint32_t bG = 0, bP = 1;
+  for (uint32_t w = 0; w < FCRT_THREADS / 64; w++) {
+    const uint32_t x = tmp[w];
+    bG = (x & 1u) | ((x >> 1) & bG);
+    bP = bP & (x >> 1);
+  }
+  return bG | (bP << 1);
+}
+
+struct FWords {
+  uint32_t w[2 * FCRT_E];
+};
+
+// Block b < nblk covers FCRT_BLOCK digits of one segment (out_pos and len in
+// limbs, res_pos in digits); blocks from nblk on copy tail ranges.  The carry
+// into a block and the look-back are those of k_crt.  Bound by HBM: 24 B read
+// and 8 B written per digit.
+__global__ void __launch_bounds__(FCRT_THREADS)
+k_fcrt(SegView sv, FCrt kc, const double* __restrict__ res, uint64_t stride, uint32_t* __restrict__ out, uint32_t nblk,
+       uint32_t* __restrict__ flags, uint32_t epoch, uint32_t polls, CopyList tails, const uint32_t* __restrict__ tin,
+       uint32_t* __restrict__ tout, uint32_t* __restrict__ err) {
+  __shared__ uint32_t tmp[FCRT_THREADS / 64], tmp2[FCRT_THREADS / 64];
+  __shared__ uint4 xv[FCRT_THREADS + 1];
+  __shared__ uint32_t s_state, s_pair, s_spec, s_spec2;
+  const uint32_t b = blockIdx.x, tid = threadIdx.x;
+  if (b >= nblk) {
+    copy_tail_block(tails, tin, tout, b - nblk);
+    return;
+  }
+  CrtSeg sg;
+  uint32_t first, end;
+  sv.find(b, &sg, &first, &end);
+  const uint64_t len = (sg.len + 1) / 2;
+  const double* r0 = res + sg.res_pos;
+  const double* r1 = r0 + stride;
+  const double* r2 = r1 + stride;
+  const uint64_t kb = (uint64_t)(b - first) * FCRT_BLOCK;
+  uint64_t ul[FCRT_E];
+  bool gk[FCRT_E], G, P;
+  fcrt_local(len, r0, r1, r2, kc, kb, xv, tmp, ul, gk, &G, &P, &s_spec);
+  const uint32_t own = fcrt_pair(tmp);
+  if (tid == 0)
+    __hip_atomic_store(flags + b, (epoch << 3) | (own << 1) | 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  uint32_t cin = 0, k = b;
+  bool done = (b == first);
+  if (!done && s_spec < 2u) {
+    cin = s_spec;
+    done = true;
+  }
+  while (!done) {
+    k--;
+    if (tid == 0) {
+      uint32_t f = 0;
+      for (uint32_t i = 0; i < polls; i++) {
+        f = __hip_atomic_load(flags + k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if ((f & 1u) && (f >> 3) == epoch) break;
+        f = 0;
+        __builtin_amdgcn_s_sleep(2);
+      }
+      s_state = f ? 1u : 2u;
+      s_pair = (f >> 1) & 3u;
+    }
+    __syncthreads();
+    const uint32_t state = s_state;
+    uint32_t pair = s_pair;
+    __syncthreads();
+    if (state == 2u) {
+      // not published yet: recompute block k's pair from its residues
+      uint64_t ul2[FCRT_E];
+      bool gk2[FCRT_E], G2, P2;
+      fcrt_local(len, r0, r1, r2, kc, (uint64_t)(k - first) * FCRT_BLOCK, xv, tmp2, ul2, gk2, &G2, &P2, &s_spec2);
+      pair = fcrt_pair(tmp2);
+    }
+    if (pair & 1u) { cin = 1; done = true; }           // block k generates a carry
+    else if (!(pair & 2u)) done = true;                 // block k absorbs any carry-in
+    else if (k == first) done = true;                   // all-propagate back to the start
+  }
+  if (tid == 0 && b + 1 == end && ((own & 1u) | ((own >> 1) & cin))) atomicOr(err, CAT_DEVERR_CARRY_OUT);
+  uint32_t wc = cin;
+  for (uint32_t w = 0; w < (tid >> 6); w++) {
+    const uint32_t x = tmp[w];
+    wc = (x & 1u) | ((x >> 1) & wc);
+  }
+  uint32_t cout;
+  bool ap;
+  uint32_t c = wave_carry(G, P, wc, &cout, &ap);
+  uint32_t* o = out + sg.out_pos;
+  const uint64_t w0 = 2 * (kb + (uint64_t)tid * FCRT_E);
+  FWords r;
+#pragma unroll
+  for (int i = 0; i < FCRT_E; i++) {
+    const uint64_t y = ul[i] + c;
+    c = (y < ul[i] || gk[i]) ? 1u : 0u;
+    r.w[2 * i] = (uint32_t)y;
+    r.w[2 * i + 1] = (uint32_t)(y >> 32);
+  }
+  if (2 * (kb + FCRT_BLOCK) <= sg.len) {
+    *(FWords*)(o + w0) = r;
+  } else {
+    bool over = false;
+#pragma unroll
+    for (int i = 0; i < 2 * FCRT_E; i++) {
+      if (w0 + i < sg.len) o[w0 + i] = r.w[i];
+      else over = over || r.w[i] != 0;
+    }
+    if (over) atomicOr(err, CAT_DEVERR_CARRY_OUT);     // a limb past la + lb
+  }
+}
+
+// ------------------------------------------------------------------ host side
+static const uint64_t kPF[2][CAT_NPRIMES] = {{1125900443713537ull, 1125905745313793ull, 1125906550620161ull},
+                                             {2251800350556161ull, 2251801155862529ull, 2251803907325953ull}};
+static const uint64_t kGF[2][CAT_NPRIMES] = {{5, 3, 6}, {6, 3, 5}};   // primitive roots
+
+uint64_t mulmod64(uint64_t a, uint64_t b, uint64_t p) { return (uint64_t)((unsigned __int128)a * b % p); }
+uint64_t powmod64(uint64_t b, uint64_t e, uint64_t p) {
+  uint64_t r = 1;
+  for (; e; e >>= 1) {
+    if (e & 1) r = mulmod64(r, b, p);
+    b = mulmod64(b, b, p);
+  }
+  return r;
+}
+uint64_t invmod64(uint64_t a, uint64_t p) { return powmod64(a % p, p - 2, p); }
+double balanced(uint64_t x, uint64_t p) { return x > p / 2 ? -(double)(p - x) : (double)x; }
+
+void fill_powers(uint64_t w, uint64_t p, size_t n, double* out) {
+  uint64_t x = 1;
+  for (size_t i = 0; i < n; i++) {
+    out[i] = balanced(x, p);
+    x = mulmod64(x, w, p);
+  }
+}
+
+FCrt g_crt[FNTT_MAX_LOGD + 1];
+
+FCrt make_crt(int logD) {
+  const uint64_t* P = kPF[fntt_set(logD)];
+  FCrt k{};
+  for (int i = 0; i < 3; i++) {
+    k.p[i] = (double)P[i];
+    k.pinv[i] = 1.0 / (double)P[i];
+  }
+  k.pi[0] = P[0];
+  k.pi[1] = P[1];
+  auto put = [&](uint64_t v, int i, double* c, double* q) {
+    *c = balanced(v % P[i], P[i]);
+    *q = *c / (double)P[i];
+  };
+  uint64_t s[3];
+  for (int i = 0; i < 3; i++) s[i] = invmod64(1ull << logD, P[i]);
+  const uint64_t c01 = invmod64(P[0] % P[1], P[1]);
+  const uint64_t c12 = invmod64(P[1] % P[2], P[2]);
+  const uint64_t c012 = mulmod64(invmod64(P[0] % P[2], P[2]), c12, P[2]);
+  put(s[0], 0, &k.k00, &k.k00q);
+  put(mulmod64(s[1], c01, P[1]), 1, &k.k11, &k.k11q);
+  put(P[1] - c01, 1, &k.k10, &k.k10q);
+  put(mulmod64(s[2], c012, P[2]), 2, &k.k22, &k.k22q);
+  put(P[2] - c012, 2, &k.k20, &k.k20q);
+  put(P[2] - c12, 2, &k.k21, &k.k21q);
+  return k;
+}
+
+#define FCHK(x)                        \
+  do {                                 \
+    const hipError_t e_ = (x);         \
+    if (e_ != hipSuccess) return e_;   \
+  } while (0)
+
+hipError_t upload(const std::vector<double>& h, const double** d) {
+  void* q = nullptr;
+  FCHK(hipMalloc(&q, h.size() * sizeof(double)));
+  FCHK(hipMemcpy(q, h.data(), h.size() * sizeof(double), hipMemcpyHostToDevice));
+  *d = (const double*)q;
+  return hipSuccess;
+}
+
+}  // namespace
+
+hipError_t fntt_init() {
+  FPrime fp[2][CAT_NPRIMES];
+  for (int s = 0; s < 2; s++) {
+    std::vector<double> tws[2], lo[2], hi[2];
+    for (int d = 0; d < 2; d++) {
+      tws[d].assign((size_t)CAT_NPRIMES * FTWS_ENTRIES, 1.0);
+      lo[d].resize((size_t)CAT_NPRIMES * FTW2);
+      hi[d].resize((size_t)CAT_NPRIMES * FTW2);
+    }
+    for (int i = 0; i < CAT_NPRIMES; i++) {
+      const uint64_t p = kPF[s][i];
+      const uint64_t w = powmod64(kGF[s][i], (p - 1) >> FNTT_MAX_LOGD, p);
+      if (powmod64(w, 1ull << (FNTT_MAX_LOGD - 1), p) != p - 1) return hipErrorUnknown;
+      FPrime& c = fp[s][i];
+      c.p = (double)p;
+      c.pinv = 1.0 / (double)p;
+      for (int d = 0; d < 2; d++) {
+        const uint64_t r = d ? invmod64(w, p) : w;
+        double* cw = d ? c.iw : c.w;
+        double* cq = d ? c.iwp : c.wp;
+        fill_powers(powmod64(r, 1ull << (FNTT_MAX_LOGD - 4), p), p, 8, cw);
+        for (int k = 0; k < 8; k++) cq[k] = cw[k] / c.p;
+        // pass tables: omega_S^(j k) over j < S / R, k < R, R the pass's radix
+        std::vector<double> pw(1u << 14);
+        for (int ls = 1; ls <= 14; ls++) {
+          const uint32_t S = 1u << ls;
+          fill_powers(powmod64(r, 1ull << (FNTT_MAX_LOGD - ls), p), p, S, pw.data());
+          const int lr = pass_logr(ls), lsr = ls - lr;
+          double* t = &tws[d][(size_t)i * FTWS_ENTRIES + S - 2];
+          for (uint32_t k = 0; k < (1u << lr); k++)
+            for (uint32_t j = 0; j < (1u << lsr); j++) t[(k << lsr) + j] = pw[(uint64_t)j * k % S];
+        }
+        fill_powers(r, p, FTW2, &lo[d][(size_t)i * FTW2]);
+        fill_powers(powmod64(r, FTW2, p), p, FTW2, &hi[d][(size_t)i * FTW2]);
+      }
+    }
+    FTables& t = g_ft[s];
+    FCHK(upload(tws[0], &t.tws));
+    FCHK(upload(tws[1], &t.itws));
+    FCHK(upload(lo[0], &t.lo));
+    FCHK(upload(lo[1], &t.ilo));
+    FCHK(upload(hi[0], &t.hi));
+    FCHK(upload(hi[1], &t.ihi));
+  }
+  for (int l = 0; l <= FNTT_MAX_LOGD; l++) g_crt[l] = make_crt(l);
+  return hipMemcpyToSymbol(HIP_SYMBOL(c_fp), fp, sizeof(fp));
+}
+
+hipError_t fntt_lds(const FBatch& b, hipStream_t st) {
+  const int lt = b.logD < 12 ? 12 : b.logD;
+  const uint64_t per = 1ull << (lt - b.logD);
+  const uint64_t tiles = (b.cnt + per - 1) / per;
+  const dim3 grid((uint32_t)(tiles * CAT_NPRIMES)), block((1u << lt) / 16);
+#define L(X)                                                                                                     \
+  case X:                                                                                                        \
+    hipLaunchKernelGGL(k_flds<X>, grid, block, 0, st, b.dv, b.m0, b.cnt, b.ain, b.bin, b.res, b.stride, g_ft[0]); \
+    break
+  switch (b.logD) {
+    L(5); L(6); L(7); L(8); L(9); L(10); L(11); L(12); L(13); L(14);
+    default: return hipErrorInvalidValue;
+  }
+#undef L
+  return hipGetLastError();
+}
+
+template <int LOGL, int PS>
+static void col_fwd_launch(const FBatch& b, int logS, bool first, int prevS, int prevL, hipStream_t st) {
+  constexpr int LOGT = LOGL <= 8 ? 12 : 13;
+  const FGeom fg{b.logD, logS, LOGT - LOGL};
+  const dim3 grid((uint32_t)((b.cnt << (b.logD - LOGT)) * CAT_NPRIMES), 1, 2), block((1u << LOGT) / 16);
+  if (first)
+    hipLaunchKernelGGL((k_fcol_fwd<LOGL, PS, true>), grid, block, 0, st, b.dv, fg, b.m0, prevS, prevL, b.ain, b.bin,
+                       b.F, g_ft[PS]);
+  else
+    hipLaunchKernelGGL((k_fcol_fwd<LOGL, PS, false>), grid, block, 0, st, b.dv, fg, b.m0, prevS, prevL, b.ain, b.bin,
+                       b.F, g_ft[PS]);
+}
+template <int LOGL, int PS>
+static void col_inv_launch(const FBatch& b, int logS, bool first, int prevS, int prevL, hipStream_t st) {
+  constexpr int LOGT = LOGL <= 8 ? 12 : 13;
+  const FGeom fg{b.logD, logS, LOGT - LOGL};
+  const dim3 grid((uint32_t)(b.cnt << (b.logD - LOGT)), CAT_NPRIMES), block((1u << LOGT) / 16);
+  if (first)
+    hipLaunchKernelGGL((k_fcol_inv<LOGL, PS, true>), grid, block, 0, st, b.dv, fg, b.m0, prevS, prevL, b.F, b.res,
+                       b.stride, g_ft[PS]);
+  else
+    hipLaunchKernelGGL((k_fcol_inv<LOGL, PS, false>), grid, block, 0, st, b.dv, fg, b.m0, prevS, prevL, b.F, b.res,
+                       b.stride, g_ft[PS]);
+}
+#define COL_SWITCH(FN)                                         \
+  if (fntt_set(b.logD) == 0) {                                 \
+    switch (logL) {                                            \
+      case 4: FN<4, 0>(b, logS, first, prevS, prevL, st); break;   \
+      case 5: FN<5, 0>(b, logS, first, prevS, prevL, st); break;   \
+      case 6: FN<6, 0>(b, logS, first, prevS, prevL, st); break;   \
+      case 7: FN<7, 0>(b, logS, first, prevS, prevL, st); break;   \
+      case 8: FN<8, 0>(b, logS, first, prevS, prevL, st); break;   \
+      case 9: FN<9, 0>(b, logS, first, prevS, prevL, st); break;   \
+      case 10: FN<10, 0>(b, logS, first, prevS, prevL, st); break; \
+      default: return hipErrorInvalidValue;                    \
+    }                                                          \
+  } else {                                                     \
+    switch (logL) {                                            \
+      case 4: FN<4, 1>(b, logS, first, prevS, prevL, st); break;   \
+      case 5: FN<5, 1>(b, logS, first, prevS, prevL, st); break;   \
+      case 6: FN<6, 1>(b, logS, first, prevS, prevL, st); break;   \
+      case 7: FN<7, 1>(b, logS, first, prevS, prevL, st); break;   \
+      case 8: FN<8, 1>(b, logS, first, prevS, prevL, st); break;   \
+      case 9: FN<9, 1>(b, logS, first, prevS, prevL, st); break;   \
+      case 10: FN<10, 1>(b, logS, first, prevS, prevL, st); break; \
+      default: return hipErrorInvalidValue;                    \
+    }                                                          \
+  }                                                            \
+  return hipGetLastError()
+
+hipError_t fntt_col_fwd(const FBatch& b, int logS, int logL, bool first, int prevS, int prevL, hipStream_t st) {
+  COL_SWITCH(col_fwd_launch);
+}
+hipError_t fntt_col_inv(const FBatch& b, int logS, int logL, bool first, int prevS, int prevL, hipStream_t st) {
+  COL_SWITCH(col_inv_launch);
+}
+
+template <int LOGM>
+static void row_launch(const FBatch& b, int logS, int logL, hipStream_t st) {
+  const dim3 grid((uint32_t)(b.cnt << (b.logD - LOGM)), CAT_NPRIMES), block((1u << LOGM) / 16);
+  if (fntt_set(b.logD) == 0)
+    hipLaunchKernelGGL((k_frow<LOGM, 0>), grid, block, 0, st, b.logD, logS, logL, b.F, g_ft[0]);
+  else
+    hipLaunchKernelGGL((k_frow<LOGM, 1>), grid, block, 0, st, b.logD, logS, logL, b.F, g_ft[1]);
+}
+hipError_t fntt_row(const FBatch& b, int logM, int logS, int logL, hipStream_t st) {
+  switch (logM) {
+    case 10: row_launch<10>(b, logS, logL, st); break;
+    case 11: row_launch<11>(b, logS, logL, st); break;
+    case 12: row_launch<12>(b, logS, logL, st); break;
+    case 13: row_launch<13>(b, logS, logL, st); break;
+    default: return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
+}
+
+hipError_t fntt_crt(const SegView& sv, int logD, const double* res, uint64_t stride, uint32_t* out, uint32_t nblk,
+                    uint32_t* flags, uint32_t epoch, uint32_t polls, const CopyList& tails, const uint32_t* tin,
+                    uint32_t* tout, uint32_t* err, hipStream_t st) {
+  hipLaunchKernelGGL(k_fcrt, dim3(nblk + tail_blocks(tails)), dim3(FCRT_THREADS), 0, st, sv, g_crt[logD], res, stride,
+                     out, nblk, flags, epoch, polls, tails, tin, tout, err);
+  return hipGetLastError();
+}

@@ -1,0 +1,50 @@
+// Host interface of the floating-point transform kernels (fntt.hip).
+#pragma once
+#include "common.hpp"
+
+#define FNTT_MAX_LOGD 26       // longest transform (64-bit digits): products of up to 2^27 limbs
+#define FNTT_SMALL_MAX_LOGD 23 // longest transform of prime set 0 (primes just above 2^50)
+#define FNTT_LDS_MIN_LOGD 5    // one-workgroup transforms
+#define FNTT_LDS_MAX_LOGD 14
+#define FNTT_ROW_MIN 10        // four-step rows
+#define FNTT_ROW_MAX 13
+#define FNTT_COL_MIN 4         // column DFTs
+#define FNTT_COL_MAX 10
+#define FCRT_E 3               // digits per thread of the carry kernel
+#define FCRT_THREADS 256
+#define FCRT_BLOCK (FCRT_E * FCRT_THREADS)
+
+struct SegView;
+
+// prime set of a transform of 2^logD digits
+inline int fntt_set(int logD) { return logD <= FNTT_SMALL_MAX_LOGD ? 0 : 1; }
+
+// Constants and twiddle tables (on the current device); once per process.
+hipError_t fntt_init();
+
+// One transform batch: products m0 .. m0 + cnt of `dv`, 2^logD digits each.
+// Residues (unreduced, times 2^logD) go to res[prime * stride + r_off + k].
+struct FBatch {
+  DescView dv;
+  uint64_t m0, cnt;
+  int logD;
+  const uint32_t* ain;
+  const uint32_t* bin;
+  double* F;             // four-step scratch: 6 * cnt * 2^logD doubles
+  double* res;
+  uint64_t stride;       // doubles between the residues of two primes
+};
+
+hipError_t fntt_lds(const FBatch& b, hipStream_t st);
+// column pass over sub-problems of 2^logS digits, L = 2^logL of them along the
+// column; outer (prevS, prevL): the pass before it, whose twiddles this pass
+// applies (0: none).  first: the operands come from limbs, the results go to
+// the residues.
+hipError_t fntt_col_fwd(const FBatch& b, int logS, int logL, bool first, int prevS, int prevL, hipStream_t st);
+hipError_t fntt_col_inv(const FBatch& b, int logS, int logL, bool first, int prevS, int prevL, hipStream_t st);
+// rows of 2^logM digits under a column pass of sub-problems 2^logS, length 2^logL
+hipError_t fntt_row(const FBatch& b, int logM, int logS, int logL, hipStream_t st);
+// residues -> limbs with carries (blocks [0, nblk) of sv; res_pos in digits)
+hipError_t fntt_crt(const SegView& sv, int logD, const double* res, uint64_t stride, uint32_t* out, uint32_t nblk,
+                    uint32_t* flags, uint32_t epoch, uint32_t polls, const CopyList& tails, const uint32_t* tin,
+                    uint32_t* tout, uint32_t* err, hipStream_t st);

@@ -265,6 +265,7 @@ cat_status init_locked(int device) {
   HIPCHK(hipSetDevice(device));
   STCHK(init_prime_set(0, kP, kGen, CAT_MAX_LOGN));
   STCHK(init_prime_set(1, kQ, kQGen, CAT_LAZY_MAX_LOGN));
+  HIPCHK(fntt_init());
   HIPCHK(hipDeviceSynchronize());
   HIPCHK(hipHostMalloc(&g.pin, 1 << 16, hipHostMallocDefault));
   // the device's own copy of the static scratch (the device is current here)
@@ -395,8 +396,13 @@ void classify(uint64_t la, uint64_t lb, int* cls, int* logN) {
   *logN = c.logN;
 }
 
+// Transforms on the FP64 units (fntt.hip) for every transform bucket, or the
+// integer transforms only (cat_lazy_primes_set below its default).
+bool g_fp = true;
+
 struct Stage {
   int cls = CLS_SCHOOL;
+  bool fp = false;         // FP64 transforms: residues are doubles, positions in 64-bit digits
   int logN = 0;
   int logM = CAT_LDS_LOGT;   // four-step row length
   int maxL = 10;             // four-step column-pass limit
@@ -459,11 +465,22 @@ MulDesc tree_desc(const TreeLevel& t, uint64_t i) {
   d.a_off = t.base[gi] + 2 * il * sz;
   d.b_off = d.a_off + sz;
   d.c_off = d.a_off;
-  d.r_off = d.a_off;
+  d.r_off = t.rbase[gi] + ((2 * il * sz) >> t.rshift);
   d.la = (uint32_t)sz;
   const uint64_t rem = t.K[gi] - (2 * il + 1) * sz;
   d.lb = (uint32_t)(rem < sz ? rem : sz);
   return d;
+}
+
+// does a stage of this class run on the FP64 transforms?
+bool use_fp(int cls) { return g_fp && (cls == CLS_LDS || cls == CLS_LARGE); }
+// room that a product (or segment) of `limbs` limbs takes in the residue
+// arrays: limbs, or 64-bit digits on the FP64 path
+uint64_t res_units(bool fp, uint64_t limbs) { return fp ? (limbs + 1) / 2 : limbs; }
+uint64_t res_words(bool fp, uint64_t units) { return fp ? 2 * units : units; }
+uint32_t crt_blocks(bool fp, uint64_t limbs) {
+  return fp ? (uint32_t)((res_units(true, limbs) + FCRT_BLOCK - 1) / FCRT_BLOCK)
+            : (uint32_t)((limbs + CAT_CRT_BLOCK - 1) / CAT_CRT_BLOCK);
 }
 
 void build_crt_segs(Stage& s) {
@@ -471,7 +488,7 @@ void build_crt_segs(Stage& s) {
   uint32_t b = 0;
   for (const CrtSeg& sg : s.host_segs) {
     s.host_pref.push_back(b);
-    const uint64_t nb = (sg.len + CAT_CRT_BLOCK - 1) / CAT_CRT_BLOCK;
+    const uint64_t nb = crt_blocks(s.fp, sg.len);
     b += (uint32_t)nb;
   }
   s.host_pref.push_back(b);
@@ -522,6 +539,9 @@ Layout layout_finish(Layout L) {
   // residues of one stage: by default bounded by everything the tree and the
   // post area can hold; callers with long power chains set a tighter bound
   if (L.res_len == 0) L.res_len = std::max(L.Kmax, L.post_cap) + 64;
+  // 64-bit digits: every group's residues may start and end one limb further
+  L.res_len = align_up(L.res_len + 3 * CAT_MAX_GROUPS, 2);
+  L.res2_len = align_up(L.res2_len, 2);
   const uint64_t big = 1ull << ceil_log2(L.res_len);
   L.F_words = (big > (1ull << CAT_LDS_LOGT)) ? 12 * big + (1ull << 20) : (1ull << 20);
   L.nblk_max = L.res_len / CAT_CRT_BLOCK + 4096;
@@ -789,6 +809,16 @@ void plan_tree(const Layout& Ly, Plan& P, bool batched) {
     t.j = (uint32_t)j;
     uint64_t m = 0;
     s.tails.n = 0;
+    {
+      const Cls c = classify2(1ull << j, 1ull << j);
+      s.cls = c.cls;
+      s.logN = c.logN;
+      s.logM = c.logM;
+      s.maxL = c.maxL;
+      s.fp = use_fp(s.cls);
+    }
+    t.rshift = s.fp ? 1 : 0;
+    uint64_t rnext = 0;   // digits
     for (uint32_t gi = 0; gi < ng; gi++) {
       const uint64_t K = gK(gi, j), b = gpos(gi, j);
       const uint64_t nodes = (K + (1ull << j) - 1) >> j;
@@ -805,19 +835,16 @@ void plan_tree(const Layout& Ly, Plan& P, bool batched) {
       }
       // CRT segment: this group's products, contiguous from its base
       const uint64_t seglen = std::min<uint64_t>(K, (nodes / 2) * (2ull << j));
-      if (nodes / 2 > 0) s.host_segs.push_back(CrtSeg{b, b, seglen});
+      t.rbase[gi] = s.fp ? rnext : b;
+      if (nodes / 2 > 0) {
+        s.host_segs.push_back(CrtSeg{b, t.rbase[gi], seglen});
+        rnext += res_units(s.fp, seglen);
+      }
     }
     t.mpref[ng] = m;
     s.nmul = m;
     s.limbs = 0;
     for (const CrtSeg& sg : s.host_segs) s.limbs += sg.len;
-    {
-      const Cls c = classify2(1ull << j, 1ull << j);
-      s.cls = c.cls;
-      s.logN = c.logN;
-      s.logM = c.logM;
-      s.maxL = c.maxL;
-    }
     s.a_base = s.b_base = in_of(j);
     s.c_base = out_of(j) + dout;
     s.tail_in_base = in_of(j);
@@ -891,6 +918,7 @@ void add_products(Plan& P, std::vector<std::pair<Item, Item>>& pairs, std::vecto
     s.logN = cc.logN;
     s.logM = cc.logM;
     s.maxL = cc.maxL;
+    s.fp = use_fp(cc.cls);
     MulDesc d;
     d.a_off = a.pos;
     d.b_off = b.pos;
@@ -912,12 +940,13 @@ void add_products(Plan& P, std::vector<std::pair<Item, Item>>& pairs, std::vecto
       t.logN = s.logN;
       t.logM = s.logM;
       t.maxL = s.maxL;
+      t.fp = s.fp;
       const size_t k1 = std::min(s.host_desc.size(), k0 + CAT_INLINE_DESC);
       uint64_t r = 0;
       for (size_t k = k0; k < k1; k++) {
         MulDesc d = s.host_desc[k];
         d.r_off = r;
-        r += (uint64_t)d.la + d.lb;
+        r += res_units(t.fp, (uint64_t)d.la + d.lb);
         t.host_desc.push_back(d);
         t.host_segs.push_back(CrtSeg{d.c_off, d.r_off, (uint64_t)d.la + d.lb});
         t.limbs += (uint64_t)d.la + d.lb;
@@ -1254,7 +1283,8 @@ cat_status make_plan(const Layout& Ly, const GroupTable& gt, Plan** out, bool de
       return CAT_ERANGE;
     }
     uint64_t rmax = 0;
-    for (const CrtSeg& sg : s->host_segs) rmax = std::max(rmax, sg.res_pos + sg.len);
+    for (const CrtSeg& sg : s->host_segs)
+      rmax = std::max(rmax, res_words(s->fp, sg.res_pos + res_units(s->fp, sg.len)));
     const uint64_t fneed = (s->cls == CLS_LARGE) ? s->nmul * 6ull << s->logN : 0;
     if (rmax > Ly.res_len || fneed > Ly.F_words || s->nblk > Ly.nblk_max) {
       free_plan(P);
@@ -1266,7 +1296,7 @@ cat_status make_plan(const Layout& Ly, const GroupTable& gt, Plan** out, bool de
   for (size_t k = 0; k < P->post_final && P->fork_count >= 0; k++) {
     const Stage& s = P->post[k];
     uint64_t rmax = 0;
-    for (const CrtSeg& sg : s.host_segs) rmax = std::max(rmax, sg.res_pos + sg.len);
+    for (const CrtSeg& sg : s.host_segs) rmax = std::max(rmax, res_words(s.fp, sg.res_pos + res_units(s.fp, sg.len)));
     const uint64_t fneed = (s.cls == CLS_LARGE) ? s.nmul * 6ull << s.logN : 0;
     if (rmax > Ly.res2_len || fneed > Ly.F2_words || s.nblk > Ly.nblk2_max) P->fork_count = -1;
   }
@@ -1308,11 +1338,20 @@ struct Exec {
 };
 
 cat_status launch_crt(Exec& X, uint32_t* out, SegView sv, uint32_t nblk, const CopyList* tails = nullptr,
-                      const uint32_t* tin = nullptr, uint32_t* tout = nullptr, bool raw = false, int as = 0) {
+                      const uint32_t* tin = nullptr, uint32_t* tout = nullptr, bool raw = false, int as = 0,
+                      int fp_logD = -1) {
   static const CopyList none{};
   const CopyList& cl = tails ? *tails : none;
   const uint32_t grid = nblk + tail_blocks(cl);
   if (grid == 0) return CAT_OK;
+  if (fp_logD >= 0) {
+    KTime kt("k_fcrt", X.st, (double)nblk * FCRT_BLOCK);
+    X.crt_epoch++;
+    HIPCHK(fntt_crt(sv, fp_logD, (const double*)X.res, X.res_stride / 2, out, nblk, X.flags, X.crt_epoch,
+                    crt_polls(nblk), cl, tin, tout, X.err, X.st));
+    X.launches++;
+    return CAT_OK;
+  }
   {
     KTime kt("k_crt", X.st, (double)nblk * CAT_CRT_BLOCK);
     X.crt_epoch++;
@@ -1349,6 +1388,55 @@ cat_status launch_crt10(Exec& X, uint32_t* out, const SegView& sv, uint32_t nblk
 
 // Products of a stage given by `dv` (cnt of them): the NTT or schoolbook part.
 uint32_t* out_base(Exec& X, const Stage& s) { return X.C ? X.C : X.W + s.c_base; }
+
+// The FP64 transform of products m0 .. m0 + cnt of `dv` (transforms of
+// 2^(logN - 1) digits), up to the residues.
+// One workgroup up to 2^FP_ONE_MAX digits, whatever class the bucket has.
+#define FP_ONE_MAX 13
+cat_status launch_fp(Exec& X, const Stage& s, const DescView& dv, uint64_t cnt) {
+  FBatch b;
+  b.dv = dv;
+  b.m0 = 0;
+  b.cnt = cnt;
+  b.logD = s.logN - 1;
+  b.ain = X.A ? X.A : X.W + s.a_base;
+  b.bin = X.B ? X.B : X.W + s.b_base;
+  b.F = (double*)X.F;
+  b.res = (double*)X.res;
+  b.stride = X.res_stride / 2;
+  if (b.logD <= FP_ONE_MAX) {
+    KTime kt("k_flds", X.st, bfly(9.0 * cnt, b.logD));
+    HIPCHK(fntt_lds(b, X.st));
+    X.launches++;
+    return CAT_OK;
+  }
+  // rows of the schedule's length, leaving column DFTs of 2^4 at least
+  const int logM = std::min({std::max(s.logM, FNTT_ROW_MIN), FNTT_ROW_MAX, b.logD - FNTT_COL_MIN});
+  const int rest = b.logD - logM;
+  const int maxL = std::min(std::max(s.maxL, 2 * FNTT_COL_MIN), FNTT_COL_MAX);
+  const int P = (rest + maxL - 1) / maxL;
+  int logL[4] = {}, logS[4] = {};
+  for (int k = 0, ls = b.logD; k < P; k++) {
+    logL[k] = rest / P + (k < rest % P ? 1 : 0);
+    logS[k] = ls;
+    ls -= logL[k];
+  }
+  const double N = (double)(1ull << b.logD);
+  for (int k = 0; k < P; k++) {
+    KTime kt("k_fcol_fwd", X.st, 6.0 * cnt * N / 2 * logL[k]);
+    HIPCHK(fntt_col_fwd(b, logS[k], logL[k], k == 0, k ? logS[k - 1] : 0, k ? logL[k - 1] : 0, X.st));
+  }
+  {
+    KTime kt("k_frow", X.st, bfly(9.0 * cnt * (1ull << rest), logM));
+    HIPCHK(fntt_row(b, logM, logS[P - 1], logL[P - 1], X.st));
+  }
+  for (int k = P - 1; k >= 0; k--) {
+    KTime kt("k_fcol_inv", X.st, 3.0 * cnt * N / 2 * logL[k]);
+    HIPCHK(fntt_col_inv(b, logS[k], logL[k], k == 0, k ? logS[k - 1] : 0, k ? logL[k - 1] : 0, X.st));
+  }
+  X.launches += 2 * P + 1;
+  return CAT_OK;
+}
 
 // prime set of a transform stage (radix-10^9 products keep the first set,
 // whose CRT kernel carries in that radix)
@@ -1397,6 +1485,7 @@ cat_status launch_products(Exec& X, const Stage& s, DescView dv, uint64_t cnt, b
     X.launches++;
     return CAT_OK;
   }
+  if (s.fp) return launch_fp(X, s, dv, cnt);
   const int as = stage_as(s);
   const NttTables tb = tables_for(as);
   const uint2 s0 = scale_pair(0, s.logN, as), s1 = scale_pair(1, s.logN, as), s2 = scale_pair(2, s.logN, as);
@@ -1609,7 +1698,7 @@ cat_status run_stage_batched(Exec& X, const Stage& s) {
     STCHK(launch_products(X, s, s.dv, s.nmul, s.cls == CLS_SCHOOL));
     if (s.cls != CLS_SCHOOL)
       STCHK(launch_crt(X, out_base(X, s), stage_segs(s), s.nblk, &s.tails, X.W + s.tail_in_base,
-                       X.W + s.tail_out_base, s.cls == CLS_COLSUM, stage_as(s)));
+                       X.W + s.tail_out_base, s.cls == CLS_COLSUM, stage_as(s), s.fp ? s.logN - 1 : -1));
     return CAT_OK;
   }
   return copy_tails(X, s);
@@ -1635,6 +1724,8 @@ cat_status run_stage_plain(Exec& X, const Stage& s) {
       one.tree.K[0] = (uint64_t)d.la + d.lb;
       one.tree.mpref[0] = 0;
       one.tree.mpref[1] = 1;
+      one.tree.rbase[0] = d.r_off;
+      one.tree.rshift = s.dv.tree.rshift;
     }
     STCHK(launch_products(X, s, one, 1));
     if (s.cls != CLS_SCHOOL) {
@@ -1642,10 +1733,11 @@ cat_status run_stage_plain(Exec& X, const Stage& s) {
       sv.segs = nullptr;
       sv.nseg = 1;
       sv.iseg[0] = CrtSeg{d.c_off, d.r_off, (uint64_t)d.la + d.lb};
-      const uint32_t nb = (uint32_t)((sv.iseg[0].len + CAT_CRT_BLOCK - 1) / CAT_CRT_BLOCK);
+      const uint32_t nb = crt_blocks(s.fp, sv.iseg[0].len);
       sv.ipref[0] = 0;
       sv.ipref[1] = nb;
-      STCHK(launch_crt(X, out_base(X, s), sv, nb, nullptr, nullptr, nullptr, s.cls == CLS_COLSUM, stage_as(s)));
+      STCHK(launch_crt(X, out_base(X, s), sv, nb, nullptr, nullptr, nullptr, s.cls == CLS_COLSUM, stage_as(s),
+                       s.fp ? s.logN - 1 : -1));
     }
   }
   return copy_tails(X, s);
@@ -1913,11 +2005,12 @@ cat_status mul_plan_create(uint32_t batch, const uint64_t* a_off, const uint64_t
     st.logN = cc.logN;
     st.logM = cc.logM;
     st.maxL = cc.maxL;
+    st.fp = use_fp(cc.cls);
     MulDesc d;
     d.a_off = a_off[i];
     d.b_off = b_off[i];
     d.c_off = c_off[i];
-    d.r_off = st.limbs;
+    d.r_off = st.host_segs.empty() ? 0 : st.host_segs.back().res_pos + res_units(st.fp, st.host_segs.back().len);
     d.la = (uint32_t)la;
     d.lb = (uint32_t)lb;
     st.host_desc.push_back(d);
@@ -1929,7 +2022,9 @@ cat_status mul_plan_create(uint32_t batch, const uint64_t* a_off, const uint64_t
     Stage& st = kv.second;
     st.nmul = st.host_desc.size();
     build_crt_segs(st);
-    if (st.cls != CLS_SCHOOL) M->res_len = std::max(M->res_len, st.limbs);
+    if (st.cls != CLS_SCHOOL)
+      M->res_len = std::max(M->res_len, res_words(st.fp, st.host_segs.back().res_pos +
+                                                             res_units(st.fp, st.host_segs.back().len)));
     if (st.cls == CLS_LARGE) M->F_words = std::max<uint64_t>(M->F_words, st.nmul * 6ull << st.logN);
     nblk = std::max<uint64_t>(nblk, st.nblk);
     M->products += st.nmul;
@@ -1937,6 +2032,7 @@ cat_status mul_plan_create(uint32_t batch, const uint64_t* a_off, const uint64_t
     M->stages.push_back(st);
   }
   M->nblk_max = nblk + 1;
+  M->res_len = align_up(M->res_len, 2);
   // the one-workgroup buckets of up to 2^g_fuse_logn coefficients in one
   // fused launch (batched form, while they hold at most FUSE_MAX_LEAVES
   // coefficient slots: beyond that the per-bucket launches run at higher
@@ -2627,6 +2723,7 @@ cat_status cat_lazy_primes_set(uint32_t max_logn) {
   std::lock_guard<std::recursive_mutex> lk(g.mu);
   if (max_logn > CAT_LAZY_MAX_LOGN) return CAT_EINVAL;
   g_lazy_logn = max_logn;
+  g_fp = max_logn == CAT_LAZY_MAX_LOGN;
   // cached plans and their graphs were made with the old setting
   if (!g.plans.empty() || !g.noalloc_plans.empty()) HIPCHK(hipDeviceSynchronize());
   for (auto& kv : g.plans) free_plan(kv.second);

@@ -58,15 +58,6 @@ __device__ __forceinline__ uint32_t tw_mul(uint32_t a, uint32_t w, uint32_t ws, 
   else return shoup(a, w, ws, p);
 }
 
-// bit reversal of an r-bit index, compile-time
-__host__ __device__ constexpr int brev_c(int x, int r) {
-  int y = 0;
-  for (int i = 0; i < r; i++) y |= ((x >> i) & 1) << (r - 1 - i);
-  return y;
-}
-
-__host__ __device__ constexpr uint32_t lds_pad(uint32_t i) { return i + (i >> 4); }
-
 // Radix-R DFT on registers, decimation in frequency: natural input, output
 // y[k] in v[brev(k)].  Set 1: inputs and outputs in [0, 2q); a butterfly
 // gives red(a + b) and (a - b + 2q) * w (the sum below 4q, the Shoup product
@@ -178,29 +169,12 @@ __device__ __forceinline__ uint32_t group_base(uint32_t g, uint32_t logSR, uint3
 // (kept in scalar registers: the table pointer is the same for a whole wave),
 // with the uniform part (k1 << logSR) as the scalar offset and the lane's j2
 // as the vector offset, so no per-read 64-bit address arithmetic is spent.
-// Word 3 of the gfx9 descriptor: 32-bit data format, which untyped loads use
-// for nothing but the range check against the table size.
-#define CAT_BUF_DW3 0x00020000
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t tw_rsrc(const uint2* tw, uint32_t entries) {
   return __builtin_amdgcn_make_buffer_rsrc((void*)tw, (short)0, (int)(entries * (uint32_t)sizeof(uint2)), CAT_BUF_DW3);
 }
 __device__ __forceinline__ uint2 tw_at(__amdgpu_buffer_rsrc_t rs, uint32_t k1, uint32_t logSR, uint32_t jo) {
   const auto v = __builtin_amdgcn_raw_buffer_load_b64(rs, jo, (int)((k1 << logSR) * (uint32_t)sizeof(uint2)), 0);
   return make_uint2(v[0], v[1]);
-}
-
-// Word arrays read and written through raw buffer resources with byte
-// offsets in one VGPR: loads past the array's end return 0 and stores there
-// are dropped (the range check of an unswizzled buffer), which the column
-// kernels use for the zero padding of their operands and the end of a product.
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t words_rsrc(const uint32_t* p, uint64_t words) {
-  return __builtin_amdgcn_make_buffer_rsrc((void*)p, (short)0, (int)(uint32_t)(words * 4u), CAT_BUF_DW3);
-}
-__device__ __forceinline__ uint32_t buf_ld(__amdgpu_buffer_rsrc_t r, uint32_t byte_off) {
-  return __builtin_amdgcn_raw_buffer_load_b32(r, (int)byte_off, 0, 0);
-}
-__device__ __forceinline__ void buf_st(__amdgpu_buffer_rsrc_t r, uint32_t byte_off, uint32_t v) {
-  __builtin_amdgcn_raw_buffer_store_b32(v, r, (int)byte_off, 0, 0);
 }
 
 template <int LOGR, bool PAD, int U, int AS, bool ZHI = false>
@@ -297,28 +271,10 @@ __device__ __forceinline__ void pass_inv(uint32_t* lds, uint32_t ngroups, uint32
   for (; g < ngroups; g += nthr) groups_inv<LOGR, PAD, 1, AS>(lds, g, nthr, logSR, logC, itw, pc);
 }
 
-// radix of the pass at sub-problem size 2^logS
-__host__ __device__ constexpr int pass_logr(int logS) { return (logS % 4) ? (logS % 4) : 4; }
 // offset of the table of size 2^s inside a per-prime pass-table block
 __host__ __device__ constexpr uint32_t tws_off(int s) { return (1u << s) - 2u; }
 #define CAT_LDS_MAX_LOGT 14  // largest transform held by one workgroup (both operands, 2^14 each)
 #define TWS_ENTRIES 32766u   // sum over s = 1..14 of 2^s
-
-// Synchronisation between two radix-16 passes.  Both have total/16 groups,
-// and the 2^logSmall elements of a sub-problem of the smaller size are written
-// and read by the same 2^logSmall consecutive groups, i.e. consecutive
-// threads; in a plain vector (logC = 0) with 2^logSmall <= 64 those sit in one
-// wave, which orders its own LDS traffic, so no workgroup barrier is needed.
-// (Next to a pass of smaller radix the group counts differ: full barrier.)
-__device__ __forceinline__ void pass_sync(int logSmall, uint32_t logC) {
-  if (logC == 0 && logSmall <= 6) {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-  } else {
-    __syncthreads();
-  }
-}
 
 // Full forward transform of size 2^logS on every sub-problem of an LDS tile
 // with `total` elements (all columns), passes from size 2^logS down.  On
@@ -391,33 +347,6 @@ __device__ __forceinline__ void ntt_inv_tile(uint32_t* lds, int logS, uint32_t t
     }
   }
   __syncthreads();
-}
-
-// frequency held at output position q of the pass-structured transform of size 2^logS
-__device__ __forceinline__ uint32_t out_freq(uint32_t q, int logS) {
-  uint32_t f = 0, mult = 1;
-  while (logS > 0) {
-    const int r = pass_logr(logS);
-    const int rest = logS - r;
-    const uint32_t k1 = q >> rest;
-    f += k1 * mult;
-    mult <<= r;
-    q &= (1u << rest) - 1;
-    logS = rest;
-  }
-  return f;
-}
-
-// Workgroups are dealt round-robin to the 8 XCDs (each with its own L2) in
-// the order of their linear index.  Neighbouring column tiles share cache
-// lines (a tile row is C words), so block b of a grid of G is renumbered to
-// put consecutive tiles on one XCD: XCD x gets the tiles
-// [x ceil(G/8), ...) in order (a bijection of [0, G) for any G).
-#define CAT_XCDS 8
-__device__ __forceinline__ uint32_t xcd_remap(uint32_t b, uint32_t G) {
-  const uint32_t q = G / CAT_XCDS, r = G % CAT_XCDS;
-  const uint32_t x = b % CAT_XCDS, k = b / CAT_XCDS;
-  return x < r ? x * (q + 1) + k : r * (q + 1) + (x - r) * q + k;
 }
 
 struct NttTables {
@@ -1570,65 +1499,6 @@ __device__ __forceinline__ void garner3(uint32_t r0, uint32_t r1, uint32_t r2, u
 // s_k = v0(k)+v1(k-1)+v2(k-2) < 3*2^32, x_k = s_k mod 2^32, y_k = s_k >> 32,
 // u_k = x_k + y_{k-1} <= 2^32 + 1 and the remaining carries are binary:
 // generate g_k = (u_k >= 2^32), propagate p_k = (u_k == 2^32 - 1).
-
-// Wave-level: carry into each lane for (g, p) with wave carry-in `cin`;
-// returns lane's carry in, and the wave carry out in *cout.
-__device__ __forceinline__ uint32_t wave_carry(bool g, bool pr, uint32_t cin, uint32_t* cout, bool* allprop) {
-  const uint64_t gm = __ballot(g), pm = __ballot(pr);
-  const uint64_t a = gm, b = gm | pm;
-  const uint64_t s1 = a + b;
-  const uint64_t c1 = s1 < a;
-  const uint64_t s2 = s1 + cin;
-  const uint64_t c2 = s2 < s1;
-  *cout = (uint32_t)(c1 | c2);
-  *allprop = (pm == ~0ull);
-  const uint64_t cm = s2 ^ pm;   // carry into each bit position
-  return (uint32_t)((cm >> (threadIdx.x & 63)) & 1ull);
-}
-
-// Segments of a CRT launch: device tables (many segments) or up to
-// CAT_INLINE_SEG segments carried in the kernel arguments.
-#define CAT_INLINE_SEG 32
-struct SegView {
-  const CrtSeg* segs;        // nullptr => inline tables
-  const uint32_t* pref;      // pref[s] = first block of segment s (nseg+1 entries)
-  const uint32_t* b2s;       // with segs: the segment of every block (one load, no search)
-  uint32_t nseg;
-  uint32_t ubl;              // > 0: uniform segments of ubl blocks each (below)
-  CrtSeg iseg[CAT_INLINE_SEG];
-  uint32_t ipref[CAT_INLINE_SEG + 1];
-  // uniform: segment s is iseg[0] with out_pos, res_pos and add_pos advanced
-  // by s * ustep[0], s * iseg[0].len and s * ustep[1]
-  uint64_t ustep[2];
-  __device__ __forceinline__ void find(uint32_t b, CrtSeg* sg, uint32_t* first, uint32_t* end,
-                                       uint32_t* segi = nullptr) const {
-    if (ubl) {
-      const uint32_t q = b / ubl;
-      *sg = iseg[0];
-      sg->out_pos += q * ustep[0];
-      sg->res_pos += q * iseg[0].len;
-      sg->add_pos += q * ustep[1];
-      *first = q * ubl;
-      *end = *first + ubl;
-      if (segi) *segi = q;
-      return;
-    }
-    const uint32_t* pr = segs ? pref : ipref;
-    uint32_t lo = 0, hi = nseg;   // pr[lo] <= b < pr[lo+1]
-    if (segs && b2s) {
-      lo = b2s[b];
-    } else {
-      while (hi - lo > 1) {
-        const uint32_t mid = (lo + hi) >> 1;
-        if (pr[mid] <= b) lo = mid; else hi = mid;
-      }
-    }
-    *sg = segs ? segs[lo] : iseg[lo];
-    *first = pr[lo];
-    *end = pr[lo + 1];
-    if (segi) *segi = lo;
-  }
-};
 
 // CRT + carry.  Workgroup b < nblk covers CAT_CRT_BLOCK limbs of one segment;
 // workgroups from nblk on copy tail ranges.  The carry into a block follows
