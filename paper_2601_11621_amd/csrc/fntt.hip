@@ -39,13 +39,13 @@
 // of up to 2^22 digits, that is transforms of up to 2^23 points; set 1 (above
 // 2^51) up to 2^25 digits, transforms of up to 2^26.
 //
-// Transform structure: passes of radix 16 (the first of radix 2^(log2 S mod
-// 4)) on registers, one thread holding 16 values, with LDS between the passes.
-// A transform of up to 2^14 points runs in one workgroup (k_flds); longer ones
-// are cut in rows of 2^10 .. 2^13 points and column DFTs of 2^4 .. 2^10 points
-// (Bailey 1990).  Both operands of a product pass through the same LDS buffer,
-// the first one's outputs waiting in registers, so a workgroup of T/16 threads
-// needs 8 T bytes of LDS: four waves per SIMD at 128 registers.
+// Transform structure: passes of radix 16 or 8 (the first of radix 2^(log2 S
+// mod 4), or mod 3) on registers, one thread holding as many values, with LDS
+// between the passes.  A transform of up to 2^14 points runs in one workgroup
+// (k_flds); longer ones are cut in rows of 2^10 .. 2^13 points and column DFTs
+// of 2^4 .. 2^10 points (Bailey 1990).  Both operands of a product pass through
+// the same LDS buffer, the first one's outputs waiting in registers, so a
+// transform of T points needs 8 T bytes of LDS.
 #include "fntt.hpp"
 
 #include <vector>
@@ -74,6 +74,8 @@ struct FCrt {
 #define FTW2_BITS 13u          // two-level table: omega_{2^26}^y = hi[y >> 13] lo[y mod 2^13]
 #define FTW2 (1u << FTW2_BITS)
 struct FTables {
+  const double* tws3;          // the same for passes of radix 8
+  const double* itws3;
   const double* tws;           // [prime][FTWS_ENTRIES]: [2^s - 2 + (k << logSR) + j] = omega_S^(j k)
   const double* itws;
   const double* lo;            // [prime][FTW2]
@@ -184,7 +186,7 @@ __device__ __forceinline__ void buf_std(__amdgpu_buffer_rsrc_t r, uint32_t voff,
   u[1] = (uint32_t)__double2hiint(x);
   __builtin_amdgcn_raw_buffer_store_b64(u, r, (int)voff, 0, 0);
 }
-template <int LOGR>
+template <int LOGR, int LE>
 __device__ __forceinline__ void ptw(double* v, const double* tws, int logSR, uint32_t j, const FPrime& c) {
   constexpr int R = 1 << LOGR;
   const __amdgpu_buffer_rsrc_t rs = ftw_rsrc(tws + ((1u << (logSR + LOGR)) - 2u), (uint32_t)R << logSR);
@@ -203,71 +205,74 @@ __device__ __forceinline__ double digit(uint32_t lo, uint32_t hi, double p, doub
 }
 
 // ------------------------------------------------------ passes in a workgroup
-// LDS element e of a tile of C = 2^logC columns (1: a plain vector) sits at
-// (e + e/16) C + column.  Every radix-16 pass after the first has one group
-// per thread: thread t = (h, c), h = t / C; its group in sub-problems of S =
-// 16 SR elements is j = h mod SR of sub-problem h / SR.
-template <int LOGSR, int PS>
+// A thread holds E = 2^LE values (LE = 3 or 4).  LDS element e of a tile of C =
+// 2^logC columns (1: a plain vector) sits at (e + e/E) C + column.  Every
+// radix-E pass after the first has one group per thread: thread t = (h, c), h
+// = t / C; its group in sub-problems of S = E SR elements is j = h mod SR of
+// sub-problem h / SR.
+template <int LE>
+__device__ __forceinline__ constexpr uint32_t fpad(uint32_t i) { return i + (i >> LE); }
+// radix (log2) of the pass at sub-problem size 2^logS
+template <int LE>
+__host__ __device__ constexpr int fpass(int logS) { return (logS % LE) ? (logS % LE) : LE; }
+
+template <int LE, int LOGSR, int PS>
 __device__ __forceinline__ void mid_fwd(double* lds, uint32_t logC, const double* tws, const FPrime& c, uint32_t tid) {
-  constexpr uint32_t SR = 1u << LOGSR;
+  constexpr uint32_t SR = 1u << LOGSR, E = 1u << LE;
   const uint32_t h = tid >> logC, j = h & (SR - 1);
-  const uint32_t b = (lds_pad(((h >> LOGSR) << (LOGSR + 4)) + j) << logC) + (tid & ((1u << logC) - 1));
-  const uint32_t st = (SR + SR / 16) << logC;
-  double v[16];
+  const uint32_t b = (fpad<LE>(((h >> LOGSR) << (LOGSR + LE)) + j) << logC) + (tid & ((1u << logC) - 1));
+  const uint32_t st = (SR + SR / E) << logC;
+  double v[E];
 #pragma unroll
-  for (int k = 0; k < 16; k++) v[k] = lds[b + k * st];
-  fdft<4, PS, false>(v, c);
-  ptw<4>(v, tws, LOGSR, j, c);
+  for (int k = 0; k < (int)E; k++) v[k] = lds[b + k * st];
+  fdft<LE, PS, false>(v, c);
+  ptw<LE, LE>(v, tws, LOGSR, j, c);
 #pragma unroll
-  for (int k = 0; k < 16; k++) lds[b + k * st] = v[brev_c(k, 4)];
+  for (int k = 0; k < (int)E; k++) lds[b + k * st] = v[brev_c(k, LE)];
 }
-template <int LOGSR, int PS>
+template <int LE, int LOGSR, int PS>
 __device__ __forceinline__ void mid_inv(double* lds, uint32_t logC, const double* itws, const FPrime& c, uint32_t tid) {
-  constexpr uint32_t SR = 1u << LOGSR;
+  constexpr uint32_t SR = 1u << LOGSR, E = 1u << LE;
   const uint32_t h = tid >> logC, j = h & (SR - 1);
-  const uint32_t b = (lds_pad(((h >> LOGSR) << (LOGSR + 4)) + j) << logC) + (tid & ((1u << logC) - 1));
-  const uint32_t st = (SR + SR / 16) << logC;
-  double v[16];
+  const uint32_t b = (fpad<LE>(((h >> LOGSR) << (LOGSR + LE)) + j) << logC) + (tid & ((1u << logC) - 1));
+  const uint32_t st = (SR + SR / E) << logC;
+  double v[E];
 #pragma unroll
-  for (int k = 0; k < 16; k++) v[brev_c(k, 4)] = lds[b + k * st];
-  ptw<4>(v, itws, LOGSR, j, c);
-  fidft<4, PS>(v, c);
+  for (int k = 0; k < (int)E; k++) v[brev_c(k, LE)] = lds[b + k * st];
+  ptw<LE, LE>(v, itws, LOGSR, j, c);
+  fidft<LE, PS>(v, c);
 #pragma unroll
-  for (int k = 0; k < 16; k++) lds[b + k * st] = v[k];
+  for (int k = 0; k < (int)E; k++) lds[b + k * st] = v[k];
 }
-// Passes of a transform of 2^LOGS points below its first one (which left
-// sub-problems of 2^(LOGS - LR), a multiple of four bits): radix-16 passes
-// through LDS until sub-problems of 16 are left, which each thread then takes
-// into registers.
-template <int LOGSUB, int PS>
+// Passes below the first one, which left sub-problems of 2^LOGSUB points
+// (LOGSUB a multiple of LE): radix-E passes through LDS until sub-problems of
+// E are left, which each thread then takes into registers.
+template <int LE, int LOGSUB, int PS>
 __device__ __forceinline__ void rest_fwd(double* lds, uint32_t logC, const double* tws, const FPrime& c, uint32_t tid) {
-  if constexpr (LOGSUB > 4) {
-    mid_fwd<LOGSUB - 4, PS>(lds, logC, tws, c, tid);
-    pass_sync(LOGSUB - 4, logC);
-    rest_fwd<LOGSUB - 4, PS>(lds, logC, tws, c, tid);
+  if constexpr (LOGSUB > LE) {
+    mid_fwd<LE, LOGSUB - LE, PS>(lds, logC, tws, c, tid);
+    pass_sync(LOGSUB - LE, logC);
+    rest_fwd<LE, LOGSUB - LE, PS>(lds, logC, tws, c, tid);
   }
 }
 // the inverse of rest_fwd, each pass followed by its synchronisation except
 // the last, which the caller does
-template <int LOGSUB, int LOGTOP, int PS>
+template <int LE, int LOGSUB, int LOGTOP, int PS>
 __device__ __forceinline__ void rest_inv(double* lds, uint32_t logC, const double* itws, const FPrime& c, uint32_t tid) {
   if constexpr (LOGSUB <= LOGTOP) {
-    mid_inv<LOGSUB - 4, PS>(lds, logC, itws, c, tid);
+    mid_inv<LE, LOGSUB - LE, PS>(lds, logC, itws, c, tid);
     if constexpr (LOGSUB < LOGTOP) pass_sync(LOGSUB, logC);
-    rest_inv<LOGSUB + 4, LOGTOP, PS>(lds, logC, itws, c, tid);
+    rest_inv<LE, LOGSUB + LE, LOGTOP, PS>(lds, logC, itws, c, tid);
   }
 }
-__device__ __forceinline__ uint32_t slot16(uint32_t tid, uint32_t logC) {
-  return (lds_pad(16 * (tid >> logC)) << logC) + (tid & ((1u << logC) - 1));
-}
 
-// First forward pass (radix 2^LR) of a tile whose elements i = 0 .. 15 of a
-// thread are the groups d + D k, D = 16 / R: group d holds x[d + D k], k < R,
-// and is group j of sub-problem `blk` (element positions j + SR k).
-template <int LR, int LOGSR, int PS, bool ZHI>
-__device__ __forceinline__ void first_fwd(double* lds, double* x, uint32_t NT, uint32_t logC, const double* tws,
+// First forward pass (radix 2^LR) of a tile whose elements i < E of a thread
+// are the groups d + D k, D = E / R: group d holds x[d + D k], k < R, and is
+// group j of its sub-problem (element positions j + SR k).
+template <int LE, int LR, int LOGSR, int PS, bool ZHI>
+__device__ __forceinline__ void first_fwd(double* lds, const double* x, uint32_t NT, uint32_t logC, const double* tws,
                                           const FPrime& c, uint32_t tid) {
-  constexpr int R = 1 << LR, D = 16 / R;
+  constexpr int R = 1 << LR, D = (1 << LE) / R;
   constexpr uint32_t SR = 1u << LOGSR;
 #pragma unroll
   for (int d = 0; d < D; d++) {
@@ -276,26 +281,26 @@ __device__ __forceinline__ void first_fwd(double* lds, double* x, uint32_t NT, u
 #pragma unroll
     for (int k = 0; k < R; k++) v[k] = (ZHI && k >= R / 2) ? 0.0 : x[d + D * k];
     fdft<LR, PS, ZHI>(v, c);
-    ptw<LR>(v, tws, LOGSR, j, c);
-    const uint32_t b = (lds_pad(((h >> LOGSR) << (LOGSR + LR)) + j) << logC) + (g & ((1u << logC) - 1));
+    ptw<LR, LE>(v, tws, LOGSR, j, c);
+    const uint32_t b = (fpad<LE>(((h >> LOGSR) << (LOGSR + LR)) + j) << logC) + (g & ((1u << logC) - 1));
 #pragma unroll
-    for (int k = 0; k < R; k++) lds[b + k * ((SR + SR / 16) << logC)] = v[brev_c(k, LR)];
+    for (int k = 0; k < R; k++) lds[b + k * ((SR + (SR >> LE)) << logC)] = v[brev_c(k, LR)];
   }
 }
 // Last inverse pass into x[d + D k].
-template <int LR, int LOGSR, int PS>
+template <int LE, int LR, int LOGSR, int PS>
 __device__ __forceinline__ void last_inv(const double* lds, double* x, uint32_t NT, uint32_t logC, const double* itws,
                                          const FPrime& c, uint32_t tid) {
-  constexpr int R = 1 << LR, D = 16 / R;
+  constexpr int R = 1 << LR, D = (1 << LE) / R;
   constexpr uint32_t SR = 1u << LOGSR;
 #pragma unroll
   for (int d = 0; d < D; d++) {
     const uint32_t g = tid + NT * d, h = g >> logC, j = h & (SR - 1);
-    const uint32_t b = (lds_pad(((h >> LOGSR) << (LOGSR + LR)) + j) << logC) + (g & ((1u << logC) - 1));
+    const uint32_t b = (fpad<LE>(((h >> LOGSR) << (LOGSR + LR)) + j) << logC) + (g & ((1u << logC) - 1));
     double v[R];
 #pragma unroll
-    for (int k = 0; k < R; k++) v[brev_c(k, LR)] = lds[b + k * ((SR + SR / 16) << logC)];
-    ptw<LR>(v, itws, LOGSR, j, c);
+    for (int k = 0; k < R; k++) v[brev_c(k, LR)] = lds[b + k * ((SR + (SR >> LE)) << logC)];
+    ptw<LR, LE>(v, itws, LOGSR, j, c);
     fidft<LR, PS>(v, c);
 #pragma unroll
     for (int k = 0; k < R; k++) x[d + D * k] = v[k];
@@ -303,22 +308,53 @@ __device__ __forceinline__ void last_inv(const double* lds, double* x, uint32_t 
 }
 // The synchronisation next to the pass of radix 2^LR over sub-problems of
 // 2^LOGSR: wave-local only when that pass too has one group per thread.
-template <int LR, int LOGSR>
-__device__ __forceinline__ void edge_sync(uint32_t logC) {
-  if constexpr (LR == 4) pass_sync(LOGSR, logC);
+template <int LE, int LR, int LOGSR>
+__device__ __forceinline__ void edge_sync() {
+  if constexpr (LR == LE) pass_sync(LOGSR, 0);
   else __syncthreads();
 }
-template <int PS>
-__device__ __forceinline__ void load16(const double* lds, double* v, uint32_t tid, uint32_t logC) {
-  const uint32_t b = slot16(tid, logC);
+// the E consecutive slots of a thread
+template <int LE>
+__device__ __forceinline__ void slots_load(const double* lds, double* v, uint32_t tid, uint32_t logC) {
+  const uint32_t b = (fpad<LE>((tid >> logC) << LE) << logC) + (tid & ((1u << logC) - 1));
 #pragma unroll
-  for (int k = 0; k < 16; k++) v[k] = lds[b + (k << logC)];
+  for (int k = 0; k < (1 << LE); k++) v[k] = lds[b + (k << logC)];
 }
-// y[k] in v[brev(k)] times w[k] likewise, then the inverse DFT of the 16 slots
-template <int PS>
-__device__ __forceinline__ void pointwise16(double* a, const double* b, const FPrime& c) {
+template <int LE>
+__device__ __forceinline__ void slots_store(double* lds, const double* v, uint32_t tid, uint32_t logC) {
+  const uint32_t b = (fpad<LE>((tid >> logC) << LE) << logC) + (tid & ((1u << logC) - 1));
 #pragma unroll
-  for (int k = 0; k < 16; k++) a[k] = mulm(red(a[k], c.p, c.pinv), b[k], c.p, c.pinv);
+  for (int k = 0; k < (1 << LE); k++) lds[b + (k << logC)] = v[k];
+}
+// the passes of one operand of a plain vector, from the values x of its first
+// pass to the outputs of the last one in v
+template <int LE, int LOGN, int PS, bool ZHI>
+__device__ __forceinline__ void vec_fwd(double* lds, const double* x, double* v, uint32_t NT, const double* tws,
+                                        const FPrime& c, uint32_t tid) {
+  constexpr int LR = fpass<LE>(LOGN), LOGSR = LOGN - LR;
+  first_fwd<LE, LR, LOGSR, PS, ZHI>(lds, x, NT, 0, tws, c, tid);
+  edge_sync<LE, LR, LOGSR>();
+  rest_fwd<LE, LOGSR, PS>(lds, 0, tws, c, tid);
+  slots_load<LE>(lds, v, tid, 0);
+}
+// a (outputs of the last but one pass of the first operand), b (of the second)
+// -> their product's inverse transform, in the order of the first pass
+template <int LE, int LOGN, int PS>
+__device__ __forceinline__ void vec_mul_inv(double* lds, double* a, double* b, uint32_t NT, const double* itws,
+                                            const FPrime& c, uint32_t tid) {
+  constexpr int LR = fpass<LE>(LOGN), LOGSR = LOGN - LR;
+  fdft<LE, PS, false>(a, c);
+  fdft<LE, PS, false>(b, c);
+#pragma unroll
+  for (int k = 0; k < (1 << LE); k++) a[k] = mulm(red(a[k], c.p, c.pinv), b[k], c.p, c.pinv);
+  fidft<LE, PS>(a, c);
+  slots_store<LE>(lds, a, tid, 0);
+  if constexpr (LOGSR > LE) {
+    pass_sync(LE, 0);
+    rest_inv<LE, 2 * LE, LOGSR, PS>(lds, 0, itws, c, tid);
+  }
+  edge_sync<LE, LR, LOGSR>();
+  last_inv<LE, LR, LOGSR, PS>(lds, a, NT, 0, itws, c, tid);
 }
 
 // Twiddles theta^(e0 + step i), i = 0 .. 15, times the 16 values of one or two
@@ -362,15 +398,25 @@ __device__ __forceinline__ uint2 limb2(__amdgpu_buffer_rsrc_t rs, uint32_t byte_
 // Whole products in one workgroup, transforms of 2^LOGD digits.  A tile holds
 // 2^LOGT slots (2^12 at least, 2^(LOGT - LOGD) products); grid: 3 x tiles,
 // renumbered so that each XCD takes a contiguous run of (tile, prime) pairs
-// and the three primes of a tile read the operands once from HBM.
-template <int LOGD>
-__global__ void __launch_bounds__((1 << (LOGD < 12 ? 12 : LOGD)) / 16) __attribute__((amdgpu_waves_per_eu(4)))
+// and the three primes of a tile read the operands once from HBM.  ZHI: no
+// operand of the batch is longer than N/2 digits.
+constexpr int flds_tile(int logD) { return logD < 12 ? 12 : logD; }
+// Values per thread: 8 (radix-8 passes, at most 66 registers, six or more waves
+// per SIMD) up to 2^13 digits, 16 at 2^14, where a workgroup has 1,024 threads.
+// Against 16 everywhere (four waves): C(10^5) 0.238 -> 0.230 ms, C(10^7) 0.619
+// -> 0.600, the 4,096-product batch 2.24 -> 2.18.  The rows of the four-step
+// path, which are bound by vector issue and HBM and not by latency, lose 3 %
+// with 8 (their twiddle loads and LDS passes weigh more): they keep 16.
+constexpr int flds_le(int logD) { return logD <= 13 ? 3 : 4; }
+template <int LOGD, bool ZHI>
+__global__ void __launch_bounds__((1 << flds_tile(LOGD)) >> flds_le(LOGD))
+    __attribute__((amdgpu_waves_per_eu(flds_le(LOGD) == 3 ? 6 : 4)))
 k_flds(DescView dv, uint64_t m0_, uint64_t nmul, const uint32_t* __restrict__ ain, const uint32_t* __restrict__ bin,
        double* __restrict__ res, uint64_t stride, FTables tb) {
-  constexpr int LOGT = LOGD < 12 ? 12 : LOGD, LR = pass_logr(LOGD), LOGSR = LOGD - LR;
-  constexpr uint32_t T = 1u << LOGT, NT = T / 16, N = 1u << LOGD, PER = T / N, SR = 1u << LOGSR;
-  constexpr int R = 1 << LR, D = 16 / R;
-  __shared__ double lds[lds_pad(T)];
+  constexpr int LOGT = flds_tile(LOGD), LE = flds_le(LOGD), LR = fpass<LE>(LOGD), LOGSR = LOGD - LR;
+  constexpr uint32_t T = 1u << LOGT, NT = T >> LE, N = 1u << LOGD, PER = T / N, SR = 1u << LOGSR;
+  constexpr int R = 1 << LR, E = 1 << LE, D = E / R;
+  __shared__ double lds[fpad<LE>(T)];
   __shared__ MulDesc ds[PER];
   const uint32_t tid = threadIdx.x;
   const uint32_t wid = xcd_remap(blockIdx.x, gridDim.x);
@@ -378,100 +424,56 @@ k_flds(DescView dv, uint64_t m0_, uint64_t nmul, const uint32_t* __restrict__ ai
   const FPrime& c = c_fp[0][prime];
   const uint64_t m0 = (uint64_t)(wid / CAT_NPRIMES) * PER;
   const uint32_t cnt = (uint32_t)min((uint64_t)PER, nmul - m0);
-  bool half = true;
   for (uint32_t i = tid; i < PER; i += NT) {
     MulDesc d{};   // slots without a product: empty operands
     if (i < cnt) d = dv.get(m0_ + m0 + i);
     ds[i] = d;
-    half = half && d.la <= N && d.lb <= N;   // at most N/2 digits each
   }
-  const bool zhi = __syncthreads_and(half ? 1 : 0) != 0;
-  const double* tws = tb.tws + (size_t)prime * FTWS_ENTRIES;
-  const double* itws = tb.itws + (size_t)prime * FTWS_ENTRIES;
-  double a[16], b[16];
+  __syncthreads();
+  const double* tws = (LE == 3 ? tb.tws3 : tb.tws) + (size_t)prime * FTWS_ENTRIES;
+  const double* itws = (LE == 3 ? tb.itws3 : tb.itws) + (size_t)prime * FTWS_ENTRIES;
+  double a[E], b[E];
   // thread t holds the elements t + NT i = group d of the first pass at k
   // (i = d + D k): position j + SR k of product blk
-  if (zhi) {
-    uint2 ra[8], rb[8];
+  constexpr int RK = ZHI ? R / 2 : R, NR = ZHI ? E / 2 : E;
+  uint2 ra[NR], rb[NR];
 #pragma unroll
-    for (int d = 0; d < D; d++) {
-      const uint32_t g = tid + NT * d, j = g & (SR - 1);
-      const MulDesc m = ds[g >> LOGSR];
+  for (int d = 0; d < D; d++) {
+    const uint32_t g = tid + NT * d, j = g & (SR - 1);
+    const MulDesc& m = ds[g >> LOGSR];
+    const uint32_t la = m.la, lb = m.lb;
+    const uint32_t *sa = ain + m.a_off, *sb = bin + m.b_off;
 #pragma unroll
-      for (int k = 0; k < R / 2; k++) {
-        const uint32_t q = 2 * (j + SR * k);
-        const uint32_t la = m.la, lb = m.lb;
-        const uint64_t qa0 = q < la ? q : 0, qa1 = q + 1 < la ? q + 1 : 0;
-        const uint64_t qb0 = q < lb ? q : 0, qb1 = q + 1 < lb ? q + 1 : 0;
-        uint2 x = make_uint2(ain[m.a_off + qa0], ain[m.a_off + qa1]);
-        uint2 y = make_uint2(bin[m.b_off + qb0], bin[m.b_off + qb1]);
-        x.x = q < la ? x.x : 0u;
-        x.y = q + 1 < la ? x.y : 0u;
-        y.x = q < lb ? y.x : 0u;
-        y.y = q + 1 < lb ? y.y : 0u;
-        ra[d + D * k] = x;
-        rb[d + D * k] = y;
-      }
+    for (int k = 0; k < RK; k++) {
+      // clamped addresses and masks: every load is issued at once
+      const uint32_t q = 2 * (j + SR * k);
+      const uint32_t x0 = sa[q < la ? q : 0], x1 = sa[q + 1 < la ? q + 1 : 0];
+      const uint32_t y0 = sb[q < lb ? q : 0], y1 = sb[q + 1 < lb ? q + 1 : 0];
+      ra[d + D * k] = make_uint2(q < la ? x0 : 0u, q + 1 < la ? x1 : 0u);
+      rb[d + D * k] = make_uint2(q < lb ? y0 : 0u, q + 1 < lb ? y1 : 0u);
     }
-#pragma unroll
-    for (int i = 0; i < 8; i++) {
-      a[i] = digit(ra[i].x, ra[i].y, c.p, c.pinv);
-      b[i] = digit(rb[i].x, rb[i].y, c.p, c.pinv);
-    }
-    first_fwd<LR, LOGSR, 0, true>(lds, a, NT, 0, tws, c, tid);
-  } else {
-#pragma unroll
-    for (int d = 0; d < D; d++) {
-      const uint32_t g = tid + NT * d, j = g & (SR - 1);
-      const MulDesc m = ds[g >> LOGSR];
-#pragma unroll
-      for (int k = 0; k < R; k++) {
-        const uint32_t q = 2 * (j + SR * k);
-        const uint32_t la = m.la, lb = m.lb;
-        const uint32_t x0 = q < la ? ain[m.a_off + q] : 0u, x1 = q + 1 < la ? ain[m.a_off + q + 1] : 0u;
-        const uint32_t y0 = q < lb ? bin[m.b_off + q] : 0u, y1 = q + 1 < lb ? bin[m.b_off + q + 1] : 0u;
-        a[d + D * k] = digit(x0, x1, c.p, c.pinv);
-        b[d + D * k] = digit(y0, y1, c.p, c.pinv);
-      }
-    }
-    first_fwd<LR, LOGSR, 0, false>(lds, a, NT, 0, tws, c, tid);
   }
-  edge_sync<LR, LOGSR>(0);
-  rest_fwd<LOGSR, 0>(lds, 0, tws, c, tid);
-  load16<0>(lds, a, tid, 0);
+#pragma unroll
+  for (int i = 0; i < NR; i++) a[i] = digit(ra[i].x, ra[i].y, c.p, c.pinv);
+  vec_fwd<LE, LOGD, 0, ZHI>(lds, a, a, NT, tws, c, tid);
   __syncthreads();
-  if (zhi) first_fwd<LR, LOGSR, 0, true>(lds, b, NT, 0, tws, c, tid);
-  else first_fwd<LR, LOGSR, 0, false>(lds, b, NT, 0, tws, c, tid);
-  edge_sync<LR, LOGSR>(0);
-  rest_fwd<LOGSR, 0>(lds, 0, tws, c, tid);
-  load16<0>(lds, b, tid, 0);
-  fdft<4, 0, false>(a, c);
-  fdft<4, 0, false>(b, c);
-  pointwise16<0>(a, b, c);
-  fidft<4, 0>(a, c);
-  {
-    const uint32_t s = slot16(tid, 0);
 #pragma unroll
-    for (int k = 0; k < 16; k++) lds[s + k] = a[k];
-  }
-  if constexpr (LOGSR > 4) {
-    pass_sync(4, 0);
-    rest_inv<8, LOGSR, 0>(lds, 0, itws, c, tid);
-  }
-  edge_sync<LR, LOGSR>(0);
-  last_inv<LR, LOGSR, 0>(lds, a, NT, 0, itws, c, tid);
+  for (int i = 0; i < NR; i++) b[i] = digit(rb[i].x, rb[i].y, c.p, c.pinv);
+  vec_fwd<LE, LOGD, 0, ZHI>(lds, b, b, NT, tws, c, tid);
+  vec_mul_inv<LE, LOGD, 0>(lds, a, b, NT, itws, c, tid);
   double* out = res + (size_t)prime * stride;
 #pragma unroll
   for (int d = 0; d < D; d++) {
     const uint32_t g = tid + NT * d, j = g & (SR - 1);
-    const MulDesc m = ds[g >> LOGSR];
+    const MulDesc& m = ds[g >> LOGSR];
     const uint32_t L = (m.la + m.lb + 1) / 2;
+    double* o = out + m.r_off;
 #pragma unroll
     for (int k = 0; k < R; k++) {
       const uint32_t pos = j + SR * k;
-      if (pos < L) out[m.r_off + pos] = a[d + D * k];
+      if (pos < L) o[pos] = a[d + D * k];
     }
-    if (j == 0 && L > N) out[m.r_off + N] = 0.0;   // la + lb = 2 N + 1: no coefficient there
+    if (j == 0 && L > N) o[N] = 0.0;   // la + lb = 2 N + 1: no coefficient there
   }
 }
 
@@ -562,11 +564,11 @@ k_fcol_fwd(DescView dv, FGeom fg, uint64_t m0_, int prevS, int prevL, const uint
 #pragma unroll
     for (int k = 0; k < 16; k++) v[k] = x[k];
   } else {
-    if (FIRST && zhi) first_fwd<LR, LOGSR, PS, FIRST>(lds, x, NT, logC, tws, c, tid);
-    else first_fwd<LR, LOGSR, PS, false>(lds, x, NT, logC, tws, c, tid);
+    if (FIRST && zhi) first_fwd<4, LR, LOGSR, PS, FIRST>(lds, x, NT, logC, tws, c, tid);
+    else first_fwd<4, LR, LOGSR, PS, false>(lds, x, NT, logC, tws, c, tid);
     __syncthreads();
-    rest_fwd<LOGSR, PS>(lds, logC, tws, c, tid);
-    load16<PS>(lds, v, tid, logC);
+    rest_fwd<4, LOGSR, PS>(lds, logC, tws, c, tid);
+    slots_load<4>(lds, v, tid, logC);
     fdft<4, PS, false>(v, c);
   }
   const uint32_t q0 = base + ((16 * (tid >> logC)) << logSig) + j0 + (tid & (C - 1));
@@ -607,15 +609,13 @@ k_fcol_inv(DescView dv, FGeom fg, uint64_t m0_, int prevS, int prevL, double* __
   }
   fidft<4, PS>(x, c);
   if constexpr (LOGL > 4) {
-    const uint32_t s = slot16(tid, logC);
-#pragma unroll
-    for (int k = 0; k < 16; k++) lds[s + (k << logC)] = x[k];
+    slots_store<4>(lds, x, tid, logC);
     __syncthreads();
     if constexpr (LOGSR > 4) {
-      rest_inv<8, LOGSR, PS>(lds, logC, itws, c, tid);
+      rest_inv<4, 8, LOGSR, PS>(lds, logC, itws, c, tid);
       __syncthreads();
     }
-    last_inv<LR, LOGSR, PS>(lds, x, NT, logC, itws, c, tid);
+    last_inv<4, LR, LOGSR, PS>(lds, x, NT, logC, itws, c, tid);
   }
   if constexpr (FIRST) {
     const MulDesc d = dv.get(m0_ + m);
@@ -647,9 +647,9 @@ k_fcol_inv(DescView dv, FGeom fg, uint64_t m0_, int prevS, int prevL, double* __
 template <int LOGM, int PS>
 __global__ void __launch_bounds__((1 << LOGM) / 16) __attribute__((amdgpu_waves_per_eu(4)))
 k_frow(int logD, int logS, int logL, double* __restrict__ F, FTables tb) {
-  constexpr int LR = pass_logr(LOGM), LOGSR = LOGM - LR;
-  constexpr uint32_t M = 1u << LOGM, NT = M / 16;
-  __shared__ double lds[lds_pad(M)];
+  constexpr int LE = 4, E = 1 << LE;
+  constexpr uint32_t M = 1u << LOGM, NT = M >> LE;
+  __shared__ double lds[fpad<LE>(M)];
   const uint32_t tid = threadIdx.x, prime = blockIdx.y;
   const FPrime& c = c_fp[PS][prime];
   const int logQ = logD - LOGM;
@@ -660,9 +660,9 @@ k_frow(int logD, int logS, int logL, double* __restrict__ F, FTables tb) {
   const double* fb = fa + N;
   const double* tws = tb.tws + (size_t)prime * FTWS_ENTRIES;
   const double* itws = tb.itws + (size_t)prime * FTWS_ENTRIES;
-  double a[16], b[16];
+  double a[E], b[E];
 #pragma unroll
-  for (int i = 0; i < 16; i++) {
+  for (int i = 0; i < E; i++) {
     a[i] = fa[tid + NT * i];
     b[i] = fb[tid + NT * i];
   }
@@ -671,40 +671,22 @@ k_frow(int logD, int logS, int logL, double* __restrict__ F, FTables tb) {
   {
     Geo<PS> gw(tb.lo + (size_t)prime * FTW2, tb.hi + (size_t)prime * FTW2, tid * fr, NT * fr, c.p, c.pinv);
 #pragma unroll
-    for (int i = 0; i < 16; i++) {
+    for (int i = 0; i < E; i++) {
       a[i] = mulm(a[i], gw.w[i & 3], c.p, c.pinv);
       b[i] = mulm(b[i], gw.w[i & 3], c.p, c.pinv);
-      if ((i & 3) == 3 && i < 15) gw.step();
+      if ((i & 3) == 3 && i < E - 1) gw.step();
     }
   }
-  first_fwd<LR, LOGSR, PS, false>(lds, a, NT, 0, tws, c, tid);
-  edge_sync<LR, LOGSR>(0);
-  rest_fwd<LOGSR, PS>(lds, 0, tws, c, tid);
-  load16<PS>(lds, a, tid, 0);
+  vec_fwd<LE, LOGM, PS, false>(lds, a, a, NT, tws, c, tid);
   __syncthreads();
-  first_fwd<LR, LOGSR, PS, false>(lds, b, NT, 0, tws, c, tid);
-  edge_sync<LR, LOGSR>(0);
-  rest_fwd<LOGSR, PS>(lds, 0, tws, c, tid);
-  load16<PS>(lds, b, tid, 0);
-  fdft<4, PS, false>(a, c);
-  fdft<4, PS, false>(b, c);
-  pointwise16<PS>(a, b, c);
-  fidft<4, PS>(a, c);
-  {
-    const uint32_t s = slot16(tid, 0);
-#pragma unroll
-    for (int k = 0; k < 16; k++) lds[s + k] = a[k];
-  }
-  pass_sync(4, 0);
-  rest_inv<8, LOGSR, PS>(lds, 0, itws, c, tid);
-  edge_sync<LR, LOGSR>(0);
-  last_inv<LR, LOGSR, PS>(lds, a, NT, 0, itws, c, tid);
+  vec_fwd<LE, LOGM, PS, false>(lds, b, b, NT, tws, c, tid);
+  vec_mul_inv<LE, LOGM, PS>(lds, a, b, NT, itws, c, tid);
   {
     Geo<PS> gw(tb.ilo + (size_t)prime * FTW2, tb.ihi + (size_t)prime * FTW2, tid * fr, NT * fr, c.p, c.pinv);
 #pragma unroll
-    for (int i = 0; i < 16; i++) {
+    for (int i = 0; i < E; i++) {
       fa[tid + NT * i] = mulm(red(a[i], c.p, c.pinv), gw.w[i & 3], c.p, c.pinv);
-      if ((i & 3) == 3 && i < 15) gw.step();
+      if ((i & 3) == 3 && i < E - 1) gw.step();
     }
   }
 }
@@ -944,6 +926,174 @@ k_fcrt(SegView sv, FCrt kc, const double* __restrict__ res, uint64_t stride, uin
   }
 }
 
+// ---------------------------------------------------------------------------
+// Products of up to 2^11 digits with the three primes and the carries in one
+// workgroup: T / 8 threads of 8 values per prime, then T / 4 threads of 4 digits
+// recombine and carry, so that the residues never leave LDS and a tree level is
+// one launch.  The tile is one product, or 2^9 slots of shorter ones: the
+// smallest that gives every prime whole waves, because a level of few products
+// is bound by how much of it one CU has to issue (tiles of 2^11 slots held three
+// waves per SIMD on one CU while the others stood idle).
+// Every product has la + lb <= 2 N limbs, so nothing is carried out of its N
+// slots and one scan over the tile serves all its products.
+#define FF_MAX_LOGD 11
+constexpr int ff_tile(int logD) { return logD < 9 ? 9 : logD; }
+constexpr int ff_threads(int logD) { return CAT_NPRIMES << (ff_tile(logD) - 3); }
+#define FF_E 4
+template <int LOGD, bool ZHI>
+__device__ __forceinline__ void ffused_tile(double* lds, MulDesc* ds, uint4* xw, uint32_t* tmp,
+                                            const uint32_t* __restrict__ ain, const uint32_t* __restrict__ bin,
+                                            uint32_t* __restrict__ out, const FTables& tb, const FCrt& kc,
+                                            uint32_t* __restrict__ err) {
+  constexpr int LE = 3, LR = fpass<LE>(LOGD), LOGSR = LOGD - LR;
+  constexpr uint32_t T = 1u << ff_tile(LOGD), NT = T >> LE, N = 1u << LOGD, SR = 1u << LOGSR, TP = fpad<LE>(T);
+  constexpr int R = 1 << LR, E = 1 << LE, D = E / R;
+  const uint32_t prime = __builtin_amdgcn_readfirstlane(threadIdx.x / NT), tid = threadIdx.x % NT;
+  const FPrime& c = c_fp[0][prime];
+  double* l = lds + prime * TP;
+  const double* tws = tb.tws3 + (size_t)prime * FTWS_ENTRIES;
+  const double* itws = tb.itws3 + (size_t)prime * FTWS_ENTRIES;
+  double a[E], b[E];
+  constexpr int RK = ZHI ? R / 2 : R, NR = ZHI ? E / 2 : E;
+  uint2 ra[NR], rb[NR];
+#pragma unroll
+  for (int d = 0; d < D; d++) {
+    const uint32_t g = tid + NT * d, j = g & (SR - 1);
+    const MulDesc& m = ds[g >> LOGSR];
+    const uint32_t la = m.la, lb = m.lb;
+    const uint32_t *sa = ain + m.a_off, *sb = bin + m.b_off;
+#pragma unroll
+    for (int k = 0; k < RK; k++) {
+      const uint32_t q = 2 * (j + SR * k);
+      const uint32_t x0 = sa[q < la ? q : 0], x1 = sa[q + 1 < la ? q + 1 : 0];
+      const uint32_t y0 = sb[q < lb ? q : 0], y1 = sb[q + 1 < lb ? q + 1 : 0];
+      ra[d + D * k] = make_uint2(q < la ? x0 : 0u, q + 1 < la ? x1 : 0u);
+      rb[d + D * k] = make_uint2(q < lb ? y0 : 0u, q + 1 < lb ? y1 : 0u);
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < NR; i++) a[i] = digit(ra[i].x, ra[i].y, c.p, c.pinv);
+  vec_fwd<LE, LOGD, 0, ZHI>(l, a, a, NT, tws, c, tid);
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < NR; i++) b[i] = digit(rb[i].x, rb[i].y, c.p, c.pinv);
+  vec_fwd<LE, LOGD, 0, ZHI>(l, b, b, NT, tws, c, tid);
+  vec_mul_inv<LE, LOGD, 0>(l, a, b, NT, itws, c, tid);
+  // the residues in order, in the slots that this thread read last
+#pragma unroll
+  for (int d = 0; d < D; d++) {
+    const uint32_t g = tid + NT * d, j = g & (SR - 1);
+    const uint32_t s = fpad<LE>(((g >> LOGSR) << LOGD) + j);
+#pragma unroll
+    for (int k = 0; k < R; k++) l[s + k * (SR + (SR >> LE))] = a[d + D * k];
+  }
+  __syncthreads();
+  // recombination and carries: thread t < T / 4 has the slots 4 t .. 4 t + 3
+  const uint32_t t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  const bool on = t < T / FF_E;
+  const uint32_t k0 = (FF_E * t) & (N - 1);
+  uint64_t a0[FF_E], a1[FF_E], lo[FF_E], ul[FF_E];
+  uint32_t a2[FF_E], h[FF_E];
+  bool gk[FF_E], G = false, P = false;
+  if (on) {
+    const uint32_t s = fpad<LE>(FF_E * t);
+#pragma unroll
+    for (int i = 0; i < FF_E; i++) fcrt_value(lds[s + i], lds[TP + s + i], lds[2 * TP + s + i], kc, a0[i], a1[i], a2[i]);
+#pragma unroll
+    for (int i = 2; i < FF_E; i++) lo[i] = fcol_sum(a0[i], a1[i - 1], a2[i - 2], &h[i]);
+    // the left neighbour's last two columns (none at a product's start)
+    const uint32_t p0 = (uint32_t)a1[FF_E - 1], p1 = (uint32_t)(a1[FF_E - 1] >> 32),
+                   p2 = a2[FF_E - 1] | (h[FF_E - 1] << 30), p3 = a2[FF_E - 2];
+    uint4 z = make_uint4(__shfl_up(p0, 1, 64), __shfl_up(p1, 1, 64), __shfl_up(p2, 1, 64), __shfl_up(p3, 1, 64));
+    if (lane == 63) xw[wave] = make_uint4(p0, p1, p2, p3);
+    ul[0] = ((uint64_t)z.y << 32) | z.x;   // kept across the barrier
+    ul[1] = ((uint64_t)z.w << 32) | z.z;
+  }
+  __syncthreads();
+  if (on) {
+    uint4 z = make_uint4((uint32_t)ul[0], (uint32_t)(ul[0] >> 32), (uint32_t)ul[1], (uint32_t)(ul[1] >> 32));
+    if (lane == 0 && wave > 0) z = xw[wave - 1];
+    if (k0 == 0) z = make_uint4(0, 0, 0, 0);
+    lo[0] = fcol_sum(a0[0], ((uint64_t)z.y << 32) | z.x, z.w, &h[0]);
+    lo[1] = fcol_sum(a0[1], a1[0], z.z & 0x3FFFFFFFu, &h[1]);
+    P = true;
+    uint32_t hp = z.z >> 30;
+#pragma unroll
+    for (int i = 0; i < FF_E; i++) {
+      ul[i] = lo[i] + hp;
+      gk[i] = ul[i] < lo[i];
+      hp = h[i];
+      const bool pr = ul[i] == ~0ull;
+      G = gk[i] || (pr && G);
+      P = P && pr;
+    }
+    uint32_t cout;
+    bool ap;
+    wave_carry(G, P, 0, &cout, &ap);
+    if (lane == 0) tmp[wave] = cout | (ap ? 2u : 0u);
+  }
+  __syncthreads();
+  if (!on) return;
+  uint32_t wc = 0;
+  for (uint32_t w = 0; w < wave; w++) {
+    const uint32_t x = tmp[w];
+    wc = (x & 1u) | ((x >> 1) & wc);
+  }
+  uint32_t cout;
+  bool ap;
+  uint32_t cy = wave_carry(G, P, wc, &cout, &ap);
+  const MulDesc& m = ds[(FF_E * t) >> LOGD];
+  const uint32_t L = m.la + m.lb, w0 = 2 * k0;
+  struct W8 {
+    uint32_t w[2 * FF_E];
+  } r;
+#pragma unroll
+  for (int i = 0; i < FF_E; i++) {
+    const uint64_t y = ul[i] + cy;
+    cy = (y < ul[i] || gk[i]) ? 1u : 0u;
+    r.w[2 * i] = (uint32_t)y;
+    r.w[2 * i + 1] = (uint32_t)(y >> 32);
+  }
+  uint32_t* o = out + m.c_off + w0;
+  if (w0 + 2 * FF_E <= L) {
+    *(W8*)o = r;
+  } else {
+    bool over = false;
+#pragma unroll
+    for (int i = 0; i < 2 * FF_E; i++) {
+      if (w0 + i < L) o[i] = r.w[i];
+      else over = over || r.w[i] != 0;
+    }
+    if (over) atomicOr(err, CAT_DEVERR_CARRY_OUT);
+  }
+}
+
+// One bucket of products of `dv`; workgroups from `tiles`
+// on copy tail ranges.
+template <int LOGD, bool ZHI>
+__global__ void __launch_bounds__(ff_threads(LOGD)) __attribute__((amdgpu_waves_per_eu(6)))
+k_ffused(DescView dv, uint64_t m0, uint64_t nmul, uint32_t tiles, const uint32_t* __restrict__ ain,
+         const uint32_t* __restrict__ bin, uint32_t* __restrict__ out, FTables tb, FCrt kc, CopyList tails,
+         const uint32_t* __restrict__ tin, uint32_t* __restrict__ tout, uint32_t* __restrict__ err) {
+  constexpr uint32_t PER = 1u << (ff_tile(LOGD) - LOGD);
+  __shared__ double lds[CAT_NPRIMES * fpad<3>(1u << ff_tile(LOGD))];
+  __shared__ MulDesc ds[PER];
+  __shared__ uint4 xw[8];
+  __shared__ uint32_t tmp[8];
+  if (blockIdx.x >= tiles) {
+    copy_tail_block(tails, tin, tout, blockIdx.x - tiles);
+    return;
+  }
+  const uint64_t i0 = (uint64_t)blockIdx.x * PER;
+  if (threadIdx.x < PER) {
+    MulDesc d{};   // slots without a product: empty operands
+    if (i0 + threadIdx.x < nmul) d = dv.get(m0 + i0 + threadIdx.x);
+    ds[threadIdx.x] = d;
+  }
+  __syncthreads();
+  ffused_tile<LOGD, ZHI>(lds, ds, xw, tmp, ain, bin, out, tb, kc, err);
+}
+
 // ------------------------------------------------------------------ host side
 static const uint64_t kPF[2][CAT_NPRIMES] = {{1125900443713537ull, 1125905745313793ull, 1125906550620161ull},
                                              {2251800350556161ull, 2251801155862529ull, 2251803907325953ull}};
@@ -1017,8 +1167,9 @@ hipError_t upload(const std::vector<double>& h, const double** d) {
 hipError_t fntt_init() {
   FPrime fp[2][CAT_NPRIMES];
   for (int s = 0; s < 2; s++) {
-    std::vector<double> tws[2], lo[2], hi[2];
+    std::vector<double> tws[2], tws3[2], lo[2], hi[2];
     for (int d = 0; d < 2; d++) {
+      tws3[d].assign((size_t)CAT_NPRIMES * FTWS_ENTRIES, 1.0);
       tws[d].assign((size_t)CAT_NPRIMES * FTWS_ENTRIES, 1.0);
       lo[d].resize((size_t)CAT_NPRIMES * FTW2);
       hi[d].resize((size_t)CAT_NPRIMES * FTW2);
@@ -1041,16 +1192,20 @@ hipError_t fntt_init() {
         for (int ls = 1; ls <= 14; ls++) {
           const uint32_t S = 1u << ls;
           fill_powers(powmod64(r, 1ull << (FNTT_MAX_LOGD - ls), p), p, S, pw.data());
-          const int lr = pass_logr(ls), lsr = ls - lr;
-          double* t = &tws[d][(size_t)i * FTWS_ENTRIES + S - 2];
-          for (uint32_t k = 0; k < (1u << lr); k++)
-            for (uint32_t j = 0; j < (1u << lsr); j++) t[(k << lsr) + j] = pw[(uint64_t)j * k % S];
+          for (int le = 3; le <= 4; le++) {
+            const int lr = le == 3 ? fpass<3>(ls) : fpass<4>(ls), lsr = ls - lr;
+            double* t = &(le == 3 ? tws3 : tws)[d][(size_t)i * FTWS_ENTRIES + S - 2];
+            for (uint32_t k = 0; k < (1u << lr); k++)
+              for (uint32_t j = 0; j < (1u << lsr); j++) t[(k << lsr) + j] = pw[(uint64_t)j * k % S];
+          }
         }
         fill_powers(r, p, FTW2, &lo[d][(size_t)i * FTW2]);
         fill_powers(powmod64(r, FTW2, p), p, FTW2, &hi[d][(size_t)i * FTW2]);
       }
     }
     FTables& t = g_ft[s];
+    FCHK(upload(tws3[0], &t.tws3));
+    FCHK(upload(tws3[1], &t.itws3));
     FCHK(upload(tws[0], &t.tws));
     FCHK(upload(tws[1], &t.itws));
     FCHK(upload(lo[0], &t.lo));
@@ -1066,13 +1221,41 @@ hipError_t fntt_lds(const FBatch& b, hipStream_t st) {
   const int lt = b.logD < 12 ? 12 : b.logD;
   const uint64_t per = 1ull << (lt - b.logD);
   const uint64_t tiles = (b.cnt + per - 1) / per;
-  const dim3 grid((uint32_t)(tiles * CAT_NPRIMES)), block((1u << lt) / 16);
-#define L(X)                                                                                                     \
-  case X:                                                                                                        \
-    hipLaunchKernelGGL(k_flds<X>, grid, block, 0, st, b.dv, b.m0, b.cnt, b.ain, b.bin, b.res, b.stride, g_ft[0]); \
+  const dim3 grid((uint32_t)(tiles * CAT_NPRIMES)), block((1u << lt) >> flds_le(b.logD));
+#define L(X)                                                                                                  \
+  case X:                                                                                                     \
+    if (b.half)                                                                                               \
+      hipLaunchKernelGGL((k_flds<X, true>), grid, block, 0, st, b.dv, b.m0, b.cnt, b.ain, b.bin, b.res,       \
+                         b.stride, g_ft[0]);                                                                  \
+    else                                                                                                      \
+      hipLaunchKernelGGL((k_flds<X, false>), grid, block, 0, st, b.dv, b.m0, b.cnt, b.ain, b.bin, b.res,      \
+                         b.stride, g_ft[0]);                                                                  \
     break
   switch (b.logD) {
     L(5); L(6); L(7); L(8); L(9); L(10); L(11); L(12); L(13); L(14);
+    default: return hipErrorInvalidValue;
+  }
+#undef L
+  return hipGetLastError();
+}
+
+bool fntt_fused_fits(int logD) { return logD >= FNTT_LDS_MIN_LOGD && logD <= FF_MAX_LOGD; }
+hipError_t fntt_fused(const FBatch& b, uint32_t* out, const CopyList& tails, const uint32_t* tin, uint32_t* tout,
+                      uint32_t* err, hipStream_t st) {
+  const uint64_t per = 1ull << (ff_tile(b.logD) - b.logD);
+  const uint32_t tiles = (uint32_t)((b.cnt + per - 1) / per);
+  const dim3 grid(tiles + tail_blocks(tails)), block(ff_threads(b.logD));
+#define L(X)                                                                                                  \
+  case X:                                                                                                     \
+    if (b.half)                                                                                               \
+      hipLaunchKernelGGL((k_ffused<X, true>), grid, block, 0, st, b.dv, b.m0, b.cnt, tiles, b.ain, b.bin,     \
+                         out, g_ft[0], g_crt[X], tails, tin, tout, err);                                      \
+    else                                                                                                      \
+      hipLaunchKernelGGL((k_ffused<X, false>), grid, block, 0, st, b.dv, b.m0, b.cnt, tiles, b.ain, b.bin,    \
+                         out, g_ft[0], g_crt[X], tails, tin, tout, err);                                      \
+    break
+  switch (b.logD) {
+    L(5); L(6); L(7); L(8); L(9); L(10); L(11);
     default: return hipErrorInvalidValue;
   }
 #undef L

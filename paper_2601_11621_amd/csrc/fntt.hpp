@@ -28,6 +28,7 @@ struct FBatch {
   DescView dv;
   uint64_t m0, cnt;
   int logD;
+  bool half;             // no operand is longer than 2^(logD - 1) digits
   const uint32_t* ain;
   const uint32_t* bin;
   double* F;             // four-step scratch: 6 * cnt * 2^logD doubles
@@ -36,6 +37,11 @@ struct FBatch {
 };
 
 hipError_t fntt_lds(const FBatch& b, hipStream_t st);
+// Products with carries in one launch (la + lb <= 2^(logD + 1) limbs each; the
+// limbs go to out + c_off), with tail copies; for the sizes that fit.
+bool fntt_fused_fits(int logD);
+hipError_t fntt_fused(const FBatch& b, uint32_t* out, const CopyList& tails, const uint32_t* tin, uint32_t* tout,
+                      uint32_t* err, hipStream_t st);
 // column pass over sub-problems of 2^logS digits, L = 2^logL of them along the
 // column; outer (prevS, prevL): the pass before it, whose twiddles this pass
 // applies (0: none).  first: the operands come from limbs, the results go to
