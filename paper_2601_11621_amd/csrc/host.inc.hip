@@ -1791,15 +1791,56 @@ cat_status capture_graph(F&& rec, hipGraphExec_t* out) {
   return CAT_OK;
 }
 
+// The post-tree stages k0 .. k1 in batched form, consecutive schoolbook stages
+// as one k_school_chain launch; fill_len words at fill_pos are cleared first.
+cat_status run_post(Exec& X, Plan& P, size_t k0, size_t k1, uint64_t fill_pos = 0, uint64_t fill_len = 0) {
+  auto chains = [&](size_t k) { return P.post[k].cls == CLS_SCHOOL && P.post[k].tails.n == 0; };
+  if (fill_len > 0 && (k0 >= k1 || !chains(k0) || fill_len > (1u << 16))) {
+    hipLaunchKernelGGL(k_fill, dim3((uint32_t)std::min<uint64_t>((fill_len + 255) / 256, 1024)), dim3(256), 0, X.st,
+                       X.W + fill_pos, fill_len, 0u);
+    LAUNCHCHK();
+    X.launches++;
+    fill_len = 0;
+  }
+  for (size_t k = k0; k < k1;) {
+    if (!chains(k)) {
+      STCHK(run_stage_batched(X, P.post[k++]));
+      continue;
+    }
+    Chain c{};
+    c.fill_pos = fill_pos;
+    c.fill_len = (uint32_t)fill_len;
+    fill_len = 0;
+    size_t n = 0;
+    double limbs = 0;
+    for (; k < k1 && chains(k) && c.nstep < CHAIN_STEPS; k++) {
+      const Stage& s = P.post[k];
+      if (n + s.host_desc.size() > CHAIN_PRODS) break;
+      for (const MulDesc& d : s.host_desc) {
+        c.p[n++] = ChainProd{(s.a_base + d.a_off) | ((uint64_t)d.la << 56), (s.b_base + d.b_off) | ((uint64_t)d.lb << 56),
+                             s.c_base + d.c_off};
+      }
+      c.pref[++c.nstep] = (uint16_t)n;
+      limbs += (double)s.limbs;
+    }
+    KTime kt("k_school_chain", X.st, limbs);
+    hipLaunchKernelGGL(k_school_chain, dim3(1), dim3(64 * CHAIN_WAVES), 0, X.st, c, X.W, X.err);
+    LAUNCHCHK();
+    X.launches++;
+  }
+  return CAT_OK;
+}
+
 // R's node: clear the limbs above R's product, then the powers and R
 cat_status run_rins_side(Exec& S, Plan& P, bool plain) {
+  if (!plain) return run_post(S, P, 0, P.post_final, P.rins_fill_pos, P.rins_fill_len);
   if (P.rins_fill_len > 0) {
     hipLaunchKernelGGL(k_fill, dim3((uint32_t)std::min<uint64_t>((P.rins_fill_len + 255) / 256, 1024)), dim3(256), 0,
                        S.st, S.W + P.rins_fill_pos, P.rins_fill_len, 0u);
     LAUNCHCHK();
     S.launches++;
   }
-  for (size_t k = 0; k < P.post_final; k++) STCHK(plain ? run_stage_plain(S, P.post[k]) : run_stage_batched(S, P.post[k]));
+  for (size_t k = 0; k < P.post_final; k++) STCHK(run_stage_plain(S, P.post[k]));
   return CAT_OK;
 }
 
@@ -1854,15 +1895,16 @@ cat_status run_phase2(Exec& X, Plan& P, bool plain) {
     S.flags = X.flags2;
     S.crt_epoch = 0;
     S.launches = 0;
-    for (size_t k = 0; k < P.post_final; k++) STCHK(run_stage_batched(S, P.post[k]));
+    STCHK(run_post(S, P, 0, P.post_final));
     HIPCHK(hipEventRecord(g.ev_join, S.st));
     HIPCHK(hipStreamWaitEvent(X.st, g.ev_join, 0));
-    for (size_t k = P.post_final; k < P.post.size(); k++) STCHK(run_stage_batched(X, P.post[k]));
+    STCHK(run_post(X, P, P.post_final, P.post.size()));
     X.launches += S.launches;
     return CAT_OK;
   }
   for (const Stage& s : st) STCHK(plain ? run_stage_plain(X, s) : run_stage_batched(X, s));
-  for (const Stage& s : P.post) STCHK(plain ? run_stage_plain(X, s) : run_stage_batched(X, s));
+  if (!plain) return run_post(X, P, 0, P.post.size());
+  for (const Stage& s : P.post) STCHK(run_stage_plain(X, s));
   return CAT_OK;
 }
 

@@ -292,26 +292,16 @@ __device__ __forceinline__ void school_cols(const uint32_t* sa, const uint32_t* 
   }
 }
 
-__global__ void __launch_bounds__(64 * SCHOOL_WAVES)
-k_school(DescView dv, uint64_t nmul, const uint32_t* __restrict__ ain, const uint32_t* __restrict__ bin,
-         uint32_t* __restrict__ out, uint32_t* __restrict__ err, uint32_t prod_blocks, CopyList tails,
-         const uint32_t* __restrict__ tin, uint32_t* __restrict__ tout) {
-  __shared__ uint32_t sa[SCHOOL_WAVES][SCHOOL_WIN];
-  __shared__ __align__(8) uint32_t sb[SCHOOL_WAVES][SCHOOL_MAX];
-  __shared__ uint32_t sv[SCHOOL_WAVES][3][2 * SCHOOL_MAX + 4];
-  if (blockIdx.x >= prod_blocks) {
-    copy_tail_block(tails, tin, tout, blockIdx.x - prod_blocks);
-    return;
-  }
-  const uint32_t w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const uint64_t mi = (uint64_t)blockIdx.x * SCHOOL_WAVES + w;
-  if (mi >= nmul) return;   // whole wave leaves together; no block barrier below
-  const MulDesc d = dv.get(uni64(mi));
+// One product of da x db limbs (both at most SCHOOL_MAX) in one wave; sa, sb, sv
+// are the wave's own LDS.
+__device__ __forceinline__ void school_wave(const uint32_t* __restrict__ pa, uint32_t da,
+                                            const uint32_t* __restrict__ pb, uint32_t db, uint32_t* __restrict__ out,
+                                            uint32_t* sa, uint32_t* sb, uint32_t (*sv)[2 * SCHOOL_MAX + 4],
+                                            uint32_t lane, uint32_t* __restrict__ err) {
   // the longer operand slides (la), the shorter one is summed over (lb)
-  const uint32_t da = uni32(d.la), db = uni32(d.lb);
   const bool swp = da < db;
-  const uint32_t* a = swp ? bin + uni64(d.b_off) : ain + uni64(d.a_off);
-  const uint32_t* b = swp ? ain + uni64(d.a_off) : bin + uni64(d.b_off);
+  const uint32_t* a = swp ? pb : pa;
+  const uint32_t* b = swp ? pa : pb;
   const uint32_t la = swp ? db : da, lb = swp ? da : db, L = la + lb;
   const uint32_t lbe = (lb + 1) & ~1u;
   {
@@ -328,35 +318,35 @@ k_school(DescView dv, uint64_t nmul, const uint32_t* __restrict__ ain, const uin
       xb[i] = t < lb ? b[t] : 0u;
     }
 #pragma unroll
-    for (int i = 0; i < SCHOOL_WIN / 64; i++) sa[w][lane + 64 * i] = xa[i];
+    for (int i = 0; i < SCHOOL_WIN / 64; i++) sa[lane + 64 * i] = xa[i];
 #pragma unroll
-    for (int i = 0; i < 2; i++) sb[w][lane + 64 * i] = xb[i];
+    for (int i = 0; i < 2; i++) sb[lane + 64 * i] = xb[i];
   }
   __builtin_amdgcn_wave_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   const uint32_t ncol = (L - 1 + 63) / 64;   // columns per lane; k < L - 1 carry the sums
   if (ncol <= 1)
-    school_cols<1>(sa[w], sb[w], lbe, lane, sv[w]);
+    school_cols<1>(sa, sb, lbe, lane, sv);
   else if (ncol == 2)
-    school_cols<2>(sa[w], sb[w], lbe, lane, sv[w]);
+    school_cols<2>(sa, sb, lbe, lane, sv);
   else if (ncol == 3)
-    school_cols<3>(sa[w], sb[w], lbe, lane, sv[w]);
+    school_cols<3>(sa, sb, lbe, lane, sv);
   else
-    school_cols<4>(sa[w], sb[w], lbe, lane, sv[w]);
-  if (lane < 3) { sv[w][0][lane] = 0; sv[w][1][lane] = 0; sv[w][2][lane] = 0; }
+    school_cols<4>(sa, sb, lbe, lane, sv);
+  if (lane < 3) { sv[0][lane] = 0; sv[1][lane] = 0; sv[2][lane] = 0; }
   __builtin_amdgcn_wave_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   // lane owns limbs 4*lane .. 4*lane+3 (position k stored at index k+3)
   constexpr int E = 4;
   const uint32_t k0 = lane * E;
   uint64_t u[E];
-  uint32_t yprev = (uint32_t)(((uint64_t)sv[w][0][k0 + 2] + sv[w][1][k0 + 1] + sv[w][2][k0]) >> 32);
+  uint32_t yprev = (uint32_t)(((uint64_t)sv[0][k0 + 2] + sv[1][k0 + 1] + sv[2][k0]) >> 32);
   bool G = false, P = true;
 #pragma unroll
   for (int i = 0; i < E; i++) {
     const uint32_t k = k0 + i;
     uint64_t s = 0;
-    if (k < L) s = (uint64_t)sv[w][0][k + 3] + sv[w][1][k + 2] + sv[w][2][k + 1];
+    if (k < L) s = (uint64_t)sv[0][k + 3] + sv[1][k + 2] + sv[2][k + 1];
     u[i] = (s & 0xFFFFFFFFull) + yprev;
     yprev = (uint32_t)(s >> 32);
     const bool g = u[i] >= (1ull << 32), pr = u[i] == 0xFFFFFFFFull;
@@ -371,9 +361,70 @@ k_school(DescView dv, uint64_t nmul, const uint32_t* __restrict__ ain, const uin
     const uint32_t k = k0 + i;
     const uint64_t t = u[i] + c;
     c = (uint32_t)(t >> 32);
-    if (k < L) out[d.c_off + k] = (uint32_t)t;
+    if (k < L) out[k] = (uint32_t)t;
   }
   if (lane == 0 && cout) atomicOr(err, CAT_DEVERR_CARRY_OUT);
+}
+
+__global__ void __launch_bounds__(64 * SCHOOL_WAVES)
+k_school(DescView dv, uint64_t nmul, const uint32_t* __restrict__ ain, const uint32_t* __restrict__ bin,
+         uint32_t* __restrict__ out, uint32_t* __restrict__ err, uint32_t prod_blocks, CopyList tails,
+         const uint32_t* __restrict__ tin, uint32_t* __restrict__ tout) {
+  __shared__ uint32_t sa[SCHOOL_WAVES][SCHOOL_WIN];
+  __shared__ __align__(8) uint32_t sb[SCHOOL_WAVES][SCHOOL_MAX];
+  __shared__ uint32_t sv[SCHOOL_WAVES][3][2 * SCHOOL_MAX + 4];
+  if (blockIdx.x >= prod_blocks) {
+    copy_tail_block(tails, tin, tout, blockIdx.x - prod_blocks);
+    return;
+  }
+  const uint32_t w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const uint64_t mi = (uint64_t)blockIdx.x * SCHOOL_WAVES + w;
+  if (mi >= nmul) return;   // whole wave leaves together; no block barrier below
+  const MulDesc d = dv.get(uni64(mi));
+  school_wave(ain + uni64(d.a_off), uni32(d.la), bin + uni64(d.b_off), uni32(d.lb), out + d.c_off, sa[w], sb[w], sv[w],
+              lane, err);
+}
+
+// A chain of schoolbook steps in one workgroup, each step's products (one wave
+// each) reading the results of earlier steps: the powers P_e and their product
+// R, whose steps hold a few short products.  As launches of their own they cost
+// 3 us each and 6 to 10 us more in a graph that has to carry the dependency from
+// one node of the side branch to the next, and the main branch waits for R: at
+// n = 10^5 the chain took 64 us of a 230 us call.  Positions are words from W;
+// a and b carry the operand's length above bit 56.
+#define CHAIN_WAVES 16
+#define CHAIN_STEPS 32
+#define CHAIN_PRODS 128
+struct ChainProd {
+  uint64_t a, b, c;
+};
+struct Chain {
+  uint32_t nstep;
+  uint32_t fill_len;        // words cleared at fill_pos
+  uint64_t fill_pos;
+  uint16_t pref[CHAIN_STEPS + 1];
+  ChainProd p[CHAIN_PRODS];
+};
+__global__ void __launch_bounds__(64 * CHAIN_WAVES)
+k_school_chain(Chain ch, uint32_t* W, uint32_t* __restrict__ err) {
+  __shared__ uint32_t sa[CHAIN_WAVES][SCHOOL_WIN];
+  __shared__ __align__(8) uint32_t sb[CHAIN_WAVES][SCHOOL_MAX];
+  __shared__ uint32_t sv[CHAIN_WAVES][3][2 * SCHOOL_MAX + 4];
+  const uint32_t w = uni32(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  for (uint32_t k = threadIdx.x; k < ch.fill_len; k += blockDim.x) W[ch.fill_pos + k] = 0;
+  for (uint32_t s = 0; s < ch.nstep; s++) {
+    for (uint32_t i = ch.pref[s] + w; i < ch.pref[s + 1]; i += CHAIN_WAVES) {
+      const ChainProd q = ch.p[i];
+      const uint64_t m = (1ull << 56) - 1;
+      school_wave(W + uni64(q.a & m), uni32((uint32_t)(q.a >> 56)), W + uni64(q.b & m), uni32((uint32_t)(q.b >> 56)),
+                  W + uni64(q.c), sa[w], sb[w], sv[w], lane, err);
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    }
+    // the step's limbs are in memory for every wave before the next one reads
+    __threadfence_block();
+    __syncthreads();
+  }
 }
 
 // ---------------------------------------------------------------------------
