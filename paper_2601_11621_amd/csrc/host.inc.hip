@@ -419,9 +419,8 @@ struct Stage {
   // carried-up nodes
   CopyList tails{};
   uint64_t tail_in_base = 0, tail_out_base = 0;
-  bool is_leaf = false;    // k_leaf<CAT_LEAF_LF>
-  TreeLevel leaf{};
-  uint64_t leaf_nodes = 0;
+  bool is_leaf = false;    // k_base: the nodes of 2^BASE_J limbs
+  BaseLevel base{};
   bool dec = false;        // radix-10^9 products (k_crt10; addends in the segments)
   bool is_fused = false;   // k_tree_fused over the levels fused.j0 .. fused.j1
   FusedTree fused{};
@@ -502,6 +501,7 @@ void build_crt_segs(Stage& s) {
 struct Layout {
   uint64_t n = 0, s = 0, i0 = 0, i_end = 0, nseg = 0;
   int seg_log = SIEVE_SEG_LOG;   // odd numbers per sieve segment (log2)
+  uint32_t ebits = 32;     // bit length that no entry of the tree exceeds
   // factorial ratios: all primes with v_p(N) > 0 (capacity np_cap) before grouping
   uint64_t np_cap = 0, nchunks = 0;
   size_t P = 0, E = 0, chunk_cnt = 0, chunk_off = 0;      // in uint32 units
@@ -516,6 +516,17 @@ struct Layout {
 };
 
 size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
+
+// bit length of x
+uint32_t bit_len(uint64_t x) { return x ? 64 - (uint32_t)__builtin_clzll(x) : 1; }
+// entries of at most `ebits` bits that eight limbs hold
+uint32_t base_s8(uint32_t ebits) { return std::min<uint32_t>(256 / std::max<uint32_t>(ebits, 1), BASE_S8_MAX); }
+// limbs that K entries take at the bottom of a tree: eight per started piece,
+// and one per entry at most
+uint64_t base_limbs(uint64_t K, uint32_t ebits) {
+  const uint32_t s8 = base_s8(ebits);
+  return std::min<uint64_t>(K, 8 * ((K + s8 - 1) / s8));
+}
 
 // Sieve segment size of the range of odd indices [i0, i_end): 2^16 odd
 // numbers when that still gives 2^10 segments (four per CU), else 2^14.
@@ -588,6 +599,7 @@ Layout make_layout(uint64_t n) {
   Layout L;
   L.n = n;
   L.s = isqrt64(2 * n);
+  L.ebits = bit_len(2 * n);
   L.i0 = (L.s + 1) / 2;
   L.i_end = n;
   L.Kmax = std::max<uint64_t>(pi_bound(2 * n), 16);
@@ -609,9 +621,8 @@ struct Plan {
   uint32_t ng = 0;
   uint32_t exps[CAT_MAX_GROUPS] = {};
   uint64_t off[CAT_MAX_GROUPS + 1] = {};
-  std::vector<Stage> batched;   // leaf kernel + levels
-  std::vector<Stage> plain;     // levels from j = 0
-  std::vector<Stage> post;      // powers, outer tree, final product (shared by both modes)
+  std::vector<Stage> tree;      // batched: base kernel + levels from BASE_J; plain: levels from 0
+  std::vector<Stage> post;      // powers, outer tree, final product
   uint64_t result_pos = 0, result_cap = 0;   // uint32 offset from workspace base
   bool result_is_one = false;
   // several requests in one plan (batched serving): group g belongs to
@@ -625,6 +636,14 @@ struct Plan {
   uint64_t post_end = 0;        // end of the post-tree arena used
   uint64_t root[CAT_MAX_GROUPS] = {};   // Q_e of group g (uint32 offset), the same in both forms
   uint64_t gbits[CAT_MAX_GROUPS] = {};  // bit-length bound of Q_e (group table)
+  uint32_t ebits[CAT_MAX_GROUPS] = {};  // bit length that no entry of the group exceeds
+  bool plain = false;                   // one product per launch, from single entries up
+  int outer_j = -1;                     // powers form: level of R's node
+  // limbs that group g takes in its tree
+  uint64_t limbs(uint32_t gi) const {
+    const uint64_t K = off[gi + 1] - off[gi];
+    return plain ? K : base_limbs(K, ebits[gi]);
+  }
   // Side branch (captured calls): after fork_count batched stages every group
   // with e >= 2 is complete, and post[0, post_final) (powers and R) may run
   // beside the remaining levels of Q_1; post[post_final..] (C = Q_1 R) waits
@@ -636,10 +655,10 @@ struct Plan {
   // that holds R (zero above its limbs), so the tree's top product is C
   // itself and no long-by-short product follows.  The other nodes of every
   // group sit 2^rins_j limbs further into the arenas than in the primes
-  // buffer.  The powers and R run before stage rins_stage[form] (batched,
-  // plain); R's product writes into that level's input arena.
+  // buffer.  The powers and R run before stage rins_stage; R's product writes
+  // into that level's input arena.
   int rins_j = -1;
-  int rins_stage[2] = {-1, -1};
+  int rins_stage = -1;
   uint64_t rins_fill_pos = 0, rins_fill_len = 0;   // R's zero limbs above its product
   uint64_t r_limbs = 0, r_bits = 0;                // size of R's product output, bit bound of R
   void* dev = nullptr;          // device tables (segments, prefixes, descriptors)
@@ -679,14 +698,16 @@ struct TreeShape {
 };
 TreeShape tree_shape(const Plan& P) {
   TreeShape sh;
-  uint64_t Kmax_g = 0, leaves = 0;
+  uint64_t Kmax_g = 0, most = 0, leaves = 0;
   for (uint32_t gi = 0; gi < P.ng; gi++) {
     Kmax_g = std::max(Kmax_g, P.off[gi + 1] - P.off[gi]);
+    most = std::max(most, P.limbs(gi));
     leaves += P.off[gi + 1] - P.off[gi];
   }
-  const int LF = CAT_LEAF_LF;
-  sh.J = ceil_log2(std::max<uint64_t>(Kmax_g, 1));
-  sh.jleaf = Kmax_g > 1 ? std::min(sh.J, LF) : 0;
+  sh.J = ceil_log2(std::max<uint64_t>(P.plain ? Kmax_g : most, 1));
+  sh.jleaf = Kmax_g > 1 && !P.plain ? BASE_J : 0;
+  sh.J = Kmax_g > 1 ? std::max(sh.J, sh.jleaf) : 0;
+  if (P.plain) return sh;
   // the consecutive levels above the leaf and schoolbook levels whose
   // products are one-workgroup transforms of at most 2^g_fuse_logn coefficients
   for (int j = std::max(sh.jleaf, 3); j < sh.J && j + 1 <= (int)g_fuse_tree_logn && leaves <= FUSE_MAX_LEAVES; j++) {
@@ -705,8 +726,9 @@ TreeShape tree_shape(const Plan& P) {
 // g's leaf k sits at off[g] + k in the primes buffer and at D + off[g] + k in
 // the arenas, D = 2^rins_j when R is a node of Q_1's tree (else 0); from
 // level rins_j on group 0 covers [off[0], off[0] + D + K_0): R's node first.
-void plan_tree(const Layout& Ly, Plan& P, bool batched) {
-  std::vector<Stage>& st = batched ? P.batched : P.plain;
+void plan_tree(const Layout& Ly, Plan& P) {
+  const bool batched = !P.plain;
+  std::vector<Stage>& st = P.tree;
   const uint32_t ng = P.ng;
   auto out_of = [&](int j) -> uint64_t { return (j % 2 == 0) ? Ly.arenaA : Ly.arenaB; };
   auto in_of = [&](int j) -> uint64_t { return j == 0 ? Ly.primes : out_of(j - 1); };
@@ -719,55 +741,49 @@ void plan_tree(const Layout& Ly, Plan& P, bool batched) {
     return D + P.off[gi];
   };
   auto gK = [&](uint32_t gi, int j) -> uint64_t {
-    const uint64_t K = P.off[gi + 1] - P.off[gi];
+    const uint64_t K = P.limbs(gi);
     return (jR >= 0 && gi == 0 && j >= jR) ? K + D : K;
   };
   const TreeShape sh = tree_shape(P);
-  const int LF = CAT_LEAF_LF;
   const int jleaf = sh.jleaf, jf0 = sh.jf0, jf1 = sh.jf1;
   int J = sh.J;
   if (jR >= 0) J = std::max(J, ceil_log2(gK(0, jR)));
-  // Q_e is complete after level jdone - 1 (at least the leaf levels), in
-  // in_of(jdone); the plain form carries early roots up to the same place.
-  // A root completed inside the fused levels is where the fused launch
-  // leaves it, in in_of(jf1 + 1), in both forms.
+  // Q_e is complete after level jdone - 1 (at least the base levels), in
+  // in_of(jdone).  A root completed inside the fused levels is where the fused
+  // launch leaves it, in in_of(jf1 + 1).
   int jdone[CAT_MAX_GROUPS];
   for (uint32_t gi = 0; gi < ng; gi++) {
-    jdone[gi] = std::max(ceil_log2(gK(gi, jR >= 0 ? J : 0)), jleaf);
+    // (single entries are their own roots: no stage)
+    jdone[gi] = J == 0 ? 0 : std::max(ceil_log2(gK(gi, jR >= 0 ? J : 0)), jleaf);
     if (jf0 >= 0 && jdone[gi] > jf0 && jdone[gi] <= jf1 + 1) jdone[gi] = jf1 + 1;
     P.root[gi] = in_of(jdone[gi]) + gpos(gi, jdone[gi]);
   }
-  P.rins_stage[batched ? 0 : 1] = -1;
+  P.rins_stage = -1;
   int jstart = 0;
   if (batched && sh.J > 0) {
-    // leaf packing covers levels 0..LF-1 (reads the primes, writes the arena)
+    // the levels below BASE_J (reads the entries, writes the arena)
     Stage s;
     s.is_leaf = true;
-    s.leaf.ngroups = ng;
-    s.leaf.j = LF;
-    uint64_t nodes = 0;
+    BaseLevel& bl = s.base;
+    bl.ngroups = ng;
     for (uint32_t gi = 0; gi < ng; gi++) {
-      s.leaf.base[gi] = P.off[gi];
-      s.leaf.K[gi] = P.off[gi + 1] - P.off[gi];
-      s.leaf.mpref[gi] = nodes;
-      nodes += (s.leaf.K[gi] + (1ull << LF) - 1) >> LF;
+      bl.src[gi] = P.off[gi];
+      bl.dst[gi] = P.off[gi];
+      bl.K[gi] = P.off[gi + 1] - P.off[gi];
+      bl.s8[gi] = base_s8(P.ebits[gi]);
+      bl.mpref[gi] = bl.nodes;
+      bl.nodes += (uint32_t)((P.limbs(gi) + (1u << BASE_J) - 1) >> BASE_J);
     }
-    s.leaf.mpref[ng] = nodes;
-    s.leaf_nodes = nodes;
+    bl.mpref[ng] = bl.nodes;
     s.a_base = Ly.primes;
     // the buffer the pairwise levels would have written last
     s.c_base = out_of(jleaf - 1) + D;
-    for (uint32_t gi = 0; gi < ng; gi++) {
-      const uint64_t K = P.off[gi + 1] - P.off[gi];
-      // products inside the packed levels: K - nodes
-      P.products += K - ((K + (1ull << LF) - 1) >> LF);
-    }
     st.push_back(s);
     jstart = jleaf;
   }
   int j = jstart;
   for (; j < J; j++) {
-    if (jR >= 0 && j == jR) P.rins_stage[batched ? 0 : 1] = (int)st.size();
+    if (jR >= 0 && j == jR) P.rins_stage = (int)st.size();
     if (batched && j == jf0) {
       // the fused levels: one workgroup per 2^FT_LOGT leaves of every group
       // that still has products there (below rins_j: positions D + off)
@@ -983,9 +999,10 @@ void plan_post(const Layout& Ly, Plan& P) {
   };
   std::vector<Chain> ch;
   for (uint32_t gi = 0; gi < P.ng; gi++) {
-    // Q_e occupies K limbs of its node; its value fits ceil(gbits / 32) of them
-    const uint64_t K = P.off[gi + 1] - P.off[gi];
-    Item q{P.root[gi], cap_of(K, P.gbits[gi]), std::min<uint64_t>(P.gbits[gi], 32 * K)};
+    // Q_e occupies its group's limbs of its node; its value fits ceil(bits / 32)
+    // of them
+    const uint64_t bits = std::min<uint64_t>(P.gbits[gi], (P.off[gi + 1] - P.off[gi]) * P.ebits[gi]);
+    Item q{P.root[gi], cap_of(P.limbs(gi), bits), bits};
     const uint32_t r = P.nreq > 1 ? P.req[gi] : 0;
     if (P.exps[gi] == 1) {
       q1[r] = q;
@@ -1078,8 +1095,8 @@ void plan_post(const Layout& Ly, Plan& P) {
       if (sg.out_pos == old) sg.out_pos = npos;
     P.rins_fill_pos = npos + P.r_limbs;
     P.rins_fill_len = (1ull << P.rins_j) - P.r_limbs;
-    const uint64_t K0 = P.off[1] - P.off[0] + (1ull << P.rins_j);
-    const uint64_t bits = P.gbits[0] + P.r_bits;
+    const uint64_t K0 = P.limbs(0) + (1ull << P.rins_j);
+    const uint64_t bits = std::min<uint64_t>(P.gbits[0], (P.off[1] - P.off[0]) * P.ebits[0]) + P.r_bits;
     P.rpos[0] = P.root[0];
     P.rcap[0] = cap_of(K0, bits);
     P.rone[0] = false;
@@ -1228,52 +1245,69 @@ int rins_level(const Layout& Ly, const Plan& P) {
   const TreeShape sh = tree_shape(P);
   int jdone2 = -1;
   for (uint32_t gi = 1; gi < P.ng; gi++) {
-    int jd = std::max(ceil_log2(P.off[gi + 1] - P.off[gi]), sh.jleaf);
+    int jd = std::max(ceil_log2(P.limbs(gi)), sh.jleaf);
     if (sh.jf0 >= 0 && jd > sh.jf0 && jd <= sh.jf1 + 1) jd = sh.jf1 + 1;
     if (P.exps[gi] >= 2) jdone2 = std::max(jdone2, jd);
   }
   const int j = std::max({ceil_log2(P.r_limbs), jdone2 + 2, sh.jleaf + 1, sh.jf1 + 1});
-  if (ceil_log2(P.off[1] - P.off[0]) < j + 2) return -1;
+  if (ceil_log2(P.limbs(0)) < j + 2) return -1;
   if ((1ull << j) + P.off[P.ng] > Ly.Kmax) return -1;
   return j;
 }
 
-cat_status make_plan(const Layout& Ly, const GroupTable& gt, Plan** out, bool device_tables = true,
-                     const uint32_t* req = nullptr, uint32_t nreq = 1) {
+// cache key of the plan of n in one form
+uint64_t plan_key(uint64_t n, bool plain) { return n | (plain ? 1ull << 63 : 0ull); }
+// ebits: per group, the bit length that none of its entries exceeds (else the
+// layout's).
+cat_status make_plan(const Layout& Ly, const GroupTable& gt, Plan** out, bool plain, bool device_tables = true,
+                     const uint32_t* req = nullptr, uint32_t nreq = 1, const uint32_t* ebits = nullptr) {
   Plan* P = new Plan();
-  P->n = Ly.n;
+  P->n = plan_key(Ly.n, plain);
+  P->plain = plain;
   P->ng = gt.ngroups;
   P->nreq = req ? nreq : 1;
+  P->outer_j = gt.outer;
   if (req)
     for (uint32_t gi = 0; gi < gt.ngroups; gi++) P->req[gi] = req[gi];
   for (uint32_t gi = 0; gi < gt.ngroups; gi++) {
     P->exps[gi] = gt.exps[gi];
     P->gbits[gi] = gt.gbits[gi];
+    P->ebits[gi] = ebits ? ebits[gi] : Ly.ebits;
   }
   for (uint32_t gi = 0; gi <= gt.ngroups; gi++) P->off[gi] = gt.off[gi];
-  auto plan_all = [&]() {
-    P->batched.clear();
-    P->plain.clear();
-    P->post.clear();
-    P->fork_count = -1;
-    P->post_final = 0;
-    plan_tree(Ly, *P, true);
-    // products and their limbs are counted from the pairwise levels of the
-    // plain form (the leaf kernel of the batched form folds the lowest levels)
-    P->products = 0;
-    P->product_limbs = 0;
-    plan_tree(Ly, *P, false);
-    plan_post(Ly, *P);
+  auto plan_all = [&](Plan& Q) {
+    auto both = [&]() {
+      Q.tree.clear();
+      Q.post.clear();
+      Q.fork_count = -1;
+      Q.post_final = 0;
+      Q.products = 0;
+      Q.product_limbs = 0;
+      plan_tree(Ly, Q);
+      plan_post(Ly, Q);
+    };
+    both();
+    const int jR = rins_level(Ly, Q);
+    if (jR >= 0) {
+      Q.rins_j = jR;
+      both();
+    }
   };
-  plan_all();
-  const int jR = rins_level(Ly, *P);
-  if (jR >= 0) {
-    P->rins_j = jR;
-    plan_all();
+  if (!plain) {
+    // products and their limbs are counted from the pairwise levels of the
+    // plain form (the base kernel of the batched form folds the lowest levels)
+    Plan Q = *P;
+    Q.plain = true;
+    plan_all(Q);
+    plan_all(*P);
+    P->products = Q.products;
+    P->product_limbs = Q.product_limbs;
+    P->levels = Q.levels;
+  } else {
+    plan_all(*P);
   }
   std::vector<Stage*> all;
-  for (auto& s : P->batched) all.push_back(&s);
-  for (auto& s : P->plain) all.push_back(&s);
+  for (auto& s : P->tree) all.push_back(&s);
   for (auto& s : P->post) all.push_back(&s);
   // the plan must fit the workspace layout sized from n alone
   for (Stage* s : all) {
@@ -1694,10 +1728,10 @@ cat_status run_stage_batched(Exec& X, const Stage& s) {
     return CAT_OK;
   }
   if (s.is_leaf) {
-    const uint32_t blocks = (uint32_t)((s.leaf_nodes + 255) / 256);
+    const uint32_t blocks = (s.base.nodes + BASE_WAVES - 1) / BASE_WAVES;
     {
-      KTime kt("k_leaf", X.st, (double)s.leaf_nodes);
-      hipLaunchKernelGGL(k_leaf<CAT_LEAF_LF>, dim3(blocks), dim3(256), 0, X.st, s.leaf, s.leaf_nodes, X.W + s.a_base,
+      KTime kt("k_base", X.st, (double)s.base.nodes);
+      hipLaunchKernelGGL(k_base, dim3(blocks), dim3(64 * BASE_WAVES), 0, X.st, s.base, X.W + s.a_base,
                          X.W + s.c_base);
     }
     LAUNCHCHK();
@@ -1844,13 +1878,14 @@ cat_status run_rins_side(Exec& S, Plan& P, bool plain) {
   return CAT_OK;
 }
 
-cat_status run_phase2(Exec& X, Plan& P, bool plain) {
-  std::vector<Stage>& st = plain ? P.plain : P.batched;
+cat_status run_phase2(Exec& X, Plan& P) {
+  const bool plain = P.plain;
+  std::vector<Stage>& st = P.tree;
   if (P.rins_j >= 0) {
     // R is a node of Q_1's tree at the level of stage sr: the powers and R
     // run before it (beside the levels that follow the completion of the
     // groups with e >= 2 when the call has a side stream)
-    const size_t sr = std::min<size_t>((size_t)P.rins_stage[plain ? 1 : 0], st.size());
+    const size_t sr = std::min<size_t>((size_t)P.rins_stage, st.size());
     if (!plain && X.side && P.fork_count >= 0) {
       const size_t nf = std::min<size_t>((size_t)P.fork_count, sr);
       for (size_t k = 0; k < nf; k++) STCHK(run_stage_batched(X, st[k]));
@@ -1911,7 +1946,9 @@ cat_status run_phase2(Exec& X, Plan& P, bool plain) {
 // ----------------------------------------------------------------------------
 // Phase 1 launches (into the workspace; primes to `primes` with capacity cap)
 // ----------------------------------------------------------------------------
-cat_status run_phase1(const Layout& Ly, char* wb, uint32_t* primes, uint64_t cap, hipStream_t st, uint64_t* launches) {
+// powers: one group of prime powers (see sieve.inc.hip) instead of one group per exponent
+cat_status run_phase1(const Layout& Ly, char* wb, uint32_t* primes, uint64_t cap, hipStream_t st, uint64_t* launches,
+                      bool powers) {
   uint32_t* W = (uint32_t*)wb;
   GroupTable* gt = (GroupTable*)(wb + Ly.gtab);
   hipLaunchKernelGGL(k_seeds, dim3(1), dim3(1024), 0, st, Ly.n, (uint32_t)Ly.s, W + Ly.seeds, (int32_t*)(W + Ly.seed_e),
@@ -1933,7 +1970,8 @@ cat_status run_phase1(const Layout& Ly, char* wb, uint32_t* primes, uint64_t cap
     LAUNCHCHK();
   }
   hipLaunchKernelGGL(k_groups, dim3(1), dim3(1024), 0, st, (uint32_t)Ly.nseg, (const uint32_t*)(W + Ly.seg_cnt),
-                     W + Ly.seg_off, (const uint32_t*)(W + Ly.seeds), (const int32_t*)(W + Ly.seed_e), primes, cap, gt);
+                     W + Ly.seg_off, (const uint32_t*)(W + Ly.seeds), (const int32_t*)(W + Ly.seed_e), primes, cap, gt,
+                     powers ? base_s8(Ly.ebits) : 0u);
   LAUNCHCHK();
   if (Ly.nseg > 0) {
     if (Ly.seg_log == SIEVE_SEG_LOG_HUGE)
@@ -1963,17 +2001,26 @@ cat_status read_groups(const Layout& Ly, char* wb, hipStream_t st, GroupTable* o
   return CAT_OK;
 }
 
-Plan* find_plan_in(std::map<uint64_t, Plan*>& plans, uint64_t n, const GroupTable& gt) {
-  auto it = plans.find(n);
+Plan* find_plan_in(std::map<uint64_t, Plan*>& plans, uint64_t n, bool plain, const GroupTable& gt) {
+  auto it = plans.find(plan_key(n, plain));
   if (it == plans.end()) return nullptr;
   Plan* P = it->second;
-  if (P->ng != gt.ngroups) return nullptr;
+  if (P->ng != gt.ngroups || P->outer_j != gt.outer) return nullptr;
   for (uint32_t k = 0; k < gt.ngroups; k++)
     if (P->exps[k] != gt.exps[k] || P->off[k + 1] != gt.off[k + 1] || P->gbits[k] != gt.gbits[k]) return nullptr;
   return P;
 }
 
-Plan* find_plan(uint64_t n, const GroupTable& gt) { return find_plan_in(g.plans, n, gt); }
+Plan* find_plan(uint64_t n, bool plain, const GroupTable& gt) { return find_plan_in(g.plans, n, plain, gt); }
+
+// C(n) in batched form takes the powers form of Phase 1 (one group, no powers
+// after the tree) unless R is kept out of the tree
+bool powers_form(bool plain) { return !plain && g_rins; }
+// primes of a group table, without the ones that pad R's node
+uint64_t table_primes(const GroupTable& gt) {
+  const uint64_t all = gt.off[gt.ngroups];
+  return gt.outer >= 0 ? all - gt.n_seed_e1 + gt.n_pow : all;
+}
 
 // Plans of the allocation-free entry point: kept apart from the main cache
 // (whose eviction destroys graphs); they hold no device memory, so dropping
@@ -2341,6 +2388,7 @@ Layout layout_phase1(uint64_t n) {
   Layout L;
   L.n = n;
   L.s = isqrt64(2 * n);
+  L.ebits = bit_len(2 * n);
   L.i0 = (L.s + 1) / 2;
   L.i_end = n;
   L.seg_log = sieve_seg_log(L.i0, L.i_end);
@@ -2539,6 +2587,7 @@ Layout make_layout_ratio(const RatioSpec& r) {
   Layout L;
   L.n = 0;
   L.s = isqrt64(r.A);
+  L.ebits = bit_len(r.A);
   L.i0 = (L.s + 1) / 2;
   L.i_end = (r.A + 1) / 2;   // odd m = 2i + 1 <= A
   L.np_cap = pi_bound(r.A) + 64;
@@ -2602,6 +2651,7 @@ cat_status read_groups_ratio(const Layout& Ly, char* wb, hipStream_t st, GroupTa
   HIPCHK(hipMemcpyAsync(g.pin, wb + Ly.gtab, sizeof(GroupTable), hipMemcpyDeviceToHost, st));
   HIPCHK(hipStreamSynchronize(st));
   memcpy(out, g.pin, sizeof(GroupTable));
+  out->outer = -1;
   if (out->err & CAT_DEVERR_NEG_EXP) return CAT_EINVAL;    // N is not an integer
   if (out->err & CAT_DEVERR_RANGE) return CAT_ERANGE;      // an exponent reaches 2^32
   if (out->err & CAT_DEVERR_BOUNDS) return CAT_EINTERNAL;
@@ -2619,13 +2669,13 @@ static cat_status exact_in_workspace(uint64_t n, const Layout& Ly, char* wb, uin
                               uint64_t launches) {
   cat_stats stats{};
   unsigned long long* top = (unsigned long long*)(wb + Ly.top);
-  STCHK(run_phase1(Ly, wb, (uint32_t*)wb + Ly.primes, Ly.Kmax, st, &launches));
+  STCHK(run_phase1(Ly, wb, (uint32_t*)wb + Ly.primes, Ly.Kmax, st, &launches, powers_form(plain)));
   GroupTable gt;
   STCHK(read_groups(Ly, wb, st, &gt));
   if (gt.err & CAT_DEVERR_BOUNDS) return CAT_EINTERNAL;
-  Plan* P = noalloc ? find_plan_in(g.noalloc_plans, n, gt) : find_plan(n, gt);
+  Plan* P = noalloc ? find_plan_in(g.noalloc_plans, n, plain, gt) : find_plan(n, plain, gt);
   if (!P) {
-    STCHK(make_plan(Ly, gt, &P, !noalloc));
+    STCHK(make_plan(Ly, gt, &P, plain, !noalloc));
     if (noalloc) remember_noalloc_plan(P);
     else remember_plan(P);
   }
@@ -2644,7 +2694,7 @@ static cat_status exact_in_workspace(uint64_t n, const Layout& Ly, char* wb, uin
     return CAT_OK;
   }
   auto record = [&](Exec& E) -> cat_status {
-    STCHK(run_phase2(E, *P, plain));
+    STCHK(run_phase2(E, *P));
     const uint32_t blocks = top_scan_blocks(P->result_cap);
     hipLaunchKernelGGL(k_top_nonzero, dim3(blocks), dim3(256), 0, E.st, W + P->result_pos, P->result_cap, top,
                        (uint32_t*)nullptr, (uint64_t)0);
@@ -2703,9 +2753,9 @@ static cat_status exact_in_workspace(uint64_t n, const Layout& Ly, char* wb, uin
   stats.products = P->products;
   stats.product_limbs = P->product_limbs;
   stats.launches = launches;
-  stats.n_primes = gt.off[gt.ngroups];
+  stats.n_primes = table_primes(gt);
   stats.levels = P->levels;
-  stats.outer_level = P->rins_j;
+  stats.outer_level = P->rins_j >= 0 ? P->rins_j : P->outer_j;
   stats.graph_replayed = replayed ? 1 : 0;
   g.stats = stats;
   if (cap < L) return CAT_ERANGE;
@@ -2873,7 +2923,7 @@ cat_status catalan_factor(uint64_t n, uint32_t* d_primes, size_t primes_cap, uin
   hipStream_t st = (hipStream_t)stream;
   uint64_t launches = 0;
   uint32_t dummy = 0;
-  STCHK(run_phase1(Ly, (char*)d_work, d_primes ? d_primes : &dummy, d_primes ? primes_cap : 0, st, &launches));
+  STCHK(run_phase1(Ly, (char*)d_work, d_primes ? d_primes : &dummy, d_primes ? primes_cap : 0, st, &launches, false));
   GroupTable gt;
   STCHK(read_groups(Ly, (char*)d_work, st, &gt));
   *n_groups = gt.ngroups;
@@ -2924,10 +2974,10 @@ cat_status catalan_exact_ex(uint64_t n, uint32_t* d_limbs, size_t cap, size_t* n
       uint64_t nl = 0;
       STCHK(capture_graph(
           [&](hipStream_t cs) -> cat_status {
-            STCHK(run_phase1(Ly, wb, (uint32_t*)wb + Ly.primes, Ly.Kmax, cs, &nl));
+            STCHK(run_phase1(Ly, wb, (uint32_t*)wb + Ly.primes, Ly.Kmax, cs, &nl, powers_form(false)));
             Exec E = make_exec(Ly, wb, cs);
             E.side = g.side_stream;
-            STCHK(run_phase2(E, *P, false));
+            STCHK(run_phase2(E, *P));
             const uint32_t blocks = top_scan_blocks(P->result_cap);
             const uint64_t ncopy = std::min<uint64_t>(P->result_cap, cap);
             hipLaunchKernelGGL(k_top_nonzero, dim3(blocks), dim3(256), 0, cs, E.W + P->result_pos, P->result_cap,
@@ -2951,15 +3001,15 @@ cat_status catalan_exact_ex(uint64_t n, uint32_t* d_limbs, size_t cap, size_t* n
     uint32_t derr = 0;
     memcpy(&L, pin + CTL_TOP, 8);
     memcpy(&derr, pin + CTL_ERR, 4);
-    if (gt.err || find_plan(n, gt) != P) return CAT_EINTERNAL;
+    if (gt.err || find_plan(n, false, gt) != P) return CAT_EINTERNAL;
     if (derr || L == 0) return CAT_EINTERNAL;
     *n_limbs = (size_t)L;
     stats.products = P->products;
     stats.product_limbs = P->product_limbs;
     stats.launches = replayed ? 1 : launches;
-    stats.n_primes = gt.off[gt.ngroups];
+    stats.n_primes = table_primes(gt);
     stats.levels = P->levels;
-  stats.outer_level = P->rins_j;
+    stats.outer_level = P->rins_j >= 0 ? P->rins_j : P->outer_j;
     stats.graph_replayed = replayed ? 1 : 0;
     g.stats = stats;
     if (cap < L) return CAT_ERANGE;
@@ -3170,7 +3220,7 @@ cat_status catalan_begin(uint64_t n, void* d_work, size_t work_bytes, void* stre
   t->wb = (char*)d_work;
   t->st = (hipStream_t)stream;
   uint64_t launches = 0;
-  cat_status s = run_phase1(t->Ly, t->wb, (uint32_t*)t->wb + t->Ly.primes, t->Ly.Kmax, t->st, &launches);
+  cat_status s = run_phase1(t->Ly, t->wb, (uint32_t*)t->wb + t->Ly.primes, t->Ly.Kmax, t->st, &launches, powers_form(false));
   if (s == CAT_OK) {
     hipError_t e = hipMemcpyAsync(t->pin, t->wb + t->Ly.gtab, sizeof(GroupTable), hipMemcpyDeviceToHost, t->st);
     if (e == hipSuccess) e = hipEventRecord(t->ev, t->st);
@@ -3208,9 +3258,9 @@ cat_status catalan_continue(cat_ticket ticket, uint32_t* d_limbs, size_t cap) {
   GroupTable gt;
   memcpy(&gt, t->pin, sizeof(GroupTable));
   if (gt.err || gt.ngroups > CAT_MAX_GROUPS) return CAT_EINTERNAL;
-  Plan* P = find_plan(t->n, gt);
+  Plan* P = find_plan(t->n, false, gt);
   if (!P) {
-    STCHK(make_plan(t->Ly, gt, &P));
+    STCHK(make_plan(t->Ly, gt, &P, false));
     remember_plan(P);
   }
   t->cap = cap;
@@ -3222,7 +3272,7 @@ cat_status catalan_continue(cat_ticket ticket, uint32_t* d_limbs, size_t cap) {
     hipLaunchKernelGGL(k_fill, dim3(1), dim3(64), 0, t->st, d_limbs, (uint64_t)1, 1u);
     LAUNCHCHK();
   } else {
-    STCHK(run_phase2(X, *P, false));
+    STCHK(run_phase2(X, *P));
     const uint32_t blocks = top_scan_blocks(P->result_cap);
     const uint64_t ncopy = std::min<uint64_t>(P->result_cap, cap);
     hipLaunchKernelGGL(k_top_nonzero, dim3(blocks), dim3(256), 0, t->st, X.W + P->result_pos, P->result_cap, top,
@@ -3324,7 +3374,8 @@ cat_status catalan_batch_begin(uint32_t k, const uint64_t* ns, void* d_work, siz
   uint64_t launches = 0;
   cat_status s = CAT_OK;
   for (uint32_t r = 0; r < k && s == CAT_OK; r++) {
-    s = run_phase1(B.p1[r], wb + B.p1_off[r], stage + B.stage[r], B.kmax[r], t->st, &launches);
+    s = run_phase1(B.p1[r], wb + B.p1_off[r], stage + B.stage[r], B.kmax[r], t->st, &launches,
+                   powers_form(false));
     if (s == CAT_OK) {
       const hipError_t e = hipMemcpyAsync(pin + bpin_gt(r), wb + B.p1_off[r] + B.p1[r].gtab, sizeof(GroupTable),
                                           hipMemcpyDeviceToHost, t->st);
@@ -3410,7 +3461,8 @@ cat_status catalan_batch_continue(cat_ticket ticket, uint32_t* const* d_limbs, c
       r1++;
     }
     GroupTable gtc{};
-    uint32_t req[CAT_MAX_GROUPS] = {};
+    gtc.outer = -1;
+    uint32_t req[CAT_MAX_GROUPS] = {}, eb[CAT_MAX_GROUPS] = {};
     std::vector<uint32_t> members;
     for (uint32_t r = r0; r < r1; r++) {
       if (b->status[r] != CAT_OK) continue;
@@ -3421,6 +3473,7 @@ cat_status catalan_batch_continue(cat_ticket ticket, uint32_t* const* d_limbs, c
         gtc.off[gtc.ngroups] = q[r] + gts[r].off[gg];
         gtc.gbits[gtc.ngroups] = gts[r].gbits[gg];
         req[gtc.ngroups] = i;
+        eb[gtc.ngroups] = B.p1[r].ebits;
         gtc.ngroups++;
       }
       gtc.off[gtc.ngroups] = q[r] + gts[r].off[gts[r].ngroups];
@@ -3428,10 +3481,10 @@ cat_status catalan_batch_continue(cat_ticket ticket, uint32_t* const* d_limbs, c
     Plan* P = nullptr;
     if (gtc.ngroups) {
       // no device tables: the plan is freed as soon as its launches are queued
-      STCHK(make_plan(B.c, gtc, &P, false, req, (uint32_t)members.size()));
+      STCHK(make_plan(B.c, gtc, &P, false, false, req, (uint32_t)members.size(), eb));
       Exec X = make_exec(B.c, cw, st);
       X.crt_epoch = epoch;
-      const cat_status rs = run_phase2(X, *P, false);
+      const cat_status rs = run_phase2(X, *P);
       epoch = X.crt_epoch;
       if (rs != CAT_OK) {
         free_plan(P);
@@ -3595,7 +3648,7 @@ cat_status factorial_ratio_exact(const uint64_t* a, uint32_t k, const uint64_t* 
   GroupTable gt;
   STCHK(read_groups_ratio(Ly, wb, st, &gt));
   Plan* P = nullptr;
-  STCHK(make_plan(Ly, gt, &P));
+  STCHK(make_plan(Ly, gt, &P, plain));
   cat_status res = CAT_OK;
   if (P->result_is_one) {
     if (cap < 1) {
@@ -3616,7 +3669,7 @@ cat_status factorial_ratio_exact(const uint64_t* a, uint32_t k, const uint64_t* 
   }
   Exec X = make_exec(Ly, wb, st);
   unsigned long long* top = (unsigned long long*)(wb + Ly.top);
-  res = run_phase2(X, *P, plain);
+  res = run_phase2(X, *P);
   if (res == CAT_OK) {
     const uint32_t blocks = top_scan_blocks(P->result_cap);
     const uint64_t ncopy = std::min<uint64_t>(P->result_cap, cap);
@@ -3634,9 +3687,9 @@ cat_status factorial_ratio_exact(const uint64_t* a, uint32_t k, const uint64_t* 
   stats.products = P->products;
   stats.product_limbs = P->product_limbs;
   stats.launches = launches + X.launches + 1;
-  stats.n_primes = gt.off[gt.ngroups];
+  stats.n_primes = table_primes(gt);
   stats.levels = P->levels;
-  stats.outer_level = P->rins_j;
+  stats.outer_level = P->rins_j >= 0 ? P->rins_j : P->outer_j;
   free_plan(P);
   g.stats = stats;
   if (res != CAT_OK) return res;
@@ -3677,41 +3730,42 @@ cat_status prime_power_product(const uint32_t* d_entries, const uint32_t* h_exps
   hipStream_t st = (hipStream_t)stream;
   char* wb = (char*)d_work;
   uint32_t* W = (uint32_t*)wb;
-  // control block cleared; entries into the tree's leaf buffer, group offsets
-  // and the bit sums in the seed buffer (unused here)
+  // control block cleared; entries into the tree's leaf buffer, with the bit
+  // sums and the longest entry of each group left in the group table
   hipLaunchKernelGGL(k_fill, dim3((uint32_t)std::min<uint64_t>((Ly.ctl_words + 255) / 256, 1024)), dim3(256), 0, st,
                      (uint32_t*)(wb + Ly.gtab), (uint64_t)Ly.ctl_words, 0u);
   LAUNCHCHK();
-  if (G.total) HIPCHK(hipMemcpyAsync(W + Ly.primes, d_entries, G.total * 4, hipMemcpyDeviceToDevice, st));
-  uint64_t* d_off = (uint64_t*)(W + Ly.seeds);
-  unsigned long long* d_bits = (unsigned long long*)(d_off + CAT_MAX_GROUPS + 2);
-  memcpy(g.pin, G.off, sizeof(uint64_t) * (G.ng + 1));
-  HIPCHK(hipMemcpyAsync(d_off, g.pin, sizeof(uint64_t) * (G.ng + 1), hipMemcpyHostToDevice, st));
-  hipLaunchKernelGGL(k_fill, dim3(1), dim3(64), 0, st, (uint32_t*)d_bits, (uint64_t)(2 * CAT_MAX_GROUPS), 0u);
-  LAUNCHCHK();
-  if (G.ng) {
-    // enough workgroups per group to keep HBM busy on the largest group
-    hipLaunchKernelGGL(k_group_bits, dim3(2048, G.ng), dim3(256), 0, st, (const uint32_t*)(W + Ly.primes),
-                       (const uint64_t*)d_off, G.ng, d_bits);
+  if (G.total) {
+    EntryGroups eg{};
+    eg.ng = G.ng;
+    for (uint32_t q = 0; q <= G.ng; q++) eg.off[q] = G.off[q];
+    const uint32_t blocks = (uint32_t)std::min<uint64_t>((G.total + 2047) / 2048, 1024);
+    hipLaunchKernelGGL(k_entries, dim3(blocks), dim3(256), 0, st, eg, d_entries, W + Ly.primes,
+                       (GroupTable*)(wb + Ly.gtab));
     LAUNCHCHK();
   }
-  HIPCHK(hipMemcpyAsync((char*)g.pin + 1024, d_bits, sizeof(uint64_t) * CAT_MAX_GROUPS, hipMemcpyDeviceToHost, st));
+  HIPCHK(hipMemcpyAsync(g.pin, wb + Ly.gtab, sizeof(GroupTable), hipMemcpyDeviceToHost, st));
   HIPCHK(hipStreamSynchronize(st));
+  GroupTable got;
+  memcpy(&got, g.pin, sizeof(got));
   GroupTable gt;
   memset(&gt, 0, sizeof(gt));
   gt.ngroups = G.ng;
+  gt.outer = -1;
+  uint32_t eb[CAT_MAX_GROUPS] = {};
   double lb = 0;
   for (uint32_t q = 0; q < G.ng; q++) {
     gt.exps[q] = G.exps[q];
     gt.off[q] = G.off[q];
-    memcpy(&gt.gbits[q], (char*)g.pin + 1024 + 8 * q, 8);
+    gt.gbits[q] = got.gbits[q];
+    eb[q] = std::max(got.exps[q], 1u);
     if (gt.gbits[q] > (G.off[q + 1] - G.off[q]) * (uint64_t)max_entry_bits) return CAT_EINVAL;
     lb += (double)G.exps[q] * (double)gt.gbits[q];
   }
   gt.off[G.ng] = G.off[G.ng];
   if (lb > 32.0 * (double)((1ull << CAT_MAX_LOGN) - 64)) return CAT_ERANGE;
   Plan* P = nullptr;
-  STCHK(make_plan(Ly, gt, &P));
+  STCHK(make_plan(Ly, gt, &P, (flags & CAT_MODE_PLAIN) != 0, true, nullptr, 1, eb));
   cat_status res = CAT_OK;
   if (P->result_is_one) {
     free_plan(P);
@@ -3727,7 +3781,7 @@ cat_status prime_power_product(const uint32_t* d_entries, const uint32_t* h_exps
   }
   Exec X = make_exec(Ly, wb, st);
   unsigned long long* top = (unsigned long long*)(wb + Ly.top);
-  res = run_phase2(X, *P, (flags & CAT_MODE_PLAIN) != 0);
+  res = run_phase2(X, *P);
   if (res == CAT_OK) {
     const uint32_t blocks = top_scan_blocks(P->result_cap);
     const uint64_t ncopy = std::min<uint64_t>(P->result_cap, cap);

@@ -16,6 +16,12 @@
 //    their groups and writes the group table (exponent ascending).
 //  * k_scatter: one workgroup per segment writes its primes in ascending
 //    order to their final place inside G_1.
+//  * Powers form (s8 > 0, for C(n) itself): every p^(e_p) is at most 2n
+//    (Kummer), so it fits a limb, and C(n) is the product of one group: the
+//    powers of the seeds, then the large primes with e_p = 1.  No power P_e is
+//    formed after the tree.  Where they are few beside the rest, the seeds'
+//    powers are padded with ones to 2^outer limbs (s8 entries per eight limbs),
+//    so that their product R is a node of that level.
 // Every group ends up with its primes ascending; G_1 = {seeds with e = 1}
 // followed by the large primes with e = 1.
 
@@ -39,6 +45,10 @@ struct GroupTable {
   uint32_t err;
   uint32_t exps[CAT_MAX_GROUPS];
   uint64_t off[CAT_MAX_GROUPS + 1];
+  // powers form (below): the seeds with e > 0, and the level of their product R
+  // in the tree (-1: not a node of its own)
+  uint32_t n_pow;
+  int32_t outer;
   // upper bound on the bit length of Q_g (sum of the bit lengths of its
   // primes; 32 per prime where not summed), which bounds the power chains
   uint64_t gbits[CAT_MAX_GROUPS];
@@ -278,7 +288,7 @@ __global__ void __launch_bounds__(SIEVE_THREADS) k_sieve(uint64_t n, uint64_t i0
 // ---------------------------------------------------------------------------
 __global__ void __launch_bounds__(1024) k_groups(uint32_t nseg, const uint32_t* seg_cnt, uint32_t* seg_off,
                                                  const uint32_t* seeds, const int32_t* seed_e,
-                                                 uint32_t* primes, uint64_t cap, GroupTable* gt) {
+                                                 uint32_t* primes, uint64_t cap, GroupTable* gt, uint32_t s8) {
   __shared__ uint32_t tmp[40];
   __shared__ uint32_t cnt_e[CAT_MAX_GROUPS + 1];
   __shared__ unsigned long long bits_e[CAT_MAX_GROUPS + 1];
@@ -306,6 +316,39 @@ __global__ void __launch_bounds__(1024) k_groups(uint32_t nseg, const uint32_t* 
   uint32_t total_large;
   uint32_t pos = block_excl_scan_1024(c, tmp, &total_large);
   for (uint32_t i = lo; i < hi; i++) { seg_off[i] = pos; pos += seg_cnt[i]; }
+  if (s8) {
+    uint32_t cc = 0, cnt;
+#pragma unroll
+    for (int i = 0; i < SCH; i++) cc += se[i] > 0;
+    uint32_t r = block_excl_scan_1024(cc, tmp, &cnt);
+#pragma unroll
+    for (int i = 0; i < SCH; i++)
+      if (se[i] > 0) {
+        uint32_t q = sd[i];
+        for (int32_t e = 1; e < se[i]; e++) q *= sd[i];   // <= 2n
+        if (r < cap) primes[r] = q;
+        r++;
+      }
+    uint32_t lv = 6;
+    while ((1u << lv) < 8 * ((cnt + s8 - 1) / s8)) lv++;
+    const uint32_t padded = (1u << (lv - 3)) * s8;
+    const bool node = 2ull * padded * 8 <= total_large && (uint64_t)padded + total_large <= cap;
+    const uint32_t first = node ? padded : cnt;
+    for (uint32_t i = cnt + tid; i < first; i += T) primes[i] = 1;
+    if (tid == 0) {
+      const uint64_t all = (uint64_t)first + total_large;
+      gt->ngroups = all ? 1 : 0;
+      gt->exps[0] = 1;
+      gt->off[0] = 0;
+      gt->off[all ? 1 : 0] = all;
+      gt->gbits[0] = 32 * all;
+      gt->n_seed_e1 = first;
+      gt->n_pow = cnt;
+      gt->outer = node ? (int32_t)lv : -1;
+      if (all > cap) atomicOr(&gt->err, CAT_DEVERR_BOUNDS);
+    }
+    return;
+  }
   // 2. seed counts per exponent
   if (tid <= CAT_MAX_GROUPS) {
     cnt_e[tid] = 0;
@@ -338,6 +381,7 @@ __global__ void __launch_bounds__(1024) k_groups(uint32_t nseg, const uint32_t* 
     }
     gt->off[g] = o;
     gt->ngroups = g;
+    gt->outer = -1;
     gt->n_seed_e1 = cnt_e[1];
     if (o > cap) atomicOr(&gt->err, CAT_DEVERR_BOUNDS);
     goff[0] = o;  // total
@@ -408,5 +452,55 @@ __global__ void __launch_bounds__(SIEVE_THREADS) k_scatter(uint64_t i0, const ui
       if (at < cap) primes[at] = (uint32_t)(2 * (i_lo + (tid * WPT + k) * 32 + b) + 1);
       at++;
     }
+  }
+}
+
+// ---------------------------------------------------------------------------
+// A caller's entries into the tree's buffer (groups off[g] .. off[g+1]), with
+// the sum of the bit lengths of each group's entries added to gt->gbits and the
+// longest one's to gt->exps (both zero before): one pass, a few atomics per
+// workgroup and group, where 2,048 workgroups per group with one atomic per wave
+// took 100 us for any number of entries.
+struct EntryGroups {
+  uint32_t ng;
+  uint64_t off[CAT_MAX_GROUPS + 1];
+};
+__global__ void __launch_bounds__(256)
+k_entries(EntryGroups eg, const uint32_t* __restrict__ in, uint32_t* __restrict__ out, GroupTable* gt) {
+  __shared__ unsigned long long sum[CAT_MAX_GROUPS];
+  __shared__ uint32_t mx[CAT_MAX_GROUPS];
+  if (threadIdx.x < CAT_MAX_GROUPS) {
+    sum[threadIdx.x] = 0;
+    mx[threadIdx.x] = 0;
+  }
+  __syncthreads();
+  uint32_t g = 0, m = 0;
+  unsigned long long s = 0;
+  const uint64_t total = eg.off[eg.ng];
+  for (uint64_t k = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; k < total;
+       k += (uint64_t)gridDim.x * blockDim.x) {
+    const uint32_t v = in[k];
+    out[k] = v;
+    if (k >= eg.off[g + 1]) {
+      if (m) {
+        atomicAdd(&sum[g], s);
+        atomicMax(&mx[g], m);
+      }
+      s = 0;
+      m = 0;
+      while (k >= eg.off[g + 1]) g++;
+    }
+    const uint32_t b = 32 - __clz(v);
+    s += b;
+    m = b > m ? b : m;
+  }
+  if (m) {
+    atomicAdd(&sum[g], s);
+    atomicMax(&mx[g], m);
+  }
+  __syncthreads();
+  if (threadIdx.x < eg.ng && mx[threadIdx.x]) {
+    atomicAdd((unsigned long long*)&gt->gbits[threadIdx.x], sum[threadIdx.x]);
+    atomicMax(&gt->exps[threadIdx.x], mx[threadIdx.x]);
   }
 }

@@ -1,94 +1,11 @@
 // Small products of the reconstruction tree (Sec. 3.2, Alg. 2: the lower
 // levels of BalancedProductTree(G_e)), plus utility kernels.
 //
-//  * k_leaf<LF>: one thread forms a node of tree level LF directly from its
-//    (up to) 2^LF consecutive primes, by multiplying a register accumulator by
-//    one 32-bit prime at a time.  The node is the same integer the pairwise
-//    tree gives (a product of the same leaves), in the same 2^LF-limb slot.
+//  * k_base: one wave forms a node of 256 limbs from its consecutive primes,
+//    eight limbs at a time by one lane, then five schoolbook levels in LDS.
 //  * k_school: one wave per product of la, lb <= 128 limbs: column sums (a
 //    lane holds up to four consecutive columns, a 64-bit sum and a carry
 //    count each), then the ballot carry-lookahead.
-
-// ---------------------------------------------------------------------------
-// Leaf packing.  Tree view: level LF, node i of group g is written at
-// base[g] + i*2^LF; `tl.mpref` is the prefix count of NODES per group.
-// The leaves and the nodes pass through LDS (row t of the tile holds thread
-// t's node, padded to 2^LF + 1 words so that the row-wise reads of the
-// threads hit distinct banks), so that the global loads and stores of a wave
-// cover whole runs of consecutive words.
-template <int LF>
-__global__ void __launch_bounds__(256)
-k_leaf(TreeLevel tl, uint64_t nnodes, const uint32_t* __restrict__ primes, uint32_t* __restrict__ out) {
-  constexpr int W = 1 << LF;
-  constexpr int RW = W + 1;
-  constexpr int NT = 256;
-  __shared__ uint32_t tile[NT * RW];
-  __shared__ uint64_t noff[NT];
-  __shared__ uint32_t ncnt[NT];
-  const uint32_t tid = threadIdx.x;
-  const uint64_t i0 = (uint64_t)blockIdx.x * NT;
-  {
-    const uint64_t i = i0 + tid;
-    uint64_t off = 0;
-    uint32_t cnt = 0;
-    if (i < nnodes) {
-      uint32_t g = 0;
-      while (g + 1 < tl.ngroups && i >= tl.mpref[g + 1]) g++;
-      const uint64_t il = i - tl.mpref[g];
-      off = tl.base[g] + il * W;
-      const uint64_t rem = tl.K[g] - il * W;
-      cnt = (uint32_t)(rem < (uint64_t)W ? rem : (uint64_t)W);
-    }
-    noff[tid] = off;
-    ncnt[tid] = cnt;
-  }
-  __syncthreads();
-  // leaf k of node t at tile[t RW + k]: lane group of W threads per node,
-  // every load in flight before the first LDS store
-  constexpr int NPR = NT / W;     // nodes per round
-  {
-    uint32_t v[W];
-#pragma unroll
-    for (int r = 0; r < W; r++) {
-      const uint32_t t = r * NPR + tid / W, k = tid % W, c = ncnt[t];
-      v[r] = c ? primes[noff[t] + (k < c ? k : c - 1)] : 0u;
-    }
-#pragma unroll
-    for (int r = 0; r < W; r++) tile[(r * NPR + tid / W) * RW + tid % W] = v[r];
-  }
-  __syncthreads();
-  const uint32_t cnt = ncnt[tid];
-  uint32_t acc[W];
-  {
-    acc[0] = tile[tid * RW];
-#pragma unroll
-    for (int k = 1; k < W; k++) acc[k] = 0;
-#pragma unroll
-    for (int k = 1; k < W; k++) {
-      if ((uint32_t)k < cnt) {
-        const uint32_t q = tile[tid * RW + k];
-        uint32_t carry = 0;
-#pragma unroll
-        for (int l = 0; l < k; l++) {
-          const uint64_t t = (uint64_t)acc[l] * q + carry;
-          acc[l] = (uint32_t)t;
-          carry = (uint32_t)(t >> 32);
-        }
-        acc[k] = carry;
-      }
-    }
-  }
-  // each thread rewrites only its own row: no barrier between its reads and
-  // its writes
-#pragma unroll
-  for (int k = 0; k < W; k++) tile[tid * RW + k] = acc[k];
-  __syncthreads();
-#pragma unroll
-  for (int r = 0; r < W; r++) {
-    const uint32_t t = r * NPR + tid / W, k = tid % W;
-    if (k < ncnt[t]) out[noff[t] + k] = tile[t * RW + k];
-  }
-}
 
 // ---------------------------------------------------------------------------
 // Schoolbook products, la, lb <= 128.  4 waves per block, one product each;
@@ -385,6 +302,177 @@ k_school(DescView dv, uint64_t nmul, const uint32_t* __restrict__ ain, const uin
               lane, err);
 }
 
+// ---------------------------------------------------------------------------
+// The bottom of the product trees: node i of a group, 256 limbs, is the product
+// of the entries [i 32 s8, (i+1) 32 s8) of the group.  s8 entries below 2^B fit
+// eight limbs when s8 B <= 256, so a node takes 32 floor(256 / B) entries and not
+// 256: the tree over C(10^7)'s 25-bit primes has 0.69 M limbs in its slots, not
+// 0.87 M, and C(10^5)'s half as many and one level less.
+// One wave per node: lanes 0 .. 31 multiply s8 entries each (an accumulator of
+// eight limbs), then five schoolbook levels (8 x 8 up to 128 x 128 limbs) with
+// four columns per lane, in the wave's own LDS and without a barrier: operand a
+// of product t at sa[3 h t + h ..), zeros on both sides, operand b at sb[h t ..).
+// About 2,600 instructions per wave; before, a thread formed 64 limbs alone
+// (2,016 dependent multiply-adds, 25 us in a level of any size) and two
+// schoolbook launches followed (7 to 18 us together).  With one group of prime
+// powers instead of a group per exponent (k_groups): C(10^3) 0.106 -> 0.064 ms,
+// C(10^5) 0.212 -> 0.138, C(10^7) 0.581 -> 0.480, C(10^8) 2.83 -> 2.53.
+#define BASE_J 8                 // nodes of 2^8 limbs
+#define BASE_S8_MAX 24
+#define BASE_WAVES 4
+struct BaseLevel {
+  uint32_t ngroups;
+  uint32_t nodes;                          // of all groups
+  uint64_t src[CAT_MAX_GROUPS];            // first entry of group g
+  uint64_t dst[CAT_MAX_GROUPS];            // limb position of its first node
+  uint64_t K[CAT_MAX_GROUPS];              // entries
+  uint32_t s8[CAT_MAX_GROUPS];             // entries per eight limbs
+  uint32_t mpref[CAT_MAX_GROUPS + 1];      // prefix count of nodes
+};
+__global__ void __launch_bounds__(64 * BASE_WAVES)
+k_base(BaseLevel bl, const uint32_t* __restrict__ in, uint32_t* __restrict__ out) {
+  __shared__ __align__(16) uint32_t sa_[BASE_WAVES][384];
+  __shared__ __align__(16) uint32_t sb_[BASE_WAVES][128];
+  __shared__ uint32_t st_[BASE_WAVES][32 * BASE_S8_MAX];
+  const uint32_t w = uni32(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const uint32_t node = uni32(blockIdx.x * BASE_WAVES + w);
+  if (node >= bl.nodes) return;   // whole wave leaves together; no block barrier below
+  uint32_t* sa = sa_[w];
+  uint32_t* sb = sb_[w];
+  uint32_t* st = st_[w];
+  uint32_t g = 0;
+  while (g + 1 < bl.ngroups && node >= bl.mpref[g + 1]) g++;
+  const uint32_t il = node - bl.mpref[g], s8 = bl.s8[g];
+  const uint64_t e0 = (uint64_t)il * 32 * s8, K = bl.K[g];
+  const uint32_t cnt = (uint32_t)min((uint64_t)(32 * s8), K - e0);   // entries of this node
+  {
+    const uint32_t* src = in + bl.src[g] + e0;
+    for (uint32_t i = lane; i < cnt; i += 64) st[i] = src[i];
+  }
+  auto wsync = [] {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  };
+  wsync();
+  // eight limbs per lane (1 where the group has ended)
+  if (lane < 32) {
+    uint32_t acc[8] = {1, 0, 0, 0, 0, 0, 0, 0};
+    const uint32_t i0 = lane * s8, i1 = min(i0 + s8, cnt);
+    for (uint32_t i = i0; i < i1; i++) {
+      const uint32_t q = st[i];
+      uint32_t carry = 0;
+#pragma unroll
+      for (int l = 0; l < 8; l++) {
+        const uint64_t t = (uint64_t)acc[l] * q + carry;
+        acc[l] = (uint32_t)t;
+        carry = (uint32_t)(t >> 32);
+      }
+    }
+    // h = 8: piece 2 t is operand a of product t, piece 2 t + 1 operand b
+    const uint32_t t = lane >> 1;
+#pragma unroll
+    for (int l = 0; l < 8; l++) {
+      if (lane & 1) {
+        sb[8 * t + l] = acc[l];
+      } else {
+        sa[24 * t + l] = 0;
+        sa[24 * t + 8 + l] = acc[l];
+        sa[24 * t + 16 + l] = 0;
+      }
+    }
+  }
+  wsync();
+  uint32_t r[4];
+  for (uint32_t lh = 3; lh <= 7; lh++) {
+    const uint32_t h = 1u << lh;
+    // columns k0 .. k0 + 3 of product t
+    const uint32_t t = (4 * lane) >> (lh + 1), k0 = (4 * lane) & (2 * h - 1);
+    const uint32_t* pa = sa + 3 * h * t + h + k0;
+    const uint32_t* pb = sb + h * t;
+    uint32_t wv[4], top[4] = {0, 0, 0, 0};
+    uint64_t acc[4] = {0, 0, 0, 0};
+#pragma unroll
+    for (int e = 0; e < 4; e++) wv[e] = pa[e];
+    const uint32_t* pw = pa;
+#pragma unroll 2
+    for (uint32_t j = 0; j < h; j += 4) {
+      const uint4 b = *(const uint4*)&pb[j];
+      const uint32_t n0 = pw[-1], n1 = pw[-2], n2 = pw[-3], n3 = pw[-4];
+      pw -= 4;
+      colsum_mac4(acc[0], acc[1], acc[2], acc[3], top[0], top[1], top[2], top[3], wv[0], wv[1], wv[2], wv[3], b.x);
+      colsum_mac4(acc[0], acc[1], acc[2], acc[3], top[0], top[1], top[2], top[3], n0, wv[0], wv[1], wv[2], b.y);
+      colsum_mac4(acc[0], acc[1], acc[2], acc[3], top[0], top[1], top[2], top[3], n1, n0, wv[0], wv[1], b.z);
+      colsum_mac4(acc[0], acc[1], acc[2], acc[3], top[0], top[1], top[2], top[3], n2, n1, n0, wv[0], b.w);
+      wv[0] = n3;
+      wv[1] = n2;
+      wv[2] = n1;
+      wv[3] = n0;
+    }
+    // limb k: lo(V_k) + mid(V_(k-1)) + hi(V_(k-2)) and carries; a product's
+    // columns take nothing from the lane of the product before it
+    const bool first = k0 == 0;
+    uint32_t m3 = __shfl_up((uint32_t)(acc[3] >> 32), 1, 64), t3 = __shfl_up(top[3], 1, 64),
+             t2 = __shfl_up(top[2], 1, 64);
+    if (first) m3 = t3 = t2 = 0;
+    uint64_t s[4];
+    s[0] = (uint64_t)(uint32_t)acc[0] + m3 + t2;
+    s[1] = (uint64_t)(uint32_t)acc[1] + (uint32_t)(acc[0] >> 32) + t3;
+    s[2] = (uint64_t)(uint32_t)acc[2] + (uint32_t)(acc[1] >> 32) + top[0];
+    s[3] = (uint64_t)(uint32_t)acc[3] + (uint32_t)(acc[2] >> 32) + top[1];
+    uint32_t y = __shfl_up((uint32_t)(s[3] >> 32), 1, 64);
+    if (first) y = 0;
+    uint64_t u[4];
+    bool G = false, P = true;
+#pragma unroll
+    for (int e = 0; e < 4; e++) {
+      u[e] = (s[e] & 0xFFFFFFFFull) + y;
+      y = (uint32_t)(s[e] >> 32);
+      const bool gg = u[e] >= (1ull << 32), pp = u[e] == 0xFFFFFFFFull;
+      G = gg || (pp && G);
+      P = P && pp;
+    }
+    // (no product carries out of its 2 h limbs, so one scan serves them all)
+    uint32_t cout;
+    bool ap;
+    uint32_t c = wave_carry(G, P, 0, &cout, &ap);
+#pragma unroll
+    for (int e = 0; e < 4; e++) {
+      const uint64_t x = u[e] + c;
+      c = (uint32_t)(x >> 32);
+      r[e] = (uint32_t)x;
+    }
+    if (lh == 7) break;
+    wsync();   // every lane has read this level's operands
+    // product t of 2 h limbs: operand a (t even) or b of product t / 2
+    const uint32_t h2 = 2 * h, t2i = t >> 1;
+    if (t & 1) {
+      *(uint4*)&sb[h2 * t2i + k0] = make_uint4(r[0], r[1], r[2], r[3]);
+    } else {
+      uint32_t* q = sa + 3 * h2 * t2i + k0;
+      *(uint4*)q = make_uint4(0, 0, 0, 0);
+      *(uint4*)(q + h2) = make_uint4(r[0], r[1], r[2], r[3]);
+      *(uint4*)(q + 2 * h2) = make_uint4(0, 0, 0, 0);
+    }
+    wsync();
+  }
+  // the node's slot: 256 limbs; in the last one eight per started piece, and one
+  // per entry at most
+  const uint64_t left = min(K, 8 * ((K + s8 - 1) / s8)) - ((uint64_t)il << BASE_J);
+  const uint32_t len = (uint32_t)min((uint64_t)256, left);
+  uint32_t* o = out + bl.dst[g] + ((uint64_t)il << BASE_J) + 4 * lane;
+  if (4 * lane + 4 <= len) {
+    struct W4 {
+      uint32_t w[4];
+    } v = {{r[0], r[1], r[2], r[3]}};
+    *(W4*)o = v;
+  } else {
+#pragma unroll
+    for (int e = 0; e < 4; e++)
+      if (4 * lane + e < len) o[e] = r[e];
+  }
+}
+
 // A chain of schoolbook steps in one workgroup, each step's products (one wave
 // each) reading the results of earlier steps: the powers P_e and their product
 // R, whose steps hold a few short products.  As launches of their own they cost
@@ -513,19 +601,6 @@ __global__ void __launch_bounds__(256) k_diff_top(const uint32_t* __restrict__ x
     for (int w = 1; w < (int)(blockDim.x >> 6); w++) best = part[w] > best ? part[w] : best;
     if (best) atomicMax(top, best);
   }
-}
-
-// Sum of the bit lengths of the entries of each group (bounds on log2 Q_g).
-__global__ void __launch_bounds__(256) k_group_bits(const uint32_t* __restrict__ x, const uint64_t* __restrict__ off,
-                                                    uint32_t ngroups, unsigned long long* __restrict__ gbits) {
-  const uint32_t g = blockIdx.y;
-  if (g >= ngroups) return;
-  unsigned long long s = 0;
-  for (uint64_t k = off[g] + (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; k < off[g + 1];
-       k += (uint64_t)gridDim.x * blockDim.x)
-    s += (unsigned long long)(32 - __clz(x[k]));
-  for (int d = 32; d >= 1; d >>= 1) s += __shfl_xor(s, d, 64);
-  if ((threadIdx.x & 63) == 0 && s) atomicAdd(&gbits[g], s);
 }
 
 // Fingerprints of a limb vector: x mod (2^32 - 5), x mod (2^32 + 1), x mod
