@@ -42,6 +42,10 @@ hipError_t fntt_lds(const FBatch& b, hipStream_t st);
 bool fntt_fused_fits(int logD);
 hipError_t fntt_fused(const FBatch& b, uint32_t* out, const CopyList& tails, const uint32_t* tin, uint32_t* tout,
                       uint32_t* err, hipStream_t st);
+// The same for several buckets over device tables: tile b is the products
+// tiles[b].x .. (tiles[b].y: logD + 1, products << 8; 2^11 slots at most).
+hipError_t fntt_fused_mix(const MulDesc* desc, const uint2* tiles, uint32_t ntiles, const uint32_t* ain,
+                          const uint32_t* bin, uint32_t* out, uint32_t* err, hipStream_t st);
 // column pass over sub-problems of 2^logS digits, L = 2^logL of them along the
 // column; outer (prevS, prevL): the pass before it, whose twiddles this pass
 // applies (0: none).  first: the operands come from limbs, the results go to

@@ -1706,6 +1706,13 @@ SegView stage_segs(const Stage& s) { return s.sv; }
 cat_status run_stage_batched(Exec& X, const Stage& s) {
   if (s.cls == CLS_FUSED) {
     if (s.host_tiles.empty()) return CAT_OK;
+    if (s.fp) {
+      KTime kt("k_ffused_mix", X.st, s.fused_bfly);
+      HIPCHK(fntt_fused_mix(s.fm.desc, s.fm.tiles, (uint32_t)s.host_tiles.size(), X.A ? X.A : X.W + s.a_base,
+                            X.B ? X.B : X.W + s.b_base, out_base(X, s), X.err, X.st));
+      X.launches++;
+      return CAT_OK;
+    }
     {
       KTime kt("k_mul_fused", X.st, s.fused_bfly);
       hipLaunchKernelGGL(k_mul_fused, dim3((uint32_t)s.host_tiles.size()), dim3(FT_THREADS), 0, X.st, s.fm,
@@ -2097,9 +2104,11 @@ struct MulPlanImpl {
 };
 
 // async_upload: the device tables are copied on `st` (ordered before the
-// plan's launches there) instead of by a synchronous copy.
+// plan's launches there) instead of by a synchronous copy.  tables = false: the
+// sizes only, nothing on the device.
 cat_status mul_plan_create(uint32_t batch, const uint64_t* a_off, const uint64_t* b_off, const uint64_t* c_off,
-                           uint32_t flags, MulPlanImpl** out, bool async_upload = false, hipStream_t upload_st = nullptr) {
+                           uint32_t flags, MulPlanImpl** out, bool async_upload = false, hipStream_t upload_st = nullptr,
+                           bool tables = true) {
   if (!a_off || !b_off || (!c_off && batch > 0)) return CAT_EINVAL;
   MulPlanImpl* M = new MulPlanImpl();
   M->batch = batch;
@@ -2154,17 +2163,22 @@ cat_status mul_plan_create(uint32_t batch, const uint64_t* a_off, const uint64_t
   if (!(flags & CAT_MODE_PLAIN) && g_fuse_logn) {
     uint64_t slots = 0;
     int nf = 0;
+    auto fuses = [](const Stage& st) {
+      return st.cls == CLS_LDS && st.logN <= (int)g_fuse_logn && (!st.fp || fp_fused(st));
+    };
     for (const Stage& st : M->stages)
-      if (st.cls == CLS_LDS && st.logN <= (int)g_fuse_logn) {
+      if (fuses(st)) {
         slots += st.nmul << st.logN;
         nf++;
       }
-    if (nf > 0 && slots <= FUSE_MAX_LEAVES) {
+    // (a single FP64 bucket is one launch by itself)
+    if (nf > (g_fp ? 1 : 0) && slots <= FUSE_MAX_LEAVES) {
       Stage f;
       f.cls = CLS_FUSED;
+      f.fp = g_fp;
       std::vector<Stage> kept;
       for (Stage& st : M->stages) {
-        if (!(st.cls == CLS_LDS && st.logN <= (int)g_fuse_logn)) {
+        if (!fuses(st)) {
           kept.push_back(st);
           continue;
         }
@@ -2196,6 +2210,10 @@ cat_status mul_plan_create(uint32_t batch, const uint64_t* a_off, const uint64_t
   M->off_res = take(3 * (M->res_len + 64) * 4);
   M->off_F = take(M->F_words * 4);
   M->total = off;
+  if (!tables) {
+    *out = M;
+    return CAT_OK;
+  }
   std::vector<Stage*> all;
   for (auto& st : M->stages) all.push_back(&st);
   cat_status e = upload_tables(all, &M->dev, true, async_upload ? &M->host_tables : nullptr, upload_st);
@@ -3078,7 +3096,7 @@ cat_status bigint_mul_workspace(uint32_t batch, const uint64_t* h_a_off, const u
   STCHK(set_device());
   std::vector<uint64_t> c(batch + 1, 0);
   MulPlanImpl* M = nullptr;
-  STCHK(mul_plan_create(batch, h_a_off, h_b_off, c.data(), 0, &M));
+  STCHK(mul_plan_create(batch, h_a_off, h_b_off, c.data(), 0, &M, false, nullptr, false));
   *workspace_bytes = M->total;
   mul_plan_free(M);
   return CAT_OK;
