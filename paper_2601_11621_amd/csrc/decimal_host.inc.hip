@@ -264,9 +264,7 @@ cat_status dec_record(const DecPlan& P, Exec X, const uint32_t* d_x, uint64_t n_
   }
   const uint32_t* dig = X.W + P.x[h & 1];
   const uint64_t nd = P.lv[h].len;
-  hipLaunchKernelGGL(k_top_nonzero, dim3((uint32_t)std::min<uint64_t>((nd + 255) / 256, 512)), dim3(256), 0, st, dig,
-                     nd, top, (uint32_t*)nullptr, (uint64_t)0);
-  LAUNCHCHK();
+  STCHK(launch_top(st, dig, nd, top, nullptr, 0));
   hipLaunchKernelGGL(k_dec_ascii, dim3((uint32_t)((nd + 255) / 256)), dim3(256), 0, st, dig,
                      (const unsigned long long*)top, d_out ? cap : (uint64_t)0, d_out, nc);
   LAUNCHCHK();

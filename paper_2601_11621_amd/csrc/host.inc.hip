@@ -145,11 +145,11 @@ uint2 h_pair2(uint32_t W, const PrimeC& pc) {
   return r;
 }
 
-// Workgroups of the result length scan (k_top_nonzero, 256 threads, one
-// atomic each): 512 up to 2^24 limbs, then one per 2^15 limbs up to 4,096, so
-// that a long result is read by enough waves to reach HBM bandwidth.
+// Workgroups of the result length scan (k_top_nonzero, 256 threads, two atomics
+// each): one per 2^12 limbs up to 512, and one per 2^15 limbs beyond 2^24, up to
+// 4,096, so that a long result is read by enough waves to reach HBM bandwidth.
 uint32_t top_scan_blocks(uint64_t cap) {
-  const uint64_t want = std::min<uint64_t>(std::max<uint64_t>(cap >> 15, 512), 4096);
+  const uint64_t want = std::min<uint64_t>(std::max<uint64_t>(std::min<uint64_t>((cap >> 12) + 8, 512), cap >> 15), 4096);
   return (uint32_t)std::max<uint64_t>(std::min<uint64_t>((cap + 255) / 256, want), 1);
 }
 
@@ -538,6 +538,7 @@ int sieve_seg_log(uint64_t i0, uint64_t i_end) {
 // byte offsets inside the control block
 #define CTL_TOP 1024
 #define CTL_ERR 1032
+#define CTL_DONE 1036    // blocks of k_top_nonzero that have finished
 #define CTL_READ 1040
 #define CTL_FLAGS 1040
 static_assert(sizeof(GroupTable) <= CTL_TOP, "group table must fit the control block head");
@@ -1953,58 +1954,82 @@ cat_status run_phase2(Exec& X, Plan& P) {
 // ----------------------------------------------------------------------------
 // Phase 1 launches (into the workspace; primes to `primes` with capacity cap)
 // ----------------------------------------------------------------------------
-// powers: one group of prime powers (see sieve.inc.hip) instead of one group per exponent
-cat_status run_phase1(const Layout& Ly, char* wb, uint32_t* primes, uint64_t cap, hipStream_t st, uint64_t* launches,
-                      bool powers) {
+// One request's part of the Phase-1 launches.  powers: one group of prime powers
+// (see sieve.inc.hip) instead of one group per exponent; pin: pinned host memory
+// that receives the group table.
+P1Req phase1_req(const Layout& Ly, char* wb, uint32_t* primes, uint64_t cap, bool powers, void* pin) {
   uint32_t* W = (uint32_t*)wb;
-  GroupTable* gt = (GroupTable*)(wb + Ly.gtab);
-  hipLaunchKernelGGL(k_seeds, dim3(1), dim3(1024), 0, st, Ly.n, (uint32_t)Ly.s, W + Ly.seeds, (int32_t*)(W + Ly.seed_e),
-                     gt, (uint32_t*)gt, (uint64_t)Ly.ctl_words);
+  P1Req r{};
+  r.n = Ly.n;
+  r.cap = cap;
+  r.s = (uint32_t)Ly.s;
+  r.nseg = (uint32_t)Ly.nseg;
+  r.s8 = powers ? base_s8(Ly.ebits) : 0;
+  r.ctl_words = (uint32_t)Ly.ctl_words;
+  r.seeds = W + Ly.seeds;
+  r.seed_e = (int32_t*)(W + Ly.seed_e);
+  r.seg_cnt = W + Ly.seg_cnt;
+  r.seg_off = W + Ly.seg_off;
+  r.bitmap = W + Ly.bitmap;
+  r.primes = primes;
+  r.gt = (GroupTable*)(wb + Ly.gtab);
+  r.pin = (GroupTable*)pin;
+  return r;
+}
+bool phase1_small(const P1Req& r) { return r.s8 && r.n <= (1ull << P1_SMALL_LOG); }
+
+template <int SL, int NR>
+cat_status launch_phase1(const P1Batch<NR>& pb, uint32_t k, uint32_t nseg, hipStream_t st, uint64_t* launches) {
+  hipLaunchKernelGGL(k_seeds<NR>, dim3(k), dim3(1024), 0, st, pb);
   LAUNCHCHK();
-  if (Ly.nseg > 0) {
-    if (Ly.seg_log == SIEVE_SEG_LOG_HUGE)
-      hipLaunchKernelGGL(k_sieve<SIEVE_SEG_LOG_HUGE>, dim3((uint32_t)Ly.nseg), dim3(SIEVE_THREADS), 0, st, Ly.n, Ly.i0,
-                         Ly.i_end, (const uint32_t*)(W + Ly.seeds), (const GroupTable*)gt, W + Ly.bitmap,
-                         W + Ly.seg_cnt);
-    else if (Ly.seg_log == SIEVE_SEG_LOG_BIG)
-      hipLaunchKernelGGL(k_sieve<SIEVE_SEG_LOG_BIG>, dim3((uint32_t)Ly.nseg), dim3(SIEVE_THREADS), 0, st, Ly.n, Ly.i0,
-                         Ly.i_end, (const uint32_t*)(W + Ly.seeds), (const GroupTable*)gt, W + Ly.bitmap,
-                         W + Ly.seg_cnt);
-    else
-      hipLaunchKernelGGL(k_sieve<SIEVE_SEG_LOG>, dim3((uint32_t)Ly.nseg), dim3(SIEVE_THREADS), 0, st, Ly.n, Ly.i0,
-                         Ly.i_end, (const uint32_t*)(W + Ly.seeds), (const GroupTable*)gt, W + Ly.bitmap,
-                         W + Ly.seg_cnt);
+  if (nseg > 0) {
+    hipLaunchKernelGGL((k_sieve<SL, NR>), dim3(nseg, k), dim3(SIEVE_THREADS), 0, st, pb);
     LAUNCHCHK();
   }
-  hipLaunchKernelGGL(k_groups, dim3(1), dim3(1024), 0, st, (uint32_t)Ly.nseg, (const uint32_t*)(W + Ly.seg_cnt),
-                     W + Ly.seg_off, (const uint32_t*)(W + Ly.seeds), (const int32_t*)(W + Ly.seed_e), primes, cap, gt,
-                     powers ? base_s8(Ly.ebits) : 0u);
+  hipLaunchKernelGGL(k_groups<NR>, dim3(k), dim3(1024), 0, st, pb);
   LAUNCHCHK();
-  if (Ly.nseg > 0) {
-    if (Ly.seg_log == SIEVE_SEG_LOG_HUGE)
-      hipLaunchKernelGGL(k_scatter<SIEVE_SEG_LOG_HUGE>, dim3((uint32_t)Ly.nseg), dim3(SIEVE_THREADS), 0, st, Ly.i0,
-                         (const uint32_t*)(W + Ly.bitmap), (const uint32_t*)(W + Ly.seg_off), (const GroupTable*)gt,
-                         primes, cap);
-    else if (Ly.seg_log == SIEVE_SEG_LOG_BIG)
-      hipLaunchKernelGGL(k_scatter<SIEVE_SEG_LOG_BIG>, dim3((uint32_t)Ly.nseg), dim3(SIEVE_THREADS), 0, st, Ly.i0,
-                         (const uint32_t*)(W + Ly.bitmap), (const uint32_t*)(W + Ly.seg_off), (const GroupTable*)gt,
-                         primes, cap);
-    else
-      hipLaunchKernelGGL(k_scatter<SIEVE_SEG_LOG>, dim3((uint32_t)Ly.nseg), dim3(SIEVE_THREADS), 0, st, Ly.i0,
-                         (const uint32_t*)(W + Ly.bitmap), (const uint32_t*)(W + Ly.seg_off), (const GroupTable*)gt,
-                         primes, cap);
+  if (nseg > 0) {
+    hipLaunchKernelGGL((k_scatter<SL, NR>), dim3(nseg, k), dim3(SIEVE_THREADS), 0, st, pb);
     LAUNCHCHK();
   }
-  *launches += Ly.nseg > 0 ? 4 : 2;
+  *launches += nseg > 0 ? 4 : 2;
+  return CAT_OK;
+}
+cat_status run_phase1(const Layout& Ly, char* wb, uint32_t* primes, uint64_t cap, hipStream_t st, uint64_t* launches,
+                      bool powers, void* pin) {
+  P1Batch<1> pb{};
+  pb.r[0] = phase1_req(Ly, wb, primes, cap, powers, pin);
+  if (phase1_small(pb.r[0])) {
+    hipLaunchKernelGGL(k_phase1_small<1>, dim3(1), dim3(1024), 0, st, pb);
+    LAUNCHCHK();
+    (*launches)++;
+    return CAT_OK;
+  }
+  if (Ly.seg_log == SIEVE_SEG_LOG_HUGE) return launch_phase1<SIEVE_SEG_LOG_HUGE, 1>(pb, 1, pb.r[0].nseg, st, launches);
+  if (Ly.seg_log == SIEVE_SEG_LOG_BIG) return launch_phase1<SIEVE_SEG_LOG_BIG, 1>(pb, 1, pb.r[0].nseg, st, launches);
+  return launch_phase1<SIEVE_SEG_LOG, 1>(pb, 1, pb.r[0].nseg, st, launches);
+}
+
+// the table that Phase 1 left in pinned memory
+cat_status read_groups(const void* pin, hipStream_t st, GroupTable* out) {
+  HIPCHK(hipStreamSynchronize(st));
+  memcpy(out, pin, sizeof(GroupTable));
+  if (out->err & CAT_DEVERR_NEG_EXP) return CAT_EINTERNAL;
+  if (out->ngroups > CAT_MAX_GROUPS) return CAT_EINTERNAL;
   return CAT_OK;
 }
 
-cat_status read_groups(const Layout& Ly, char* wb, hipStream_t st, GroupTable* out) {
-  HIPCHK(hipMemcpyAsync(g.pin, wb + Ly.gtab, sizeof(GroupTable), hipMemcpyDeviceToHost, st));
-  HIPCHK(hipStreamSynchronize(st));
-  memcpy(out, g.pin, sizeof(GroupTable));
-  if (out->err & CAT_DEVERR_NEG_EXP) return CAT_EINTERNAL;
-  if (out->ngroups > CAT_MAX_GROUPS) return CAT_EINTERNAL;
+// Length of the result at x[0 .. n) to *top, its first ncopy limbs to dst, and
+// the pub_words words at pub (the length among them; `done` is a zeroed counter)
+// to pinned memory.
+cat_status launch_top(hipStream_t st, const uint32_t* x, uint64_t n, unsigned long long* top, uint32_t* dst,
+                      uint64_t ncopy, uint32_t* done = nullptr, const void* pub = nullptr, void* pub_dst = nullptr,
+                      uint32_t pub_words = 0) {
+  TopBatch<1> tb;
+  tb.r[0] = TopReq{x, n, top, dst, ncopy};
+  hipLaunchKernelGGL(k_top_nonzero<1>, dim3(top_scan_blocks(n)), dim3(256), 0, st, tb, done, (const uint32_t*)pub,
+                     (uint32_t*)pub_dst, pub_words);
+  LAUNCHCHK();
   return CAT_OK;
 }
 
@@ -2439,7 +2464,7 @@ struct BatchLayout {
   std::vector<uint64_t> kmax;      // prime capacity of each request
   std::vector<uint64_t> stage;     // request's primes in the staging array (uint32 units)
   Layout c;                        // Phase 2 of all requests
-  size_t c_off = 0, tops_off = 0, total = 0;
+  size_t c_off = 0, total = 0;
 };
 
 BatchLayout make_batch_layout(uint32_t k, const uint64_t* ns) {
@@ -2466,8 +2491,6 @@ BatchLayout make_batch_layout(uint32_t k, const uint64_t* ns) {
   B.c = layout_finish(L);
   B.c_off = off;
   off = align_up(off + B.c.total, 256);
-  B.tops_off = off;
-  off = align_up(off + 8 * (size_t)k, 256);
   B.total = off;
   return B;
 }
@@ -2491,9 +2514,7 @@ void batch_free(BatchState* b) {
 
 // byte offsets inside a batch's pinned buffer
 inline size_t bpin_gt(uint32_t r) { return (size_t)r * sizeof(GroupTable); }
-inline size_t bpin_tops() { return (size_t)CAT_BATCH_MAX * sizeof(GroupTable); }
-inline size_t bpin_err() { return bpin_tops() + 8 * CAT_BATCH_MAX; }
-static_assert(CAT_BATCH_MAX * sizeof(GroupTable) + 8 * CAT_BATCH_MAX + 16 <= BATCH_PIN, "batch pinned buffer");
+static_assert(CAT_BATCH_MAX * sizeof(GroupTable) <= BATCH_PIN && CTL_READ <= BATCH_PIN, "batch pinned buffer");
 
 }  // namespace
 
@@ -2687,9 +2708,10 @@ static cat_status exact_in_workspace(uint64_t n, const Layout& Ly, char* wb, uin
                               uint64_t launches) {
   cat_stats stats{};
   unsigned long long* top = (unsigned long long*)(wb + Ly.top);
-  STCHK(run_phase1(Ly, wb, (uint32_t*)wb + Ly.primes, Ly.Kmax, st, &launches, powers_form(plain)));
+  STCHK(run_phase1(Ly, wb, (uint32_t*)wb + Ly.primes, Ly.Kmax, st, &launches, powers_form(plain),
+                   g.pin));
   GroupTable gt;
-  STCHK(read_groups(Ly, wb, st, &gt));
+  STCHK(read_groups(g.pin, st, &gt));
   if (gt.err & CAT_DEVERR_BOUNDS) return CAT_EINTERNAL;
   Plan* P = noalloc ? find_plan_in(g.noalloc_plans, n, plain, gt) : find_plan(n, plain, gt);
   if (!P) {
@@ -2713,10 +2735,8 @@ static cat_status exact_in_workspace(uint64_t n, const Layout& Ly, char* wb, uin
   }
   auto record = [&](Exec& E) -> cat_status {
     STCHK(run_phase2(E, *P));
-    const uint32_t blocks = top_scan_blocks(P->result_cap);
-    hipLaunchKernelGGL(k_top_nonzero, dim3(blocks), dim3(256), 0, E.st, W + P->result_pos, P->result_cap, top,
-                       (uint32_t*)nullptr, (uint64_t)0);
-    LAUNCHCHK();
+    STCHK(launch_top(E.st, W + P->result_pos, P->result_cap, top, nullptr, 0, (uint32_t*)(wb + Ly.gtab + CTL_DONE),
+                     top, g.pin, 3));
     E.launches++;
     return CAT_OK;
   };
@@ -2758,8 +2778,7 @@ static cat_status exact_in_workspace(uint64_t n, const Layout& Ly, char* wb, uin
     STCHK(record(X));
     launches += X.launches;
   }
-  // top limb index and error word (adjacent in the control block)
-  HIPCHK(hipMemcpyAsync(g.pin, wb + Ly.top, 12, hipMemcpyDeviceToHost, st));
+  // (the last launch left the length and the error word in pinned memory)
   HIPCHK(hipStreamSynchronize(st));
   uint64_t L = 0;
   uint32_t derr = 0;
@@ -2941,9 +2960,10 @@ cat_status catalan_factor(uint64_t n, uint32_t* d_primes, size_t primes_cap, uin
   hipStream_t st = (hipStream_t)stream;
   uint64_t launches = 0;
   uint32_t dummy = 0;
-  STCHK(run_phase1(Ly, (char*)d_work, d_primes ? d_primes : &dummy, d_primes ? primes_cap : 0, st, &launches, false));
+  STCHK(run_phase1(Ly, (char*)d_work, d_primes ? d_primes : &dummy, d_primes ? primes_cap : 0, st, &launches, false,
+                   g.pin));
   GroupTable gt;
-  STCHK(read_groups(Ly, (char*)d_work, st, &gt));
+  STCHK(read_groups(g.pin, st, &gt));
   *n_groups = gt.ngroups;
   for (uint32_t k = 0; k < gt.ngroups; k++) h_exps[k] = gt.exps[k];
   for (uint32_t k = 0; k <= gt.ngroups; k++) h_off[k] = gt.off[k];
@@ -2992,15 +3012,14 @@ cat_status catalan_exact_ex(uint64_t n, uint32_t* d_limbs, size_t cap, size_t* n
       uint64_t nl = 0;
       STCHK(capture_graph(
           [&](hipStream_t cs) -> cat_status {
-            STCHK(run_phase1(Ly, wb, (uint32_t*)wb + Ly.primes, Ly.Kmax, cs, &nl, powers_form(false)));
+            STCHK(run_phase1(Ly, wb, (uint32_t*)wb + Ly.primes, Ly.Kmax, cs, &nl, powers_form(false), nullptr));
             Exec E = make_exec(Ly, wb, cs);
             E.side = g.side_stream;
             STCHK(run_phase2(E, *P));
-            const uint32_t blocks = top_scan_blocks(P->result_cap);
-            const uint64_t ncopy = std::min<uint64_t>(P->result_cap, cap);
-            hipLaunchKernelGGL(k_top_nonzero, dim3(blocks), dim3(256), 0, cs, E.W + P->result_pos, P->result_cap,
-                               top, d_limbs, ncopy);
-            LAUNCHCHK();
+            // group table, length and error word go to pinned memory
+            STCHK(launch_top(cs, E.W + P->result_pos, P->result_cap, top, d_limbs,
+                             std::min<uint64_t>(P->result_cap, cap), (uint32_t*)(wb + Ly.gtab + CTL_DONE),
+                             wb + Ly.gtab, g.pin, CTL_READ / 4));
             nl += E.launches + 1;
             return CAT_OK;
           },
@@ -3009,9 +3028,7 @@ cat_status catalan_exact_ex(uint64_t n, uint32_t* d_limbs, size_t cap, size_t* n
       launches = nl;
     }
     HIPCHK(hipGraphLaunch(ge, st));
-    // group table, top and error word in one copy
-    char* pin = (char*)g.pin;
-    HIPCHK(hipMemcpyAsync(pin, wb + Ly.gtab, CTL_READ, hipMemcpyDeviceToHost, st));
+    const char* pin = (const char*)g.pin;
     HIPCHK(hipStreamSynchronize(st));
     GroupTable gt;
     memcpy(&gt, pin, sizeof(GroupTable));
@@ -3238,10 +3255,10 @@ cat_status catalan_begin(uint64_t n, void* d_work, size_t work_bytes, void* stre
   t->wb = (char*)d_work;
   t->st = (hipStream_t)stream;
   uint64_t launches = 0;
-  cat_status s = run_phase1(t->Ly, t->wb, (uint32_t*)t->wb + t->Ly.primes, t->Ly.Kmax, t->st, &launches, powers_form(false));
+  cat_status s = run_phase1(t->Ly, t->wb, (uint32_t*)t->wb + t->Ly.primes, t->Ly.Kmax, t->st, &launches, powers_form(false),
+                            t->pin);
   if (s == CAT_OK) {
-    hipError_t e = hipMemcpyAsync(t->pin, t->wb + t->Ly.gtab, sizeof(GroupTable), hipMemcpyDeviceToHost, t->st);
-    if (e == hipSuccess) e = hipEventRecord(t->ev, t->st);
+    const hipError_t e = hipEventRecord(t->ev, t->st);
     if (e != hipSuccess) {
       g.last_err = (int)e;
       s = CAT_EDEVICE;
@@ -3291,13 +3308,8 @@ cat_status catalan_continue(cat_ticket ticket, uint32_t* d_limbs, size_t cap) {
     LAUNCHCHK();
   } else {
     STCHK(run_phase2(X, *P));
-    const uint32_t blocks = top_scan_blocks(P->result_cap);
-    const uint64_t ncopy = std::min<uint64_t>(P->result_cap, cap);
-    hipLaunchKernelGGL(k_top_nonzero, dim3(blocks), dim3(256), 0, t->st, X.W + P->result_pos, P->result_cap, top,
-                       d_limbs, ncopy);
-    LAUNCHCHK();
-    // top and error word, adjacent in the control block
-    HIPCHK(hipMemcpyAsync(t->pin + CTL_TOP, t->wb + t->Ly.top, 12, hipMemcpyDeviceToHost, t->st));
+    STCHK(launch_top(t->st, X.W + P->result_pos, P->result_cap, top, d_limbs, std::min<uint64_t>(P->result_cap, cap),
+                     (uint32_t*)(t->wb + t->Ly.gtab + CTL_DONE), top, t->pin + CTL_TOP, 3));
   }
   HIPCHK(hipEventRecord(t->ev, t->st));
   t->state = 2;
@@ -3391,18 +3403,33 @@ cat_status catalan_batch_begin(uint32_t k, const uint64_t* ns, void* d_work, siz
   uint32_t* stage = (uint32_t*)(wb + B.c_off) + B.c.arenaA;
   uint64_t launches = 0;
   cat_status s = CAT_OK;
+  // Phase 1 of all requests together: the small ones in one launch, the others
+  // in one sequence of launches (longer sieve segments by themselves)
+  static_assert(CAT_BATCH_MAX <= P1_MAX, "the requests of a batch share launches");
+  P1Batch<P1_MAX> small{}, rest{};
+  uint32_t nsm = 0, nr = 0, nseg = 0;
   for (uint32_t r = 0; r < k && s == CAT_OK; r++) {
-    s = run_phase1(B.p1[r], wb + B.p1_off[r], stage + B.stage[r], B.kmax[r], t->st, &launches,
-                   powers_form(false));
-    if (s == CAT_OK) {
-      const hipError_t e = hipMemcpyAsync(pin + bpin_gt(r), wb + B.p1_off[r] + B.p1[r].gtab, sizeof(GroupTable),
-                                          hipMemcpyDeviceToHost, t->st);
-      if (e != hipSuccess) {
-        g.last_err = (int)e;
-        s = CAT_EDEVICE;
-      }
+    const P1Req q = phase1_req(B.p1[r], wb + B.p1_off[r], stage + B.stage[r], B.kmax[r], powers_form(false),
+                               pin + bpin_gt(r));
+    if (phase1_small(q)) {
+      small.r[nsm++] = q;
+    } else if (B.p1[r].seg_log == SIEVE_SEG_LOG) {
+      rest.r[nr++] = q;
+      nseg = std::max(nseg, q.nseg);
+    } else {
+      s = run_phase1(B.p1[r], wb + B.p1_off[r], stage + B.stage[r], B.kmax[r], t->st, &launches, powers_form(false),
+                     pin + bpin_gt(r));
     }
   }
+  if (s == CAT_OK && nsm) {
+    hipLaunchKernelGGL(k_phase1_small<P1_MAX>, dim3(nsm), dim3(1024), 0, t->st, small);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) {
+      g.last_err = (int)e;
+      s = CAT_EDEVICE;
+    }
+  }
+  if (s == CAT_OK && nr) s = launch_phase1<SIEVE_SEG_LOG, P1_MAX>(rest, nr, nseg, t->st, &launches);
   if (s == CAT_OK) {
     const hipError_t e = hipEventRecord(t->ev, t->st);
     if (e != hipSuccess) {
@@ -3462,13 +3489,16 @@ cat_status catalan_batch_continue(cat_ticket ticket, uint32_t* const* d_limbs, c
                        0, st, ml, (const uint32_t*)(W + B.c.arenaA), W + B.c.primes);
     LAUNCHCHK();
   }
-  // control block (look-back flags, error word) and the top indices cleared
-  unsigned long long* tops = (unsigned long long*)(wb + B.tops_off);
+  // control block (look-back flags, error word, and the top indices in the place
+  // of the group table) cleared
+  unsigned long long* tops = (unsigned long long*)(cw + B.c.gtab);
+  static_assert(8 * CAT_BATCH_MAX <= CTL_TOP, "the top indices fit the control block's head");
   hipLaunchKernelGGL(k_fill, dim3((uint32_t)std::min<uint64_t>((B.c.ctl_words + 255) / 256, 1024)), dim3(256), 0, st,
                      (uint32_t*)(cw + B.c.gtab), (uint64_t)B.c.ctl_words, 0u);
   LAUNCHCHK();
-  hipLaunchKernelGGL(k_fill, dim3(1), dim3(64), 0, st, (uint32_t*)tops, (uint64_t)(2 * k), 0u);
-  LAUNCHCHK();
+  TopBatch<CAT_BATCH_MAX> tb{};
+  uint32_t nt = 0;
+  uint64_t tmax = 0;
   // chunks of whole requests with at most CAT_MAX_GROUPS groups each
   uint32_t epoch = 0;
   uint32_t r0 = 0;
@@ -3516,8 +3546,8 @@ cat_status catalan_batch_continue(cat_ticket ticket, uint32_t* const* d_limbs, c
         if (caps[r] >= 1) hipLaunchKernelGGL(k_fill, dim3(1), dim3(64), 0, st, d_limbs[r], (uint64_t)1, 1u);
         hipLaunchKernelGGL(k_fill, dim3(1), dim3(64), 0, st, (uint32_t*)(tops + r), (uint64_t)1, 1u);
       } else {
-        hipLaunchKernelGGL(k_top_nonzero, dim3(top_scan_blocks(P->rcap[i])), dim3(256), 0, st, W + P->rpos[i],
-                           P->rcap[i], tops + r, d_limbs[r], std::min<uint64_t>(P->rcap[i], caps[r]));
+        tb.r[nt++] = TopReq{W + P->rpos[i], P->rcap[i], tops + r, d_limbs[r], std::min<uint64_t>(P->rcap[i], caps[r])};
+        tmax = std::max(tmax, P->rcap[i]);
       }
       hipError_t e = hipGetLastError();
       if (e != hipSuccess) {
@@ -3529,8 +3559,16 @@ cat_status catalan_batch_continue(cat_ticket ticket, uint32_t* const* d_limbs, c
     if (P) free_plan(P);
     r0 = r1;
   }
-  HIPCHK(hipMemcpyAsync(b->pin + bpin_tops(), tops, 8 * (size_t)k, hipMemcpyDeviceToHost, st));
-  HIPCHK(hipMemcpyAsync(b->pin + bpin_err(), cw + B.c.err, 4, hipMemcpyDeviceToHost, st));
+  if (nt) {
+    // every result's length and copy, and the control block's head to the host
+    // (lengths and error word; the pinned copies of the group tables are spent)
+    hipLaunchKernelGGL(k_top_nonzero<CAT_BATCH_MAX>, dim3(top_scan_blocks(tmax), nt), dim3(256), 0, st, tb,
+                       (uint32_t*)(cw + B.c.gtab + CTL_DONE), (const uint32_t*)(cw + B.c.gtab), (uint32_t*)b->pin,
+                       (uint32_t)(CTL_READ / 4));
+    LAUNCHCHK();
+  } else {
+    HIPCHK(hipMemcpyAsync(b->pin, cw + B.c.gtab, CTL_READ, hipMemcpyDeviceToHost, st));
+  }
   HIPCHK(hipEventRecord(t->ev, st));
   b->cap.assign(caps, caps + k);
   t->state = 2;
@@ -3556,11 +3594,11 @@ cat_status catalan_batch_end(cat_ticket ticket, size_t* n_limbs, cat_status* req
     return CAT_EDEVICE;
   }
   uint32_t derr = 0;
-  memcpy(&derr, b->pin + bpin_err(), 4);
+  memcpy(&derr, b->pin + CTL_ERR, 4);
   cat_status first = CAT_OK;
   for (uint32_t r = 0; r < b->B.k; r++) {
     uint64_t L = 0;
-    memcpy(&L, b->pin + bpin_tops() + 8 * (size_t)r, 8);
+    memcpy(&L, b->pin + 8 * (size_t)r, 8);
     cat_status s = b->status[r];
     n_limbs[r] = s == CAT_OK ? (size_t)L : 0;
     if (s == CAT_OK) {
@@ -3689,13 +3727,9 @@ cat_status factorial_ratio_exact(const uint64_t* a, uint32_t k, const uint64_t* 
   unsigned long long* top = (unsigned long long*)(wb + Ly.top);
   res = run_phase2(X, *P);
   if (res == CAT_OK) {
-    const uint32_t blocks = top_scan_blocks(P->result_cap);
-    const uint64_t ncopy = std::min<uint64_t>(P->result_cap, cap);
-    hipLaunchKernelGGL(k_top_nonzero, dim3(blocks), dim3(256), 0, st, X.W + P->result_pos, P->result_cap, top, d_limbs,
-                       ncopy);
-    hipError_t e = hipGetLastError();
-    if (e == hipSuccess) e = hipMemcpyAsync(g.pin, wb + Ly.top, 12, hipMemcpyDeviceToHost, st);
-    if (e == hipSuccess) e = hipStreamSynchronize(st);
+    res = launch_top(st, X.W + P->result_pos, P->result_cap, top, d_limbs, std::min<uint64_t>(P->result_cap, cap),
+                     (uint32_t*)(wb + Ly.gtab + CTL_DONE), top, g.pin, 3);
+    const hipError_t e = hipStreamSynchronize(st);
     if (e != hipSuccess) {
       g.last_err = (int)e;
       res = CAT_EDEVICE;
@@ -3801,13 +3835,9 @@ cat_status prime_power_product(const uint32_t* d_entries, const uint32_t* h_exps
   unsigned long long* top = (unsigned long long*)(wb + Ly.top);
   res = run_phase2(X, *P);
   if (res == CAT_OK) {
-    const uint32_t blocks = top_scan_blocks(P->result_cap);
-    const uint64_t ncopy = std::min<uint64_t>(P->result_cap, cap);
-    hipLaunchKernelGGL(k_top_nonzero, dim3(blocks), dim3(256), 0, st, X.W + P->result_pos, P->result_cap, top, d_limbs,
-                       ncopy);
-    hipError_t e = hipGetLastError();
-    if (e == hipSuccess) e = hipMemcpyAsync(g.pin, wb + Ly.top, 12, hipMemcpyDeviceToHost, st);
-    if (e == hipSuccess) e = hipStreamSynchronize(st);
+    res = launch_top(st, X.W + P->result_pos, P->result_cap, top, d_limbs, std::min<uint64_t>(P->result_cap, cap),
+                     (uint32_t*)(wb + Ly.gtab + CTL_DONE), top, g.pin, 3);
+    const hipError_t e = hipStreamSynchronize(st);
     if (e != hipSuccess) {
       g.last_err = (int)e;
       res = CAT_EDEVICE;
@@ -3947,9 +3977,7 @@ cat_status bigint_decimal_digits(const uint32_t* d_x, size_t n_limbs, uint64_t* 
   hipLaunchKernelGGL(k_fill, dim3(1), dim3(64), 0, st, (uint32_t*)top, (uint64_t)2, 0u);
   LAUNCHCHK();
   if (n_limbs) {
-    hipLaunchKernelGGL(k_top_nonzero, dim3(top_scan_blocks(n_limbs)), dim3(256), 0, st, d_x, (uint64_t)n_limbs, top,
-                       (uint32_t*)nullptr, (uint64_t)0);
-    LAUNCHCHK();
+    STCHK(launch_top(st, d_x, n_limbs, top, nullptr, 0));
   }
   HIPCHK(hipMemcpyAsync(g.pin, top, 8, hipMemcpyDeviceToHost, st));
   HIPCHK(hipStreamSynchronize(st));

@@ -54,6 +54,25 @@ struct GroupTable {
   uint64_t gbits[CAT_MAX_GROUPS];
 };
 
+// Phase 1 of up to NR requests in the same launches (grid.y: the request).
+struct P1Req {
+  uint64_t n, cap;            // cap: room for the entries at `primes`
+  uint32_t s, nseg, s8, ctl_words;   // s8: entries per eight limbs (powers form), or 0
+  uint32_t* seeds;
+  int32_t* seed_e;
+  uint32_t* seg_cnt;
+  uint32_t* seg_off;
+  uint32_t* bitmap;
+  uint32_t* primes;
+  GroupTable* gt;             // opens the call's control block of ctl_words words
+  GroupTable* pin;            // pinned host memory: the table's copy for the host
+};
+#define P1_MAX 32
+template <int NR>
+struct P1Batch {
+  P1Req r[NR];
+};
+
 // Exclusive scan over a block of up to 16 wave64s.  tmp: >= 40 words.
 __device__ __forceinline__ uint32_t block_excl_scan_1024(uint32_t v, uint32_t* tmp, uint32_t* total) {
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
@@ -219,10 +238,17 @@ __device__ void mark_segment(uint32_t* bits, uint64_t i_lo, uint32_t len, const 
 }
 
 // ---------------------------------------------------------------------------
-// ctl: the call's control block (group table first), ctl_words words, cleared
-// here before anything else of the call writes to it.
-__global__ void __launch_bounds__(1024) k_seeds(uint64_t n, uint32_t s, uint32_t* seeds, int32_t* seed_e,
-                                                GroupTable* gt, uint32_t* __restrict__ ctl, uint64_t ctl_words) {
+// The control block is cleared here before anything else of the call writes to
+// it.
+template <int NR>
+__global__ void __launch_bounds__(1024) k_seeds(P1Batch<NR> pb) {
+  const P1Req& q_ = pb.r[NR == 1 ? 0 : blockIdx.x];
+  const uint64_t n = q_.n, ctl_words = q_.ctl_words;
+  const uint32_t s = q_.s;
+  uint32_t* seeds = q_.seeds;
+  int32_t* seed_e = q_.seed_e;
+  GroupTable* gt = q_.gt;
+  uint32_t* ctl = (uint32_t*)gt;
   __shared__ uint8_t comp[65536];
   __shared__ uint32_t tmp[40];
   __shared__ uint32_t small[64];
@@ -252,10 +278,15 @@ __global__ void __launch_bounds__(1024) k_seeds(uint64_t n, uint32_t s, uint32_t
 // ---------------------------------------------------------------------------
 // Segment k covers odd indices i in [i0 + k*SEG, min(i0 + (k+1)*SEG, i_end)),
 // i.e. odd numbers m = 2i+1 in (s, 2n].
-template <int SL>
-__global__ void __launch_bounds__(SIEVE_THREADS) k_sieve(uint64_t n, uint64_t i0, uint64_t i_end,
-                                                const uint32_t* seeds, const GroupTable* gt,
-                                                uint32_t* bitmap, uint32_t* seg_cnt) {
+template <int SL, int NR>
+__global__ void __launch_bounds__(SIEVE_THREADS) k_sieve(P1Batch<NR> pb) {
+  const P1Req& q_ = pb.r[NR == 1 ? 0 : blockIdx.y];
+  if (NR > 1 && blockIdx.x >= q_.nseg) return;
+  const uint64_t n = q_.n, i0 = (q_.s + 1) / 2, i_end = n;
+  const uint32_t* seeds = q_.seeds;
+  const GroupTable* gt = q_.gt;
+  uint32_t* bitmap = q_.bitmap;
+  uint32_t* seg_cnt = q_.seg_cnt;
   constexpr uint32_t SEG = 1u << SL, WORDS = SEG / 32;
   __shared__ uint32_t bits[WORDS];
   __shared__ uint32_t tmp[40];
@@ -286,9 +317,66 @@ __global__ void __launch_bounds__(SIEVE_THREADS) k_sieve(uint64_t n, uint64_t i0
 }
 
 // ---------------------------------------------------------------------------
-__global__ void __launch_bounds__(1024) k_groups(uint32_t nseg, const uint32_t* seg_cnt, uint32_t* seg_off,
-                                                 const uint32_t* seeds, const int32_t* seed_e,
-                                                 uint32_t* primes, uint64_t cap, GroupTable* gt, uint32_t s8) {
+// The powers form of the group table: the seeds' powers, ascending, at the
+// front of `primes` (padded with ones to R's node where that is taken), the
+// large primes after them.  Returns where those begin.
+template <int SCH>
+__device__ __forceinline__ uint32_t place_powers(const uint32_t* sd, const int32_t* se, uint32_t total_large,
+                                                 uint32_t s8, uint32_t* primes, uint64_t cap, GroupTable* gt,
+                                                 uint32_t* tmp) {
+  const uint32_t T = blockDim.x, tid = threadIdx.x;
+  uint32_t cc = 0, cnt;
+#pragma unroll
+  for (int i = 0; i < SCH; i++) cc += se[i] > 0;
+  uint32_t r = block_excl_scan_1024(cc, tmp, &cnt);
+#pragma unroll
+  for (int i = 0; i < SCH; i++)
+    if (se[i] > 0) {
+      uint32_t q = sd[i];
+      for (int32_t e = 1; e < se[i]; e++) q *= sd[i];   // <= 2n
+      if (r < cap) primes[r] = q;
+      r++;
+    }
+  uint32_t lv = 6;
+  while ((1u << lv) < 8 * ((cnt + s8 - 1) / s8)) lv++;
+  const uint32_t padded = (1u << (lv - 3)) * s8;
+  const bool node = 16ull * padded <= total_large && (uint64_t)padded + total_large <= cap;
+  const uint32_t first = node ? padded : cnt;
+  for (uint32_t i = cnt + tid; i < first; i += T) primes[i] = 1;
+  if (tid == 0) {
+    const uint64_t all = (uint64_t)first + total_large;
+    gt->ngroups = all ? 1 : 0;
+    gt->exps[0] = 1;
+    gt->off[0] = 0;
+    gt->off[all ? 1 : 0] = all;
+    gt->gbits[0] = 32 * all;
+    gt->n_seed_e1 = first;
+    gt->n_pow = cnt;
+    gt->outer = node ? (int32_t)lv : -1;
+    if (all > cap) atomicOr(&gt->err, CAT_DEVERR_BOUNDS);
+  }
+  return first;
+}
+// the finished table to the host's copy
+__device__ __forceinline__ void publish_table(const GroupTable* gt, GroupTable* pin) {
+  __threadfence_block();
+  __syncthreads();
+  if (pin)
+    for (uint32_t k = threadIdx.x; k < sizeof(GroupTable) / 4; k += blockDim.x)
+      ((uint32_t*)pin)[k] = ((const volatile uint32_t*)gt)[k];
+}
+
+template <int NR>
+__global__ void __launch_bounds__(1024) k_groups(P1Batch<NR> pb) {
+  const P1Req& q_ = pb.r[NR == 1 ? 0 : blockIdx.x];
+  const uint32_t nseg = q_.nseg, s8 = q_.s8;
+  const uint32_t* seg_cnt = q_.seg_cnt;
+  uint32_t* seg_off = q_.seg_off;
+  const uint32_t* seeds = q_.seeds;
+  const int32_t* seed_e = q_.seed_e;
+  uint32_t* primes = q_.primes;
+  const uint64_t cap = q_.cap;
+  GroupTable* gt = q_.gt;
   __shared__ uint32_t tmp[40];
   __shared__ uint32_t cnt_e[CAT_MAX_GROUPS + 1];
   __shared__ unsigned long long bits_e[CAT_MAX_GROUPS + 1];
@@ -317,36 +405,8 @@ __global__ void __launch_bounds__(1024) k_groups(uint32_t nseg, const uint32_t* 
   uint32_t pos = block_excl_scan_1024(c, tmp, &total_large);
   for (uint32_t i = lo; i < hi; i++) { seg_off[i] = pos; pos += seg_cnt[i]; }
   if (s8) {
-    uint32_t cc = 0, cnt;
-#pragma unroll
-    for (int i = 0; i < SCH; i++) cc += se[i] > 0;
-    uint32_t r = block_excl_scan_1024(cc, tmp, &cnt);
-#pragma unroll
-    for (int i = 0; i < SCH; i++)
-      if (se[i] > 0) {
-        uint32_t q = sd[i];
-        for (int32_t e = 1; e < se[i]; e++) q *= sd[i];   // <= 2n
-        if (r < cap) primes[r] = q;
-        r++;
-      }
-    uint32_t lv = 6;
-    while ((1u << lv) < 8 * ((cnt + s8 - 1) / s8)) lv++;
-    const uint32_t padded = (1u << (lv - 3)) * s8;
-    const bool node = 2ull * padded * 8 <= total_large && (uint64_t)padded + total_large <= cap;
-    const uint32_t first = node ? padded : cnt;
-    for (uint32_t i = cnt + tid; i < first; i += T) primes[i] = 1;
-    if (tid == 0) {
-      const uint64_t all = (uint64_t)first + total_large;
-      gt->ngroups = all ? 1 : 0;
-      gt->exps[0] = 1;
-      gt->off[0] = 0;
-      gt->off[all ? 1 : 0] = all;
-      gt->gbits[0] = 32 * all;
-      gt->n_seed_e1 = first;
-      gt->n_pow = cnt;
-      gt->outer = node ? (int32_t)lv : -1;
-      if (all > cap) atomicOr(&gt->err, CAT_DEVERR_BOUNDS);
-    }
+    place_powers<SCH>(sd, se, total_large, s8, primes, cap, gt, tmp);
+    publish_table(gt, q_.pin);
     return;
   }
   // 2. seed counts per exponent
@@ -402,12 +462,19 @@ __global__ void __launch_bounds__(1024) k_groups(uint32_t nseg, const uint32_t* 
         if (at < cap) primes[at] = sd[i];
       }
   }
+  publish_table(gt, q_.pin);
 }
 
 // ---------------------------------------------------------------------------
-template <int SL>
-__global__ void __launch_bounds__(SIEVE_THREADS) k_scatter(uint64_t i0, const uint32_t* bitmap, const uint32_t* seg_off,
-                                                  const GroupTable* gt, uint32_t* primes, uint64_t cap) {
+template <int SL, int NR>
+__global__ void __launch_bounds__(SIEVE_THREADS) k_scatter(P1Batch<NR> pb) {
+  const P1Req& q_ = pb.r[NR == 1 ? 0 : blockIdx.y];
+  if (NR > 1 && blockIdx.x >= q_.nseg) return;
+  const uint64_t i0 = (q_.s + 1) / 2, cap = q_.cap;
+  const uint32_t* bitmap = q_.bitmap;
+  const uint32_t* seg_off = q_.seg_off;
+  const GroupTable* gt = q_.gt;
+  uint32_t* primes = q_.primes;
   __shared__ uint32_t tmp[40];
   const uint32_t tid = threadIdx.x;
   constexpr uint32_t SEG = 1u << SL, WORDS = SEG / 32;
@@ -453,6 +520,128 @@ __global__ void __launch_bounds__(SIEVE_THREADS) k_scatter(uint64_t i0, const ui
       at++;
     }
   }
+}
+
+// ---------------------------------------------------------------------------
+// The whole of Phase 1 in its powers form in one workgroup, for n up to 2^17:
+// the odd numbers up to 2n are one bit map in LDS.  The four launches above cost
+// 7 to 10 us each at this size whatever they do.
+// The odd primes below 64 strike their multiples word by word with a periodic
+// pattern (bit b of word w is the number M + 2 b, M = m_lo + 64 w; the first
+// multiple of q is at b = -M / 2 mod q), the other seeds one wave each.
+#define P1_SMALL_LOG 17
+#define P1_SMALL_SEEDS 1024       // numbers up to sqrt(2^18)
+template <uint32_t Q>
+__device__ __forceinline__ void strike(uint32_t& v, uint32_t M, uint32_t s) {
+  if (Q > s) return;
+  constexpr uint64_t pat = [] {
+    uint64_t x = 0;
+    for (uint32_t b = 0; b < 64; b += Q) x |= 1ull << b;
+    return x;
+  }();
+  const uint32_t r = ((Q - M % Q) * ((Q + 1) / 2)) % Q;
+  v &= ~(uint32_t)(pat << r);
+}
+template <int NR>
+__global__ void __launch_bounds__(1024) k_phase1_small(P1Batch<NR> pb) {
+  constexpr uint32_t WORDS = (1u << P1_SMALL_LOG) / 32, WPT = WORDS / 1024;
+  const P1Req& q_ = pb.r[NR == 1 ? 0 : blockIdx.x];
+  __shared__ uint32_t bits[WORDS];
+  __shared__ uint32_t sd_[P1_SMALL_SEEDS];
+  __shared__ uint32_t tmp[40];
+  const uint32_t T = blockDim.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const uint32_t n = (uint32_t)q_.n, s = q_.s, n2 = 2 * n;
+  GroupTable* gt = q_.gt;
+  for (uint32_t k = tid; k < q_.ctl_words; k += T) ((uint32_t*)gt)[k] = 0u;
+  __threadfence_block();
+  // the seeds q <= s, one candidate per thread
+  bool isq = tid >= 2 && tid <= s;
+  for (uint32_t d = 2; d * d <= tid; d++)
+    if (tid % d == 0) isq = false;
+  uint32_t ns;
+  const uint32_t at = block_excl_scan_1024(isq ? 1u : 0u, tmp, &ns);
+  if (isq) sd_[at] = tid;
+  __syncthreads();
+  // exponent of the thread's seed
+  uint32_t sd[1] = {tid < ns ? sd_[tid] : 1u};
+  int32_t se[1] = {0};
+  if (tid < ns) {
+    const uint32_t q = sd[0];
+    const int32_t a = (int32_t)legendre_dev(n2, q), b = (int32_t)legendre_dev(n, q);
+    uint32_t m = n + 1;
+    int32_t c = 0;
+    while (m % q == 0) { m /= q; c++; }
+    se[0] = a - 2 * b - c;
+    if (se[0] < 0) atomicOr(&gt->err, CAT_DEVERR_NEG_EXP);
+  }
+  // odd m = 2 (i0 + x) + 1 in (s, 2n], x < len
+  const uint32_t i0 = (s + 1) / 2, len = n > i0 ? n - i0 : 0, m_lo = 2 * i0 + 1;
+#pragma unroll
+  for (uint32_t k = 0; k < WPT; k++) {
+    const uint32_t w = tid + T * k, b0 = 32 * w;
+    uint32_t v = b0 + 32 <= len ? ~0u : b0 < len ? (1u << (len - b0)) - 1u : 0u;
+    if (v) {
+      const uint32_t M = m_lo + 64 * w;
+      strike<3>(v, M, s);
+      strike<5>(v, M, s);
+      strike<7>(v, M, s);
+      strike<11>(v, M, s);
+      strike<13>(v, M, s);
+      strike<17>(v, M, s);
+      strike<19>(v, M, s);
+      strike<23>(v, M, s);
+      strike<29>(v, M, s);
+      strike<31>(v, M, s);
+      strike<37>(v, M, s);
+      strike<41>(v, M, s);
+      strike<43>(v, M, s);
+      strike<47>(v, M, s);
+      strike<53>(v, M, s);
+      strike<59>(v, M, s);
+      strike<61>(v, M, s);
+    }
+    bits[w] = v;
+  }
+  __syncthreads();
+  for (uint32_t k = 18 + wave; k < ns; k += T / 64) {   // seeds[18] = 67
+    const uint32_t q = sd_[k];
+    uint32_t t = (m_lo + q - 1) / q;
+    t |= 1;   // the first odd multiple q t >= m_lo (q t > s >= q, so t >= 3)
+    for (uint32_t x = (q * t - m_lo) / 2 + lane * q; x < len; x += 64 * q)
+      atomicAnd(&bits[x >> 5], ~(1u << (x & 31)));
+  }
+  __syncthreads();
+  // the primes with e_p = 1 of the thread's words, ascending
+  uint32_t keep[WPT], cnt = 0;
+#pragma unroll
+  for (uint32_t k = 0; k < WPT; k++) {
+    const uint32_t w = tid * WPT + k;
+    uint32_t v = bits[w], kp = 0;
+    while (v) {
+      const uint32_t b = __ffs(v) - 1;
+      v &= v - 1;
+      const uint32_t p = m_lo + 64 * w + 2 * b;
+      const uint32_t r = n % p;
+      if ((2 * r >= p ? 1u : 0u) != (r == p - 1 ? 1u : 0u)) kp |= 1u << b;
+    }
+    keep[k] = kp;
+    cnt += __popc(kp);
+  }
+  uint32_t total;
+  const uint32_t pos = block_excl_scan_1024(cnt, tmp, &total);
+  const uint32_t first = place_powers<1>(sd, se, total, q_.s8, q_.primes, q_.cap, gt, tmp);
+  uint64_t o = (uint64_t)first + pos;
+#pragma unroll
+  for (uint32_t k = 0; k < WPT; k++) {
+    uint32_t v = keep[k];
+    while (v) {
+      const uint32_t b = __ffs(v) - 1;
+      v &= v - 1;
+      if (o < q_.cap) q_.primes[o] = m_lo + 64 * (tid * WPT + k) + 2 * b;
+      o++;
+    }
+  }
+  publish_table(gt, q_.pin);
 }
 
 // ---------------------------------------------------------------------------

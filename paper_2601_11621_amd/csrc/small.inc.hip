@@ -545,12 +545,31 @@ __global__ void k_fill(uint32_t* __restrict__ p, uint64_t n, uint32_t v) {
 }
 
 // Highest index with a nonzero limb, +1 (0 if all zero) -> *top; limbs below
-// ncopy are also copied to dst (the caller's output).  Each block reduces in
-// LDS and issues one atomicMax.
-__global__ void __launch_bounds__(256) k_top_nonzero(const uint32_t* __restrict__ x, uint64_t n,
-                                                     unsigned long long* top, uint32_t* __restrict__ dst,
-                                                     uint64_t ncopy) {
+// ncopy are also copied to dst (the caller's output).  One result per grid.y;
+// each block reduces in LDS and issues one atomicMax.  With `pub`, the last block
+// of the launch (a counter at *done, zero before) copies pub_words words from
+// there to pinned host memory: the lengths and the error word reach the host with
+// the launch itself, where a copy of its own took another 12 us.
+struct TopReq {
+  const uint32_t* x;
+  uint64_t n;
+  unsigned long long* top;
+  uint32_t* dst;
+  uint64_t ncopy;
+};
+template <int NR>
+struct TopBatch {
+  TopReq r[NR];
+};
+template <int NR>
+__global__ void __launch_bounds__(256)
+k_top_nonzero(TopBatch<NR> tb, uint32_t* done, const uint32_t* pub, uint32_t* pub_dst, uint32_t pub_words) {
   __shared__ unsigned long long part[4];
+  __shared__ uint32_t s_last;
+  const TopReq& q = tb.r[NR == 1 ? 0 : blockIdx.y];
+  const uint32_t* __restrict__ x = q.x;
+  uint32_t* __restrict__ dst = q.dst;
+  const uint64_t n = q.n, ncopy = q.ncopy;
   unsigned long long best = 0;
   for (uint64_t k = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; k < n; k += (uint64_t)gridDim.x * blockDim.x) {
     const uint32_t v = x[k];
@@ -565,7 +584,18 @@ __global__ void __launch_bounds__(256) k_top_nonzero(const uint32_t* __restrict_
   __syncthreads();
   if (threadIdx.x == 0) {
     for (int w = 1; w < (int)(blockDim.x >> 6); w++) best = part[w] > best ? part[w] : best;
-    if (best) atomicMax(top, best);
+    if (best) atomicMax(q.top, best);
+    if (pub) {
+      __threadfence();
+      s_last = atomicAdd(done, 1u) + 1 == gridDim.x * gridDim.y;
+    }
+  }
+  if (!pub) return;
+  __syncthreads();
+  if (s_last) {
+    __threadfence();
+    for (uint32_t k = threadIdx.x; k < pub_words; k += blockDim.x)
+      pub_dst[k] = __hip_atomic_load(pub + k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
 }
 
