@@ -526,21 +526,40 @@ __global__ void __launch_bounds__(SIEVE_THREADS) k_scatter(P1Batch<NR> pb) {
 // The whole of Phase 1 in its powers form in one workgroup, for n up to 2^17:
 // the odd numbers up to 2n are one bit map in LDS.  The four launches above cost
 // 7 to 10 us each at this size whatever they do.
-// The odd primes below 64 strike their multiples word by word with a periodic
+// The odd primes below 32 strike their multiples word by word with a periodic
 // pattern (bit b of word w is the number M + 2 b, M = m_lo + 64 w; the first
-// multiple of q is at b = -M / 2 mod q), the other seeds one wave each.
+// multiple of q is at b = -M / 2 mod q, which moves by a constant from one of a
+// thread's words to the next), the other seeds one wave each.  Divisions of
+// numbers below 2^19 are single-precision products: (m + 1/2) / q is 1 / (2 q)
+// away from an integer, further than the roundings of the reciprocal and the
+// product reach.
 #define P1_SMALL_LOG 17
 #define P1_SMALL_SEEDS 1024       // numbers up to sqrt(2^18)
-template <uint32_t Q>
-__device__ __forceinline__ void strike(uint32_t& v, uint32_t M, uint32_t s) {
+// floor(m / q) for m < 2^19, with rq = 1 / q to two units in the last place
+__device__ __forceinline__ uint32_t div_small(uint32_t m, float rq) { return (uint32_t)(((float)m + 0.5f) * rq); }
+__device__ __forceinline__ uint32_t legendre_small(uint32_t m, float rq) {
+  uint32_t s = 0;
+  while (m) {
+    m = div_small(m, rq);
+    s += m;
+  }
+  return s;
+}
+template <uint32_t Q, int WPT>
+__device__ __forceinline__ void strike(uint32_t* v, uint32_t M, uint32_t step, uint32_t s) {
   if (Q > s) return;
   constexpr uint64_t pat = [] {
     uint64_t x = 0;
     for (uint32_t b = 0; b < 64; b += Q) x |= 1ull << b;
     return x;
   }();
-  const uint32_t r = ((Q - M % Q) * ((Q + 1) / 2)) % Q;
-  v &= ~(uint32_t)(pat << r);
+  uint32_t r = ((Q - M % Q) * ((Q + 1) / 2)) % Q;
+  const uint32_t d = (32 * step) % Q;   // words of a thread are `step` words apart
+#pragma unroll
+  for (int k = 0; k < WPT; k++) {
+    v[k] &= ~(uint32_t)(pat << r);
+    r = r >= d ? r - d : r + Q - d;
+  }
 }
 template <int NR>
 __global__ void __launch_bounds__(1024) k_phase1_small(P1Batch<NR> pb) {
@@ -555,9 +574,9 @@ __global__ void __launch_bounds__(1024) k_phase1_small(P1Batch<NR> pb) {
   for (uint32_t k = tid; k < q_.ctl_words; k += T) ((uint32_t*)gt)[k] = 0u;
   __threadfence_block();
   // the seeds q <= s, one candidate per thread
-  bool isq = tid >= 2 && tid <= s;
-  for (uint32_t d = 2; d * d <= tid; d++)
-    if (tid % d == 0) isq = false;
+  bool isq = tid == 2 || (tid > 2 && tid <= s && (tid & 1));
+  for (uint32_t d = 3; isq && d * d <= tid; d += 2)
+    if (tid == d * div_small(tid, __builtin_amdgcn_rcpf((float)d))) isq = false;
   uint32_t ns;
   const uint32_t at = block_excl_scan_1024(isq ? 1u : 0u, tmp, &ns);
   if (isq) sd_[at] = tid;
@@ -567,45 +586,46 @@ __global__ void __launch_bounds__(1024) k_phase1_small(P1Batch<NR> pb) {
   int32_t se[1] = {0};
   if (tid < ns) {
     const uint32_t q = sd[0];
-    const int32_t a = (int32_t)legendre_dev(n2, q), b = (int32_t)legendre_dev(n, q);
+    const float rq = __builtin_amdgcn_rcpf((float)q);
+    const int32_t a = (int32_t)legendre_small(n2, rq), b = (int32_t)legendre_small(n, rq);
     uint32_t m = n + 1;
     int32_t c = 0;
-    while (m % q == 0) { m /= q; c++; }
+    for (uint32_t t = div_small(m, rq); t * q == m; t = div_small(m, rq)) {
+      m = t;
+      c++;
+    }
     se[0] = a - 2 * b - c;
     if (se[0] < 0) atomicOr(&gt->err, CAT_DEVERR_NEG_EXP);
   }
   // odd m = 2 (i0 + x) + 1 in (s, 2n], x < len
   const uint32_t i0 = (s + 1) / 2, len = n > i0 ? n - i0 : 0, m_lo = 2 * i0 + 1;
+  {
+    uint32_t v[WPT];
 #pragma unroll
-  for (uint32_t k = 0; k < WPT; k++) {
-    const uint32_t w = tid + T * k, b0 = 32 * w;
-    uint32_t v = b0 + 32 <= len ? ~0u : b0 < len ? (1u << (len - b0)) - 1u : 0u;
-    if (v) {
-      const uint32_t M = m_lo + 64 * w;
-      strike<3>(v, M, s);
-      strike<5>(v, M, s);
-      strike<7>(v, M, s);
-      strike<11>(v, M, s);
-      strike<13>(v, M, s);
-      strike<17>(v, M, s);
-      strike<19>(v, M, s);
-      strike<23>(v, M, s);
-      strike<29>(v, M, s);
-      strike<31>(v, M, s);
-      strike<37>(v, M, s);
-      strike<41>(v, M, s);
-      strike<43>(v, M, s);
-      strike<47>(v, M, s);
-      strike<53>(v, M, s);
-      strike<59>(v, M, s);
-      strike<61>(v, M, s);
+    for (uint32_t k = 0; k < WPT; k++) {
+      const uint32_t b0 = 32 * (tid + 1024 * k);
+      v[k] = b0 + 32 <= len ? ~0u : b0 < len ? (1u << (len - b0)) - 1u : 0u;
     }
-    bits[w] = v;
+    if (v[0]) {
+      const uint32_t M = m_lo + 64 * tid;
+      strike<3, WPT>(v, M, 1024, s);
+      strike<5, WPT>(v, M, 1024, s);
+      strike<7, WPT>(v, M, 1024, s);
+      strike<11, WPT>(v, M, 1024, s);
+      strike<13, WPT>(v, M, 1024, s);
+      strike<17, WPT>(v, M, 1024, s);
+      strike<19, WPT>(v, M, 1024, s);
+      strike<23, WPT>(v, M, 1024, s);
+      strike<29, WPT>(v, M, 1024, s);
+      strike<31, WPT>(v, M, 1024, s);
+    }
+#pragma unroll
+    for (uint32_t k = 0; k < WPT; k++) bits[tid + 1024 * k] = v[k];
   }
   __syncthreads();
-  for (uint32_t k = 18 + wave; k < ns; k += T / 64) {   // seeds[18] = 67
+  for (uint32_t k = 11 + wave; k < ns; k += T / 64) {   // seeds[11] = 37
     const uint32_t q = sd_[k];
-    uint32_t t = (m_lo + q - 1) / q;
+    uint32_t t = div_small(m_lo + q - 1, __builtin_amdgcn_rcpf((float)q));
     t |= 1;   // the first odd multiple q t >= m_lo (q t > s >= q, so t >= 3)
     for (uint32_t x = (q * t - m_lo) / 2 + lane * q; x < len; x += 64 * q)
       atomicAnd(&bits[x >> 5], ~(1u << (x & 31)));
@@ -621,7 +641,7 @@ __global__ void __launch_bounds__(1024) k_phase1_small(P1Batch<NR> pb) {
       const uint32_t b = __ffs(v) - 1;
       v &= v - 1;
       const uint32_t p = m_lo + 64 * w + 2 * b;
-      const uint32_t r = n % p;
+      const uint32_t r = n - p * div_small(n, __builtin_amdgcn_rcpf((float)p));
       if ((2 * r >= p ? 1u : 0u) != (r == p - 1 ? 1u : 0u)) kp |= 1u << b;
     }
     keep[k] = kp;
