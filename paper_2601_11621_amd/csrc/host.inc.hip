@@ -665,11 +665,9 @@ struct Plan {
   void* dev = nullptr;          // device tables (segments, prefixes, descriptors)
   uint64_t products = 0, product_limbs = 0;
   uint32_t levels = 0;
-  // graph caches: workspace base -> exec (Phase 2 only); (workspace, output,
-  // capacity) -> exec of the whole call (Phase 1 + Phase 2 + copy)
-  std::map<uintptr_t, hipGraphExec_t> graphs;
+  // graph cache: (workspace, output, capacity) -> exec of the whole call
+  // (Phase 1 + Phase 2 + copy)
   std::map<std::vector<uintptr_t>, hipGraphExec_t> full_graphs;
-  std::vector<uintptr_t> graphs_order;
   std::vector<std::vector<uintptr_t>> full_graphs_order;
 };
 
@@ -1228,7 +1226,6 @@ cat_status upload_tables(std::vector<Stage*>& all, void** dev, bool device_table
 }
 
 void free_plan(Plan* P) {
-  for (auto& kv : P->graphs) (void)hipGraphExecDestroy(kv.second);
   for (auto& kv : P->full_graphs) (void)hipGraphExecDestroy(kv.second);
   if (P->dev) (void)hipFree(P->dev);
   delete P;
@@ -2045,6 +2042,10 @@ Plan* find_plan_in(std::map<uint64_t, Plan*>& plans, uint64_t n, bool plain, con
 
 Plan* find_plan(uint64_t n, bool plain, const GroupTable& gt) { return find_plan_in(g.plans, n, plain, gt); }
 
+// A repeated call of at most five launches (Phase 1, three stages, the length)
+// queues them itself: the launch of a graph takes longer to start (C(10^3) 57 us
+// as a graph, 47.5 as three launches; C(10^5), ten launches, 124.5 and 126.8).
+bool few_launches(const Plan& P) { return P.tree.size() + P.post.size() <= 3; }
 // C(n) in batched form takes the powers form of Phase 1 (one group, no powers
 // after the tree) unless R is kept out of the tree
 bool powers_form(bool plain) { return !plain && g_rins; }
@@ -2699,13 +2700,11 @@ cat_status read_groups_ratio(const Layout& Ly, char* wb, hipStream_t st, GroupTa
 }
 
 // The general form of a C(n) call in a given workspace: Phase 1, the group
-// table to the host, the plan of n (cached by n), Phase 2 as launches or as
-// one captured graph, the normalisation and the copy of the result to
-// d_limbs.  With `noalloc` nothing is allocated on the device: the plan comes
+// table to the host, the plan of n (cached by n), Phase 2, the normalisation
+// and the copy of the result to d_limbs.  With `noalloc` nothing is allocated on the device: the plan comes
 // from a cache of its own whose plans carry no device tables and no graphs.
 static cat_status exact_in_workspace(uint64_t n, const Layout& Ly, char* wb, uint32_t* d_limbs, size_t cap,
-                              size_t* n_limbs, hipStream_t st, bool plain, bool use_graph, bool noalloc,
-                              uint64_t launches) {
+                              size_t* n_limbs, hipStream_t st, bool plain, bool noalloc, uint64_t launches) {
   cat_stats stats{};
   unsigned long long* top = (unsigned long long*)(wb + Ly.top);
   STCHK(run_phase1(Ly, wb, (uint32_t*)wb + Ly.primes, Ly.Kmax, st, &launches, powers_form(plain),
@@ -2735,49 +2734,15 @@ static cat_status exact_in_workspace(uint64_t n, const Layout& Ly, char* wb, uin
   }
   auto record = [&](Exec& E) -> cat_status {
     STCHK(run_phase2(E, *P));
-    STCHK(launch_top(E.st, W + P->result_pos, P->result_cap, top, nullptr, 0, (uint32_t*)(wb + Ly.gtab + CTL_DONE),
-                     top, g.pin, 3));
+    STCHK(launch_top(E.st, W + P->result_pos, P->result_cap, top, d_limbs, std::min<uint64_t>(P->result_cap, cap),
+                     (uint32_t*)(wb + Ly.gtab + CTL_DONE), top, g.pin, 3));
     E.launches++;
     return CAT_OK;
   };
-  bool replayed = false;
-  if (use_graph) {
-    hipGraphExec_t ge = nullptr;
-    auto it = P->graphs.find((uintptr_t)wb);
-    if (it != P->graphs.end()) {
-      ge = it->second;
-      replayed = true;
-    } else {
-      Exec C = X;
-      C.st = g.cap_stream;
-      C.side = g.side_stream;
-      HIPCHK(hipStreamBeginCapture(g.cap_stream, hipStreamCaptureModeThreadLocal));
-      cat_status s = record(C);
-      hipGraph_t graph = nullptr;
-      hipError_t e = hipStreamEndCapture(g.cap_stream, &graph);
-      if (s != CAT_OK) {
-        if (graph) (void)hipGraphDestroy(graph);
-        return s;
-      }
-      if (e != hipSuccess) {
-        g.last_err = (int)e;
-        return CAT_EDEVICE;
-      }
-      e = hipGraphInstantiate(&ge, graph, nullptr, nullptr, 0);
-      (void)hipGraphDestroy(graph);
-      if (e != hipSuccess) {
-        g.last_err = (int)e;
-        return CAT_EDEVICE;
-      }
-      cache_graph(P->graphs, P->graphs_order, (uintptr_t)wb, ge);
-      launches += C.launches;
-    }
-    HIPCHK(hipGraphLaunch(ge, st));
-    if (replayed) launches += 1;
-  } else {
-    STCHK(record(X));
-    launches += X.launches;
-  }
+  // (the first call for n: its launches are queued one by one, and the call after
+  // it captures the whole of it as a graph)
+  STCHK(record(X));
+  launches += X.launches;
   // (the last launch left the length and the error word in pinned memory)
   HIPCHK(hipStreamSynchronize(st));
   uint64_t L = 0;
@@ -2793,12 +2758,8 @@ static cat_status exact_in_workspace(uint64_t n, const Layout& Ly, char* wb, uin
   stats.n_primes = table_primes(gt);
   stats.levels = P->levels;
   stats.outer_level = P->rins_j >= 0 ? P->rins_j : P->outer_j;
-  stats.graph_replayed = replayed ? 1 : 0;
   g.stats = stats;
-  if (cap < L) return CAT_ERANGE;
-  HIPCHK(hipMemcpyAsync(d_limbs, W + P->result_pos, L * 4, hipMemcpyDeviceToDevice, st));
-  HIPCHK(hipStreamSynchronize(st));
-  return CAT_OK;
+  return cap < L ? CAT_ERANGE : CAT_OK;
 }
 
 extern "C" {
@@ -3002,32 +2963,35 @@ cat_status catalan_exact_ex(uint64_t n, uint32_t* d_limbs, size_t cap, size_t* n
   if (use_graph && pit != g.plans.end() && !pit->second->result_is_one) {
     Plan* P = pit->second;
     const std::vector<uintptr_t> key{(uintptr_t)wb, (uintptr_t)d_limbs, (uintptr_t)cap};
-    hipGraphExec_t ge = nullptr;
     bool replayed = false;
-    auto git = P->full_graphs.find(key);
-    if (git != P->full_graphs.end()) {
-      ge = git->second;
-      replayed = true;
-    } else {
-      uint64_t nl = 0;
-      STCHK(capture_graph(
-          [&](hipStream_t cs) -> cat_status {
-            STCHK(run_phase1(Ly, wb, (uint32_t*)wb + Ly.primes, Ly.Kmax, cs, &nl, powers_form(false), nullptr));
-            Exec E = make_exec(Ly, wb, cs);
-            E.side = g.side_stream;
-            STCHK(run_phase2(E, *P));
-            // group table, length and error word go to pinned memory
-            STCHK(launch_top(cs, E.W + P->result_pos, P->result_cap, top, d_limbs,
-                             std::min<uint64_t>(P->result_cap, cap), (uint32_t*)(wb + Ly.gtab + CTL_DONE),
-                             wb + Ly.gtab, g.pin, CTL_READ / 4));
-            nl += E.launches + 1;
-            return CAT_OK;
-          },
-          &ge));
-      cache_graph(P->full_graphs, P->full_graphs_order, key, ge);
+    uint64_t nl = 0;
+    auto record = [&](hipStream_t cs, hipStream_t side) -> cat_status {
+      STCHK(run_phase1(Ly, wb, (uint32_t*)wb + Ly.primes, Ly.Kmax, cs, &nl, powers_form(false), nullptr));
+      Exec E = make_exec(Ly, wb, cs);
+      E.side = side;
+      STCHK(run_phase2(E, *P));
+      // group table, length and error word go to pinned memory
+      STCHK(launch_top(cs, E.W + P->result_pos, P->result_cap, top, d_limbs, std::min<uint64_t>(P->result_cap, cap),
+                       (uint32_t*)(wb + Ly.gtab + CTL_DONE), wb + Ly.gtab, g.pin, CTL_READ / 4));
+      nl += E.launches + 1;
+      return CAT_OK;
+    };
+    if (few_launches(*P)) {
+      STCHK(record(st, nullptr));
       launches = nl;
+    } else {
+      hipGraphExec_t ge = nullptr;
+      auto git = P->full_graphs.find(key);
+      if (git != P->full_graphs.end()) {
+        ge = git->second;
+        replayed = true;
+      } else {
+        STCHK(capture_graph([&](hipStream_t cs) { return record(cs, g.side_stream); }, &ge));
+        cache_graph(P->full_graphs, P->full_graphs_order, key, ge);
+        launches = nl;
+      }
+      HIPCHK(hipGraphLaunch(ge, st));
     }
-    HIPCHK(hipGraphLaunch(ge, st));
     const char* pin = (const char*)g.pin;
     HIPCHK(hipStreamSynchronize(st));
     GroupTable gt;
@@ -3050,7 +3014,7 @@ cat_status catalan_exact_ex(uint64_t n, uint32_t* d_limbs, size_t cap, size_t* n
     if (cap < L) return CAT_ERANGE;
     return CAT_OK;
   }
-  return exact_in_workspace(n, Ly, wb, d_limbs, cap, n_limbs, st, plain, use_graph, false, launches);
+  return exact_in_workspace(n, Ly, wb, d_limbs, cap, n_limbs, st, plain, false, launches);
 }
 
 
@@ -3622,7 +3586,7 @@ cat_status catalan_exact_noalloc(uint64_t n, uint32_t* d_limbs, size_t cap, size
   if (!g.scratch_ptr) return CAT_EINTERNAL;
   g.in_noalloc = true;
   const cat_status s = exact_in_workspace(n, Ly, (char*)g.scratch_ptr, d_limbs, cap, n_limbs, (hipStream_t)stream,
-                                          false, false, true, 0);
+                                          false, true, 0);
   g.in_noalloc = false;
   return s;
 }
