@@ -136,17 +136,19 @@ struct TreeLevel {
 
 #define CAT_INLINE_DESC 16
 
-// Uniform batch: product i reads a at a0 + i*sa and b at b0 + i*sb (la, lb
-// limbs each) and writes c at c0 + i*sc; residues at i*(la+lb).
+// A level of decimal joins (even lengths, 64-bit digits): product i < sq reads a
+// at a0 + i sa (la limbs; la_last for product `last`) and writes residues at
+// digit i (la + lb) / 2; the second operand, lb limbs at b0, is the same for
+// all.  Product sq is b squared.
 struct UniDesc {
-  uint64_t a0, sa, b0, sb, c0, sc;
-  uint32_t la, lb;
+  uint64_t a0, sa, b0;
+  uint32_t la, lb, la_last, last, sq;
 };
 
 struct DescView {
   const MulDesc* table;  // device table (large explicit batches), or
   uint32_t ninl;         // > 0: explicit descriptors carried in the kernel arguments, or
-  uint32_t uni;          // > 0: uniform batch, or
+  uint32_t uni;          // > 0: a level of decimal joins, or
   MulDesc inl[CAT_INLINE_DESC];
   UniDesc u;
   TreeLevel tree;        // tree mode
@@ -155,11 +157,11 @@ struct DescView {
     if (ninl) return inl[i];
     if (uni) {
       MulDesc d;
-      d.a_off = u.a0 + i * u.sa;
-      d.b_off = u.b0 + i * u.sb;
-      d.c_off = u.c0 + i * u.sc;
-      d.r_off = i * ((uint64_t)u.la + u.lb);
-      d.la = u.la;
+      d.a_off = i == u.sq ? u.b0 : u.a0 + i * u.sa;
+      d.b_off = u.b0;
+      d.c_off = 0;             // the segments say where the digits go
+      d.r_off = i * (((uint64_t)u.la + u.lb) / 2);
+      d.la = i == u.sq ? u.lb : i == u.last ? u.la_last : u.la;
       d.lb = u.lb;
       return d;
     }
@@ -180,11 +182,35 @@ struct DescView {
 };
 
 // CRT/carry segments: out[out_pos + k] for k < len from residues at res_pos + k
-// (radix-10^9 products also add the digits add[add_pos + k] for k < add_len).
+// (decimal joins also add the limbs add[add_pos + k] for k < add_len).
 struct CrtSeg {
   uint64_t out_pos, res_pos, len;
   uint64_t add_pos, add_len;
 };
+
+// ------------------------------------------------------------ radix 10^18
+#define DEC_B 1000000000000000000ull
+#define DEC_D 16000000000000000000ull       // 16 B: the normalised divisor
+#define DEC_V ((uint64_t)(~(unsigned __int128)0 / DEC_D - ((unsigned __int128)1 << 64)))
+// floor((r 2^64 + w) / D) and its remainder, for r < D: two-by-one division
+// with a precomputed reciprocal (Moller and Granlund, "Improved division by
+// invariant integers", IEEE TC 2011, Algorithm 4)
+__device__ __forceinline__ uint64_t div_d(uint64_t r, uint64_t w, uint64_t* rem) {
+  const unsigned __int128 q = (unsigned __int128)DEC_V * r + (((unsigned __int128)(r + 1) << 64) | w);
+  uint64_t q1 = (uint64_t)(q >> 64);
+  const uint64_t q0 = (uint64_t)q;
+  uint64_t rr = w - q1 * DEC_D;
+  if (rr > q0) {
+    q1--;
+    rr += DEC_D;
+  }
+  if (rr >= DEC_D) {
+    q1++;
+    rr -= DEC_D;
+  }
+  *rem = rr;
+  return q1;
+}
 
 // Bits of the device error word
 #define CAT_DEVERR_CARRY_OUT 1u     // a product overflowed its la+lb limbs
@@ -323,17 +349,29 @@ struct SegView {
   uint32_t ubl;              // > 0: uniform segments of ubl blocks each (below)
   CrtSeg iseg[CAT_INLINE_SEG];
   uint32_t ipref[CAT_INLINE_SEG + 1];
-  // uniform: segment s is iseg[0] with out_pos, res_pos and add_pos advanced
-  // by s * ustep[0], s * iseg[0].len and s * ustep[1]
-  uint64_t ustep[2];
+  // uniform: segment s is iseg[0] with out_pos, add_pos and res_pos advanced
+  // by s * ustep[0 .. 2]; segment ulast is ulast_len long, segment usq goes to
+  // usq_pos and adds nothing
+  uint64_t ustep[3];
+  uint64_t ulast_len, usq_pos;
+  uint32_t ulast, usq;
+  __device__ __forceinline__ CrtSeg uniform(uint32_t q) const {
+    CrtSeg sg = iseg[0];
+    sg.out_pos += q * ustep[0];
+    sg.add_pos += q * ustep[1];
+    sg.res_pos += q * ustep[2];
+    if (q == ulast) sg.len = ulast_len;
+    if (q == usq) {
+      sg.out_pos = usq_pos;
+      sg.add_pos = sg.add_len = 0;
+    }
+    return sg;
+  }
   __device__ __forceinline__ void find(uint32_t b, CrtSeg* sg, uint32_t* first, uint32_t* end,
                                        uint32_t* segi = nullptr) const {
     if (ubl) {
       const uint32_t q = b / ubl;
-      *sg = iseg[0];
-      sg->out_pos += q * ustep[0];
-      sg->res_pos += q * iseg[0].len;
-      sg->add_pos += q * ustep[1];
+      *sg = uniform(q);
       *first = q * ubl;
       *end = *first + ubl;
       if (segi) *segi = q;

@@ -515,6 +515,7 @@ k_fcol_fwd(DescView dv, FGeom fg, uint64_t m0_, int prevS, int prevL, const uint
   uint64_t m;
   uint32_t base, j0;
   fg.locate(LOGL, wid / CAT_NPRIMES, &m, &base, &j0);
+  if (op && m && dv.uni) return;     // one second operand for the whole batch
   const int logSig = fg.logS - LOGL;
   const uint64_t N = 1ull << fg.logD;
   double* f = F + ((m * 3 + prime) * 2 + op) * N;
@@ -646,7 +647,7 @@ k_fcol_inv(DescView dv, FGeom fg, uint64_t m0_, int prevS, int prevL, double* __
 // instructions.
 template <int LOGM, int PS>
 __global__ void __launch_bounds__((1 << LOGM) / 16) __attribute__((amdgpu_waves_per_eu(4)))
-k_frow(int logD, int logS, int logL, double* __restrict__ F, FTables tb) {
+k_frow(int logD, int logS, int logL, int bshared, double* __restrict__ F, FTables tb) {
   constexpr int LE = 4, E = 1 << LE;
   constexpr uint32_t M = 1u << LOGM, NT = M >> LE;
   __shared__ double lds[fpad<LE>(M)];
@@ -657,7 +658,8 @@ k_frow(int logD, int logS, int logL, double* __restrict__ F, FTables tb) {
   const uint64_t m = blockIdx.x >> logQ;
   const uint32_t q = blockIdx.x & ((1u << logQ) - 1);
   double* fa = F + ((m * 3 + prime) * 2 + 0) * N + ((uint64_t)q << LOGM);
-  const double* fb = fa + N;
+  // a common second operand: product 0's
+  const double* fb = F + (((bshared ? 0 : m) * 3 + prime) * 2 + 1) * N + ((uint64_t)q << LOGM);
   const double* tws = tb.tws + (size_t)prime * FTWS_ENTRIES;
   const double* itws = tb.itws + (size_t)prime * FTWS_ENTRIES;
   double a[E], b[E];
@@ -716,11 +718,82 @@ __device__ __forceinline__ void fcrt_value(double r0, double r1, double r2, cons
   v1 = (uint64_t)m2;
   v2 = (uint32_t)(m2 >> 64);
 }
-// s = a + b + c as s mod 2^64 and the carry h = s >> 64
+// The column value in the radix of the carries, v0 + v1 R + v2 R^2: R = 2^64, or
+// with DEC R = 10^18 (decimal joins; digits below R) after `add` is added.  There
+// V < 2^25 R^2 + R, so both quotients that are below 2^31 come from FP64 (off by
+// one at most, and seen from the remainder) and one division by the reciprocal is
+// left: with d = 16 R, (u2, u1, u0) = 16 V, u1's remainder mod d tells an
+// overestimate (just below 2^64) from an underestimate (just above d).
+template <bool DEC>
+__device__ __forceinline__ void fcol_value(double r0, double r1, double r2, const FCrt& k, uint64_t add, uint64_t& v0,
+                                           uint64_t& v1, uint32_t& v2) {
+  fcrt_value(r0, r1, r2, k, v0, v1, v2);
+  if constexpr (DEC) {
+    v0 += add;
+    const uint32_t c = v0 < add;
+    v1 += c;
+    v2 += (v1 < c);
+    const uint32_t u2 = (v2 << 4) | (uint32_t)(v1 >> 60);
+    const uint64_t u1 = (v1 << 4) | (v0 >> 60), u0 = v0 << 4;
+    uint32_t q1 = (uint32_t)(((double)u2 * 0x1p64 + (double)u1) * (1.0 / (double)DEC_D));
+    uint64_t r = u1 - q1 * DEC_D;
+    if (r >= DEC_D) {
+      const bool under = r - DEC_D < (1ull << 60);
+      q1 = under ? q1 + 1 : q1 - 1;
+      r = under ? r - DEC_D : r + DEC_D;
+    }
+    const uint64_t q0 = div_d(r, u0, &r);
+    v0 = r >> 4;
+    v2 = (uint32_t)(((double)q1 * 0x1p64 + (double)q0) * (1.0 / (double)DEC_B));
+    v1 = q0 - v2 * DEC_B;
+    if ((int64_t)v1 < 0) {
+      v2--;
+      v1 += DEC_B;
+    } else if (v1 >= DEC_B) {
+      v2++;
+      v1 -= DEC_B;
+    }
+  }
+}
+// s = a + b + c as s mod R and the carry h = s / R
+template <bool DEC>
 __device__ __forceinline__ uint64_t fcol_sum(uint64_t a, uint64_t b, uint64_t c, uint32_t* h) {
   const uint64_t t = a + b, s = t + c;
-  *h = (t < a) + (s < c);
-  return s;
+  if constexpr (DEC) {
+    *h = (s >= DEC_B) + (s >= 2 * DEC_B);
+    return s - *h * DEC_B;
+  } else {
+    *h = (t < a) + (s < c);
+    return s;
+  }
+}
+// u = lo + carries of the column before (at most 2): does it generate a carry,
+// does it pass one on?
+template <bool DEC>
+__device__ __forceinline__ bool fcol_gen(uint64_t u, uint64_t lo) {
+  return DEC ? u >= DEC_B : u < lo;
+}
+template <bool DEC>
+__device__ __forceinline__ bool fcol_prop(uint64_t u) {
+  return u == (DEC ? DEC_B - 1 : ~0ull);
+}
+// the digit u + c and its carry
+template <bool DEC>
+__device__ __forceinline__ uint64_t fcol_digit(uint64_t u, bool gk, uint32_t* c) {
+  uint64_t y = u + *c;
+  if constexpr (DEC) {
+    *c = y >= DEC_B;
+    if (*c) y -= DEC_B;
+  } else {
+    *c = (y < u || gk) ? 1u : 0u;
+  }
+  return y;
+}
+// digit k of the addend (limbs at `add`, add_len of them)
+__device__ __forceinline__ uint64_t add_digit(const uint32_t* __restrict__ add, uint64_t add_len, uint64_t k) {
+  const uint64_t q = 2 * k < add_len ? 2 * k : 0;
+  const uint64_t x = ((uint64_t)add[q + 1] << 32) | add[q];
+  return 2 * k < add_len ? x : 0;
 }
 
 // Positions kb + E tid .. of a block, as in k_crt: digit k is v0(k) + v1(k-1)
@@ -730,9 +803,11 @@ __device__ __forceinline__ uint64_t fcol_sum(uint64_t a, uint64_t b, uint64_t c,
 // every u of them propagates they also decide the carry into the block
 // (*spec: 0 or 1, else 2).
 #define FCRT_CTX 16
+template <bool DEC>
 __device__ __forceinline__ void fcrt_local(uint64_t len, const double* __restrict__ r0, const double* __restrict__ r1,
-                                           const double* __restrict__ r2, const FCrt& kc, uint64_t kb, uint4* xv,
-                                           uint32_t* tmp, uint64_t* ul, bool* gk, bool* Gt, bool* Pt, uint32_t* spec) {
+                                           const double* __restrict__ r2, const uint32_t* __restrict__ add,
+                                           uint64_t add_len, const FCrt& kc, uint64_t kb, uint4* xv, uint32_t* tmp,
+                                           uint64_t* ul, bool* gk, bool* Gt, bool* Pt, uint32_t* spec) {
   static_assert(FCRT_E >= 3, "a thread's last column must lie inside the thread");
   const uint32_t tid = threadIdx.x;
   const uint64_t k0 = kb + (uint64_t)tid * FCRT_E;
@@ -761,28 +836,34 @@ __device__ __forceinline__ void fcrt_local(uint64_t len, const double* __restric
     y1 = r1[kb + tid - FCRT_CTX];
     y2 = r2[kb + tid - FCRT_CTX];
   }
+  uint64_t ad[FCRT_E] = {}, yd = 0;
+  if constexpr (DEC) {
+#pragma unroll
+    for (int i = 0; i < FCRT_E; i++) ad[i] = add_digit(add, add_len, k0 + i);
+    if (lctx) yd = add_digit(add, add_len, kb + tid - FCRT_CTX);
+  }
   uint64_t a0[FCRT_E], a1[FCRT_E], lo[FCRT_E];
   uint32_t a2[FCRT_E], h[FCRT_E];
 #pragma unroll
-  for (int i = 0; i < FCRT_E; i++) fcrt_value(x0[i], x1[i], x2[i], kc, a0[i], a1[i], a2[i]);
+  for (int i = 0; i < FCRT_E; i++) fcol_value<DEC>(x0[i], x1[i], x2[i], kc, ad[i], a0[i], a1[i], a2[i]);
 #pragma unroll
-  for (int i = 2; i < FCRT_E; i++) lo[i] = fcol_sum(a0[i], a1[i - 1], a2[i - 2], &h[i]);
+  for (int i = 2; i < FCRT_E; i++) lo[i] = fcol_sum<DEC>(a0[i], a1[i - 1], a2[i - 2], &h[i]);
   uint4 bctx = make_uint4(0, 0, 0, 0);
   uint32_t sp = 2;
   if (tid < 64) {
     uint64_t c0, c1;
     uint32_t c2;
-    fcrt_value(y0, y1, y2, kc, c0, c1, c2);
+    fcol_value<DEC>(y0, y1, y2, kc, yd, c0, c1, c2);
     const uint64_t b1 = __shfl_up((unsigned long long)c1, 1, 64);
     const uint32_t b2 = __shfl_up(c2, 1, 64), d2 = __shfl_up(c2, 2, 64);
     uint32_t hh;
-    const uint64_t cl = fcol_sum(c0, b1, d2, &hh);          // column kb - CTX + tid (lanes >= 2)
+    const uint64_t cl = fcol_sum<DEC>(c0, b1, d2, &hh);          // column kb - CTX + tid (lanes >= 2)
     const uint32_t hq = __shfl_up(hh, 1, 64);
     const uint64_t cu = cl + hq;                            // u of it (lanes >= 3)
-    const bool g = cu < cl;
+    const bool g = fcol_gen<DEC>(cu, cl);
     const bool valid = tid >= 3 && tid < FCRT_CTX;
     const uint64_t gm = __ballot(valid && g);
-    const uint64_t dm = gm | __ballot(valid && !g && cu != ~0ull);
+    const uint64_t dm = gm | __ballot(valid && !g && !fcol_prop<DEC>(cu));
     if (dm) sp = (uint32_t)((gm >> (63 - __builtin_clzll(dm))) & 1ull);
     bctx = make_uint4((uint32_t)c1, (uint32_t)(c1 >> 32), c2 | (hh << 30), b2);
   }
@@ -795,16 +876,16 @@ __device__ __forceinline__ void fcrt_local(uint64_t len, const double* __restric
   __syncthreads();
   const uint4 z = xv[tid];
   const uint32_t zv2 = z.z & 0x3FFFFFFFu;
-  lo[0] = fcol_sum(a0[0], ((uint64_t)z.y << 32) | z.x, z.w, &h[0]);
-  lo[1] = fcol_sum(a0[1], a1[0], zv2, &h[1]);
+  lo[0] = fcol_sum<DEC>(a0[0], ((uint64_t)z.y << 32) | z.x, z.w, &h[0]);
+  lo[1] = fcol_sum<DEC>(a0[1], a1[0], zv2, &h[1]);
   bool G = false, P = true;
   uint32_t hp = z.z >> 30;
 #pragma unroll
   for (int i = 0; i < FCRT_E; i++) {
     ul[i] = lo[i] + hp;
-    gk[i] = ul[i] < lo[i];
+    gk[i] = fcol_gen<DEC>(ul[i], lo[i]);
     hp = h[i];
-    const bool pr = ul[i] == ~0ull;
+    const bool pr = fcol_prop<DEC>(ul[i]);
     G = gk[i] || (pr && G);
     P = P && pr;
   }
@@ -834,10 +915,12 @@ struct FWords {
 // limbs, res_pos in digits); blocks from nblk on copy tail ranges.  The carry
 // into a block and the look-back are those of k_crt.  Bound by HBM: 24 B read
 // and 8 B written per digit.
+// DEC: radix-10^18 digits, plus the segments' addends (limbs relative to `add`).
+template <bool DEC>
 __global__ void __launch_bounds__(FCRT_THREADS)
-k_fcrt(SegView sv, FCrt kc, const double* __restrict__ res, uint64_t stride, uint32_t* __restrict__ out, uint32_t nblk,
-       uint32_t* __restrict__ flags, uint32_t epoch, uint32_t polls, CopyList tails, const uint32_t* __restrict__ tin,
-       uint32_t* __restrict__ tout, uint32_t* __restrict__ err) {
+k_fcrt(SegView sv, FCrt kc, const double* __restrict__ res, uint64_t stride, const uint32_t* __restrict__ add,
+       uint32_t* __restrict__ out, uint32_t nblk, uint32_t* __restrict__ flags, uint32_t epoch, uint32_t polls, CopyList tails,
+       const uint32_t* __restrict__ tin, uint32_t* __restrict__ tout, uint32_t* __restrict__ err) {
   __shared__ uint32_t tmp[FCRT_THREADS / 64], tmp2[FCRT_THREADS / 64];
   __shared__ uint4 xv[FCRT_THREADS + 1];
   __shared__ uint32_t s_state, s_pair, s_spec, s_spec2;
@@ -854,9 +937,15 @@ k_fcrt(SegView sv, FCrt kc, const double* __restrict__ res, uint64_t stride, uin
   const double* r1 = r0 + stride;
   const double* r2 = r1 + stride;
   const uint64_t kb = (uint64_t)(b - first) * FCRT_BLOCK;
+  const uint32_t* ad = nullptr;
+  if constexpr (DEC) {
+    if (kb >= len) return;     // a shorter last segment: its end is before these blocks
+    end = first + (uint32_t)((len + FCRT_BLOCK - 1) / FCRT_BLOCK);
+    ad = add + sg.add_pos;
+  }
   uint64_t ul[FCRT_E];
   bool gk[FCRT_E], G, P;
-  fcrt_local(len, r0, r1, r2, kc, kb, xv, tmp, ul, gk, &G, &P, &s_spec);
+  fcrt_local<DEC>(len, r0, r1, r2, ad, sg.add_len, kc, kb, xv, tmp, ul, gk, &G, &P, &s_spec);
   const uint32_t own = fcrt_pair(tmp);
   if (tid == 0)
     __hip_atomic_store(flags + b, (epoch << 3) | (own << 1) | 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -887,7 +976,8 @@ k_fcrt(SegView sv, FCrt kc, const double* __restrict__ res, uint64_t stride, uin
       // not published yet: recompute block k's pair from its residues
       uint64_t ul2[FCRT_E];
       bool gk2[FCRT_E], G2, P2;
-      fcrt_local(len, r0, r1, r2, kc, (uint64_t)(k - first) * FCRT_BLOCK, xv, tmp2, ul2, gk2, &G2, &P2, &s_spec2);
+      fcrt_local<DEC>(len, r0, r1, r2, ad, sg.add_len, kc, (uint64_t)(k - first) * FCRT_BLOCK, xv, tmp2, ul2, gk2, &G2,
+                      &P2, &s_spec2);
       pair = fcrt_pair(tmp2);
     }
     if (pair & 1u) { cin = 1; done = true; }           // block k generates a carry
@@ -908,8 +998,7 @@ k_fcrt(SegView sv, FCrt kc, const double* __restrict__ res, uint64_t stride, uin
   FWords r;
 #pragma unroll
   for (int i = 0; i < FCRT_E; i++) {
-    const uint64_t y = ul[i] + c;
-    c = (y < ul[i] || gk[i]) ? 1u : 0u;
+    const uint64_t y = fcol_digit<DEC>(ul[i], gk[i], &c);
     r.w[2 * i] = (uint32_t)y;
     r.w[2 * i + 1] = (uint32_t)(y >> 32);
   }
@@ -940,8 +1029,9 @@ k_fcrt(SegView sv, FCrt kc, const double* __restrict__ res, uint64_t stride, uin
 constexpr int ff_tile(int logD) { return logD < 9 ? 9 : logD; }
 constexpr int ff_threads(int logD) { return CAT_NPRIMES << (ff_tile(logD) - 3); }
 #define FF_E 4
-template <int LOGD, bool ZHI, int LOGT = ff_tile(LOGD)>
-__device__ __forceinline__ void ffused_tile(double* lds, MulDesc* ds, uint4* xw, uint32_t* tmp,
+// DEC: the carries in radix 10^18, with the addends and lengths of the segments sg.
+template <int LOGD, bool ZHI, int LOGT = ff_tile(LOGD), bool DEC = false>
+__device__ __forceinline__ void ffused_tile(double* lds, MulDesc* ds, CrtSeg* sg, uint4* xw, uint32_t* tmp,
                                             const uint32_t* __restrict__ ain, const uint32_t* __restrict__ bin,
                                             uint32_t* __restrict__ out, const FTables& tb, const FCrt& kc,
                                             uint32_t* __restrict__ err) {
@@ -998,9 +1088,16 @@ __device__ __forceinline__ void ffused_tile(double* lds, MulDesc* ds, uint4* xw,
   if (on) {
     const uint32_t s = fpad<LE>(FF_E * t);
 #pragma unroll
-    for (int i = 0; i < FF_E; i++) fcrt_value(lds[s + i], lds[TP + s + i], lds[2 * TP + s + i], kc, a0[i], a1[i], a2[i]);
+    for (int i = 0; i < FF_E; i++) {
+      uint64_t ad = 0;
+      if constexpr (DEC) {
+        const CrtSeg& q = sg[(FF_E * t) >> LOGD];
+        ad = add_digit(ain + q.add_pos, q.add_len, k0 + i);
+      }
+      fcol_value<DEC>(lds[s + i], lds[TP + s + i], lds[2 * TP + s + i], kc, ad, a0[i], a1[i], a2[i]);
+    }
 #pragma unroll
-    for (int i = 2; i < FF_E; i++) lo[i] = fcol_sum(a0[i], a1[i - 1], a2[i - 2], &h[i]);
+    for (int i = 2; i < FF_E; i++) lo[i] = fcol_sum<DEC>(a0[i], a1[i - 1], a2[i - 2], &h[i]);
     // the left neighbour's last two columns (none at a product's start)
     const uint32_t p0 = (uint32_t)a1[FF_E - 1], p1 = (uint32_t)(a1[FF_E - 1] >> 32),
                    p2 = a2[FF_E - 1] | (h[FF_E - 1] << 30), p3 = a2[FF_E - 2];
@@ -1014,16 +1111,16 @@ __device__ __forceinline__ void ffused_tile(double* lds, MulDesc* ds, uint4* xw,
     uint4 z = make_uint4((uint32_t)ul[0], (uint32_t)(ul[0] >> 32), (uint32_t)ul[1], (uint32_t)(ul[1] >> 32));
     if (lane == 0 && wave > 0) z = xw[wave - 1];
     if (k0 == 0) z = make_uint4(0, 0, 0, 0);
-    lo[0] = fcol_sum(a0[0], ((uint64_t)z.y << 32) | z.x, z.w, &h[0]);
-    lo[1] = fcol_sum(a0[1], a1[0], z.z & 0x3FFFFFFFu, &h[1]);
+    lo[0] = fcol_sum<DEC>(a0[0], ((uint64_t)z.y << 32) | z.x, z.w, &h[0]);
+    lo[1] = fcol_sum<DEC>(a0[1], a1[0], z.z & 0x3FFFFFFFu, &h[1]);
     P = true;
     uint32_t hp = z.z >> 30;
 #pragma unroll
     for (int i = 0; i < FF_E; i++) {
       ul[i] = lo[i] + hp;
-      gk[i] = ul[i] < lo[i];
+      gk[i] = fcol_gen<DEC>(ul[i], lo[i]);
       hp = h[i];
-      const bool pr = ul[i] == ~0ull;
+      const bool pr = fcol_prop<DEC>(ul[i]);
       G = gk[i] || (pr && G);
       P = P && pr;
     }
@@ -1043,18 +1140,24 @@ __device__ __forceinline__ void ffused_tile(double* lds, MulDesc* ds, uint4* xw,
   bool ap;
   uint32_t cy = wave_carry(G, P, wc, &cout, &ap);
   const MulDesc& m = ds[(FF_E * t) >> LOGD];
-  const uint32_t L = m.la + m.lb, w0 = 2 * k0;
+  uint32_t L = m.la + m.lb;
+  uint64_t cpos = m.c_off;
+  if constexpr (DEC) {
+    const CrtSeg& q = sg[(FF_E * t) >> LOGD];
+    L = (uint32_t)q.len;
+    cpos = q.out_pos;
+  }
+  const uint32_t w0 = 2 * k0;
   struct W8 {
     uint32_t w[2 * FF_E];
   } r;
 #pragma unroll
   for (int i = 0; i < FF_E; i++) {
-    const uint64_t y = ul[i] + cy;
-    cy = (y < ul[i] || gk[i]) ? 1u : 0u;
+    const uint64_t y = fcol_digit<DEC>(ul[i], gk[i], &cy);
     r.w[2 * i] = (uint32_t)y;
     r.w[2 * i + 1] = (uint32_t)(y >> 32);
   }
-  uint32_t* o = out + m.c_off + w0;
+  uint32_t* o = out + cpos + w0;
   if (w0 + 2 * FF_E <= L) {
     *(W8*)o = r;
   } else {
@@ -1091,7 +1194,39 @@ k_ffused(DescView dv, uint64_t m0, uint64_t nmul, uint32_t tiles, const uint32_t
     ds[threadIdx.x] = d;
   }
   __syncthreads();
-  ffused_tile<LOGD, ZHI>(lds, ds, xw, tmp, ain, bin, out, tb, kc, err);
+  ffused_tile<LOGD, ZHI>(lds, ds, nullptr, xw, tmp, ain, bin, out, tb, kc, err);
+}
+
+// A level of decimal joins (operands of at most N/2 digits): product i has the
+// segment i of sv, addends relative to `ain`.
+template <int LOGD>
+__global__ void __launch_bounds__(ff_threads(LOGD)) __attribute__((amdgpu_waves_per_eu(6)))
+k_ffused10(DescView dv, SegView sv, uint64_t nmul, uint32_t tiles, const uint32_t* __restrict__ ain,
+           const uint32_t* __restrict__ bin, uint32_t* __restrict__ out, FTables tb, FCrt kc, CopyList tails,
+           const uint32_t* __restrict__ tin, uint32_t* __restrict__ tout, uint32_t* __restrict__ err) {
+  constexpr uint32_t PER = 1u << (ff_tile(LOGD) - LOGD);
+  __shared__ double lds[CAT_NPRIMES * fpad<3>(1u << ff_tile(LOGD))];
+  __shared__ MulDesc ds[PER];
+  __shared__ CrtSeg sg[PER];
+  __shared__ uint4 xw[8];
+  __shared__ uint32_t tmp[8];
+  if (blockIdx.x >= tiles) {
+    copy_tail_block(tails, tin, tout, blockIdx.x - tiles);
+    return;
+  }
+  const uint64_t i0 = (uint64_t)blockIdx.x * PER;
+  if (threadIdx.x < PER) {
+    MulDesc d{};
+    CrtSeg q{};
+    if (i0 + threadIdx.x < nmul) {
+      d = dv.get(i0 + threadIdx.x);
+      q = sv.uniform((uint32_t)i0 + threadIdx.x);
+    }
+    ds[threadIdx.x] = d;
+    sg[threadIdx.x] = q;
+  }
+  __syncthreads();
+  ffused_tile<LOGD, true, ff_tile(LOGD), true>(lds, ds, sg, xw, tmp, ain, bin, out, tb, kc, err);
 }
 
 // Several short buckets of a generic batch in one launch: workgroup b takes the
@@ -1117,7 +1252,7 @@ k_ffused_mix(const MulDesc* __restrict__ desc, const uint2* __restrict__ tiles, 
   __syncthreads();
 #define T(X)                                                                                   \
   case X:                                                                                      \
-    ffused_tile<X, false, FF_MAX_LOGD>(lds, ds, xw, tmp, ain, bin, out, tb, c_fcrt[X], err);   \
+    ffused_tile<X, false, FF_MAX_LOGD>(lds, ds, nullptr, xw, tmp, ain, bin, out, tb, c_fcrt[X], err);   \
     break
   switch (logD) {
     T(5); T(6); T(7); T(8); T(9); T(10); T(11);
@@ -1295,6 +1430,24 @@ hipError_t fntt_fused(const FBatch& b, uint32_t* out, const CopyList& tails, con
   return hipGetLastError();
 }
 
+hipError_t fntt_fused10(const FBatch& b, const SegView& sv, uint32_t* out, const CopyList& tails, const uint32_t* tin,
+                        uint32_t* tout, uint32_t* err, hipStream_t st) {
+  const uint64_t per = 1ull << (ff_tile(b.logD) - b.logD);
+  const uint32_t tiles = (uint32_t)((b.cnt + per - 1) / per);
+  const dim3 grid(tiles + tail_blocks(tails)), block(ff_threads(b.logD));
+#define L(X)                                                                                                    \
+  case X:                                                                                                       \
+    hipLaunchKernelGGL((k_ffused10<X>), grid, block, 0, st, b.dv, sv, b.cnt, tiles, b.ain, b.bin, out, g_ft[0], \
+                       g_crt[X], tails, tin, tout, err);                                                        \
+    break
+  switch (b.logD) {
+    L(5); L(6); L(7); L(8); L(9); L(10); L(11);
+    default: return hipErrorInvalidValue;
+  }
+#undef L
+  return hipGetLastError();
+}
+
 hipError_t fntt_fused_mix(const MulDesc* desc, const uint2* tiles, uint32_t ntiles, const uint32_t* ain,
                           const uint32_t* bin, uint32_t* out, uint32_t* err, hipStream_t st) {
   hipLaunchKernelGGL(k_ffused_mix, dim3(ntiles), dim3(ff_threads(FF_MAX_LOGD)), 0, st, desc, tiles, ain, bin, out,
@@ -1363,9 +1516,11 @@ template <int LOGM>
 static void row_launch(const FBatch& b, int logS, int logL, hipStream_t st) {
   const dim3 grid((uint32_t)(b.cnt << (b.logD - LOGM)), CAT_NPRIMES), block((1u << LOGM) / 16);
   if (fntt_set(b.logD) == 0)
-    hipLaunchKernelGGL((k_frow<LOGM, 0>), grid, block, 0, st, b.logD, logS, logL, b.F, g_ft[0]);
+    hipLaunchKernelGGL((k_frow<LOGM, 0>), grid, block, 0, st, b.logD, logS, logL, b.dv.uni, b.F,
+                       g_ft[0]);
   else
-    hipLaunchKernelGGL((k_frow<LOGM, 1>), grid, block, 0, st, b.logD, logS, logL, b.F, g_ft[1]);
+    hipLaunchKernelGGL((k_frow<LOGM, 1>), grid, block, 0, st, b.logD, logS, logL, b.dv.uni, b.F,
+                       g_ft[1]);
 }
 hipError_t fntt_row(const FBatch& b, int logM, int logS, int logL, hipStream_t st) {
   switch (logM) {
@@ -1378,10 +1533,15 @@ hipError_t fntt_row(const FBatch& b, int logM, int logS, int logL, hipStream_t s
   return hipGetLastError();
 }
 
-hipError_t fntt_crt(const SegView& sv, int logD, const double* res, uint64_t stride, uint32_t* out, uint32_t nblk,
-                    uint32_t* flags, uint32_t epoch, uint32_t polls, const CopyList& tails, const uint32_t* tin,
-                    uint32_t* tout, uint32_t* err, hipStream_t st) {
-  hipLaunchKernelGGL(k_fcrt, dim3(nblk + tail_blocks(tails)), dim3(FCRT_THREADS), 0, st, sv, g_crt[logD], res, stride,
-                     out, nblk, flags, epoch, polls, tails, tin, tout, err);
+hipError_t fntt_crt(const SegView& sv, int logD, const double* res, uint64_t stride, const uint32_t* add, uint32_t* out,
+                    uint32_t nblk, uint32_t* flags, uint32_t epoch, uint32_t polls, const CopyList& tails,
+                    const uint32_t* tin, uint32_t* tout, uint32_t* err, hipStream_t st) {
+  const dim3 grid(nblk + tail_blocks(tails)), block(FCRT_THREADS);
+  if (add)
+    hipLaunchKernelGGL((k_fcrt<true>), grid, block, 0, st, sv, g_crt[logD], res, stride, add, out, nblk, flags, epoch,
+                       polls, tails, tin, tout, err);
+  else
+    hipLaunchKernelGGL((k_fcrt<false>), grid, block, 0, st, sv, g_crt[logD], res, stride, add, out, nblk, flags, epoch,
+                       polls, tails, tin, tout, err);
   return hipGetLastError();
 }

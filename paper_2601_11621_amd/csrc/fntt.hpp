@@ -42,6 +42,10 @@ hipError_t fntt_lds(const FBatch& b, hipStream_t st);
 bool fntt_fused_fits(int logD);
 hipError_t fntt_fused(const FBatch& b, uint32_t* out, const CopyList& tails, const uint32_t* tin, uint32_t* tout,
                       uint32_t* err, hipStream_t st);
+// One level of decimal joins (uniform batch, segment i of sv for product i,
+// addends relative to b.ain), for the same sizes.
+hipError_t fntt_fused10(const FBatch& b, const SegView& sv, uint32_t* out, const CopyList& tails, const uint32_t* tin,
+                        uint32_t* tout, uint32_t* err, hipStream_t st);
 // The same for several buckets over device tables: tile b is the products
 // tiles[b].x .. (tiles[b].y: logD + 1, products << 8; 2^11 slots at most).
 hipError_t fntt_fused_mix(const MulDesc* desc, const uint2* tiles, uint32_t ntiles, const uint32_t* ain,
@@ -54,7 +58,8 @@ hipError_t fntt_col_fwd(const FBatch& b, int logS, int logL, bool first, int pre
 hipError_t fntt_col_inv(const FBatch& b, int logS, int logL, bool first, int prevS, int prevL, hipStream_t st);
 // rows of 2^logM digits under a column pass of sub-problems 2^logS, length 2^logL
 hipError_t fntt_row(const FBatch& b, int logM, int logS, int logL, hipStream_t st);
-// residues -> limbs with carries (blocks [0, nblk) of sv; res_pos in digits)
-hipError_t fntt_crt(const SegView& sv, int logD, const double* res, uint64_t stride, uint32_t* out, uint32_t nblk,
-                    uint32_t* flags, uint32_t epoch, uint32_t polls, const CopyList& tails, const uint32_t* tin,
-                    uint32_t* tout, uint32_t* err, hipStream_t st);
+// residues -> limbs with carries (blocks [0, nblk) of sv; res_pos in digits);
+// with `add`, in radix 10^18 with the addends of the segments (relative to it)
+hipError_t fntt_crt(const SegView& sv, int logD, const double* res, uint64_t stride, const uint32_t* add, uint32_t* out,
+                    uint32_t nblk, uint32_t* flags, uint32_t epoch, uint32_t polls, const CopyList& tails,
+                    const uint32_t* tin, uint32_t* tout, uint32_t* err, hipStream_t st);

@@ -56,7 +56,6 @@ struct Lib {
   hipStream_t cap_stream = nullptr;
   hipStream_t side_stream = nullptr;            // second branch of captured calls
   hipEvent_t ev_fork = nullptr, ev_join = nullptr;
-  std::vector<hipEvent_t> dec_ev;               // decimal conversion: P_j ready
   // kernel timer: events around every launch of one named kernel
   std::string timer_name;
   std::vector<std::pair<hipEvent_t, hipEvent_t>> timer_ev;
@@ -421,7 +420,6 @@ struct Stage {
   uint64_t tail_in_base = 0, tail_out_base = 0;
   bool is_leaf = false;    // k_base: the nodes of 2^BASE_J limbs
   BaseLevel base{};
-  bool dec = false;        // radix-10^9 products (k_crt10; addends in the segments)
   bool is_fused = false;   // k_tree_fused over the levels fused.j0 .. fused.j1
   FusedTree fused{};
   uint32_t fused_tiles = 0;
@@ -1379,8 +1377,8 @@ cat_status launch_crt(Exec& X, uint32_t* out, SegView sv, uint32_t nblk, const C
   if (fp_logD >= 0) {
     KTime kt("k_fcrt", X.st, (double)nblk * FCRT_BLOCK);
     X.crt_epoch++;
-    HIPCHK(fntt_crt(sv, fp_logD, (const double*)X.res, X.res_stride / 2, out, nblk, X.flags, X.crt_epoch,
-                    crt_polls(nblk), cl, tin, tout, X.err, X.st));
+    HIPCHK(fntt_crt(sv, fp_logD, (const double*)X.res, X.res_stride / 2, nullptr, out, nblk, X.flags,
+                    X.crt_epoch, crt_polls(nblk), cl, tin, tout, X.err, X.st));
     X.launches++;
     return CAT_OK;
   }
@@ -1396,22 +1394,6 @@ cat_status launch_crt(Exec& X, uint32_t* out, SegView sv, uint32_t nblk, const C
     else
       hipLaunchKernelGGL((k_crt<false, 1>), dim3(grid), dim3(CAT_CRT_THREADS), 0, X.st, sv, X.res, X.res_stride, out,
                          nblk, X.flags, X.crt_epoch, crt_polls(nblk), cl, tin, tout, X.err);
-  }
-  LAUNCHCHK();
-  X.launches++;
-  return CAT_OK;
-}
-
-// Radix-10^9 CRT + carry + addend (addends are read relative to the workspace).
-cat_status launch_crt10(Exec& X, uint32_t* out, const SegView& sv, uint32_t nblk, const CopyList* tails,
-                        const uint32_t* tin, uint32_t* tout) {
-  const uint32_t grid = nblk + tail_blocks(*tails);
-  if (grid == 0) return CAT_OK;
-  {
-    KTime kt("k_crt10", X.st, (double)nblk * DEC_CRT_BLOCK);
-    X.crt_epoch++;
-    hipLaunchKernelGGL(k_crt10, dim3(grid), dim3(DEC_CRT_THREADS), 0, X.st, sv, X.res, X.res_stride, out, X.W, nblk,
-                       X.flags, X.crt_epoch, crt_polls(nblk), *tails, tin, tout, X.err);
   }
   LAUNCHCHK();
   X.launches++;
@@ -1486,10 +1468,9 @@ cat_status launch_fp(Exec& X, const Stage& s, const DescView& dv, uint64_t cnt) 
   return CAT_OK;
 }
 
-// prime set of a transform stage (radix-10^9 products keep the first set,
-// whose CRT kernel carries in that radix)
+// prime set of a transform stage
 int stage_as(const Stage& s) {
-  if (s.dec || (s.cls != CLS_LDS && s.cls != CLS_LARGE)) return 0;
+  if (s.cls != CLS_LDS && s.cls != CLS_LARGE) return 0;
   return (uint32_t)s.logN <= g_lazy_logn ? 1 : 0;
 }
 
@@ -1545,34 +1526,19 @@ cat_status launch_products(Exec& X, const Stage& s, DescView dv, uint64_t cnt, b
     const uint64_t per = (1ull << lt) >> s.logN;
     const uint64_t tiles = (cnt + per - 1) / per;
     const dim3 grid((uint32_t)(tiles * CAT_NPRIMES)), block((1u << lt) / 16);
-    // a second operand common to all products (decimal joins): transformed
-    // once per prime into the stage scratch, then reused, where the stage is
-    // large enough for the saved transforms to outweigh the extra launch
-    const bool constb = dv.uni && dv.u.sb == 0 && cnt > 1 && (cnt << s.logN) >= (1ull << 21);
-    KTime kt("k_ntt_lds", X.st, constb ? bfly(6.0 * cnt + 3.0, s.logN) : bfly(9.0 * cnt, s.logN));
-#define LDS_LAUNCH(LT, BM, G)                                                                                \
+    KTime kt("k_ntt_lds", X.st, bfly(9.0 * cnt, s.logN));
+#define LDS_LAUNCH(LT)                                                                                        \
   do {                                                                                                         \
     if (as == 0)                                                                                               \
-      hipLaunchKernelGGL((k_ntt_lds<LT, BM, 0>), G, block, 0, X.st, dv, cnt, s.logN, ain, bin, X.res,          \
-                         X.res_stride, tb, s0, s1, s2, X.F);                                                   \
+      hipLaunchKernelGGL((k_ntt_lds<LT, 0>), grid, block, 0, X.st, dv, cnt, s.logN, ain, bin, X.res,           \
+                         X.res_stride, tb, s0, s1, s2);                                                        \
     else                                                                                                       \
-      hipLaunchKernelGGL((k_ntt_lds<LT, BM, 1>), G, block, 0, X.st, dv, cnt, s.logN, ain, bin, X.res,          \
-                         X.res_stride, tb, s0, s1, s2, X.F);                                                   \
+      hipLaunchKernelGGL((k_ntt_lds<LT, 1>), grid, block, 0, X.st, dv, cnt, s.logN, ain, bin, X.res,           \
+                         X.res_stride, tb, s0, s1, s2);                                                        \
   } while (0)
-    if (constb) {
-      if (lt == 12) LDS_LAUNCH(12, 1, dim3(CAT_NPRIMES));
-      else if (lt == 13) LDS_LAUNCH(13, 1, dim3(CAT_NPRIMES));
-      else LDS_LAUNCH(14, 1, dim3(CAT_NPRIMES));
-      LAUNCHCHK();
-      X.launches++;
-      if (lt == 12) LDS_LAUNCH(12, 2, grid);
-      else if (lt == 13) LDS_LAUNCH(13, 2, grid);
-      else LDS_LAUNCH(14, 2, grid);
-    } else {
-      if (lt == 12) LDS_LAUNCH(12, 0, grid);
-      else if (lt == 13) LDS_LAUNCH(13, 0, grid);
-      else LDS_LAUNCH(14, 0, grid);
-    }
+    if (lt == 12) LDS_LAUNCH(12);
+    else if (lt == 13) LDS_LAUNCH(13);
+    else LDS_LAUNCH(14);
 #undef LDS_LAUNCH
     LAUNCHCHK();
     X.launches++;
@@ -1592,15 +1558,11 @@ cat_status launch_products(Exec& X, const Stage& s, DescView dv, uint64_t cnt, b
   for (int k = 0; k + 1 < pp.P; k++) defer[k] = pp.logC[k + 1] <= 8;
   auto self_tw = [&](int k) { return (k + 1 < pp.P && !defer[k]) ? 1 : 0; };
   auto pre_tw = [&](int k) { return (k >= 1 && defer[k - 1]) ? 1 : 0; };
-  // A second operand that is the same for every product (the power P_j of a
-  // decimal join) is transformed once: its column passes for product 0 only,
-  // its row transforms once (k_row mode 1), reused by every product (mode 2).
-  const bool constb = dv.uni && dv.u.sb == 0 && cnt > 1;
-  auto pass_fwd = [&](const PassGeom& pg, int k, int plS, int plL, uint64_t gx, uint32_t nop, int op_base) {
-    const dim3 grid((uint32_t)(gx * CAT_NPRIMES), 1, nop);
+  auto pass_fwd = [&](const PassGeom& pg, int k, int plS, int plL, uint64_t gx) {
+    const dim3 grid((uint32_t)(gx * CAT_NPRIMES), 1, 2);
 #define PASS_FWD(LT, A)                                                                                            \
   hipLaunchKernelGGL((k_pass_fwd<LT, A>), grid, dim3(NTT_COL_THREADS), 0, X.st, dv, pg, k == 0 ? 1 : 0, self_tw(k), \
-                     pre_tw(k), plS, plL, op_base, ain, bin, X.F, tb)
+                     pre_tw(k), plS, plL, ain, bin, X.F, tb)
     if (logT == NTT_COL_LOGT_SMALL) {
       if (as == 0) PASS_FWD(NTT_COL_LOGT_SMALL, 0);
       else PASS_FWD(NTT_COL_LOGT_SMALL, 1);
@@ -1613,19 +1575,11 @@ cat_status launch_products(Exec& X, const Stage& s, DescView dv, uint64_t cnt, b
   for (int k = 0; k < pp.P; k++) {
     PassGeom pg{s.logN, pp.logS[k], pp.logL[k], pp.logC[k]};
     const int plS = k >= 1 ? pp.logS[k - 1] : 0, plL = k >= 1 ? pp.logL[k - 1] : 0;
-    const uint64_t gx1 = 1ull << (s.logN - pp.logL[k] - pp.logC[k]);   // tiles of one product
-    const uint64_t gx = cnt * gx1;
+    const uint64_t gx = cnt << (s.logN - pp.logL[k] - pp.logC[k]);
     // L-point DFTs of both operands, 3 primes: (N/2) log2 L butterflies each
-    KTime kt("k_pass_fwd", X.st, (constb ? 3.0 * (cnt + 1) : 6.0 * cnt) * N / 2 * pp.logL[k]);
-    if (constb) {
-      pass_fwd(pg, k, plS, plL, gx, 1, 0);
-      LAUNCHCHK();
-      pass_fwd(pg, k, plS, plL, gx1, 1, 1);
-    } else {
-      pass_fwd(pg, k, plS, plL, gx, 2, 0);
-    }
+    KTime kt("k_pass_fwd", X.st, 6.0 * cnt * N / 2 * pp.logL[k]);
+    pass_fwd(pg, k, plS, plL, gx);
     LAUNCHCHK();
-    if (constb) X.launches++;
   }
   {
     // row DFTs: two forward and one inverse per row, 3 primes
@@ -1634,11 +1588,11 @@ cat_status launch_products(Exec& X, const Stage& s, DescView dv, uint64_t cnt, b
     // rows share the 2^12 tile
     const int lt = logM == 11 ? 11 : std::max(logM, CAT_LDS_LOGT);
     const dim3 block((1u << lt) / 16);
-    auto row = [&](uint64_t nprod, int bmode) {
-      const dim3 grid((uint32_t)(nprod << logR1), CAT_NPRIMES);
+    const dim3 grid((uint32_t)(cnt << logR1), CAT_NPRIMES);
+    KTime kt("k_row", X.st, bfly(9.0 * rows, logM));
 #define ROW(LT, A)                                                                                              \
   hipLaunchKernelGGL((k_row<LT, A>), grid, block, 0, X.st, s.logN, logM, pp.logS[pp.P - 1], pp.logL[pp.P - 1], \
-                     bmode, X.F, tb, s0, s1, s2)
+                     X.F, tb, s0, s1, s2)
       if (lt == 11) {
         if (as == 0) ROW(11, 0);
         else ROW(11, 1);
@@ -1653,16 +1607,6 @@ cat_status launch_products(Exec& X, const Stage& s, DescView dv, uint64_t cnt, b
         else ROW(14, 1);
       }
 #undef ROW
-    };
-    KTime kt("k_row", X.st, constb ? bfly(6.0 * rows + 3.0 * (1ull << logR1), logM) : bfly(9.0 * rows, logM));
-    if (constb) {
-      row(1, 1);
-      LAUNCHCHK();
-      X.launches++;
-      row(cnt, 2);
-    } else {
-      row(cnt, 0);
-    }
   }
   LAUNCHCHK();
   for (int k = pp.P - 1; k >= 0; k--) {
@@ -1742,11 +1686,6 @@ cat_status run_stage_batched(Exec& X, const Stage& s) {
     LAUNCHCHK();
     X.launches++;
     return CAT_OK;
-  }
-  if (s.nmul > 0 && s.dec) {
-    if (s.cls == CLS_SCHOOL) return CAT_EINTERNAL;
-    STCHK(launch_products(X, s, s.dv, s.nmul));
-    return launch_crt10(X, out_base(X, s), s.sv, s.nblk, &s.tails, X.W + s.tail_in_base, X.W + s.tail_out_base);
   }
   if (s.nmul > 0 && fp_fused(s)) {
     const FBatch b = fp_batch(X, s, s.dv, s.nmul);

@@ -423,12 +423,7 @@ __device__ __forceinline__ uint32_t out_residue(uint32_t x, uint32_t p) {
 // Writes res[prime][r_off + j] = (a*b)_j mod p for j < la+lb.
 // Tile of 2^LOGT coefficient slots (T/N products), 2^LOGT/16 threads, so every
 // radix-16 pass gives each thread two groups over the two operands.
-// BMODE 0: both operands per product.  BMODE 1 and 2 serve a stage whose
-// second operand is one array for every product: mode 1, launched with one
-// workgroup per prime, leaves its transform in fb[prime][0 .. N); mode 2
-// loads that beside each first operand and transforms only the latter.  The
-// grid
-// is 3 x tiles workgroups; workgroup ids are renumbered so that each XCD takes
+// The grid is 3 x tiles workgroups; workgroup ids are renumbered so that each XCD takes
 // a contiguous run of (tile, prime) pairs: the three primes of a tile run one
 // after another on one XCD and read the operands once from HBM into its L2.
 // First forward and last inverse pass of a packed tile on registers: the
@@ -499,11 +494,11 @@ __device__ __forceinline__ void lds_last_inv(const uint32_t* lds, uint32_t* dst,
   }
 }
 
-template <int LOGT, int BMODE, int AS>
+template <int LOGT, int AS>
 __global__ void __launch_bounds__((1 << LOGT) / 16)
 k_ntt_lds(DescView dv, uint64_t nmul, int logN, const uint32_t* __restrict__ ain, const uint32_t* __restrict__ bin,
-          uint32_t* __restrict__ res, uint64_t res_stride, NttTables tb, uint2 scale0, uint2 scale1, uint2 scale2,
-          uint32_t* __restrict__ fb) {
+          uint32_t* __restrict__ res, uint64_t res_stride, NttTables tb, uint2 scale0, uint2 scale1,
+          uint2 scale2) {
   constexpr uint32_t TT = 1u << LOGT;
   __shared__ uint32_t lds[lds_pad(2 * TT)];
   __shared__ MulDesc ds[64];
@@ -520,35 +515,18 @@ k_ntt_lds(DescView dv, uint64_t nmul, int logN, const uint32_t* __restrict__ ain
   const uint32_t T = cnt << logN;                  // live slots
   const uint2* tws = tb.tws + (size_t)prime * TWS_ENTRIES;
   const uint2* itws = tb.itws + (size_t)prime * TWS_ENTRIES;
-  // A second operand that is the same for every product (the power P_j of a
-  // decimal join): BMODE 1 (one workgroup per prime) transforms it once and
-  // stores the N words as they stand in LDS to fb[prime][.]; BMODE 2 loads
-  // them into every product's slot and transforms only the first operands.
-  if constexpr (BMODE == 1) {
-    const MulDesc d = ds[0];
-    for (uint32_t t = threadIdx.x; t < N; t += blockDim.x)
-      lds[lds_pad(t)] = in_limb<AS>(t < d.lb ? bin[d.b_off + t] : 0u, p);
-    __syncthreads();
-    ntt_fwd_tile<true, AS>(lds, logN, N, 0, tws, pc);
-    __syncthreads();
-    for (uint32_t t = threadIdx.x; t < N; t += blockDim.x) fb[(size_t)prime * N + t] = lds[lds_pad(t)];
-    return;
-  }
   // Packed tiles (every tree level): the tile's products have la = lb = N/2
   // and lie back to back, a then b, in one array, with their residues at the
   // same relative positions, so the tile reads T consecutive words and writes
   // T consecutive residues
-  bool packed = false;
-  if constexpr (BMODE == 0) {
-    bool ok = true;
-    if (threadIdx.x < cnt) {
-      const MulDesc d = ds[threadIdx.x], d0 = ds[0];
-      const uint64_t rel = (uint64_t)threadIdx.x << logN;
-      ok = d.la == (N >> 1) && d.lb == (N >> 1) && d.a_off == d0.a_off + rel && d.b_off == d.a_off + (N >> 1) &&
-           d.r_off == d0.r_off + rel;
-    }
-    packed = __syncthreads_and(ok ? 1 : 0) != 0 && ain == bin;
+  bool ok = true;
+  if (threadIdx.x < cnt) {
+    const MulDesc d = ds[threadIdx.x], d0 = ds[0];
+    const uint64_t rel = (uint64_t)threadIdx.x << logN;
+    ok = d.la == (N >> 1) && d.lb == (N >> 1) && d.a_off == d0.a_off + rel && d.b_off == d.a_off + (N >> 1) &&
+         d.r_off == d0.r_off + rel;
   }
+  const bool packed = __syncthreads_and(ok ? 1 : 0) != 0 && ain == bin;
   // 2^12-slot packed tiles of transforms of 2^9 .. 2^12 points: the first
   // forward pass (radix 2^lr, groups of positions j + 256 k) and the last
   // inverse pass run on registers, since a thread's loaded and stored words
@@ -557,7 +535,7 @@ k_ntt_lds(DescView dv, uint64_t nmul, int logN, const uint32_t* __restrict__ ain
   // (2^12 tiles: transforms of 2^9 .. 2^12 points; 2^13: 2^13; 2^14: 2^13
   // and 2^14, where 2^(logN - pass_logr(logN)) is a multiple of the thread
   // count)
-  const bool regp = BMODE == 0 && packed &&
+  const bool regp = packed &&
                     (LOGT == 12 ? logN >= 9 : LOGT == 13 ? logN == 13 : LOGT == 14 ? logN >= 13 : false);
   const int logSR1 = logN - pass_logr(logN);
   if (regp) {
@@ -615,25 +593,20 @@ k_ntt_lds(DescView dv, uint64_t nmul, int logN, const uint32_t* __restrict__ ain
       const MulDesc d = ds[m];
       const uint32_t ka = j < d.la ? 0xFFFFFFFFu : 0u, kb = j < d.lb ? 0xFFFFFFFFu : 0u;
       xa[i] = ain[d.a_off + (j & ka)] & ka;
-      if constexpr (BMODE == 2)
-        xb[i] = fb[(size_t)prime * N + j];
-      else
-        xb[i] = bin[d.b_off + (j & kb)] & kb;
+      xb[i] = bin[d.b_off + (j & kb)] & kb;
     }
 #pragma unroll
     for (int i = 0; i < 16; i++) {
       const uint32_t t = threadIdx.x + i * NT;
       lds[lds_pad(t)] = in_limb<AS>(xa[i], p);
-      lds[lds_pad(TT + t)] = BMODE == 2 ? xb[i] : in_limb<AS>(xb[i], p);
+      lds[lds_pad(TT + t)] = in_limb<AS>(xb[i], p);
     }
   }
   // slots past T of a partial tile repeat the last live slot; their
   // sub-problems are independent and never read back
   __syncthreads();
   // A occupies [0, T), B [TT, TT + T); transform both as one tile
-  if constexpr (BMODE == 2) {
-    ntt_fwd_tile<true, AS>(lds, logN, T, 0, tws, pc);
-  } else if (regp) {
+  if (regp) {
     // the passes after the first but the last
     if (T == TT) {
       ntt_fwd_tile<true, AS>(lds, logSR1, 2 * TT, 0, tws, pc, threadIdx.x, blockDim.x, false, 4);
@@ -850,14 +823,14 @@ __device__ __forceinline__ void col_first_fwd(uint32_t* lds, const uint32_t* v, 
 
 template <int LOGT, int AS>
 __global__ void __launch_bounds__(NTT_COL_THREADS)
-k_pass_fwd(DescView dv, PassGeom pg, int first, int tw, int pre, int plogS, int plogL, int op_base,
+k_pass_fwd(DescView dv, PassGeom pg, int first, int tw, int pre, int plogS, int plogL,
            const uint32_t* __restrict__ ain, const uint32_t* __restrict__ bin, uint32_t* __restrict__ F,
            NttTables tb) {
   __shared__ uint32_t lds[1u << LOGT];
   // x: (tile, prime) pairs, XCD-contiguous; the three primes of a tile of the
   // first pass read the same operand words
   const uint32_t wid = xcd_remap(blockIdx.x, gridDim.x);
-  const uint32_t prime = wid % CAT_NPRIMES, op = op_base + blockIdx.z;
+  const uint32_t prime = wid % CAT_NPRIMES, op = blockIdx.z;
   const PrimeC& pc = primec<AS>(prime);
   const uint32_t p = pc.p;
   uint64_t m, base;
@@ -1326,13 +1299,8 @@ __device__ __forceinline__ void row_last_inv(const uint32_t* lds, uint32_t* vo, 
 // Rows of M = 2^logM <= 2^LOGT elements; 2^LOGT/16 threads.
 template <int LOGT, int AS>
 __global__ void __launch_bounds__((1 << LOGT) / 16)
-// bmode 0: both operands per product.  A stage whose second operand is the
-// same for every product computes that operand's row transforms once:
-// bmode 1 (rows of product 0 only) transforms them and stores the tile as it
-// stands in LDS; bmode 2 then loads it into the second half for every
-// product and transforms only the first operand.
-k_row(int logN, int logM, int logSl, int logLl, int bmode, uint32_t* __restrict__ F, NttTables tb, uint2 scale0,
-      uint2 scale1, uint2 scale2) {
+k_row(int logN, int logM, int logSl, int logLl, uint32_t* __restrict__ F, NttTables tb, uint2 scale0, uint2 scale1,
+      uint2 scale2) {
   constexpr uint32_t TT = 1u << LOGT;
   __shared__ uint32_t lds[lds_pad(2 * TT)];
   const uint32_t prime = blockIdx.y;
@@ -1344,7 +1312,7 @@ k_row(int logN, int logM, int logSl, int logLl, int bmode, uint32_t* __restrict_
   const uint64_t m = blockIdx.x >> logR1;
   const uint32_t q = blockIdx.x & ((1u << logR1) - 1);
   uint32_t* fa = F + ((m * 3 + prime) * 2 + 0) * N + ((uint64_t)q << logM);
-  uint32_t* fb = F + (((bmode ? 0 : m) * 3 + prime) * 2 + 1) * N + ((uint64_t)q << logM);
+  uint32_t* fb = F + ((m * 3 + prime) * 2 + 1) * N + ((uint64_t)q << logM);
   constexpr uint32_t NT = TT / 16;                 // blockDim.x
   // The twiddles of the column pass next to the rows (sub-problems of
   // S = 2^logSl, rows of L = 2^logLl): position j of row q takes
@@ -1358,26 +1326,7 @@ k_row(int logN, int logM, int logSl, int logLl, int bmode, uint32_t* __restrict_
   uint2 w = tw2(flo, fhi, ((threadIdx.x * fr) << ysh) & ymask, pc);
   const uint2 R = tw2(flo, fhi, ((NT * fr) << ysh) & ymask, pc);
   const uint2* tws = tb.tws + (size_t)prime * TWS_ENTRIES;
-  if (bmode == 1) {
-    for (uint32_t t = threadIdx.x; t < M; t += NT) {
-      lds[lds_pad(t)] = data_tw<AS>(fb[t], w, p);
-      w.x = mul_tw(w.x, R.x, R.y, p);
-      w.y = w.x * pc.pinv;
-    }
-    __syncthreads();
-    ntt_fwd_tile<true, AS>(lds, logM, M, 0, tws, pc);
-    __syncthreads();
-    for (uint32_t t = threadIdx.x; t < M; t += NT) fb[t] = lds[lds_pad(t)];
-    return;
-  }
-  if (bmode == 2) {
-    for (uint32_t t = threadIdx.x; t < M; t += NT) {
-      lds[lds_pad(t)] = data_tw<AS>(fa[t], w, p);
-      lds[lds_pad(M + t)] = fb[t];
-      w.x = mul_tw(w.x, R.x, R.y, p);
-      w.y = w.x * pc.pinv;
-    }
-  } else if (M == TT) {
+  if (M == TT) {
     // full rows: all 32 loads of the thread in flight before the first use
     uint32_t va[16], vb[16];
 #pragma unroll
@@ -1407,7 +1356,7 @@ k_row(int logN, int logM, int logSl, int logLl, int bmode, uint32_t* __restrict_
   // forward pass, the pointwise product and the first inverse pass run on
   // registers too (mid), except in rows of 2^13, where the extra registers
   // would cost that tile its second workgroup per CU
-  const bool full = M == TT && bmode == 0;
+  const bool full = M == TT;
   const bool mid = full && LOGT != 13;
   if (mid) {
     ntt_fwd_tile<true, AS>(lds, LOGT - pass_logr(LOGT), 2 * M, 0, tws, pc, threadIdx.x, blockDim.x, false, 4);
@@ -1416,7 +1365,7 @@ k_row(int logN, int logM, int logSl, int logLl, int bmode, uint32_t* __restrict_
   } else if (full) {
     ntt_fwd_tile<true, AS>(lds, LOGT - pass_logr(LOGT), 2 * M, 0, tws, pc);   // the passes after the first
   } else {
-    ntt_fwd_tile<true, AS>(lds, logM, bmode == 2 ? M : 2 * M, 0, tws, pc);
+    ntt_fwd_tile<true, AS>(lds, logM, 2 * M, 0, tws, pc);
   }
   if (mid) {
   } else if (M == TT) {
