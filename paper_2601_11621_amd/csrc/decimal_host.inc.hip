@@ -42,8 +42,6 @@ bool dec_stage(Stage* s, uint64_t np, UniDesc u, const CrtSeg& seg, uint64_t ste
   if (k > FNTT_MAX_LOGD) return false;
   s->fp = true;
   s->logN = std::max(k, FNTT_LDS_MIN_LOGD) + 1;
-  s->logM = g_tune.log_row[s->logN];
-  s->maxL = g_tune.log_pass[s->logN];
   s->nmul = np + (sq ? 1 : 0);
   s->limbs = s->nmul * len;
   u.last = (uint32_t)(np - 1);

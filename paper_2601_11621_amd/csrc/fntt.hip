@@ -1524,10 +1524,8 @@ static void row_launch(const FBatch& b, int logS, int logL, hipStream_t st) {
 }
 hipError_t fntt_row(const FBatch& b, int logM, int logS, int logL, hipStream_t st) {
   switch (logM) {
-    case 10: row_launch<10>(b, logS, logL, st); break;
     case 11: row_launch<11>(b, logS, logL, st); break;
     case 12: row_launch<12>(b, logS, logL, st); break;
-    case 13: row_launch<13>(b, logS, logL, st); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
