@@ -56,6 +56,7 @@ struct Lib {
   hipStream_t cap_stream = nullptr;
   hipStream_t side_stream = nullptr;            // second branch of captured calls
   hipEvent_t ev_fork = nullptr, ev_join = nullptr;
+  hipEvent_t ev_table = nullptr;                // a published group table
   // kernel timer: events around every launch of one named kernel
   std::string timer_name;
   std::vector<std::pair<hipEvent_t, hipEvent_t>> timer_ev;
@@ -273,6 +274,7 @@ cat_status init_locked(int device) {
   HIPCHK(hipStreamCreateWithFlags(&g.cap_stream, hipStreamNonBlocking));
   HIPCHK(hipStreamCreateWithFlags(&g.side_stream, hipStreamNonBlocking));
   HIPCHK(hipEventCreateWithFlags(&g.ev_fork, hipEventDisableTiming));
+  HIPCHK(hipEventCreateWithFlags(&g.ev_table, hipEventDisableTiming));
   HIPCHK(hipEventCreateWithFlags(&g.ev_join, hipEventDisableTiming));
   g.inited = true;
   return CAT_OK;
@@ -731,6 +733,7 @@ void plan_tree(const Layout& Ly, Plan& P) {
   auto in_of = [&](int j) -> uint64_t { return j == 0 ? Ly.primes : out_of(j - 1); };
   const int jR = P.rins_j;
   const uint64_t D = jR >= 0 ? (1ull << jR) : 0;
+  st.reserve(CAT_MAX_LOGN + 2);
   // first leaf and leaf count of group g at level j (input side)
   auto gpos = [&](uint32_t gi, int j) -> uint64_t {
     if (j == 0) return P.off[gi];
@@ -775,7 +778,7 @@ void plan_tree(const Layout& Ly, Plan& P) {
     s.a_base = Ly.primes;
     // the buffer the pairwise levels would have written last
     s.c_base = out_of(jleaf - 1) + D;
-    st.push_back(s);
+    st.push_back(std::move(s));
     jstart = jleaf;
   }
   int j = jstart;
@@ -808,7 +811,7 @@ void plan_tree(const Layout& Ly, Plan& P) {
       }
       s.a_base = in_of(jf0);
       s.c_base = out_of(jf1);
-      st.push_back(s);
+      st.push_back(std::move(s));
       j = jf1;
       continue;
     }
@@ -865,7 +868,7 @@ void plan_tree(const Layout& Ly, Plan& P) {
     build_crt_segs(s);
     P.products += m;
     P.product_limbs += s.limbs;
-    st.push_back(s);
+    st.push_back(std::move(s));
   }
   P.levels = (uint32_t)j;
   if (batched) {
@@ -969,7 +972,7 @@ void add_products(Plan& P, std::vector<std::pair<Item, Item>>& pairs, std::vecto
       build_crt_segs(t);
       P.products += t.nmul;
       P.product_limbs += t.limbs;
-      P.post.push_back(t);
+      P.post.push_back(std::move(t));
     }
   }
 }
@@ -1293,8 +1296,17 @@ cat_status make_plan(const Layout& Ly, const GroupTable& gt, Plan** out, bool pl
     // products and their limbs are counted from the pairwise levels of the
     // plain form (the base kernel of the batched form folds the lowest levels)
     Plan Q = *P;
-    Q.plain = true;
-    plan_all(Q);
+    if (P->ng == 1 && P->exps[0] == 1) {
+      const uint64_t K = P->off[1] - P->off[0];
+      for (; (1ull << Q.levels) < K; Q.levels++) {
+        const uint64_t m = ((K + (1ull << Q.levels) - 1) >> Q.levels) / 2;
+        Q.products += m;
+        Q.product_limbs += std::min<uint64_t>(K, m * (2ull << Q.levels));
+      }
+    } else {
+      Q.plain = true;
+      plan_all(Q);
+    }
     plan_all(*P);
     P->products = Q.products;
     P->product_limbs = Q.product_limbs;
@@ -2589,28 +2601,39 @@ Layout make_layout_ratio(const RatioSpec& r) {
 }
 
 cat_status run_phase1_ratio(const Layout& Ly, const RatioSpec& r, char* wb, uint32_t* primes, uint64_t cap,
-                            hipStream_t st, uint64_t* launches) {
+                            uint32_t ebits, hipStream_t st, uint64_t* launches) {
   uint32_t* W = (uint32_t*)wb;
   GroupTable* gt = (GroupTable*)(wb + Ly.gtab);
   RatioCounts* rc = (RatioCounts*)(wb + Ly.rcounts);
-  hipLaunchKernelGGL(k_rseeds, dim3(1), dim3(1024), 0, st, r.rt, (uint32_t)Ly.s, W + Ly.seeds, W + Ly.seed_e, gt,
-                     (uint32_t*)gt, (uint64_t)Ly.ctl_words, rc);
+  hipLaunchKernelGGL(k_rseeds, dim3(1), dim3(1024), 0, st, r.rt, (uint32_t)Ly.s, ebits, W + Ly.seeds, W + Ly.seed_e,
+                     gt, (uint32_t*)gt, (uint64_t)Ly.ctl_words, rc);
   LAUNCHCHK();
   if (Ly.nseg > 0) {
-    hipLaunchKernelGGL(k_rsieve, dim3((uint32_t)Ly.nseg), dim3(SIEVE_THREADS), 0, st, r.rt, Ly.i0, Ly.i_end,
-                       (const uint32_t*)(W + Ly.seeds), gt, W + Ly.bitmap, W + Ly.seg_cnt);
+    hipLaunchKernelGGL(k_rsieve, dim3((uint32_t)Ly.nseg), dim3(SIEVE_THREADS), 0, st, r.rt, Ly.i0, Ly.i_end, ebits,
+                       (const uint32_t*)(W + Ly.seeds), gt, W + Ly.bitmap, W + Ly.seg_cnt, rc);
     LAUNCHCHK();
   }
-  hipLaunchKernelGGL(k_rscan, dim3(1), dim3(1024), 0, st, (uint32_t)Ly.nseg, (const uint32_t*)(W + Ly.seg_cnt),
+  hipLaunchKernelGGL(k_rscan, dim3(1), dim3(1024), 0, st, (uint32_t)Ly.nseg, ebits, (const uint32_t*)(W + Ly.seg_cnt),
                      W + Ly.seg_off, (const uint32_t*)(W + Ly.seeds), (const uint32_t*)(W + Ly.seed_e), gt, W + Ly.P,
-                     W + Ly.E, (uint64_t)Ly.np_cap, rc);
+                     W + Ly.E, (uint64_t)Ly.np_cap, rc, primes, cap, (GroupTable*)g.pin);
   LAUNCHCHK();
+  if (ebits) HIPCHK(hipEventRecord(g.ev_table, st));
   if (Ly.nseg > 0) {
-    hipLaunchKernelGGL(k_rscatter, dim3((uint32_t)Ly.nseg), dim3(SIEVE_THREADS), 0, st, r.rt, Ly.i0,
+    hipLaunchKernelGGL(k_rscatter, dim3((uint32_t)Ly.nseg), dim3(SIEVE_THREADS), 0, st, r.rt, Ly.i0, ebits,
                        (const uint32_t*)(W + Ly.bitmap), (const uint32_t*)(W + Ly.seg_off), (const GroupTable*)gt,
-                       W + Ly.P, W + Ly.E, (uint64_t)Ly.np_cap);
+                       (const RatioCounts*)rc, W + Ly.P, W + Ly.E, (uint64_t)Ly.np_cap, primes, cap);
     LAUNCHCHK();
   }
+  *launches += Ly.nseg > 0 ? 4 : 2;
+  return CAT_OK;
+}
+
+// the groups by exponent bits, from the primes and exponents of run_phase1_ratio
+cat_status run_bits_ratio(const Layout& Ly, char* wb, uint32_t* primes, uint64_t cap, hipStream_t st,
+                          uint64_t* launches) {
+  uint32_t* W = (uint32_t*)wb;
+  GroupTable* gt = (GroupTable*)(wb + Ly.gtab);
+  RatioCounts* rc = (RatioCounts*)(wb + Ly.rcounts);
   hipLaunchKernelGGL(k_rbits, dim3((uint32_t)Ly.nchunks), dim3(256), 0, st, (const uint32_t*)(W + Ly.P),
                      (const uint32_t*)(W + Ly.E), (const RatioCounts*)rc, W + Ly.chunk_cnt, rc);
   LAUNCHCHK();
@@ -2623,21 +2646,24 @@ cat_status run_phase1_ratio(const Layout& Ly, const RatioSpec& r, char* wb, uint
                      (const uint32_t*)(W + Ly.E), (const RatioCounts*)rc, (const uint32_t*)(W + Ly.chunk_off),
                      (const GroupTable*)gt, primes, cap);
   LAUNCHCHK();
-  *launches += Ly.nseg > 0 ? 8 : 6;
+  *launches += 4;
   return CAT_OK;
 }
 
-// the group table of a ratio's Phase 1, with its error word mapped
-cat_status read_groups_ratio(const Layout& Ly, char* wb, hipStream_t st, GroupTable* out) {
-  HIPCHK(hipMemcpyAsync(g.pin, wb + Ly.gtab, sizeof(GroupTable), hipMemcpyDeviceToHost, st));
-  HIPCHK(hipStreamSynchronize(st));
-  memcpy(out, g.pin, sizeof(GroupTable));
+cat_status check_groups_ratio(GroupTable* out) {
   out->outer = -1;
   if (out->err & CAT_DEVERR_NEG_EXP) return CAT_EINVAL;    // N is not an integer
   if (out->err & CAT_DEVERR_RANGE) return CAT_ERANGE;      // an exponent reaches 2^32
   if (out->err & CAT_DEVERR_BOUNDS) return CAT_EINTERNAL;
   if (out->ngroups > CAT_MAX_GROUPS) return CAT_EINTERNAL;
   return CAT_OK;
+}
+
+cat_status read_groups_ratio(const Layout& Ly, char* wb, hipStream_t st, GroupTable* out) {
+  HIPCHK(hipMemcpyAsync(g.pin, wb + Ly.gtab, sizeof(GroupTable), hipMemcpyDeviceToHost, st));
+  HIPCHK(hipStreamSynchronize(st));
+  memcpy(out, g.pin, sizeof(GroupTable));
+  return check_groups_ratio(out);
 }
 
 // The general form of a C(n) call in a given workspace: Phase 1, the group
@@ -3569,8 +3595,10 @@ cat_status factorial_ratio_factor(const uint64_t* a, uint32_t k, const uint64_t*
   hipStream_t st = (hipStream_t)stream;
   uint64_t launches = 0;
   uint32_t dummy = 0;
-  STCHK(run_phase1_ratio(Ly, r, (char*)d_work, d_primes ? d_primes : &dummy, d_primes ? primes_cap : 0, st,
-                         &launches));
+  uint32_t* primes = d_primes ? d_primes : &dummy;
+  const uint64_t pcap = d_primes ? primes_cap : 0;
+  STCHK(run_phase1_ratio(Ly, r, (char*)d_work, primes, pcap, 0, st, &launches));
+  STCHK(run_bits_ratio(Ly, (char*)d_work, primes, pcap, st, &launches));
   GroupTable gt;
   const cat_status e = read_groups_ratio(Ly, (char*)d_work, st, &gt);
   if (e != CAT_OK && !(e == CAT_EINTERNAL && (gt.err & CAT_DEVERR_BOUNDS))) return e;
@@ -3605,9 +3633,24 @@ cat_status factorial_ratio_exact(const uint64_t* a, uint32_t k, const uint64_t* 
   char* wb = (char*)d_work;
   const bool plain = (flags & CAT_MODE_PLAIN) != 0;
   uint64_t launches = 0;
-  STCHK(run_phase1_ratio(Ly, r, wb, (uint32_t*)wb + Ly.primes, Ly.Kmax, st, &launches));
-  GroupTable gt;
-  STCHK(read_groups_ratio(Ly, wb, st, &gt));
+  uint32_t* primes = (uint32_t*)wb + Ly.primes;
+  const uint32_t ebits = powers_form(plain) ? Ly.ebits : 0;
+  STCHK(run_phase1_ratio(Ly, r, wb, primes, Ly.Kmax, ebits, st, &launches));
+  GroupTable gt{};
+  bool pw = ebits != 0;
+  if (pw) {
+    HIPCHK(hipEventSynchronize(g.ev_table));
+    memcpy(&gt, g.pin, sizeof(GroupTable));
+    pw = gt.ngroups != ~0u;
+  }
+  if (!pw) {
+    STCHK(run_bits_ratio(Ly, wb, primes, Ly.Kmax, st, &launches));
+    STCHK(read_groups_ratio(Ly, wb, st, &gt));
+  } else if (const cat_status e = check_groups_ratio(&gt); e != CAT_OK) {
+    HIPCHK(hipStreamSynchronize(st));
+    return e;
+  }
+  const uint64_t entries = pw ? gt.n_pow : table_primes(gt);
   Plan* P = nullptr;
   STCHK(make_plan(Ly, gt, &P, plain));
   cat_status res = CAT_OK;
@@ -3644,7 +3687,7 @@ cat_status factorial_ratio_exact(const uint64_t* a, uint32_t k, const uint64_t* 
   stats.products = P->products;
   stats.product_limbs = P->product_limbs;
   stats.launches = launches + X.launches + 1;
-  stats.n_primes = table_primes(gt);
+  stats.n_primes = entries;
   stats.levels = P->levels;
   stats.outer_level = P->rins_j >= 0 ? P->rins_j : P->outer_j;
   free_plan(P);
