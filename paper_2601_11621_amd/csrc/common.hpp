@@ -179,6 +179,14 @@ struct DescView {
     d.lb = (uint32_t)(rem < sz ? rem : sz);
     return d;
   }
+  // where the residues of the segment of product i start (a group of a tree
+  // level is one segment, any other product its own)
+  __device__ __forceinline__ uint64_t seg_base(uint64_t i, const MulDesc& d) const {
+    if (table || ninl || uni) return d.r_off;
+    uint32_t g = 0;
+    while (g + 1 < tree.ngroups && i >= tree.mpref[g + 1]) g++;
+    return tree.rbase[g];
+  }
 };
 
 // CRT/carry segments: out[out_pos + k] for k < len from residues at res_pos + k

@@ -192,11 +192,11 @@ cat_status launch_join(Exec& X, const Stage& s) {
     X.launches++;
     return CAT_OK;
   }
-  STCHK(launch_fp(X, s, s.dv, s.nmul));
+  STCHK(launch_fp(X, s, s.dv, s.nmul, X.W));
   KTime kt("k_fcrt10", X.st, (double)s.nblk * FCRT_BLOCK);
   X.crt_epoch++;
-  HIPCHK(fntt_crt(s.sv, s.logN - 1, (const double*)X.res, X.res_stride / 2, X.W, X.W, s.nblk, X.flags, X.crt_epoch,
-                  crt_polls(s.nblk), s.tails, tin, tout, X.err, X.st));
+  HIPCHK(fntt_crt(s.sv, s.logN - 1, fp_run_log(s, s.nmul), (const double*)X.res, X.res_stride / 2, X.W, X.W, s.nblk,
+                  X.flags, X.crt_epoch, crt_polls(s.nblk), s.tails, tin, tout, X.err, X.st));
   X.launches++;
   return CAT_OK;
 }

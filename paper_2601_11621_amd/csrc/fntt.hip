@@ -704,10 +704,9 @@ __device__ __forceinline__ double canon(double x, double p, double pinv) {
 __device__ __forceinline__ uint64_t to_u52(double x) {
   return (uint64_t)__double_as_longlong(x + 4503599627370496.0) & 0xFFFFFFFFFFFFFull;
 }
-__device__ __forceinline__ void fcrt_value(double r0, double r1, double r2, const FCrt& k, uint64_t& v0, uint64_t& v1,
-                                           uint32_t& v2) {
-  const double x0 = canon(mulc(r0, k.k00, k.k00q, k.p[0]), k.p[0], k.pinv[0]);
-  const double x1 = canon(mulc(r1, k.k11, k.k11q, k.p[1]) + mulc(x0, k.k10, k.k10q, k.p[1]), k.p[1], k.pinv[1]);
+// from x0, x1 and the third residue
+__device__ __forceinline__ void fcrt_join(double x0, double x1, double r2, const FCrt& k, uint64_t& v0, uint64_t& v1,
+                                          uint32_t& v2) {
   const double x2 = canon(mulc(r2, k.k22, k.k22q, k.p[2]) + (mulc(x0, k.k20, k.k20q, k.p[2]) +
                                                              mulc(x1, k.k21, k.k21q, k.p[2])),
                           k.p[2], k.pinv[2]);
@@ -718,42 +717,49 @@ __device__ __forceinline__ void fcrt_value(double r0, double r1, double r2, cons
   v1 = (uint64_t)m2;
   v2 = (uint32_t)(m2 >> 64);
 }
+__device__ __forceinline__ void fcrt_value(double r0, double r1, double r2, const FCrt& k, uint64_t& v0, uint64_t& v1,
+                                           uint32_t& v2) {
+  const double x0 = canon(mulc(r0, k.k00, k.k00q, k.p[0]), k.p[0], k.pinv[0]);
+  const double x1 = canon(mulc(r1, k.k11, k.k11q, k.p[1]) + mulc(x0, k.k10, k.k10q, k.p[1]), k.p[1], k.pinv[1]);
+  fcrt_join(x0, x1, r2, k, v0, v1, v2);
+}
 // The column value in the radix of the carries, v0 + v1 R + v2 R^2: R = 2^64, or
 // with DEC R = 10^18 (decimal joins; digits below R) after `add` is added.  There
 // V < 2^25 R^2 + R, so both quotients that are below 2^31 come from FP64 (off by
 // one at most, and seen from the remainder) and one division by the reciprocal is
 // left: with d = 16 R, (u2, u1, u0) = 16 V, u1's remainder mod d tells an
 // overestimate (just below 2^64) from an underestimate (just above d).
+__device__ __forceinline__ void dec_split(uint64_t add, uint64_t& v0, uint64_t& v1, uint32_t& v2) {
+  v0 += add;
+  const uint32_t c = v0 < add;
+  v1 += c;
+  v2 += (v1 < c);
+  const uint32_t u2 = (v2 << 4) | (uint32_t)(v1 >> 60);
+  const uint64_t u1 = (v1 << 4) | (v0 >> 60), u0 = v0 << 4;
+  uint32_t q1 = (uint32_t)(((double)u2 * 0x1p64 + (double)u1) * (1.0 / (double)DEC_D));
+  uint64_t r = u1 - q1 * DEC_D;
+  if (r >= DEC_D) {
+    const bool under = r - DEC_D < (1ull << 60);
+    q1 = under ? q1 + 1 : q1 - 1;
+    r = under ? r - DEC_D : r + DEC_D;
+  }
+  const uint64_t q0 = div_d(r, u0, &r);
+  v0 = r >> 4;
+  v2 = (uint32_t)(((double)q1 * 0x1p64 + (double)q0) * (1.0 / (double)DEC_B));
+  v1 = q0 - v2 * DEC_B;
+  if ((int64_t)v1 < 0) {
+    v2--;
+    v1 += DEC_B;
+  } else if (v1 >= DEC_B) {
+    v2++;
+    v1 -= DEC_B;
+  }
+}
 template <bool DEC>
 __device__ __forceinline__ void fcol_value(double r0, double r1, double r2, const FCrt& k, uint64_t add, uint64_t& v0,
                                            uint64_t& v1, uint32_t& v2) {
   fcrt_value(r0, r1, r2, k, v0, v1, v2);
-  if constexpr (DEC) {
-    v0 += add;
-    const uint32_t c = v0 < add;
-    v1 += c;
-    v2 += (v1 < c);
-    const uint32_t u2 = (v2 << 4) | (uint32_t)(v1 >> 60);
-    const uint64_t u1 = (v1 << 4) | (v0 >> 60), u0 = v0 << 4;
-    uint32_t q1 = (uint32_t)(((double)u2 * 0x1p64 + (double)u1) * (1.0 / (double)DEC_D));
-    uint64_t r = u1 - q1 * DEC_D;
-    if (r >= DEC_D) {
-      const bool under = r - DEC_D < (1ull << 60);
-      q1 = under ? q1 + 1 : q1 - 1;
-      r = under ? r - DEC_D : r + DEC_D;
-    }
-    const uint64_t q0 = div_d(r, u0, &r);
-    v0 = r >> 4;
-    v2 = (uint32_t)(((double)q1 * 0x1p64 + (double)q0) * (1.0 / (double)DEC_B));
-    v1 = q0 - v2 * DEC_B;
-    if ((int64_t)v1 < 0) {
-      v2--;
-      v1 += DEC_B;
-    } else if (v1 >= DEC_B) {
-      v2++;
-      v1 -= DEC_B;
-    }
-  }
+  if constexpr (DEC) dec_split(add, v0, v1, v2);
 }
 // s = a + b + c as s mod R and the carry h = s / R
 template <bool DEC>
@@ -907,6 +913,164 @@ __device__ __forceinline__ uint32_t fcrt_pair(const uint32_t* tmp) {
   return bG | (bP << 1);
 }
 
+// The outermost inverse column pass of all three primes with the recombination:
+// the residues stay in registers, and digits leave instead of them.  A wave's
+// lanes hold runs of CR = min(C, 64) neighbouring digits (C columns of a tile);
+// the carries inside a run are resolved here (shuffles and ballots), and what
+// leaves it at the top, below 2^96, goes to two words per run: 8 + 16 / CR B
+// written per digit and read again by the carry kernel instead of 24.
+// Bound by HBM: 24 B read per digit.  About 200 registers (the first two primes'
+// values, the loads of the next one), so two waves per SIMD; with three, which
+// spill, it is 3 % slower at C(2,050,572,903).  There: the carry kernel 0.44 -> 0.24
+// ms a level, this pass as long as k_fcol_inv; 69.1 -> 67.6 ms in all.
+template <int LOGL, int PS, bool DEC>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
+k_fcol_crt(DescView dv, SegView sv, FGeom fg, FCrt kc, const double* __restrict__ F, double* __restrict__ res,
+           uint64_t stride, const uint32_t* __restrict__ add, FTables tb) {
+  constexpr int LOGT = 12, LR = pass_logr(LOGL), LOGSR = LOGL - LR;
+  constexpr uint32_t T = 1u << LOGT, NT = T / 16;
+  constexpr uint32_t logC = LOGT - LOGL, logCR = logC < 6 ? logC : 6;
+  constexpr uint32_t C = 1u << logC, RI = NT >> logC, CR = 1u << logCR;
+  __shared__ double lds[LOGL > 4 ? ((1u << LOGL) + (1u << LOGL) / 16) * C : 1];
+  const uint32_t tid = threadIdx.x, lane = tid & (CR - 1);
+  uint64_t m;
+  uint32_t base, j0;
+  fg.locate(LOGL, xcd_remap(blockIdx.x, gridDim.x), &m, &base, &j0);
+  const int logSig = fg.logS - LOGL;
+  const uint64_t N = 1ull << fg.logD;
+  const uint32_t q0 = base + ((16 * (tid >> logC)) << logSig) + j0 + (tid & (C - 1));
+  auto load = [&](int prime, double* y) {
+    const double* f = F + (m * 3 + prime) * 2 * N;
+    const __amdgpu_buffer_rsrc_t rf =
+        __builtin_amdgcn_make_buffer_rsrc((void*)f, (short)0, (int)(uint32_t)(N * 8), CAT_BUF_DW3);
+#pragma unroll
+    for (int k = 0; k < 16; k++) y[k] = buf_ldd(rf, (q0 + ((uint32_t)k << logSig)) * 8u, 0);
+  };
+  double x[16], nx[16], y0[16], y1[16];
+  load(0, nx);
+  for (int prime = 0; prime < CAT_NPRIMES; prime++) {
+    const FPrime& c = c_fp[PS][prime];
+    const double* itws = tb.itws + (size_t)prime * FTWS_ENTRIES;
+#pragma unroll
+    for (int k = 0; k < 16; k++) x[brev_c(k, 4)] = nx[k];
+    if (prime + 1 < CAT_NPRIMES) load(prime + 1, nx);   // in flight during this prime's passes
+    fidft<4, PS>(x, c);
+    if constexpr (LOGL > 4) {
+      if (prime) __syncthreads();
+      slots_store<4>(lds, x, tid, logC);
+      __syncthreads();
+      if constexpr (LOGSR > 4) {
+        rest_inv<4, 8, LOGSR, PS>(lds, logC, itws, c, tid);
+        __syncthreads();
+      }
+      last_inv<4, LR, LOGSR, PS>(lds, x, NT, logC, itws, c, tid);
+    }
+    if (prime == 0) {
+#pragma unroll
+      for (int i = 0; i < 16; i++) y0[i] = canon(mulc(x[i], kc.k00, kc.k00q, kc.p[0]), kc.p[0], kc.pinv[0]);
+    } else if (prime == 1) {
+#pragma unroll
+      for (int i = 0; i < 16; i++)
+        y1[i] = canon(mulc(x[i], kc.k11, kc.k11q, kc.p[1]) + mulc(y0[i], kc.k10, kc.k10q, kc.p[1]), kc.p[1], kc.pinv[1]);
+    }
+  }
+  const MulDesc d = dv.get(m);
+  const uint64_t L = ((uint64_t)d.la + d.lb + 1) / 2;
+  uint64_t* out = (uint64_t*)res + d.r_off;
+  const uint64_t sb = dv.seg_base(m, d);
+  uint64_t* ev = (uint64_t*)(res + stride) + sb;
+  const uint32_t run0 = (uint32_t)((d.r_off - sb) >> logCR);
+  const uint32_t pos0 = base + ((tid >> logC) << logSig) + j0 + (tid & (C - 1));   // element i: + (RI i) << logSig
+  const uint32_t* ad = nullptr;
+  uint64_t add_len = 0;
+  if constexpr (DEC) {
+    const CrtSeg sg = sv.uniform((uint32_t)m);
+    ad = add + sg.add_pos;
+    add_len = sg.add_len;
+  }
+  constexpr uint64_t TOP = CR == 64 ? 1ull << 63 : ((~0ull / ((1ull << CR) - 1)) << (CR - 1));
+#pragma unroll
+  for (int i = 0; i < 16; i++) {
+    const uint32_t k = pos0 + ((RI * i) << logSig);
+    uint64_t v0, v1;
+    uint32_t v2;
+    fcrt_join(y0[i], y1[i], x[i], kc, v0, v1, v2);
+    if constexpr (DEC) dec_split(add_digit(ad, add_len, k), v0, v1, v2);
+    uint64_t t1 = __shfl_up((unsigned long long)v1, 1, 64);
+    const uint32_t b2 = __shfl_up(v2, 1, 64);
+    uint32_t t2 = __shfl_up(v2, 2, 64), h;
+    if (lane < 1) t1 = 0;
+    if (lane < 2) t2 = 0;
+    const uint64_t lo = fcol_sum<DEC>(v0, t1, t2, &h);
+    const uint32_t hp = __shfl_up(h, 1, 64);
+    const uint64_t u = lo + (lane ? hp : 0);
+    const bool gk = fcol_gen<DEC>(u, lo), pr = fcol_prop<DEC>(u);
+    const uint64_t gm = __ballot(gk) & ~TOP, bm = (__ballot(pr) & ~TOP) | gm;
+    const uint64_t cm = (gm + bm) ^ gm ^ bm;            // carry into each lane
+    uint32_t cy = (uint32_t)((cm >> (tid & 63)) & 1ull);
+    const uint64_t dg = fcol_digit<DEC>(u, gk, &cy);
+    if (k < L) out[k] = dg;
+    if (lane == CR - 1 && k + 1 <= L) {
+      // v1 of this digit, v2 of the one below and the carries; v2 above them
+      uint32_t eh;
+      const uint64_t e0 = fcol_sum<DEC>(v1, b2, (uint64_t)h + cy, &eh);
+      const uint64_t at = 2 * (uint64_t)(run0 + ((k + 1) >> logCR));
+      ev[at] = e0;
+      ev[at + 1] = (uint64_t)v2 + eh;
+    }
+  }
+  if (L > N && base == 0 && j0 == 0 && tid == 0) out[N] = 0;
+}
+
+// The digits and run carries of k_fcol_crt, in the role of fcrt_local: u = digit
+// + what its run's neighbour left, and binary carries.
+template <bool DEC>
+__device__ __forceinline__ void fpart_local(uint64_t len, const uint64_t* __restrict__ dg,
+                                            const uint64_t* __restrict__ ev, uint32_t logCR, uint64_t kb,
+                                            uint32_t* tmp, uint64_t* ul, bool* gk, bool* Gt, bool* Pt, uint32_t* spec) {
+  const uint32_t tid = threadIdx.x, CR = 1u << logCR;
+  const uint64_t k0 = kb + (uint64_t)tid * FCRT_E;
+  auto extra = [&](uint64_t k) -> uint64_t {
+    const uint32_t r = (uint32_t)k & (CR - 1);
+    return r < 2 && k >= CR && k < len ? ev[2 * (k >> logCR) + r] : 0;
+  };
+  uint64_t lo[FCRT_E], e[FCRT_E], cl = 0, ce = 0;
+#pragma unroll
+  for (int i = 0; i < FCRT_E; i++) {
+    const uint64_t k = k0 + i;
+    lo[i] = k < len ? dg[k] : 0;
+    e[i] = extra(k);
+  }
+  const bool lctx = tid < FCRT_CTX && kb >= FCRT_CTX;
+  if (lctx) {
+    cl = dg[kb + tid - FCRT_CTX];
+    ce = extra(kb + tid - FCRT_CTX);
+  }
+  if (tid < 64) {
+    const uint64_t cu = cl + ce;
+    const bool g = fcol_gen<DEC>(cu, cl);
+    const uint64_t gm = __ballot(lctx && g);
+    const uint64_t dm = gm | __ballot(lctx && !g && !fcol_prop<DEC>(cu));
+    if (tid == 0) *spec = dm ? (uint32_t)((gm >> (63 - __builtin_clzll(dm))) & 1ull) : 2u;
+  }
+  bool G = false, P = true;
+#pragma unroll
+  for (int i = 0; i < FCRT_E; i++) {
+    ul[i] = lo[i] + e[i];
+    gk[i] = fcol_gen<DEC>(ul[i], lo[i]);
+    const bool pr = fcol_prop<DEC>(ul[i]);
+    G = gk[i] || (pr && G);
+    P = P && pr;
+  }
+  *Gt = G;
+  *Pt = P;
+  uint32_t cout;
+  bool ap;
+  wave_carry(G, P, 0, &cout, &ap);
+  if ((tid & 63) == 0) tmp[tid >> 6] = cout | (ap ? 2u : 0u);
+  __syncthreads();
+}
+
 struct FWords {
   uint32_t w[2 * FCRT_E];
 };
@@ -916,9 +1080,10 @@ struct FWords {
 // into a block and the look-back are those of k_crt.  Bound by HBM: 24 B read
 // and 8 B written per digit.
 // DEC: radix-10^18 digits, plus the segments' addends (limbs relative to `add`).
-template <bool DEC>
+// PART: the digits and run carries of k_fcol_crt (runs of 2^logCR; the addends are in).
+template <bool DEC, bool PART>
 __global__ void __launch_bounds__(FCRT_THREADS)
-k_fcrt(SegView sv, FCrt kc, const double* __restrict__ res, uint64_t stride, const uint32_t* __restrict__ add,
+k_fcrt(SegView sv, FCrt kc, uint32_t logCR, const double* __restrict__ res, uint64_t stride, const uint32_t* __restrict__ add,
        uint32_t* __restrict__ out, uint32_t nblk, uint32_t* __restrict__ flags, uint32_t epoch, uint32_t polls, CopyList tails,
        const uint32_t* __restrict__ tin, uint32_t* __restrict__ tout, uint32_t* __restrict__ err) {
   __shared__ uint32_t tmp[FCRT_THREADS / 64], tmp2[FCRT_THREADS / 64];
@@ -945,7 +1110,9 @@ k_fcrt(SegView sv, FCrt kc, const double* __restrict__ res, uint64_t stride, con
   }
   uint64_t ul[FCRT_E];
   bool gk[FCRT_E], G, P;
-  fcrt_local<DEC>(len, r0, r1, r2, ad, sg.add_len, kc, kb, xv, tmp, ul, gk, &G, &P, &s_spec);
+  const uint64_t *dg = (const uint64_t*)r0, *ev = (const uint64_t*)r1;
+  if constexpr (PART) fpart_local<DEC>(len, dg, ev, logCR, kb, tmp, ul, gk, &G, &P, &s_spec);
+  else fcrt_local<DEC>(len, r0, r1, r2, ad, sg.add_len, kc, kb, xv, tmp, ul, gk, &G, &P, &s_spec);
   const uint32_t own = fcrt_pair(tmp);
   if (tid == 0)
     __hip_atomic_store(flags + b, (epoch << 3) | (own << 1) | 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -976,8 +1143,9 @@ k_fcrt(SegView sv, FCrt kc, const double* __restrict__ res, uint64_t stride, con
       // not published yet: recompute block k's pair from its residues
       uint64_t ul2[FCRT_E];
       bool gk2[FCRT_E], G2, P2;
-      fcrt_local<DEC>(len, r0, r1, r2, ad, sg.add_len, kc, (uint64_t)(k - first) * FCRT_BLOCK, xv, tmp2, ul2, gk2, &G2,
-                      &P2, &s_spec2);
+      const uint64_t kb2 = (uint64_t)(k - first) * FCRT_BLOCK;
+      if constexpr (PART) fpart_local<DEC>(len, dg, ev, logCR, kb2, tmp2, ul2, gk2, &G2, &P2, &s_spec2);
+      else fcrt_local<DEC>(len, r0, r1, r2, ad, sg.add_len, kc, kb2, xv, tmp2, ul2, gk2, &G2, &P2, &s_spec2);
       pair = fcrt_pair(tmp2);
     }
     if (pair & 1u) { cin = 1; done = true; }           // block k generates a carry
@@ -985,6 +1153,11 @@ k_fcrt(SegView sv, FCrt kc, const double* __restrict__ res, uint64_t stride, con
     else if (k == first) done = true;                   // all-propagate back to the start
   }
   if (tid == 0 && b + 1 == end && ((own & 1u) | ((own >> 1) & cin))) atomicOr(err, CAT_DEVERR_CARRY_OUT);
+  if constexpr (PART) {   // what the last run left above the segment
+    const uint64_t q = len >> logCR;
+    if (tid == 0 && b + 1 == end && (len & ((1ull << logCR) - 1)) == 0 && q && (ev[2 * q] | ev[2 * q + 1]))
+      atomicOr(err, CAT_DEVERR_CARRY_OUT);
+  }
   uint32_t wc = cin;
   for (uint32_t w = 0; w < (tid >> 6); w++) {
     const uint32_t x = tmp[w];
@@ -1531,15 +1704,46 @@ hipError_t fntt_row(const FBatch& b, int logM, int logS, int logL, hipStream_t s
   return hipGetLastError();
 }
 
-hipError_t fntt_crt(const SegView& sv, int logD, const double* res, uint64_t stride, const uint32_t* add, uint32_t* out,
-                    uint32_t nblk, uint32_t* flags, uint32_t epoch, uint32_t polls, const CopyList& tails,
-                    const uint32_t* tin, uint32_t* tout, uint32_t* err, hipStream_t st) {
-  const dim3 grid(nblk + tail_blocks(tails)), block(FCRT_THREADS);
+template <int LOGL, int PS>
+static void col_crt_launch(const FBatch& b, int logS, const SegView& sv, const uint32_t* add, hipStream_t st) {
+  constexpr int LOGT = 12;
+  const FGeom fg{b.logD, logS, LOGT - LOGL};
+  const dim3 grid((uint32_t)(b.cnt << (b.logD - LOGT))), block((1u << LOGT) / 16);
   if (add)
-    hipLaunchKernelGGL((k_fcrt<true>), grid, block, 0, st, sv, g_crt[logD], res, stride, add, out, nblk, flags, epoch,
-                       polls, tails, tin, tout, err);
+    hipLaunchKernelGGL((k_fcol_crt<LOGL, PS, true>), grid, block, 0, st, b.dv, sv, fg, g_crt[b.logD], b.F, b.res,
+                       b.stride, add, g_ft[PS]);
   else
-    hipLaunchKernelGGL((k_fcrt<false>), grid, block, 0, st, sv, g_crt[logD], res, stride, add, out, nblk, flags, epoch,
-                       polls, tails, tin, tout, err);
+    hipLaunchKernelGGL((k_fcol_crt<LOGL, PS, false>), grid, block, 0, st, b.dv, sv, fg, g_crt[b.logD], b.F, b.res,
+                       b.stride, add, g_ft[PS]);
+}
+hipError_t fntt_col_crt(const FBatch& b, int logL, const SegView& sv, const uint32_t* add, hipStream_t st) {
+#define L(X)                                                                     \
+  case X:                                                                        \
+    if (fntt_set(b.logD) == 0) col_crt_launch<X, 0>(b, b.logD, sv, add, st);     \
+    else col_crt_launch<X, 1>(b, b.logD, sv, add, st);                           \
+    break
+  switch (logL) {
+    L(4); L(5); L(6); L(7);
+    default: return hipErrorInvalidValue;
+  }
+#undef L
+  return hipGetLastError();
+}
+
+hipError_t fntt_crt(const SegView& sv, int logD, int logCR, const double* res, uint64_t stride, const uint32_t* add,
+                    uint32_t* out, uint32_t nblk, uint32_t* flags, uint32_t epoch, uint32_t polls,
+                    const CopyList& tails, const uint32_t* tin, uint32_t* tout, uint32_t* err, hipStream_t st) {
+  const dim3 grid(nblk + tail_blocks(tails)), block(FCRT_THREADS);
+#define L(D, P)                                                                                                       \
+  hipLaunchKernelGGL((k_fcrt<D, P>), grid, block, 0, st, sv, g_crt[logD], (uint32_t)logCR, res, stride, add, out,     \
+                     nblk, flags, epoch, polls, tails, tin, tout, err)
+  if (add) {
+    if (logCR) L(true, true);
+    else L(true, false);
+  } else {
+    if (logCR) L(false, true);
+    else L(false, false);
+  }
+#undef L
   return hipGetLastError();
 }

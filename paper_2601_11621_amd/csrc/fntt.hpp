@@ -59,6 +59,12 @@ hipError_t fntt_col_inv(const FBatch& b, int logS, int logL, bool first, int pre
 hipError_t fntt_row(const FBatch& b, int logM, int logS, int logL, hipStream_t st);
 // residues -> limbs with carries (blocks [0, nblk) of sv; res_pos in digits);
 // with `add`, in radix 10^18 with the addends of the segments (relative to it)
-hipError_t fntt_crt(const SegView& sv, int logD, const double* res, uint64_t stride, const uint32_t* add, uint32_t* out,
-                    uint32_t nblk, uint32_t* flags, uint32_t epoch, uint32_t polls, const CopyList& tails,
-                    const uint32_t* tin, uint32_t* tout, uint32_t* err, hipStream_t st);
+// (logCR > 0: the digits and run carries of fntt_col_crt instead of residues)
+hipError_t fntt_crt(const SegView& sv, int logD, int logCR, const double* res, uint64_t stride, const uint32_t* add,
+                    uint32_t* out, uint32_t nblk, uint32_t* flags, uint32_t epoch, uint32_t polls,
+                    const CopyList& tails, const uint32_t* tin, uint32_t* tout, uint32_t* err, hipStream_t st);
+// The outermost inverse pass (2^logL) with the recombination: digits, and what
+// carries out of each run of 2^fntt_run_log(logL) of them.  `add`: decimal joins.
+hipError_t fntt_col_crt(const FBatch& b, int logL, const SegView& sv, const uint32_t* add, hipStream_t st);
+#define FNTT_RUN_MAX_LOGL 7
+inline int fntt_run_log(int logL) { return std::min(12 - logL, 6); }

@@ -1381,7 +1381,7 @@ struct Exec {
 
 cat_status launch_crt(Exec& X, uint32_t* out, SegView sv, uint32_t nblk, const CopyList* tails = nullptr,
                       const uint32_t* tin = nullptr, uint32_t* tout = nullptr, bool raw = false, int as = 0,
-                      int fp_logD = -1) {
+                      int fp_logD = -1, int run_log = 0) {
   static const CopyList none{};
   const CopyList& cl = tails ? *tails : none;
   const uint32_t grid = nblk + tail_blocks(cl);
@@ -1389,7 +1389,7 @@ cat_status launch_crt(Exec& X, uint32_t* out, SegView sv, uint32_t nblk, const C
   if (fp_logD >= 0) {
     KTime kt("k_fcrt", X.st, (double)nblk * FCRT_BLOCK);
     X.crt_epoch++;
-    HIPCHK(fntt_crt(sv, fp_logD, (const double*)X.res, X.res_stride / 2, nullptr, out, nblk, X.flags,
+    HIPCHK(fntt_crt(sv, fp_logD, run_log, (const double*)X.res, X.res_stride / 2, nullptr, out, nblk, X.flags,
                     X.crt_epoch, crt_polls(nblk), cl, tin, tout, X.err, X.st));
     X.launches++;
     return CAT_OK;
@@ -1439,12 +1439,47 @@ bool fp_fused(const Stage& s) {
     if ((uint64_t)d.la + d.lb > (1ull << s.logN)) return false;
   return true;
 }
+// Four-step schedule.  Rows of 2^12 digits (2^11 under the shortest column DFT)
+// and as few column passes as fit, at every size: with rows of 2^11 / 2^13 C(10^8)
+// takes 2.51 / 2.78 ms instead of 2.41, 5 10^6 x 3 10^6 limbs 0.357 / 0.363
+// instead of 0.300; 2^13 at any one size lost up to 3 %, 2^11 won nothing beyond
+// noise.
+struct FpPasses {
+  int P = 0, logM = 0, logL[4] = {}, logS[4] = {};
+};
+FpPasses fp_passes(int logD) {
+  FpPasses f;
+  f.logM = std::min(FNTT_ROW_MAX, logD - FNTT_COL_MIN);
+  const int rest = logD - f.logM;
+  f.P = (rest + FNTT_COL_MAX - 1) / FNTT_COL_MAX;
+  for (int k = 0, ls = logD; k < f.P; k++) {
+    f.logL[k] = rest / f.P + (k < rest % f.P ? 1 : 0);
+    f.logS[k] = ls;
+    ls -= f.logL[k];
+  }
+  return f;
+}
+// Does the outermost inverse pass of cnt products recombine too (runs of 2^result
+// digits; 0: no)?  From 2^22 digits a batch, where the residues no longer stay in
+// the memory-side cache (C(10^8), below it: 2.39 -> 2.51 ms, C(3 10^8): 9.37 ->
+// 9.25), with columns of at most 2^7: longer ones leave runs of 8 or 16 digits, a
+// tile of three primes then has too few waves to hide its barriers (one level of
+// C(2,050,572,903), pass and carries: 2^4 1.02 -> 0.75 ms, 2^7 1.16 -> 1.00, 2^8
+// 1.22 -> 1.20, 2^9 1.17 -> 1.49).
+#define FP_RUN_MIN_LOG 22
+int fp_run_log(const Stage& s, uint64_t cnt) {
+  const int logD = s.logN - 1;
+  if (!s.fp || logD <= FNTT_LDS_MAX_LOGD || (cnt << logD) < (1ull << FP_RUN_MIN_LOG)) return 0;
+  const int logL = fp_passes(logD).logL[0];
+  return logL <= FNTT_RUN_MAX_LOGL ? fntt_run_log(logL) : 0;
+}
+
 // The FP64 transform of products m0 .. m0 + cnt of `dv` (transforms of
 // 2^(logN - 1) digits), up to the residues.
 // One workgroup up to 2^FNTT_LDS_MAX_LOGD digits, whatever class the bucket has
 // (2^14 digits in 128 KB of LDS against the four-step path: the 4,096-product
 // batch 2.26 -> 2.17 ms, C(3 10^7) 1.29 -> 1.26 ms).
-cat_status launch_fp(Exec& X, const Stage& s, const DescView& dv, uint64_t cnt) {
+cat_status launch_fp(Exec& X, const Stage& s, const DescView& dv, uint64_t cnt, const uint32_t* add = nullptr) {
   const FBatch b = fp_batch(X, s, dv, cnt);
   if (b.logD <= FNTT_LDS_MAX_LOGD) {
     KTime kt("k_flds", X.st, bfly(9.0 * cnt, b.logD));
@@ -1452,29 +1487,22 @@ cat_status launch_fp(Exec& X, const Stage& s, const DescView& dv, uint64_t cnt) 
     X.launches++;
     return CAT_OK;
   }
-  // Rows of 2^12 digits (2^11 under the shortest column DFT) and as few column
-  // passes as fit, at every size: with rows of 2^11 / 2^13 C(10^8) takes 2.51 /
-  // 2.78 ms instead of 2.41, 5 10^6 x 3 10^6 limbs 0.357 / 0.363 instead of
-  // 0.300; 2^13 at any one size lost up to 3 %, 2^11 won nothing beyond noise.
-  const int logM = std::min(FNTT_ROW_MAX, b.logD - FNTT_COL_MIN);
-  const int rest = b.logD - logM;
-  const int P = (rest + FNTT_COL_MAX - 1) / FNTT_COL_MAX;
-  int logL[4] = {}, logS[4] = {};
-  for (int k = 0, ls = b.logD; k < P; k++) {
-    logL[k] = rest / P + (k < rest % P ? 1 : 0);
-    logS[k] = ls;
-    ls -= logL[k];
-  }
+  const auto [P, logM, logL, logS] = fp_passes(b.logD);
   const double N = (double)(1ull << b.logD);
   for (int k = 0; k < P; k++) {
     KTime kt("k_fcol_fwd", X.st, 6.0 * b.cnt * N / 2 * logL[k]);
     HIPCHK(fntt_col_fwd(b, logS[k], logL[k], k == 0, k ? logS[k - 1] : 0, k ? logL[k - 1] : 0, X.st));
   }
   {
-    KTime kt("k_frow", X.st, bfly(9.0 * b.cnt * (1ull << rest), logM));
+    KTime kt("k_frow", X.st, bfly(9.0 * b.cnt * (1ull << (b.logD - logM)), logM));
     HIPCHK(fntt_row(b, logM, logS[P - 1], logL[P - 1], X.st));
   }
   for (int k = P - 1; k >= 0; k--) {
+    if (k == 0 && fp_run_log(s, cnt)) {
+      KTime kt("k_fcol_crt", X.st, 3.0 * b.cnt * N / 2 * logL[k]);
+      HIPCHK(fntt_col_crt(b, logL[k], s.sv, add, X.st));
+      break;
+    }
     KTime kt("k_fcol_inv", X.st, 3.0 * b.cnt * N / 2 * logL[k]);
     HIPCHK(fntt_col_inv(b, logS[k], logL[k], k == 0, k ? logS[k - 1] : 0, k ? logL[k - 1] : 0, X.st));
   }
@@ -1715,7 +1743,7 @@ cat_status run_stage_batched(Exec& X, const Stage& s) {
     STCHK(launch_products(X, s, s.dv, s.nmul, s.cls == CLS_SCHOOL));
     if (s.cls != CLS_SCHOOL)
       STCHK(launch_crt(X, out_base(X, s), stage_segs(s), s.nblk, &s.tails, X.W + s.tail_in_base,
-                       X.W + s.tail_out_base, s.cls == CLS_COLSUM, stage_as(s), s.fp ? s.logN - 1 : -1));
+                       X.W + s.tail_out_base, s.cls == CLS_COLSUM, stage_as(s), s.fp ? s.logN - 1 : -1, fp_run_log(s, s.nmul)));
     return CAT_OK;
   }
   return copy_tails(X, s);
@@ -1754,7 +1782,7 @@ cat_status run_stage_plain(Exec& X, const Stage& s) {
       sv.ipref[0] = 0;
       sv.ipref[1] = nb;
       STCHK(launch_crt(X, out_base(X, s), sv, nb, nullptr, nullptr, nullptr, s.cls == CLS_COLSUM, stage_as(s),
-                       s.fp ? s.logN - 1 : -1));
+                       s.fp ? s.logN - 1 : -1, fp_run_log(s, 1)));
     }
   }
   return copy_tails(X, s);
