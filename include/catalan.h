@@ -172,9 +172,7 @@ cat_status bigint_decimal_digits(const uint32_t* d_x, size_t n_limbs, uint64_t* 
  * bigint_to_decimal: d_work of at least that many bytes (device, caller-owned,
  * contents undefined afterwards; CAT_ENOMEM if smaller); d_x, d_out and d_work
  * must not overlap; synchronises `stream`; CAT_EINTERNAL if a device check
- * failed.  The first call for a given (n_limbs, d_x, d_out, cap, d_work)
- * captures the conversion as a HIP graph that later calls with the same
- * arguments replay (the library keeps up to 32 such graphs). */
+ * failed. */
 cat_status decimal_sizes(size_t n_limbs, size_t* max_chars, size_t* workspace_bytes);
 cat_status bigint_to_decimal(const uint32_t* d_x, size_t n_limbs, char* d_out, size_t cap, size_t* n_chars,
                              void* d_work, size_t work_bytes, void* stream);
@@ -335,7 +333,9 @@ cat_status cat_get_stats(cat_stats* out);
  * 2^max(k, log_row[k]) slots per operand (log_row 12..14: 2^(log_row - k)
  * products and 2^log_row / 16 threads per workgroup), 2 = four-step
  * transform with rows of 2^log_row[k] words (8..14, < k) and column passes of
- * at most 2^log_pass[k] points (4..10).  Every schedule gives the same bits.
+ * at most 2^log_pass[k] points (4..10).  log_row and log_pass bind the integer
+ * transforms; the FP64 ones (the default) have a fixed schedule and take from
+ * cls only that the bucket is a transform.  Every schedule gives the same bits.
  * cat_tune_set(NULL) restores the defaults; CAT_EINVAL for an invalid table.
  * Setting a table drops the cached C(n) plans. */
 typedef struct {
@@ -400,14 +400,16 @@ cat_status cat_lazy_primes_set(uint32_t max_logn);
 cat_status cat_lookback_polls_set(uint32_t polls);
 
 /* Kernel timer (measurement only).  cat_timer_set(name) brackets every later
- * launch of the named kernel ("k_ntt_lds", "k_row", "k_pass_fwd", "k_pass_inv",
- * "k_tree_fused", "k_crt", "k_school", "k_leaf", "k_residues") with HIP
- * events on the stream it is launched on, outside graph capture; NULL or ""
- * stops it.  Each call resets the
+ * launch of the named kernel ("k_frow", "k_fcol_fwd", "k_fcol_inv",
+ * "k_fcol_crt", "k_flds", "k_ffused", "k_ffused_mix", "k_fcrt", of decimal text
+ * "k_ffused10", "k_fcrt10", "k_dec_leaf" and "k_dec_ascii", of the integer
+ * transforms "k_ntt_lds", "k_row", "k_pass_fwd", "k_pass_inv", "k_tree_fused",
+ * "k_crt", and "k_base", "k_school", "k_residues") with HIP events on the stream it
+ * is launched on, outside graph capture; NULL or "" stops it.  Each call resets the
  * counters.  cat_timer_get waits for the recorded events and returns the summed
  * kernel time, the launch count and the algorithmic work of those launches
  * (radix-2 butterflies for NTT kernels, limbs for k_crt, k_school and
- * k_residues, nodes for k_leaf).  Calls of catalan_exact_noalloc are not
+ * k_residues, digits for k_fcrt, nodes for k_base).  Calls of catalan_exact_noalloc are not
  * timed. */
 cat_status cat_timer_set(const char* kernel);
 cat_status cat_timer_get(double* ms, uint64_t* launches, double* work);

@@ -1,9 +1,10 @@
 // Shared definitions of the gfx950 Catalan library: modular arithmetic for the
-// three NTT primes, descriptor structs, launch constants.
+// three 32-bit NTT primes, descriptor structs, launch constants.
 //
 // Every multiplication of the reconstruction phase (Sec. 3.2, Alg. 2 of
 // arXiv 2601.11621) is an exact product of little-endian uint32 limb vectors.
-// Large products go through a cyclic convolution modulo three primes
+// Large products go through the FP64 transforms (fntt.hip), or on request (see
+// cat_lazy_primes_set) through a cyclic convolution modulo three primes
 //   p0 = 3*2^30+1, p1 = 13*2^28+1, p2 = 29*2^27+1   (all in (2^31, 2^32),
 // 2-adicity >= 27, product ~2^95.1), one 32-bit limb per coefficient, and are
 // recombined with Garner's CRT.  Exactness: a coefficient of a la x lb limb

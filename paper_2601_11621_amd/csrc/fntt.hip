@@ -42,7 +42,7 @@
 // Transform structure: passes of radix 16 or 8 (the first of radix 2^(log2 S
 // mod 4), or mod 3) on registers, one thread holding as many values, with LDS
 // between the passes.  A transform of up to 2^14 points runs in one workgroup
-// (k_flds); longer ones are cut in rows of 2^10 .. 2^13 points and column DFTs
+// (k_flds); longer ones are cut in rows of 2^11 or 2^12 points and column DFTs
 // of 2^4 .. 2^10 points (Bailey 1990).  Both operands of a product pass through
 // the same LDS buffer, the first one's outputs waiting in registers, so a
 // transform of T points needs 8 T bytes of LDS.

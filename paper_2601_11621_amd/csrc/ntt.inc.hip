@@ -1,5 +1,6 @@
 // Exact big-integer products for the reconstruction phase (Sec. 3.2, Alg. 2):
 // cyclic convolution modulo three 32-bit primes by number-theoretic transforms.
+// (The integer form, taken on request; the default is the FP64 form in fntt.hip.)
 //
 // Transform structure (all integer, in LDS):
 //  * A length-S transform is split as S = R * (S/R) (R = 2^r <= 16): each

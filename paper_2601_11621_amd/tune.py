@@ -12,6 +12,10 @@ in a tree level) and keeps the fastest:
   * k > 14:  four-step transform, rows of 2^10 .. 2^14, column passes of at
              most 2^6 / 2^8 / 2^10 points.
 
+Rows and column passes bind the integer transforms only (cat_lazy_primes_set
+below 23); with the FP64 transforms, the default, those candidates run the same
+kernels and differ by noise.
+
 Every candidate's output is compared bit for bit with the default schedule's;
 a candidate that differs is an error (schedules change speed, never bits).
 

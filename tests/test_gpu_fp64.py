@@ -68,9 +68,8 @@ def test_products_around_a_power_of_two(cat, k):
 @pytest.mark.parametrize("log_row", [10, 11, 12, 13])
 @pytest.mark.parametrize("log_pass", [4, 9, 10])
 def test_rows_and_column_passes(cat, log_row, log_pass):
-    """Every row length, and column parts in one pass of up to 2^10 points or
-    in two (the second applying the first's twiddles), at transforms of 2^15
-    to 2^20 digits."""
+    """Transforms of 2^15 to 2^20 digits under every row and column length that
+    the schedule table can ask for."""
     rng = np.random.default_rng(100 * log_row + log_pass)
     base = cat.get_tuning()
     t = {k: (list(v) if isinstance(v, list) else v) for k, v in base.items()}

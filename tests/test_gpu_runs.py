@@ -72,6 +72,16 @@ def test_batches(cat, k):
         assert np.array_equal(got, want), i
 
 
+# 2^23 digits (the first prime set) and 2^24 (the second): two column passes, the
+# second applying the first's twiddles
+@pytest.mark.parametrize("la,lb", [(2**23, 2**23 - 3), (2**23 + 5, 2**23 + 64)])
+def test_two_column_passes(cat, la, lb):
+    print("two passes", la, lb, flush=True)
+    a, b = (cat.from_numpy(np.full(n, 0xFFFFFFFF, dtype=np.uint32)) for n in (la, lb))
+    c, _ = cat.mul_batched(a, [0, la], b, [0, lb])
+    assert np.array_equal(cat.to_numpy(c)[:la + lb], _ones_product(la, lb))
+
+
 @pytest.mark.parametrize("L,kind", [(8_000_003, "random"), (9_100_000, "ones")])
 def test_decimal(cat, L, kind):
     x = np.full(L, 0xFFFFFFFF, dtype=np.uint32)
