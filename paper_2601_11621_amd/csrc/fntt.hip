@@ -1198,7 +1198,7 @@ k_fcrt(SegView sv, FCrt kc, uint32_t logCR, const double* __restrict__ res, uint
 // waves per SIMD on one CU while the others stood idle).
 // Every product has la + lb <= 2 N limbs, so nothing is carried out of its N
 // slots and one scan over the tile serves all its products.
-#define FF_MAX_LOGD 11
+#define FF_MAX_LOGD FNTT_FUSED_MAX_LOGD
 constexpr int ff_tile(int logD) { return logD < 9 ? 9 : logD; }
 constexpr int ff_threads(int logD) { return CAT_NPRIMES << (ff_tile(logD) - 3); }
 #define FF_E 4

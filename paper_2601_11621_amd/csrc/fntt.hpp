@@ -6,6 +6,7 @@
 #define FNTT_SMALL_MAX_LOGD 23 // longest transform of prime set 0 (primes just above 2^50)
 #define FNTT_LDS_MIN_LOGD 5    // one-workgroup transforms
 #define FNTT_LDS_MAX_LOGD 14
+#define FNTT_FUSED_MAX_LOGD 11 // with recombination and carries in the same workgroup
 #define FNTT_ROW_MAX 12        // four-step rows (2^11 and 2^12 digits)
 #define FNTT_COL_MIN 4         // column DFTs
 #define FNTT_COL_MAX 10

@@ -1433,8 +1433,14 @@ FBatch fp_batch(Exec& X, const Stage& s, const DescView& dv, uint64_t cnt) {
 }
 // transform and carries in one launch?  (A product of 2^logN + 1 limbs has a
 // carry into a digit past its slots: the general path.)
+// A tree level of at most 64 products of 2^11 digits takes a launch more: one CU
+// would hold the three primes of a product while three quarters of the chip
+// stand idle (n = 6 10^4 .. 1.5 10^6: 2 to 5 % faster, C(10^5) 0.123 -> 0.119 ms;
+// at all sizes eight mixed requests 0.624 -> 0.634).
+#define FF_FEW 64
 bool fp_fused(const Stage& s) {
   if (!s.fp || !fntt_fused_fits(s.logN - 1)) return false;
+  if (s.logN - 1 == FNTT_FUSED_MAX_LOGD && s.host_desc.empty() && s.nmul <= FF_FEW) return false;
   for (const MulDesc& d : s.host_desc)
     if ((uint64_t)d.la + d.lb > (1ull << s.logN)) return false;
   return true;
