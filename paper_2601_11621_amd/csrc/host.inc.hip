@@ -3461,10 +3461,8 @@ cat_status catalan_batch_continue(cat_ticket ticket, uint32_t* const* d_limbs, c
   hipLaunchKernelGGL(k_fill, dim3((uint32_t)std::min<uint64_t>((B.c.ctl_words + 255) / 256, 1024)), dim3(256), 0, st,
                      (uint32_t*)(cw + B.c.gtab), (uint64_t)B.c.ctl_words, 0u);
   LAUNCHCHK();
-  TopBatch<CAT_BATCH_MAX> tb{};
-  uint32_t nt = 0;
-  uint64_t tmax = 0;
   // chunks of whole requests with at most CAT_MAX_GROUPS groups each
+  bool published = false;
   uint32_t epoch = 0;
   uint32_t r0 = 0;
   while (r0 < k) {
@@ -3504,6 +3502,9 @@ cat_status catalan_batch_continue(cat_ticket ticket, uint32_t* const* d_limbs, c
         return rs;
       }
     }
+    TopBatch<CAT_BATCH_MAX> tb{};
+    uint32_t nt = 0;
+    uint64_t tmax = 0;
     for (uint32_t i = 0; i < (uint32_t)members.size(); i++) {
       const uint32_t r = members[i];
       if (!P || P->rone[i]) {
@@ -3522,18 +3523,21 @@ cat_status catalan_batch_continue(cat_ticket ticket, uint32_t* const* d_limbs, c
       }
     }
     if (P) free_plan(P);
+    if (nt) {
+      // the length and the copy of every result of this plan, before the next
+      // plan's post area takes their place; with the last one the control block's
+      // head to the host (lengths and error word; the pinned copies of the group
+      // tables are spent)
+      published = r1 == k;
+      hipLaunchKernelGGL(k_top_nonzero<CAT_BATCH_MAX>, dim3(top_scan_blocks(tmax), nt), dim3(256), 0, st, tb,
+                         (uint32_t*)(cw + B.c.gtab + CTL_DONE),
+                         published ? (const uint32_t*)(cw + B.c.gtab) : (const uint32_t*)nullptr, (uint32_t*)b->pin,
+                         (uint32_t)(CTL_READ / 4));
+      LAUNCHCHK();
+    }
     r0 = r1;
   }
-  if (nt) {
-    // every result's length and copy, and the control block's head to the host
-    // (lengths and error word; the pinned copies of the group tables are spent)
-    hipLaunchKernelGGL(k_top_nonzero<CAT_BATCH_MAX>, dim3(top_scan_blocks(tmax), nt), dim3(256), 0, st, tb,
-                       (uint32_t*)(cw + B.c.gtab + CTL_DONE), (const uint32_t*)(cw + B.c.gtab), (uint32_t*)b->pin,
-                       (uint32_t)(CTL_READ / 4));
-    LAUNCHCHK();
-  } else {
-    HIPCHK(hipMemcpyAsync(b->pin, cw + B.c.gtab, CTL_READ, hipMemcpyDeviceToHost, st));
-  }
+  if (!published) HIPCHK(hipMemcpyAsync(b->pin, cw + B.c.gtab, CTL_READ, hipMemcpyDeviceToHost, st));
   HIPCHK(hipEventRecord(t->ev, st));
   b->cap.assign(caps, caps + k);
   t->state = 2;
