@@ -1254,14 +1254,18 @@ int rins_level(const Layout& Ly, const Plan& P) {
   return j;
 }
 
-// cache key of the plan of n in one form
-uint64_t plan_key(uint64_t n, bool plain) { return n | (plain ? 1ull << 63 : 0ull); }
+// cache key of the plan of n in one form (of Phase 2: plain or batched; of the
+// table: powers or groups)
+uint64_t plan_key(uint64_t n, bool plain, bool powers) {
+  return n | (plain ? 1ull << 63 : 0ull) | (powers ? 1ull << 62 : 0ull);
+}
 // ebits: per group, the bit length that none of its entries exceeds (else the
 // layout's).
 cat_status make_plan(const Layout& Ly, const GroupTable& gt, Plan** out, bool plain, bool device_tables = true,
-                     const uint32_t* req = nullptr, uint32_t nreq = 1, const uint32_t* ebits = nullptr) {
+                     const uint32_t* req = nullptr, uint32_t nreq = 1, const uint32_t* ebits = nullptr,
+                     bool powers = false) {
   Plan* P = new Plan();
-  P->n = plan_key(Ly.n, plain);
+  P->n = plan_key(Ly.n, plain, powers);
   P->plain = plain;
   P->ng = gt.ngroups;
   P->nreq = req ? nreq : 1;
@@ -2017,8 +2021,8 @@ cat_status launch_top(hipStream_t st, const uint32_t* x, uint64_t n, unsigned lo
   return CAT_OK;
 }
 
-Plan* find_plan_in(std::map<uint64_t, Plan*>& plans, uint64_t n, bool plain, const GroupTable& gt) {
-  auto it = plans.find(plan_key(n, plain));
+Plan* find_plan_in(std::map<uint64_t, Plan*>& plans, uint64_t n, bool plain, bool powers, const GroupTable& gt) {
+  auto it = plans.find(plan_key(n, plain, powers));
   if (it == plans.end()) return nullptr;
   Plan* P = it->second;
   if (P->ng != gt.ngroups || P->outer_j != gt.outer) return nullptr;
@@ -2027,7 +2031,9 @@ Plan* find_plan_in(std::map<uint64_t, Plan*>& plans, uint64_t n, bool plain, con
   return P;
 }
 
-Plan* find_plan(uint64_t n, bool plain, const GroupTable& gt) { return find_plan_in(g.plans, n, plain, gt); }
+Plan* find_plan(uint64_t n, bool plain, bool powers, const GroupTable& gt) {
+  return find_plan_in(g.plans, n, plain, powers, gt);
+}
 
 // A repeated call of at most five launches (Phase 1, three stages, the length)
 // queues them itself: the launch of a graph takes longer to start (C(10^3) 57 us
@@ -2355,6 +2361,7 @@ struct Ticket {
   hipEvent_t ev = nullptr;
   char* pin = nullptr;
   bool one = false;           // C(n) = 1
+  bool powers = false;        // Phase 1 was queued in its powers form
   uint64_t cap = 0;
   BatchState* batch = nullptr;   // a batch of requests (catalan_batch_*)
 };
@@ -2708,14 +2715,14 @@ static cat_status exact_in_workspace(uint64_t n, const Layout& Ly, char* wb, uin
                               size_t* n_limbs, hipStream_t st, bool plain, bool noalloc, uint64_t launches) {
   cat_stats stats{};
   unsigned long long* top = (unsigned long long*)(wb + Ly.top);
-  STCHK(run_phase1(Ly, wb, (uint32_t*)wb + Ly.primes, Ly.Kmax, st, &launches, powers_form(plain),
-                   g.pin));
+  const bool powers = powers_form(plain);
+  STCHK(run_phase1(Ly, wb, (uint32_t*)wb + Ly.primes, Ly.Kmax, st, &launches, powers, g.pin));
   GroupTable gt;
   STCHK(read_groups(g.pin, st, &gt));
   if (gt.err & CAT_DEVERR_BOUNDS) return CAT_EINTERNAL;
-  Plan* P = noalloc ? find_plan_in(g.noalloc_plans, n, plain, gt) : find_plan(n, plain, gt);
+  Plan* P = find_plan_in(noalloc ? g.noalloc_plans : g.plans, n, plain, powers, gt);
   if (!P) {
-    STCHK(make_plan(Ly, gt, &P, plain, !noalloc));
+    STCHK(make_plan(Ly, gt, &P, plain, !noalloc, nullptr, 1, nullptr, powers));
     if (noalloc) remember_noalloc_plan(P);
     else remember_plan(P);
   }
@@ -2957,17 +2964,18 @@ cat_status catalan_exact_ex(uint64_t n, uint32_t* d_limbs, size_t cap, size_t* n
   cat_stats stats{};
   uint64_t launches = 0;
   unsigned long long* top = (unsigned long long*)(wb + Ly.top);
-  // Fast path: the plan of n is known (it depends only on n).  One graph runs
-  // Phase 1, Phase 2, the normalisation and the copy out; the group table the
-  // device computed is checked against the plan afterwards.
-  auto pit = g.plans.find(n);
+  // Fast path: the plan of n is known (it depends only on n and the form).  One
+  // graph runs Phase 1, Phase 2, the normalisation and the copy out; the group
+  // table the device computed is checked against the plan afterwards.
+  const bool powers = powers_form(false);
+  auto pit = g.plans.find(plan_key(n, false, powers));
   if (use_graph && pit != g.plans.end() && !pit->second->result_is_one) {
     Plan* P = pit->second;
     const std::vector<uintptr_t> key{(uintptr_t)wb, (uintptr_t)d_limbs, (uintptr_t)cap};
     bool replayed = false;
     uint64_t nl = 0;
     auto record = [&](hipStream_t cs, hipStream_t side) -> cat_status {
-      STCHK(run_phase1(Ly, wb, (uint32_t*)wb + Ly.primes, Ly.Kmax, cs, &nl, powers_form(false), nullptr));
+      STCHK(run_phase1(Ly, wb, (uint32_t*)wb + Ly.primes, Ly.Kmax, cs, &nl, powers, nullptr));
       Exec E = make_exec(Ly, wb, cs);
       E.side = side;
       STCHK(run_phase2(E, *P));
@@ -3001,7 +3009,7 @@ cat_status catalan_exact_ex(uint64_t n, uint32_t* d_limbs, size_t cap, size_t* n
     uint32_t derr = 0;
     memcpy(&L, pin + CTL_TOP, 8);
     memcpy(&derr, pin + CTL_ERR, 4);
-    if (gt.err || find_plan(n, false, gt) != P) return CAT_EINTERNAL;
+    if (gt.err || find_plan(n, false, powers, gt) != P) return CAT_EINTERNAL;
     if (derr || L == 0) return CAT_EINTERNAL;
     *n_limbs = (size_t)L;
     stats.products = P->products;
@@ -3220,7 +3228,8 @@ cat_status catalan_begin(uint64_t n, void* d_work, size_t work_bytes, void* stre
   t->wb = (char*)d_work;
   t->st = (hipStream_t)stream;
   uint64_t launches = 0;
-  cat_status s = run_phase1(t->Ly, t->wb, (uint32_t*)t->wb + t->Ly.primes, t->Ly.Kmax, t->st, &launches, powers_form(false),
+  t->powers = powers_form(false);
+  cat_status s = run_phase1(t->Ly, t->wb, (uint32_t*)t->wb + t->Ly.primes, t->Ly.Kmax, t->st, &launches, t->powers,
                             t->pin);
   if (s == CAT_OK) {
     const hipError_t e = hipEventRecord(t->ev, t->st);
@@ -3258,9 +3267,9 @@ cat_status catalan_continue(cat_ticket ticket, uint32_t* d_limbs, size_t cap) {
   GroupTable gt;
   memcpy(&gt, t->pin, sizeof(GroupTable));
   if (gt.err || gt.ngroups > CAT_MAX_GROUPS) return CAT_EINTERNAL;
-  Plan* P = find_plan(t->n, false, gt);
+  Plan* P = find_plan(t->n, false, t->powers, gt);
   if (!P) {
-    STCHK(make_plan(t->Ly, gt, &P, false));
+    STCHK(make_plan(t->Ly, gt, &P, false, true, nullptr, 1, nullptr, t->powers));
     remember_plan(P);
   }
   t->cap = cap;
