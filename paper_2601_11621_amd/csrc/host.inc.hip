@@ -3660,6 +3660,16 @@ cat_status factorial_ratio_factor(const uint64_t* a, uint32_t k, const uint64_t*
   return CAT_OK;
 }
 
+// Waits for `st` where a call ends early (the table of a ratio is read before the
+// kernel that follows it has run).
+struct Drain {
+  hipStream_t st;
+  bool on = true;
+  ~Drain() {
+    if (on) (void)hipStreamSynchronize(st);
+  }
+};
+
 cat_status factorial_ratio_exact(const uint64_t* a, uint32_t k, const uint64_t* b, uint32_t m, uint32_t* d_limbs,
                                  size_t cap, size_t* n_limbs, void* d_work, size_t work_bytes, void* stream,
                                  uint32_t flags) {
@@ -3682,6 +3692,7 @@ cat_status factorial_ratio_exact(const uint64_t* a, uint32_t k, const uint64_t* 
   uint64_t launches = 0;
   uint32_t* primes = (uint32_t*)wb + Ly.primes;
   const uint32_t ebits = powers_form(plain) ? Ly.ebits : 0;
+  Drain drain{st};
   STCHK(run_phase1_ratio(Ly, r, wb, primes, Ly.Kmax, ebits, st, &launches));
   GroupTable gt{};
   bool pw = ebits != 0;
@@ -3693,9 +3704,8 @@ cat_status factorial_ratio_exact(const uint64_t* a, uint32_t k, const uint64_t* 
   if (!pw) {
     STCHK(run_bits_ratio(Ly, wb, primes, Ly.Kmax, st, &launches));
     STCHK(read_groups_ratio(Ly, wb, st, &gt));
-  } else if (const cat_status e = check_groups_ratio(&gt); e != CAT_OK) {
-    HIPCHK(hipStreamSynchronize(st));
-    return e;
+  } else {
+    STCHK(check_groups_ratio(&gt));
   }
   const uint64_t entries = pw ? gt.n_pow : table_primes(gt);
   Plan* P = nullptr;
@@ -3725,6 +3735,7 @@ cat_status factorial_ratio_exact(const uint64_t* a, uint32_t k, const uint64_t* 
     res = launch_top(st, X.W + P->result_pos, P->result_cap, top, d_limbs, std::min<uint64_t>(P->result_cap, cap),
                      (uint32_t*)(wb + Ly.gtab + CTL_DONE), top, g.pin, 3);
     const hipError_t e = hipStreamSynchronize(st);
+    drain.on = false;
     if (e != hipSuccess) {
       g.last_err = (int)e;
       res = CAT_EDEVICE;
