@@ -476,6 +476,8 @@ bool use_fp(int cls) { return g_fp && (cls == CLS_LDS || cls == CLS_LARGE); }
 // room that a product (or segment) of `limbs` limbs takes in the residue
 // arrays: limbs, or 64-bit digits on the FP64 path
 uint64_t res_units(bool fp, uint64_t limbs) { return fp ? (limbs + 1) / 2 : limbs; }
+// limbs between the residue arrays of two primes (whole 64-bit digits)
+uint64_t res_stride(uint64_t limbs) { return limbs & ~1ull; }
 uint64_t res_words(bool fp, uint64_t units) { return fp ? 2 * units : units; }
 uint32_t crt_blocks(bool fp, uint64_t limbs) {
   return fp ? (uint32_t)((res_units(true, limbs) + FCRT_BLOCK - 1) / FCRT_BLOCK)
@@ -550,10 +552,10 @@ Layout layout_finish(Layout L) {
   L.nseg = L.i_end > L.i0 ? (L.i_end - L.i0 + seg - 1) / seg : 0;
   // residues of one stage: by default bounded by everything the tree and the
   // post area can hold; callers with long power chains set a tighter bound
+  // (64 limbs beyond the sum of a stage's products: as 64-bit digits each of at
+  // most CAT_MAX_GROUPS segments takes up to one limb more)
   if (L.res_len == 0) L.res_len = std::max(L.Kmax, L.post_cap) + 64;
-  // 64-bit digits: every group's residues may start and end one limb further
-  L.res_len = align_up(L.res_len + 3 * CAT_MAX_GROUPS, 2);
-  L.res2_len = align_up(L.res2_len, 2);
+  static_assert(CAT_MAX_GROUPS + 1 <= 64 && CAT_INLINE_DESC <= CAT_MAX_GROUPS, "room for the digits of every segment");
   const uint64_t big = 1ull << ceil_log2(L.res_len);
   L.F_words = (big > (1ull << CAT_LDS_LOGT)) ? 12 * big + (1ull << 20) : (1ull << 20);
   L.nblk_max = L.res_len / CAT_CRT_BLOCK + 4096;
@@ -1332,7 +1334,7 @@ cat_status make_plan(const Layout& Ly, const GroupTable& gt, Plan** out, bool pl
     for (const CrtSeg& sg : s->host_segs)
       rmax = std::max(rmax, res_words(s->fp, sg.res_pos + res_units(s->fp, sg.len)));
     const uint64_t fneed = (s->cls == CLS_LARGE) ? s->nmul * 6ull << s->logN : 0;
-    if (rmax > Ly.res_len || fneed > Ly.F_words || s->nblk > Ly.nblk_max) {
+    if (rmax > res_stride(Ly.res_len) || fneed > Ly.F_words || s->nblk > Ly.nblk_max) {
       free_plan(P);
       return CAT_EINTERNAL;
     }
@@ -1344,7 +1346,7 @@ cat_status make_plan(const Layout& Ly, const GroupTable& gt, Plan** out, bool pl
     uint64_t rmax = 0;
     for (const CrtSeg& sg : s.host_segs) rmax = std::max(rmax, res_words(s.fp, sg.res_pos + res_units(s.fp, sg.len)));
     const uint64_t fneed = (s.cls == CLS_LARGE) ? s.nmul * 6ull << s.logN : 0;
-    if (rmax > Ly.res2_len || fneed > Ly.F2_words || s.nblk > Ly.nblk2_max) P->fork_count = -1;
+    if (rmax > res_stride(Ly.res2_len) || fneed > Ly.F2_words || s.nblk > Ly.nblk2_max) P->fork_count = -1;
   }
   if (P->post_end > Ly.post + Ly.post_cap) {
     free_plan(P);
@@ -2090,12 +2092,12 @@ Exec make_exec(const Layout& Ly, char* wb, hipStream_t st) {
   Exec X;
   X.W = (uint32_t*)wb;
   X.res = X.W + Ly.res;
-  X.res_stride = Ly.res_len;
+  X.res_stride = res_stride(Ly.res_len);
   X.F = X.W + Ly.F;
   X.err = (uint32_t*)(wb + Ly.err);
   X.flags = (uint32_t*)(wb + Ly.gtab + CTL_FLAGS);
   X.res2 = X.W + Ly.res2;
-  X.res2_stride = Ly.res2_len;
+  X.res2_stride = res_stride(Ly.res2_len);
   X.F2 = X.W + Ly.F2;
   X.flags2 = X.flags + Ly.nblk_max;
   X.st = st;
