@@ -2011,12 +2011,13 @@ cat_status read_groups(const void* pin, hipStream_t st, GroupTable* out) {
 
 // Length of the result at x[0 .. n) to *top, its first ncopy limbs to dst, and
 // the pub_words words at pub (the length among them; `done` is a zeroed counter)
-// to pinned memory.
+// to pinned memory; with `tail`, the limbs from ncopy to the length (at most
+// `tail`) too.
 cat_status launch_top(hipStream_t st, const uint32_t* x, uint64_t n, unsigned long long* top, uint32_t* dst,
                       uint64_t ncopy, uint32_t* done = nullptr, const void* pub = nullptr, void* pub_dst = nullptr,
-                      uint32_t pub_words = 0) {
+                      uint32_t pub_words = 0, uint64_t tail = 0) {
   TopBatch<1> tb;
-  tb.r[0] = TopReq{x, n, top, dst, ncopy};
+  tb.r[0] = TopReq{x, n, top, dst, ncopy, tail};
   hipLaunchKernelGGL(k_top_nonzero<1>, dim3(top_scan_blocks(n)), dim3(256), 0, st, tb, done, (const uint32_t*)pub,
                      (uint32_t*)pub_dst, pub_words);
   LAUNCHCHK();
@@ -2044,6 +2045,12 @@ bool few_launches(const Plan& P) { return P.tree.size() + P.post.size() <= 3; }
 // C(n) in batched form takes the powers form of Phase 1 (one group, no powers
 // after the tree) unless R is kept out of the tree
 bool powers_form(bool plain) { return !plain && g_rins; }
+// a length that C(n) certainly has (its logarithm is known to far less than a bit)
+uint64_t limbs_at_least(uint64_t n) {
+  const double x = (double)n;
+  const double bits = (std::lgamma(2 * x + 1) - std::lgamma(x + 1) - std::lgamma(x + 2)) / std::log(2.0);
+  return bits > 64.0 ? (uint64_t)(bits / 32.0) - 1 : 0;
+}
 // primes of a group table, without the ones that pad R's node
 uint64_t table_primes(const GroupTable& gt) {
   const uint64_t all = gt.off[gt.ngroups];
@@ -2744,8 +2751,9 @@ static cat_status exact_in_workspace(uint64_t n, const Layout& Ly, char* wb, uin
   }
   auto record = [&](Exec& E) -> cat_status {
     STCHK(run_phase2(E, *P));
-    STCHK(launch_top(E.st, W + P->result_pos, P->result_cap, top, d_limbs, std::min<uint64_t>(P->result_cap, cap),
-                     (uint32_t*)(wb + Ly.gtab + CTL_DONE), top, g.pin, 3));
+    const uint64_t most = std::min<uint64_t>(P->result_cap, cap);
+    STCHK(launch_top(E.st, W + P->result_pos, P->result_cap, top, d_limbs, std::min(most, limbs_at_least(n)),
+                     (uint32_t*)(wb + Ly.gtab + CTL_DONE), top, g.pin, 3, most));
     E.launches++;
     return CAT_OK;
   };
@@ -3523,7 +3531,8 @@ cat_status catalan_batch_continue(cat_ticket ticket, uint32_t* const* d_limbs, c
         if (caps[r] >= 1) hipLaunchKernelGGL(k_fill, dim3(1), dim3(64), 0, st, d_limbs[r], (uint64_t)1, 1u);
         hipLaunchKernelGGL(k_fill, dim3(1), dim3(64), 0, st, (uint32_t*)(tops + r), (uint64_t)1, 1u);
       } else {
-        tb.r[nt++] = TopReq{W + P->rpos[i], P->rcap[i], tops + r, d_limbs[r], std::min<uint64_t>(P->rcap[i], caps[r])};
+        tb.r[nt++] =
+            TopReq{W + P->rpos[i], P->rcap[i], tops + r, d_limbs[r], std::min<uint64_t>(P->rcap[i], caps[r]), 0};
         tmax = std::max(tmax, P->rcap[i]);
       }
       hipError_t e = hipGetLastError();

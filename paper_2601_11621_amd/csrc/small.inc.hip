@@ -545,7 +545,9 @@ __global__ void k_fill(uint32_t* __restrict__ p, uint64_t n, uint32_t v) {
 }
 
 // Highest index with a nonzero limb, +1 (0 if all zero) -> *top; limbs below
-// ncopy are also copied to dst (the caller's output).  One result per grid.y;
+// ncopy are also copied to dst (the caller's output), and with `tail` the last
+// block copies those from there to the length, at most `tail`, so that nothing is
+// written behind the result (one result only, with `pub`).  One result per grid.y;
 // each block reduces in LDS and issues one atomicMax.  With `pub`, the last block
 // of the launch (a counter at *done, zero before) copies pub_words words from
 // there to pinned host memory: the lengths and the error word reach the host with
@@ -556,7 +558,7 @@ struct TopReq {
   uint64_t n;
   unsigned long long* top;
   uint32_t* dst;
-  uint64_t ncopy;
+  uint64_t ncopy, tail;
 };
 template <int NR>
 struct TopBatch {
@@ -606,6 +608,11 @@ k_top_nonzero(TopBatch<NR> tb, uint32_t* done, const uint32_t* pub, uint32_t* pu
     __threadfence();
     for (uint32_t k = threadIdx.x; k < pub_words; k += blockDim.x)
       pub_dst[k] = __hip_atomic_load(pub + k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if constexpr (NR == 1) {
+      const unsigned long long len = __hip_atomic_load(q.top, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      const uint64_t end = min((uint64_t)len, q.tail);
+      for (uint64_t k = ncopy + threadIdx.x; k < end; k += blockDim.x) dst[k] = x[k];
+    }
   }
 }
 
