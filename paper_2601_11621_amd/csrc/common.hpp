@@ -153,7 +153,7 @@ struct DescView {
   MulDesc inl[CAT_INLINE_DESC];
   UniDesc u;
   TreeLevel tree;        // tree mode
-  __device__ __forceinline__ MulDesc get(uint64_t i) const {
+  __host__ __device__ __forceinline__ MulDesc get(uint64_t i) const {
     if (table) return table[i];
     if (ninl) return inl[i];
     if (uni) {
@@ -178,6 +178,13 @@ struct DescView {
     d.la = (uint32_t)sz;
     uint64_t rem = tree.K[g] - (2 * il + 1) * sz;
     d.lb = (uint32_t)(rem < sz ? rem : sz);
+    return d;
+  }
+  // slot i of a tile over the products first .. end: those past the end have empty
+  // operands, at the first one's place (a masked load still reads a limb there)
+  __host__ __device__ __forceinline__ MulDesc slot(uint64_t i, uint64_t first, uint64_t end) const {
+    MulDesc d = get(i < end ? i : first);
+    if (i >= end) d.la = d.lb = 0;
     return d;
   }
   // where the residues of the segment of product i start (a group of a tree

@@ -424,11 +424,7 @@ k_flds(DescView dv, uint64_t m0_, uint64_t nmul, const uint32_t* __restrict__ ai
   const FPrime& c = c_fp[0][prime];
   const uint64_t m0 = (uint64_t)(wid / CAT_NPRIMES) * PER;
   const uint32_t cnt = (uint32_t)min((uint64_t)PER, nmul - m0);
-  for (uint32_t i = tid; i < PER; i += NT) {
-    MulDesc d{};   // slots without a product: empty operands
-    if (i < cnt) d = dv.get(m0_ + m0 + i);
-    ds[i] = d;
-  }
+  for (uint32_t i = tid; i < PER; i += NT) ds[i] = dv.slot(m0_ + m0 + i, m0_ + m0, m0_ + m0 + cnt);
   __syncthreads();
   const double* tws = (LE == 3 ? tb.tws3 : tb.tws) + (size_t)prime * FTWS_ENTRIES;
   const double* itws = (LE == 3 ? tb.itws3 : tb.itws) + (size_t)prime * FTWS_ENTRIES;
@@ -1361,11 +1357,7 @@ k_ffused(DescView dv, uint64_t m0, uint64_t nmul, uint32_t tiles, const uint32_t
     return;
   }
   const uint64_t i0 = (uint64_t)blockIdx.x * PER;
-  if (threadIdx.x < PER) {
-    MulDesc d{};   // slots without a product: empty operands
-    if (i0 + threadIdx.x < nmul) d = dv.get(m0 + i0 + threadIdx.x);
-    ds[threadIdx.x] = d;
-  }
+  if (threadIdx.x < PER) ds[threadIdx.x] = dv.slot(m0 + i0 + threadIdx.x, m0 + i0, m0 + nmul);
   __syncthreads();
   ffused_tile<LOGD, ZHI>(lds, ds, nullptr, xw, tmp, ain, bin, out, tb, kc, err);
 }
@@ -1389,13 +1381,9 @@ k_ffused10(DescView dv, SegView sv, uint64_t nmul, uint32_t tiles, const uint32_
   }
   const uint64_t i0 = (uint64_t)blockIdx.x * PER;
   if (threadIdx.x < PER) {
-    MulDesc d{};
     CrtSeg q{};
-    if (i0 + threadIdx.x < nmul) {
-      d = dv.get(i0 + threadIdx.x);
-      q = sv.uniform((uint32_t)i0 + threadIdx.x);
-    }
-    ds[threadIdx.x] = d;
+    if (i0 + threadIdx.x < nmul) q = sv.uniform((uint32_t)i0 + threadIdx.x);
+    ds[threadIdx.x] = dv.slot(i0 + threadIdx.x, i0, nmul);
     sg[threadIdx.x] = q;
   }
   __syncthreads();
@@ -1418,8 +1406,8 @@ k_ffused_mix(const MulDesc* __restrict__ desc, const uint2* __restrict__ tiles, 
   const int logD = (int)(tl.y & 255u) - 1;
   const uint32_t cnt = tl.y >> 8;
   if (threadIdx.x < (1u << (FF_MAX_LOGD - logD))) {
-    MulDesc d{};
-    if (threadIdx.x < cnt) d = desc[tl.x + threadIdx.x];
+    MulDesc d = desc[tl.x + (threadIdx.x < cnt ? threadIdx.x : 0)];
+    if (threadIdx.x >= cnt) d.la = d.lb = 0;   // as DescView::slot
     ds[threadIdx.x] = d;
   }
   __syncthreads();
