@@ -378,15 +378,18 @@ cat_status cat_outer_node_set(uint32_t on);
 /* Prime set of the transform products (Sec. 3.2: every multiplication of
  * the reconstruction phase).  The default, max_logn = 23: three primes above
  * 2^50 (2^51 from 2^24 points on) over 64-bit digits, with the modular
- * arithmetic on the FP64 units.  max_logn < 23: integer transforms over 32-bit
- * limbs; products whose transform has at most 2^max_logn points use three
- * primes below 2^30 (105 2^23 + 1, 107 2^23 + 1, 119 2^23 + 1), whose
- * 4q < 2^32 lets the butterflies leave their values unreduced between
- * operations, larger ones (all of them for max_logn = 0) the three primes in
- * (2^31, 2^32).  Each set covers every coefficient in its range, so the result
- * is the same bit for bit either way.  Cached C(n) and batched-multiply plans
- * are dropped.  Returns CAT_EINVAL above 23. */
+ * arithmetic on the FP64 units.  max_logn < 23, or any max_logn under
+ * cat_integer_transforms_set(1): integer transforms over 32-bit limbs; products
+ * whose transform has at most 2^max_logn points use three primes below 2^30
+ * (105 2^23 + 1, 107 2^23 + 1, 119 2^23 + 1), whose 4q < 2^32 lets the
+ * butterflies leave their values unreduced between operations, larger ones (all
+ * of them for max_logn = 0) the three primes in (2^31, 2^32).  Each set covers
+ * every coefficient in its range, so the result is the same bit for bit either
+ * way; decimal text always takes the FP64 transforms.  Cached C(n) and
+ * batched-multiply plans are dropped.  Returns CAT_EINVAL above 23 (the switch:
+ * above 1). */
 cat_status cat_lazy_primes_set(uint32_t max_logn);
+cat_status cat_integer_transforms_set(uint32_t on);
 
 /* Carry look-back between CRT blocks (diagnostics and tests).  A block reads
  * the generate / propagate pair of the block before it from a flag that block

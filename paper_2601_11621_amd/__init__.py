@@ -34,7 +34,7 @@ EXPORTS = [
     "factorial_ratio_sizes", "factorial_ratio_factor", "factorial_ratio_exact",
     "prime_power_product_sizes", "prime_power_product", "bigint_compare",
     "decimal_sizes", "bigint_to_decimal", "catalan_exact_noalloc", "catalan_noalloc_max_bytes",
-    "cat_fused_levels_set", "cat_lazy_primes_set", "cat_outer_node_set", "bigint_decimal_digits_workspace", "bigint_decimal_digits", "bigint_mul_check",
+    "cat_fused_levels_set", "cat_lazy_primes_set", "cat_integer_transforms_set", "cat_outer_node_set", "bigint_decimal_digits_workspace", "bigint_decimal_digits", "bigint_mul_check",
     "catalan_batch_sizes", "catalan_batch_begin", "catalan_batch_continue", "catalan_batch_end",
     "cat_valu_rate",
 ]
@@ -132,6 +132,7 @@ def load(path: str = LIB_PATH):
         "catalan_exact_noalloc": ([ctypes.c_uint64, vp, ctypes.c_size_t, szp, vp], st),
         "catalan_noalloc_max_bytes": ([szp], st),
         "cat_fused_levels_set": ([ctypes.c_uint32], st),
+        "cat_integer_transforms_set": ([ctypes.c_uint32], st),
         "cat_lazy_primes_set": ([ctypes.c_uint32], st),
         "cat_outer_node_set": ([ctypes.c_uint32], st),
         "bigint_decimal_digits_workspace": ([ctypes.c_size_t, szp], st),
@@ -238,6 +239,13 @@ def set_lazy_primes(max_logn: int = 23) -> None:
     primes below 2^30 with unreduced butterfly ranges (0: the primes above
     2^31 everywhere).  The results are the same bit for bit either way."""
     _check(load().cat_lazy_primes_set(int(max_logn)), "cat_lazy_primes_set")
+
+
+def set_integer_transforms(on: bool = False) -> None:
+    """True: integer transforms over 32-bit limbs whatever set_lazy_primes says
+    (with its 23: the primes below 2^30 up to 2^23 points, those above 2^31
+    beyond).  The results are the same bit for bit either way."""
+    _check(load().cat_integer_transforms_set(1 if on else 0), "cat_integer_transforms_set")
 
 
 def set_outer_node(on: bool = True) -> None:

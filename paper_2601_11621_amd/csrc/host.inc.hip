@@ -398,8 +398,9 @@ void classify(uint64_t la, uint64_t lb, int* cls, int* logN) {
 }
 
 // Transforms on the FP64 units (fntt.hip) for every transform bucket, or the
-// integer transforms only (cat_lazy_primes_set below its default).
-bool g_fp = true;
+// integer transforms only (cat_integer_transforms_set, or cat_lazy_primes_set
+// below its default).
+bool g_fp = true, g_integer = false;
 
 struct Stage {
   int cls = CLS_SCHOOL;
@@ -2852,12 +2853,10 @@ cat_status cat_outer_node_set(uint32_t on) {
   return CAT_OK;
 }
 
-cat_status cat_lazy_primes_set(uint32_t max_logn) {
-  std::lock_guard<std::recursive_mutex> lk(g.mu);
-  if (max_logn > CAT_LAZY_MAX_LOGN) return CAT_EINVAL;
-  g_lazy_logn = max_logn;
-  g_fp = max_logn == CAT_LAZY_MAX_LOGN;
-  // cached plans and their graphs were made with the old setting
+// which transforms the settings ask for; cached plans and their graphs were made
+// with the old ones
+static cat_status transforms_changed() {
+  g_fp = !g_integer && g_lazy_logn == CAT_LAZY_MAX_LOGN;
   if (!g.plans.empty() || !g.noalloc_plans.empty()) HIPCHK(hipDeviceSynchronize());
   for (auto& kv : g.plans) free_plan(kv.second);
   g.plans.clear();
@@ -2867,6 +2866,20 @@ cat_status cat_lazy_primes_set(uint32_t max_logn) {
   g.noalloc_order.clear();
   mul_cache_clear();
   return CAT_OK;
+}
+
+cat_status cat_lazy_primes_set(uint32_t max_logn) {
+  std::lock_guard<std::recursive_mutex> lk(g.mu);
+  if (max_logn > CAT_LAZY_MAX_LOGN) return CAT_EINVAL;
+  g_lazy_logn = max_logn;
+  return transforms_changed();
+}
+
+cat_status cat_integer_transforms_set(uint32_t on) {
+  std::lock_guard<std::recursive_mutex> lk(g.mu);
+  if (on > 1) return CAT_EINVAL;
+  g_integer = on != 0;
+  return transforms_changed();
 }
 
 cat_status cat_lookback_polls_set(uint32_t polls) {
