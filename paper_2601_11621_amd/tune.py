@@ -4,7 +4,7 @@ For every bucket 2^k it times the valid schedules on a synthetic level of
 balanced products (la = lb = 2^(k-1) limbs, about 2^22 coefficients in all, as
 in a tree level) and keeps the fastest:
 
-  * k <= 8:  schoolbook kernel vs the one-workgroup transform (this sets the
+  * k <= 8:  schoolbook kernel vs the FP64 transform, the default (this sets the
              schoolbook threshold on operand length);
   * k <= 14: one-workgroup transform with tiles of 2^12, 2^13 or 2^14 slots
              (products per workgroup and workgroup size: 2^(t-k) and 2^t / 16
@@ -12,9 +12,9 @@ in a tree level) and keeps the fastest:
   * k > 14:  four-step transform, rows of 2^10 .. 2^14, column passes of at
              most 2^6 / 2^8 / 2^10 points.
 
-Rows and column passes bind the integer transforms only (cat_lazy_primes_set
-below 23); with the FP64 transforms, the default, those candidates run the same
-kernels and differ by noise.
+Classes, tiles, rows and column passes bind the integer transforms only, so these
+candidates are timed with the integer transforms; the FP64 transforms have one
+schedule, timed beside them ("fp64").
 
 Every candidate's output is compared bit for bit with the default schedule's;
 a candidate that differs is an error (schedules change speed, never bits).
@@ -50,6 +50,10 @@ def _time_plan(cat, a_off, b_off, da, db, c, reps):
     return float(np.median(ts)) * 1e3
 
 
+# candidates of the default transforms (the others: integer transforms)
+_DEFAULT_TRANSFORMS = ("school", "fp64")
+
+
 def autotune(max_k: int = 24, reps: int = 5, total_log2: int = 22, verbose: bool = True, min_k: int = 7,
              start: dict | None = None) -> dict:
     """Tune buckets min_k..max_k.  `start` (a previous result) supplies the
@@ -83,7 +87,8 @@ def autotune(max_k: int = 24, reps: int = 5, total_log2: int = 22, verbose: bool
         ref_plan(da, db, ref)
         ref_plan.check()
         ref_plan.close()
-        cands = []
+        below = {"school_max": min(half - 1, 128) if half <= 128 else 128}   # the bucket is a transform
+        cands = [("fp64", below)]
         if half <= 128:
             cands.append(("school", {"school_max": 128}))
         if k <= 14:
@@ -94,17 +99,14 @@ def autotune(max_k: int = 24, reps: int = 5, total_log2: int = 22, verbose: bool
                 if eff in seen:
                     continue
                 seen.add(eff)
-                cands.append(("lds_t%d" % eff, {"school_max": min(half - 1, 128) if half <= 128 else 128, "cls": 1,
-                                                "log_row": lt}))
+                cands.append(("lds_t%d" % eff, dict(below, cls=1, log_row=lt)))
             for lr in range(8, k):
-                cands.append(("rows%d" % lr, {"school_max": min(half - 1, 128) if half <= 128 else 128, "cls": 2,
-                                              "log_row": lr, "log_pass": 10}))
+                cands.append(("rows%d" % lr, dict(below, cls=2, log_row=lr, log_pass=10)))
         else:
             for lr in (10, 11, 12, 13, 14):
                 for lp in (6, 8, 10):
                     if k - lr > 0:
-                        cands.append(("rows%d_pass%d" % (lr, lp),
-                                      {"school_max": 128, "cls": 2, "log_row": lr, "log_pass": lp}))
+                        cands.append(("rows%d_pass%d" % (lr, lp), dict(below, cls=2, log_row=lr, log_pass=lp)))
         res = {}
         for name, cfg in cands:
             t = json.loads(json.dumps(table))
@@ -118,20 +120,22 @@ def autotune(max_k: int = 24, reps: int = 5, total_log2: int = 22, verbose: bool
                 cat.set_tuning(t)
             except Exception:
                 continue
-            ms = _time_plan(cat, a_off, b_off, da, db, c, reps)
+            cat.set_integer_transforms(name not in _DEFAULT_TRANSFORMS)
+            try:
+                ms = _time_plan(cat, a_off, b_off, da, db, c, reps)
+            finally:
+                cat.set_integer_transforms(False)
             if not torch.equal(c, ref):
                 raise RuntimeError("schedule %s of bucket 2^%d changed the product bits" % (name, k))
             res[name] = (ms, cfg)
-        best = min(res, key=lambda x: res[x][0])
+        best = min((x for x in res if x not in _DEFAULT_TRANSFORMS), key=lambda x: res[x][0])
         cfg = res[best][1]
-        if best == "school":
+        table["cls"][k] = cfg["cls"]
+        table["log_row"][k] = cfg["log_row"]
+        if cfg["cls"] == 2:
+            table["log_pass"][k] = cfg["log_pass"]
+        if "school" in res and res["school"][0] < res["fp64"][0]:
             school_max = half
-        else:
-            if "cls" in cfg:
-                table["cls"][k] = cfg["cls"]
-                table["log_row"][k] = cfg["log_row"]
-                if cfg["cls"] == 2:
-                    table["log_pass"][k] = cfg["log_pass"]
         meas[k] = {n: round(v[0], 4) for n, v in res.items()}
         meas = dict(sorted(meas.items()))
         if verbose:
