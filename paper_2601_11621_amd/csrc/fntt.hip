@@ -84,7 +84,6 @@ struct FTables {
   const double* ihi;
 };
 FTables g_ft[2];
-uint64_t g_fpr[2][CAT_NPRIMES];
 
 // ------------------------------------------------------------------ arithmetic
 __device__ __forceinline__ double red(double a, double p, double pinv) {
@@ -1616,55 +1615,64 @@ hipError_t fntt_fused_mix(const MulDesc* desc, const uint2* tiles, uint32_t ntil
   return hipGetLastError();
 }
 
+// The launches below instantiate what fp_passes asks for.
 template <int LOGL, int PS>
-static void col_fwd_launch(const FBatch& b, int logS, bool first, int prevS, int prevL, hipStream_t st) {
+static hipError_t col_fwd_launch(const FBatch& b, int logS, bool first, int prevS, int prevL, hipStream_t st) {
   constexpr int LOGT = LOGL <= 8 ? 12 : 13;
   const FGeom fg{b.logD, logS, LOGT - LOGL};
   const dim3 grid((uint32_t)((b.cnt << (b.logD - LOGT)) * CAT_NPRIMES), 1, 2), block((1u << LOGT) / 16);
-  if (first)
-    hipLaunchKernelGGL((k_fcol_fwd<LOGL, PS, true>), grid, block, 0, st, b.dv, fg, b.m0, prevS, prevL, b.ain, b.bin,
-                       b.F, g_ft[PS]);
-  else
-    hipLaunchKernelGGL((k_fcol_fwd<LOGL, PS, false>), grid, block, 0, st, b.dv, fg, b.m0, prevS, prevL, b.ain, b.bin,
-                       b.F, g_ft[PS]);
+  if constexpr (fcol_used(PS, LOGL, true)) {
+    if (first) {
+      hipLaunchKernelGGL((k_fcol_fwd<LOGL, PS, true>), grid, block, 0, st, b.dv, fg, b.m0, prevS, prevL, b.ain, b.bin,
+                         b.F, g_ft[PS]);
+      return hipGetLastError();
+    }
+  }
+  if constexpr (fcol_used(PS, LOGL, false)) {
+    if (!first) {
+      hipLaunchKernelGGL((k_fcol_fwd<LOGL, PS, false>), grid, block, 0, st, b.dv, fg, b.m0, prevS, prevL, b.ain, b.bin,
+                         b.F, g_ft[PS]);
+      return hipGetLastError();
+    }
+  }
+  return hipErrorInvalidValue;
 }
 template <int LOGL, int PS>
-static void col_inv_launch(const FBatch& b, int logS, bool first, int prevS, int prevL, hipStream_t st) {
+static hipError_t col_inv_launch(const FBatch& b, int logS, bool first, int prevS, int prevL, hipStream_t st) {
   constexpr int LOGT = LOGL <= 8 ? 12 : 13;
   const FGeom fg{b.logD, logS, LOGT - LOGL};
   const dim3 grid((uint32_t)(b.cnt << (b.logD - LOGT)), CAT_NPRIMES), block((1u << LOGT) / 16);
-  if (first)
-    hipLaunchKernelGGL((k_fcol_inv<LOGL, PS, true>), grid, block, 0, st, b.dv, fg, b.m0, prevS, prevL, b.F, b.res,
-                       b.stride, g_ft[PS]);
-  else
-    hipLaunchKernelGGL((k_fcol_inv<LOGL, PS, false>), grid, block, 0, st, b.dv, fg, b.m0, prevS, prevL, b.F, b.res,
-                       b.stride, g_ft[PS]);
+  if constexpr (fcol_residues_used(PS, LOGL)) {
+    if (first) {
+      hipLaunchKernelGGL((k_fcol_inv<LOGL, PS, true>), grid, block, 0, st, b.dv, fg, b.m0, prevS, prevL, b.F, b.res,
+                         b.stride, g_ft[PS]);
+      return hipGetLastError();
+    }
+  }
+  if constexpr (fcol_used(PS, LOGL, false)) {
+    if (!first) {
+      hipLaunchKernelGGL((k_fcol_inv<LOGL, PS, false>), grid, block, 0, st, b.dv, fg, b.m0, prevS, prevL, b.F, b.res,
+                         b.stride, g_ft[PS]);
+      return hipGetLastError();
+    }
+  }
+  return hipErrorInvalidValue;
 }
-#define COL_SWITCH(FN)                                         \
-  if (fntt_set(b.logD) == 0) {                                 \
-    switch (logL) {                                            \
-      case 4: FN<4, 0>(b, logS, first, prevS, prevL, st); break;   \
-      case 5: FN<5, 0>(b, logS, first, prevS, prevL, st); break;   \
-      case 6: FN<6, 0>(b, logS, first, prevS, prevL, st); break;   \
-      case 7: FN<7, 0>(b, logS, first, prevS, prevL, st); break;   \
-      case 8: FN<8, 0>(b, logS, first, prevS, prevL, st); break;   \
-      case 9: FN<9, 0>(b, logS, first, prevS, prevL, st); break;   \
-      case 10: FN<10, 0>(b, logS, first, prevS, prevL, st); break; \
-      default: return hipErrorInvalidValue;                    \
-    }                                                          \
-  } else {                                                     \
-    switch (logL) {                                            \
-      case 4: FN<4, 1>(b, logS, first, prevS, prevL, st); break;   \
-      case 5: FN<5, 1>(b, logS, first, prevS, prevL, st); break;   \
-      case 6: FN<6, 1>(b, logS, first, prevS, prevL, st); break;   \
-      case 7: FN<7, 1>(b, logS, first, prevS, prevL, st); break;   \
-      case 8: FN<8, 1>(b, logS, first, prevS, prevL, st); break;   \
-      case 9: FN<9, 1>(b, logS, first, prevS, prevL, st); break;   \
-      case 10: FN<10, 1>(b, logS, first, prevS, prevL, st); break; \
-      default: return hipErrorInvalidValue;                    \
-    }                                                          \
-  }                                                            \
-  return hipGetLastError()
+#define COL_SWITCH(FN)                                                                                          \
+  switch (logL) {                                                                                               \
+    COL_CASE(FN, 4);                                                                                            \
+    COL_CASE(FN, 5);                                                                                            \
+    COL_CASE(FN, 6);                                                                                            \
+    COL_CASE(FN, 7);                                                                                            \
+    COL_CASE(FN, 8);                                                                                            \
+    COL_CASE(FN, 9);                                                                                            \
+    COL_CASE(FN, 10);                                                                                           \
+    default: return hipErrorInvalidValue;                                                                       \
+  }
+#define COL_CASE(FN, X)                                                                                         \
+  case X:                                                                                                       \
+    return fntt_set(b.logD) == 0 ? FN<X, 0>(b, logS, first, prevS, prevL, st)                                   \
+                                 : FN<X, 1>(b, logS, first, prevS, prevL, st)
 
 hipError_t fntt_col_fwd(const FBatch& b, int logS, int logL, bool first, int prevS, int prevL, hipStream_t st) {
   COL_SWITCH(col_fwd_launch);
@@ -1673,49 +1681,49 @@ hipError_t fntt_col_inv(const FBatch& b, int logS, int logL, bool first, int pre
   COL_SWITCH(col_inv_launch);
 }
 
-template <int LOGM>
-static void row_launch(const FBatch& b, int logS, int logL, hipStream_t st) {
-  const dim3 grid((uint32_t)(b.cnt << (b.logD - LOGM)), CAT_NPRIMES), block((1u << LOGM) / 16);
-  if (fntt_set(b.logD) == 0)
-    hipLaunchKernelGGL((k_frow<LOGM, 0>), grid, block, 0, st, b.logD, logS, logL, b.dv.uni, b.F,
-                       g_ft[0]);
-  else
-    hipLaunchKernelGGL((k_frow<LOGM, 1>), grid, block, 0, st, b.logD, logS, logL, b.dv.uni, b.F,
-                       g_ft[1]);
+template <int LOGM, int PS>
+static hipError_t row_launch(const FBatch& b, int logS, int logL, hipStream_t st) {
+  if constexpr (frow_used(PS, LOGM)) {
+    const dim3 grid((uint32_t)(b.cnt << (b.logD - LOGM)), CAT_NPRIMES), block((1u << LOGM) / 16);
+    hipLaunchKernelGGL((k_frow<LOGM, PS>), grid, block, 0, st, b.logD, logS, logL, b.dv.uni, b.F, g_ft[PS]);
+    return hipGetLastError();
+  }
+  return hipErrorInvalidValue;
 }
 hipError_t fntt_row(const FBatch& b, int logM, int logS, int logL, hipStream_t st) {
+  const bool set1 = fntt_set(b.logD) != 0;
   switch (logM) {
-    case 11: row_launch<11>(b, logS, logL, st); break;
-    case 12: row_launch<12>(b, logS, logL, st); break;
+    case 11: return set1 ? row_launch<11, 1>(b, logS, logL, st) : row_launch<11, 0>(b, logS, logL, st);
+    case 12: return set1 ? row_launch<12, 1>(b, logS, logL, st) : row_launch<12, 0>(b, logS, logL, st);
     default: return hipErrorInvalidValue;
   }
-  return hipGetLastError();
 }
 
 template <int LOGL, int PS>
-static void col_crt_launch(const FBatch& b, int logS, const SegView& sv, const uint32_t* add, hipStream_t st) {
-  constexpr int LOGT = 12;
-  const FGeom fg{b.logD, logS, LOGT - LOGL};
-  const dim3 grid((uint32_t)(b.cnt << (b.logD - LOGT))), block((1u << LOGT) / 16);
-  if (add)
-    hipLaunchKernelGGL((k_fcol_crt<LOGL, PS, true>), grid, block, 0, st, b.dv, sv, fg, g_crt[b.logD], b.F, b.res,
-                       b.stride, add, g_ft[PS]);
-  else
-    hipLaunchKernelGGL((k_fcol_crt<LOGL, PS, false>), grid, block, 0, st, b.dv, sv, fg, g_crt[b.logD], b.F, b.res,
-                       b.stride, add, g_ft[PS]);
+static hipError_t col_crt_launch(const FBatch& b, int logS, const SegView& sv, const uint32_t* add, hipStream_t st) {
+  if constexpr (fcol_used(PS, LOGL, true)) {
+    constexpr int LOGT = 12;
+    const FGeom fg{b.logD, logS, LOGT - LOGL};
+    const dim3 grid((uint32_t)(b.cnt << (b.logD - LOGT))), block((1u << LOGT) / 16);
+    if (add)
+      hipLaunchKernelGGL((k_fcol_crt<LOGL, PS, true>), grid, block, 0, st, b.dv, sv, fg, g_crt[b.logD], b.F, b.res,
+                         b.stride, add, g_ft[PS]);
+    else
+      hipLaunchKernelGGL((k_fcol_crt<LOGL, PS, false>), grid, block, 0, st, b.dv, sv, fg, g_crt[b.logD], b.F, b.res,
+                         b.stride, add, g_ft[PS]);
+    return hipGetLastError();
+  }
+  return hipErrorInvalidValue;
 }
 hipError_t fntt_col_crt(const FBatch& b, int logL, const SegView& sv, const uint32_t* add, hipStream_t st) {
-#define L(X)                                                                     \
-  case X:                                                                        \
-    if (fntt_set(b.logD) == 0) col_crt_launch<X, 0>(b, b.logD, sv, add, st);     \
-    else col_crt_launch<X, 1>(b, b.logD, sv, add, st);                           \
-    break
+#define L(X)                                                                                                   \
+  case X: return fntt_set(b.logD) == 0 ? col_crt_launch<X, 0>(b, b.logD, sv, add, st)                          \
+                                       : col_crt_launch<X, 1>(b, b.logD, sv, add, st)
   switch (logL) {
     L(4); L(5); L(6); L(7);
     default: return hipErrorInvalidValue;
   }
 #undef L
-  return hipGetLastError();
 }
 
 hipError_t fntt_crt(const SegView& sv, int logD, int logCR, const double* res, uint64_t stride, const uint32_t* add,

@@ -2,6 +2,8 @@
 #pragma once
 #include "common.hpp"
 
+#include <algorithm>
+
 #define FNTT_MAX_LOGD 26       // longest transform (64-bit digits): products of up to 2^27 limbs
 #define FNTT_SMALL_MAX_LOGD 23 // longest transform of prime set 0 (primes just above 2^50)
 #define FNTT_LDS_MIN_LOGD 5    // one-workgroup transforms
@@ -14,10 +16,54 @@
 #define FCRT_THREADS 256
 #define FCRT_BLOCK (FCRT_E * FCRT_THREADS)
 
-struct SegView;
-
 // prime set of a transform of 2^logD digits
-inline int fntt_set(int logD) { return logD <= FNTT_SMALL_MAX_LOGD ? 0 : 1; }
+constexpr int fntt_set(int logD) { return logD <= FNTT_SMALL_MAX_LOGD ? 0 : 1; }
+
+// Four-step schedule.  Rows of 2^12 digits (2^11 under the shortest column DFT)
+// and as few column passes as fit, at every size: with rows of 2^11 / 2^13 C(10^8)
+// takes 2.51 / 2.78 ms instead of 2.41, 5 10^6 x 3 10^6 limbs 0.357 / 0.363
+// instead of 0.300; 2^13 at any one size lost up to 3 %, 2^11 won nothing beyond
+// noise.
+struct FpPasses {
+  int P = 0, logM = 0, logL[4] = {}, logS[4] = {};
+};
+constexpr FpPasses fp_passes(int logD) {
+  FpPasses f;
+  f.logM = std::min(FNTT_ROW_MAX, logD - FNTT_COL_MIN);
+  const int rest = logD - f.logM;
+  f.P = (rest + FNTT_COL_MAX - 1) / FNTT_COL_MAX;
+  for (int k = 0, ls = logD; k < f.P; k++) {
+    f.logL[k] = rest / f.P + (k < rest % f.P ? 1 : 0);
+    f.logS[k] = ls;
+    ls -= f.logL[k];
+  }
+  return f;
+}
+// Which kernels that schedule launches (fntt.hip instantiates no others): column
+// passes of 2^logL as a transform's outermost pass or as a later one, rows of
+// 2^logM, the outermost inverse pass with residues (not always replaced by
+// fntt_col_crt).
+#define FP_RUN_MIN_LOG 22      // fntt_col_crt: from 2^22 digits a batch
+#define FNTT_RUN_MAX_LOGL 7    // and with columns of at most 2^7 (see fp_run_log)
+constexpr bool fcol_used(int set, int logL, bool outer) {
+  for (int d = FNTT_LDS_MAX_LOGD + 1; d <= FNTT_MAX_LOGD; d++) {
+    const FpPasses f = fp_passes(d);
+    for (int k = 0; k < f.P; k++)
+      if (fntt_set(d) == set && (k == 0) == outer && f.logL[k] == logL) return true;
+  }
+  return false;
+}
+constexpr bool fcol_residues_used(int set, int logL) {
+  for (int d = FNTT_LDS_MAX_LOGD + 1; d <= FNTT_MAX_LOGD; d++)
+    if (fntt_set(d) == set && fp_passes(d).logL[0] == logL && (d < FP_RUN_MIN_LOG || logL > FNTT_RUN_MAX_LOGL))
+      return true;
+  return false;
+}
+constexpr bool frow_used(int set, int logM) {
+  for (int d = FNTT_LDS_MAX_LOGD + 1; d <= FNTT_MAX_LOGD; d++)
+    if (fntt_set(d) == set && fp_passes(d).logM == logM) return true;
+  return false;
+}
 
 // Constants and twiddle tables (on the current device); once per process.
 hipError_t fntt_init();
@@ -67,5 +113,4 @@ hipError_t fntt_crt(const SegView& sv, int logD, int logCR, const double* res, u
 // The outermost inverse pass (2^logL) with the recombination: digits, and what
 // carries out of each run of 2^fntt_run_log(logL) of them.  `add`: decimal joins.
 hipError_t fntt_col_crt(const FBatch& b, int logL, const SegView& sv, const uint32_t* add, hipStream_t st);
-#define FNTT_RUN_MAX_LOGL 7
 inline int fntt_run_log(int logL) { return std::min(12 - logL, 6); }

@@ -1236,9 +1236,8 @@ void free_plan(Plan* P) {
 }
 
 // R = prod_{e>=2} P_e enters Q_1's tree as a node of level j (returned; -1:
-// the final product Q_1 R stays).  j leaves two levels of Q_1 between the
-// completion of the last group with e >= 2 and R's level, for the powers and
-// R to run beside them; it lies above the leaf and fused levels and holds R's
+// the final product Q_1 R stays).  j lies two levels above the completion of
+// the last group with e >= 2, above the base and fused levels, and holds R's
 // product.  Taken when R's node is at most a quarter of Q_1's tree and the
 // arenas have room for the extra 2^j leaves.
 bool g_rins = true;
@@ -1452,26 +1451,6 @@ bool fp_fused(const Stage& s) {
     if ((uint64_t)d.la + d.lb > (1ull << s.logN)) return false;
   return true;
 }
-// Four-step schedule.  Rows of 2^12 digits (2^11 under the shortest column DFT)
-// and as few column passes as fit, at every size: with rows of 2^11 / 2^13 C(10^8)
-// takes 2.51 / 2.78 ms instead of 2.41, 5 10^6 x 3 10^6 limbs 0.357 / 0.363
-// instead of 0.300; 2^13 at any one size lost up to 3 %, 2^11 won nothing beyond
-// noise.
-struct FpPasses {
-  int P = 0, logM = 0, logL[4] = {}, logS[4] = {};
-};
-FpPasses fp_passes(int logD) {
-  FpPasses f;
-  f.logM = std::min(FNTT_ROW_MAX, logD - FNTT_COL_MIN);
-  const int rest = logD - f.logM;
-  f.P = (rest + FNTT_COL_MAX - 1) / FNTT_COL_MAX;
-  for (int k = 0, ls = logD; k < f.P; k++) {
-    f.logL[k] = rest / f.P + (k < rest % f.P ? 1 : 0);
-    f.logS[k] = ls;
-    ls -= f.logL[k];
-  }
-  return f;
-}
 // Does the outermost inverse pass of cnt products recombine too (runs of 2^result
 // digits; 0: no)?  From 2^22 digits a batch, where the residues no longer stay in
 // the memory-side cache (C(10^8), below it: 2.39 -> 2.51 ms, C(3 10^8): 9.37 ->
@@ -1479,7 +1458,6 @@ FpPasses fp_passes(int logD) {
 // tile of three primes then has too few waves to hide its barriers (one level of
 // C(2,050,572,903), pass and carries: 2^4 1.02 -> 0.75 ms, 2^7 1.16 -> 1.00, 2^8
 // 1.22 -> 1.20, 2^9 1.17 -> 1.49).
-#define FP_RUN_MIN_LOG 22
 int fp_run_log(const Stage& s, uint64_t cnt) {
   const int logD = s.logN - 1;
   if (!s.fp || logD <= FNTT_LDS_MAX_LOGD || (cnt << logD) < (1ull << FP_RUN_MIN_LOG)) return 0;
@@ -1881,32 +1859,12 @@ cat_status run_phase2(Exec& X, Plan& P) {
   const bool plain = P.plain;
   std::vector<Stage>& st = P.tree;
   if (P.rins_j >= 0) {
-    // R is a node of Q_1's tree at the level of stage sr: the powers and R
-    // run before it (beside the levels that follow the completion of the
-    // groups with e >= 2 when the call has a side stream)
+    // R is a node of Q_1's tree at the level of stage sr: the powers and R run
+    // before it (a call with a side stream has no such node: C(n) in its powers
+    // form is one group, and with the node off R stays out of the tree)
     const size_t sr = std::min<size_t>((size_t)P.rins_stage, st.size());
-    if (!plain && X.side && P.fork_count >= 0) {
-      const size_t nf = std::min<size_t>((size_t)P.fork_count, sr);
-      for (size_t k = 0; k < nf; k++) STCHK(run_stage_batched(X, st[k]));
-      HIPCHK(hipEventRecord(g.ev_fork, X.st));
-      HIPCHK(hipStreamWaitEvent(X.side, g.ev_fork, 0));
-      for (size_t k = nf; k < sr; k++) STCHK(run_stage_batched(X, st[k]));
-      Exec S = X;
-      S.st = X.side;
-      S.res = X.res2;
-      S.res_stride = X.res2_stride;
-      S.F = X.F2;
-      S.flags = X.flags2;
-      S.crt_epoch = 0;
-      S.launches = 0;
-      STCHK(run_rins_side(S, P, false));
-      HIPCHK(hipEventRecord(g.ev_join, S.st));
-      HIPCHK(hipStreamWaitEvent(X.st, g.ev_join, 0));
-      X.launches += S.launches;
-    } else {
-      for (size_t k = 0; k < sr; k++) STCHK(plain ? run_stage_plain(X, st[k]) : run_stage_batched(X, st[k]));
-      STCHK(run_rins_side(X, P, plain));
-    }
+    for (size_t k = 0; k < sr; k++) STCHK(plain ? run_stage_plain(X, st[k]) : run_stage_batched(X, st[k]));
+    STCHK(run_rins_side(X, P, plain));
     for (size_t k = sr; k < st.size(); k++) STCHK(plain ? run_stage_plain(X, st[k]) : run_stage_batched(X, st[k]));
     return CAT_OK;
   }
