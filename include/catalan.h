@@ -256,7 +256,7 @@ cat_status catalan_end(cat_ticket ticket, size_t* n_limbs);
 cat_status cat_ticket_release(cat_ticket ticket);
 
 /* Batches of C(n) requests (continuous batching in a request loop): the
- * requests' Phase 1 runs request by request, then Phase 2 of all of them is
+ * requests' Phase 1 shares its launches, then Phase 2 of all of them is
  * planned together, so that each tree level of every request, and each step
  * of their powers and outer products, is one launch per kernel stage (at most
  * CAT_MAX_GROUPS exponent groups per plan; a batch with more runs as several
@@ -286,8 +286,8 @@ cat_status catalan_batch_end(cat_ticket ticket, size_t* n_limbs, cat_status* req
 
 /* Reusable plans for repeated batches of the same shape (the batched form
  * of a tree level).  cat_mul_plan_create buckets the products by transform
- * length (schoolbook for la, lb <= 128; LDS-resident NTT up to 2^12
- * coefficients; four-step NTT above) and uploads the descriptor tables;
+ * length (schoolbook for la, lb <= 128; one-workgroup transforms up to la + lb - 1
+ * = 2^15 limbs; four-step transforms above) and uploads the descriptor tables;
  * cat_mul_plan_exec queues the products on `stream` (with CAT_MODE_GRAPH the
  * launch sequence is captured on first use and replayed as one HIP graph per
  * set of pointers); cat_mul_plan_check synchronises `stream` and reports a
@@ -313,7 +313,9 @@ cat_status bigint_residues(const uint32_t* d_x, size_t n, uint64_t* h_res, void*
  * once per kernel), and the sum of la+lb over all products; outer_level is
  * the level of Q_1's product tree at which R = prod_{e>=2} P_e entered as a
  * node (-1: C was formed as Q_1 R after the tree; 0 for calls without a
- * product tree, such as bigint_mul_batched). */
+ * product tree, such as bigint_mul_batched).  C(n) in its default form is one
+ * tree over the powers p^(e_p), and R, there the product of the powers of the
+ * primes up to sqrt(2n), the first node of that level. */
 typedef struct {
   uint64_t products;
   uint64_t launches;
@@ -334,8 +336,8 @@ cat_status cat_get_stats(cat_stats* out);
  * products and 2^log_row / 16 threads per workgroup), 2 = four-step
  * transform with rows of 2^log_row[k] words (8..14, < k) and column passes of
  * at most 2^log_pass[k] points (4..10).  log_row and log_pass bind the integer
- * transforms; the FP64 ones (the default) have a fixed schedule and take from
- * cls only that the bucket is a transform.  Every schedule gives the same bits.
+ * transforms (cat_integer_transforms_set); the FP64 ones (the default) have a
+ * fixed schedule and take from cls only that the bucket is a transform.  Every schedule gives the same bits.
  * cat_tune_set(NULL) restores the defaults; CAT_EINVAL for an invalid table.
  * Setting a table drops the cached C(n) plans. */
 typedef struct {
@@ -357,8 +359,9 @@ cat_status cat_tune_get(cat_tuning* t);
  * (bigint_mul_batched, batched form): the buckets of at most 2^max_logn
  * coefficients in one launch over a tile table.
  * max_logn = 0 turns both off (every level or bucket is then a transform
- * launch and a carry launch); 4..12 turns both on up to 2^max_logn;
- * CAT_FUSED_DEFAULT restores the defaults: generic batches fused up to 2^12,
+ * launch and a carry launch, or on the FP64 units one launch where the transform
+ * has at most 2^12 coefficients); 4..12 turns both on up to 2^max_logn (tree
+ * levels on the integer transforms); CAT_FUSED_DEFAULT restores the defaults: generic batches fused up to 2^12,
  * tree levels not fused (the separate launches are at least as fast).  The
  * result is the same bit for bit either way.  Cached C(n) plans are dropped. */
 #define CAT_FUSED_DEFAULT 0xFFFFFFFFu

@@ -225,8 +225,8 @@ FUSED_DEFAULT = 0xFFFFFFFF
 
 def set_fused_levels(max_logn: Optional[int] = 12) -> None:
     """Fuse the tree levels, and the buckets of a generic batch, with
-    transforms of up to 2^max_logn coefficients into one launch (0: every
-    level or bucket is a transform and a carry launch; None: the library's
+    transforms of up to 2^max_logn coefficients into one launch (0: launches of
+    its own for every level or bucket; None: the library's
     defaults, generic batches fused up to 2^12 and tree levels not fused).
     Same results either way."""
     v = FUSED_DEFAULT if max_logn is None else int(max_logn)

@@ -12,7 +12,9 @@
 // one butterfly level less.
 //
 // Numbers.  A residue is a signed integer held exactly in a double, any
-// representative with |x| < 2^53.  With h = fl(a w), l = a w - h (exact by
+// representative with |x| < 2^53.  The product is the FMA form of van der Hoeven,
+// Lecerf and Quintin ("Modular SIMD arithmetic in Mathemagix", ACM TOMS 2016),
+// with the quotient rounded to nearest and the last correction left out: with h = fl(a w), l = a w - h (exact by
 // FMA) and q = rint(fl(h / p)), the value (h - q p) + l is exactly a w - q p:
 // h - q p is an integer below 2^53, so its FMA does not round, and neither
 // does the last sum.  q is within 1/2 + e of a w / p, where e collects the
@@ -400,8 +402,10 @@ __device__ __forceinline__ uint2 limb2(__amdgpu_buffer_rsrc_t rs, uint32_t byte_
 // and the three primes of a tile read the operands once from HBM.  ZHI: no
 // operand of the batch is longer than N/2 digits.
 constexpr int flds_tile(int logD) { return logD < 12 ? 12 : logD; }
-// Values per thread: 8 (radix-8 passes, at most 66 registers, six or more waves
-// per SIMD) up to 2^13 digits, 16 at 2^14, where a workgroup has 1,024 threads.
+// Values per thread: 8 (radix-8 passes, at most 64 registers, room for eight waves
+// per SIMD) up to 2^12 digits and at 2^13 (66 registers: seven waves, of which a
+// workgroup of 1,024 threads fills four, so one stays on a CU); 16 at 2^14, where a
+// workgroup has 1,024 threads too.
 // Against 16 everywhere (four waves): C(10^5) 0.238 -> 0.230 ms, C(10^7) 0.619
 // -> 0.600, the 4,096-product batch 2.24 -> 2.18.  The rows of the four-step
 // path, which are bound by vector issue and HBM and not by latency, lose 3 %
@@ -639,7 +643,7 @@ k_fcol_inv(DescView dv, FGeom fg, uint64_t m0_, int prevS, int prevL, double* __
 // forward transforms, the pointwise product, the inverse transform and the
 // inverse twiddles.  Grid: rows of the batch x primes.  Bound by vector issue
 // and by HBM at once: 24 B per digit slot and prime, about 260 FP64
-// instructions.
+// instructions.  126 registers for rows of 2^12; rows of 2^11 spill two.
 template <int LOGM, int PS>
 __global__ void __launch_bounds__((1 << LOGM) / 16) __attribute__((amdgpu_waves_per_eu(4)))
 k_frow(int logD, int logS, int logL, int bshared, double* __restrict__ F, FTables tb) {

@@ -592,7 +592,7 @@ Layout layout_finish(Layout L) {
   }
   // control block, cleared by Phase 1 (k_seeds / k_rseeds): group table | top
   // | error word | CRT look-back flags of the main and the side branch; the
-  // first CTL_READ bytes go back to the host in one copy
+  // last kernel of a call writes the first CTL_READ bytes to pinned host memory
   L.gtab = take(CTL_FLAGS + 4 * (L.nblk_max + L.nblk2_max));
   L.top = L.gtab + CTL_TOP;
   L.err = L.gtab + CTL_ERR;
@@ -907,7 +907,9 @@ inline uint64_t cap_of(uint64_t alloc, uint64_t bits) {
 // A long times a short operand (la >= 8 lb) beyond the schoolbook bound:
 // column sums cost la lb 32x32 multiply-adds (two VALU instructions each,
 // about 2.5 with the window's shifts and LDS reads) in one pass; the transform
-// costs 9 (N/2) log2 N butterflies (about 14 each).  Against the four-step
+// costs 9 (N/2) log2 N butterflies of the integer form (about 14 each), which the
+// figures here were taken with; against the FP64 transforms, which have half the
+// points, the line was not measured again.  Against the four-step
 // path (four launches per product) the column sums are chosen up to 1.25
 // times the transform's instruction count: on a batch of 4,096 uneven
 // products the time is 4.64, 4.54, 4.55 and 4.56 ms at 0.75, 1.25, 1.9 and
@@ -1443,8 +1445,8 @@ FBatch fp_batch(Exec& X, const Stage& s, const DescView& dv, uint64_t cnt) {
 // carry into a digit past its slots: the general path.)
 // A tree level of at most 64 products of 2^11 digits takes a launch more: one CU
 // would hold the three primes of a product while three quarters of the chip
-// stand idle (n = 6 10^4 .. 1.5 10^6: 2 to 5 % faster, C(10^5) 0.123 -> 0.119 ms;
-// at all sizes eight mixed requests 0.624 -> 0.634).
+// stand idle (C(10^5) 125 -> 121 us, C(4 10^5) 198 -> 190, C(1.5 10^6) 252 -> 244;
+// at all sizes eight mixed requests 0.624 -> 0.634 ms).
 #define FF_FEW 64
 bool fp_fused(const Stage& s) {
   if (!s.fp || !fntt_fused_fits(s.logN - 1)) return false;
