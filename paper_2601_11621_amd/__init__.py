@@ -369,8 +369,8 @@ def batch_sizes(ns) -> int:
 
 
 def exact_batch(ns, stream=None):
-    """C(n) for every n of ns (at most BATCH_MAX) as one batch: Phase 1 per
-    request, Phase 2 of all of them planned and launched together.  Returns
+    """C(n) for every n of ns (at most BATCH_MAX) as one batch: both phases of
+    all of them planned and launched together.  Returns
     a list of limb tensors (bit-identical to exact(n))."""
     torch = _torch()
     lib = load()

@@ -2592,7 +2592,7 @@ uint64_t ratio_limbs_bound(const RatioSpec& r) {
 Layout make_layout_ratio(const RatioSpec& r) {
   Layout L;
   L.n = 0;
-  L.s = isqrt64(r.A);
+  L.s = std::max<uint64_t>(isqrt64(r.A), 2);   // (2 is a seed: the sieve above holds odd numbers)
   L.ebits = bit_len(r.A);
   L.i0 = (L.s + 1) / 2;
   L.i_end = (r.A + 1) / 2;   // odd m = 2i + 1 <= A
